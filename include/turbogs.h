@@ -60,8 +60,9 @@ extern "C" {
 #define TGS_PARAM_ROWS 59
 #define TGS_MOMENT_STRIDE 64 /* floats per Gaussian in the moment arrays m, v */
 #define TGS_COUNTER_SLOTS 64 /* slots per counter of tgs_render_fwd */
-#define TGS_RENDER_CHUNKS 8     /* backward workgroups per tile when the forward keeps state */
-#define TGS_RENDER_CHUNK_LEN 32 /* list positions per backward chunk (the last takes the rest) */
+#define TGS_RENDER_CHUNKS 8      /* equal chunks of a tile's list in the backward when the forward keeps state */
+#define TGS_RENDER_CHUNK_LEN 32  /* their list positions */
+#define TGS_RENDER_LONG_CHUNKS 4 /* chunks after them: 2, 4, 8 times as long, the last takes the rest */
 
 enum {
   TGS_OK = 0,
@@ -314,9 +315,10 @@ int32_t tgs_bin_sort_continue_async(const float* splat, int64_t n, const int32_t
  *   state     nullable, tgs_render_state_size(n_slots, max_per_tile) bytes
  *             (n_slots = n_st, or tiles_x * tiles_y in dense mode with
  *             max_per_tile 256), 16-byte aligned: each pixel's transmittance
- *             and accumulated colour (float4 T, r, g, b) at list positions
- *             c * TGS_RENDER_CHUNK_LEN, c = 1 .. TGS_RENDER_CHUNKS - 1, where
- *             the walk reaches them; lets tgs_render_bwd split each tile's
+ *             and accumulated colour (float4 T, r, g, b) at the first list
+ *             position of every chunk but the first (TGS_RENDER_CHUNKS chunks
+ *             of TGS_RENDER_CHUNK_LEN positions, then TGS_RENDER_LONG_CHUNKS
+ *             longer ones), where the walk reaches them; lets tgs_render_bwd split each tile's
  *             replay into chunks */
 size_t tgs_render_state_size(int32_t n_slots, int32_t max_per_tile);
 int32_t tgs_render_fwd(const float* splat, const uint32_t* vals, const uint32_t* ranges,
@@ -363,9 +365,8 @@ int32_t tgs_render_fwd_cont(const float* splat, const uint32_t* vals, const uint
  *   g2d      [n][9] float, accumulated (+=): dL/d(centre x, y; conic a, b, c;
  *            opacity; r, g, b)
  *   state    nullable: the forward's state record for the same call
- *            arguments.  Given, each tile's replay runs as TGS_RENDER_CHUNKS
- *            workgroups, chunk c starting at list position
- *            c * TGS_RENDER_CHUNK_LEN from the recorded state (the last chunk
+ *            arguments.  Given, each tile's replay runs as one workgroup per
+ *            chunk, starting from the recorded state (the last chunk
  *            takes the rest of the list); the per-pixel arithmetic is the
  *            same as the single-workgroup replay, only the order of the
  *            gradient atomics differs.
@@ -393,20 +394,17 @@ int32_t tgs_render_bwd2(const float* splat, const uint32_t* vals, const uint32_t
                         uint8_t* touched, const float* err, int64_t n, float* stats, void* stream);
 
 /* tgs_render_bwd with bitwise-reproducible gradients: the same adjoint and
- * the same per-Gaussian wave sums, but each wave stores its nine sums of
- * a pair into a per-(pair, wave) record of the workspace instead of adding
- * them to g2d with float atomics (whose order varies run to run); a second
- * pass adds, per Gaussian, the records of its pairs in a fixed order (the
- * tiles of its rectangle row by row, then the waves) and adds the total to
- * g2d.  Same inputs give the same bits on every run.  touched as in
+ * the same sums over a tile's samples, but each pair's nine sums go to a
+ * record of the workspace instead of being added to g2d with float atomics
+ * (whose order varies run to run); a second pass adds, per Gaussian, the
+ * records of its pairs in a fixed order (the tiles of its rectangle row by
+ * row) and adds the total to g2d.  Same inputs give the same bits on every run.  touched as in
  * tgs_render_bwd.
  *   depth, rect  the tgs_project outputs the lists were built from
  *   n            Gaussians; n_pairs the pair count tgs_bin_sort returned
  *   ws           tgs_render_bwd_det_workspace_size(n_pairs, max_per_tile,
  *                dense) bytes, 16-byte aligned (cleared by the call):
- *                36 bytes per pair and wave of a tile's workgroup (one wave
- *                up to 64 samples per tile, two up to 128, four above and
- *                in dense mode)
+ *                36 bytes per pair
  * The density-control variant keeps its atomics (tgs_render_bwd_density). */
 size_t tgs_render_bwd_det_workspace_size(int64_t n_pairs, int32_t max_per_tile, int32_t dense);
 int32_t tgs_render_bwd_deterministic(const float* splat, const uint32_t* vals, const uint32_t* ranges,
@@ -468,7 +466,7 @@ int32_t tgs_error_init(const float* out_dense, const float* gt, int32_t height, 
  *   err       [P] float per-pixel error e(p), indexed like ncontrib (the
  *             tgs_loss err output in sparse mode)
  *   state     nullable: that call's state record; given, each tile's walk
- *             runs as TGS_RENDER_CHUNKS workgroups as in tgs_render_bwd
+ *             runs as one workgroup per chunk as in tgs_render_bwd
  *             (same per-pixel arithmetic, another order of the atomics)
  *   n         number of Gaussians (ids in vals must be below n)
  *   stats     [n][4] float, 16-byte aligned, accumulated (+=); entry 3 of

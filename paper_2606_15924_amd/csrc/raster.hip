@@ -12,15 +12,14 @@
 // accumulated colour from the forward outputs (final colour and the number
 // of contributors), so nothing per Gaussian or per (pixel, Gaussian) is
 // stored.  Optionally the forward records each pixel's (T, accumulated
-// colour) every TGS_RENDER_CHUNK_LEN list positions; the backward then runs
-// one workgroup per (tile, chunk of TGS_RENDER_CHUNK_LEN positions, the last
-// of TGS_RENDER_CHUNKS chunks taking the rest) that starts from the
+// colour) at the first position of every chunk of the list (chunk_begin); the
+// backward then runs one workgroup per (tile, chunk) that starts from the
 // recorded state.  The replay performs the same operations in the same
 // order, so every per-lane value equals the unchunked one; at 64 samples
 // per tile this turns one wave per tile into several, which the SIMDs need
-// to hide latency.  Per Gaussian, each lane's contribution to the nine screen-space
-// gradients is summed across the wave (lane-half swaps, then DPP within rows
-// of 16), and nine lanes of the wave issue one float atomic each.
+// to hide latency.  The nine screen-space gradients of a Gaussian are moments
+// over the pixels, so the sums over a wave's 64 pixels run on the matrix cores
+// (see render_bwd_kernel); the batch's sums then leave in one pass of atomics.
 //
 // Both walks keep the next batch's loads in flight while the current batch
 // is evaluated: at 64 samples per tile a tile is one wave, so there are few
@@ -89,27 +88,39 @@ __device__ __forceinline__ uint32_t list_id(const RasterArgs& a, const TileList&
 // alpha there would carry percent-level errors.)  Staged: A = -a/2 log2(e),
 // beta, D = -delta/2 log2(e), so p2 = A w^2 + D dy^2 with w = dx + beta dy is
 // log2(e) * power and G = exp(power) = 2^p2.
+// Chunks of a tile's list: TGS_RENDER_CHUNKS of TGS_RENDER_CHUNK_LEN positions,
+// then TGS_RENDER_LONG_CHUNKS of twice that length, each twice as long as the
+// one before it and the last taking the rest.  Most walks end within the equal
+// chunks (115 positions on average in the benchmark's scenes); those of a few
+// percent of the tiles run to 400-850 positions, and one workgroup over all of
+// the rest was the tail of the launch.  Equal chunks to the end would launch
+// several empty workgroups per tile instead (0.25 ns each).
+constexpr int kChunks = TGS_RENDER_CHUNKS + TGS_RENDER_LONG_CHUNKS;
+
+__device__ __forceinline__ uint32_t chunk_begin(int c) {
+  constexpr uint32_t kEqual = TGS_RENDER_CHUNKS * TGS_RENDER_CHUNK_LEN;
+  return c <= TGS_RENDER_CHUNKS ? (uint32_t)(c * TGS_RENDER_CHUNK_LEN)
+                                : kEqual + 2u * TGS_RENDER_CHUNK_LEN * ((1u << (c - TGS_RENDER_CHUNKS)) - 1u);
+}
+
+// The chunk that begins at position pos > 0, or 0 when none does.
+__device__ __forceinline__ int chunk_at(uint32_t pos) {
+  if (pos % TGS_RENDER_CHUNK_LEN != 0) return 0;
+  if (pos <= (uint32_t)(TGS_RENDER_CHUNKS * TGS_RENDER_CHUNK_LEN)) return (int)(pos / TGS_RENDER_CHUNK_LEN);
+#pragma unroll
+  for (int c = TGS_RENDER_CHUNKS + 1; c < kChunks; ++c)
+    if (pos == chunk_begin(c)) return c;
+  return 0;
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kUnroll = 8;   // forward: alphas evaluated per group
-constexpr int kUnrollB = 2;  // backward
+constexpr int kUnrollB = 2;  // density back-projection
 
 __device__ __forceinline__ float splat_exponent(float dx, float dy, float A, float beta, float D) {
 #pragma clang fp contract(off)
   const float w = __builtin_fmaf(beta, dy, dx);
   const float ww = w * w, yy = dy * dy;
-  return __builtin_fmaf(A, ww, D * yy);
-}
-
-// The same exponent (same operations, bit-identical), also returning the
-// products dx^2, dx dy, dy^2 for the conic gradient.
-__device__ __forceinline__ float splat_exponent_p(float dx, float dy, float A, float beta, float D, float& xx,
-                                                  float& xy, float& yy) {
-#pragma clang fp contract(off)
-  xx = dx * dx;
-  yy = dy * dy;
-  xy = dx * dy;
-  const float w = __builtin_fmaf(beta, dy, dx);
-  const float ww = w * w;
   return __builtin_fmaf(A, ww, D * yy);
 }
 
@@ -223,10 +234,10 @@ __global__ void __launch_bounds__(kBlock) render_fwd_kernel(RasterArgs a, float4
     for (int j = 0; j < cnt; j += kUnroll) {
       if (__ballot(!done) == 0ull) break;  // the whole wave has terminated
       const uint32_t pos = pos0 + (uint32_t)j;  // uniform; chunk starts are multiples of kUnroll
-      if (state != nullptr && pos % TGS_RENDER_CHUNK_LEN == 0 && pos > 0 &&
-          pos < (uint32_t)(TGS_RENDER_CHUNKS * TGS_RENDER_CHUNK_LEN))
-        state[((int64_t)slot * (TGS_RENDER_CHUNKS - 1) + pos / TGS_RENDER_CHUNK_LEN - 1) * kBlock + tid] =
-            make_float4(T, c0, c1, c2);
+      if (state != nullptr) {
+        const int c = chunk_at(pos);  // uniform
+        if (c > 0) state[((int64_t)slot * (kChunks - 1) + c - 1) * kBlock + tid] = make_float4(T, c0, c1, c2);
+      }
       float al[kUnroll], pw[kUnroll], cr[kUnroll], cg[kUnroll], cb[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
@@ -306,92 +317,12 @@ __device__ __forceinline__ float row_sum16(float v) {
   return v;  // every lane of a row holds the row's sum
 }
 
-// Which of the nine sums a lane holds after the reduction below, and
-// whether it issues that sum's atomic: row r of register R_k (rows of 16
-// lanes) holds one field, lanes 0 and 1 of every row issue r0's and r1's
-// field, lane 2 of row 0 issues field 8.  With the density sums (thirteen
-// fields) lane 2 of every row issues one of fields 8-11 and lane 3 of row 0
-// field 12.  Fixed per lane, so computed once.
-struct Sum9Lane {
-  int field;   // 0..12, or -1 when the lane issues no atomic
-  int which;   // 0: r0, 1: r1, 2: r2, 3: r3
-};
-
-__device__ __forceinline__ Sum9Lane sum9_lane(bool thirteen = false) {
-  const int lane = lane_id(), k = lane & 15, row = lane >> 4;
-  Sum9Lane s;
-  s.which = k < 4 ? k : 0;
-  const int f = k * 4 + ((row & 1) << 1) + (row >> 1);
-  if (k < 2) s.field = f;
-  else if (k == 2) s.field = (thirteen || row == 0) ? f : -1;
-  else s.field = (thirteen && k == 3 && row == 0) ? f : -1;
-  return s;
-}
-
-// Sums each of v[0..8] over the wave and adds the nine sums to dst[0..8]
-// with one atomic instruction.  Halves of the wave are folded pairwise with
-// the lane swaps (64 -> 32 -> 16 lanes per value), then each row of 16 is
-// reduced with DPP; row r of register R_k then holds the sum of one field.
-// dst is wave-uniform (a scalar address).
-__device__ __forceinline__ void wave_sum9_atomic(const float (&v)[9], float* __restrict__ dst, const Sum9Lane& sl) {
-  const float p01 = swap_sum32(v[0], v[1]);
-  const float p23 = swap_sum32(v[2], v[3]);
-  const float p45 = swap_sum32(v[4], v[5]);
-  const float p67 = swap_sum32(v[6], v[7]);
-  const float p8 = swap_sum32(v[8], 0.f);
-  // rows of r0: fields 0, 2, 1, 3; rows of r1: 4, 6, 5, 7; row 0 of r2: 8
-  const float r0 = row_sum16(swap_sum16(p01, p23));
-  const float r1 = row_sum16(swap_sum16(p45, p67));
-  const float r2 = row_sum16(swap_sum16(p8, 0.f));
-  float val = sl.which == 0 ? r0 : (sl.which == 1 ? r1 : r2);
-  // every lane takes its sum here, with the whole wave active, so the last
-  // DPP step stays one fused add instead of a move out of the branch below
-  asm volatile("" : "+v"(val));
-  if (sl.field >= 0 && val != 0.f) unsafeAtomicAdd(&dst[sl.field], val);
-}
-
-// The same nine wave sums, stored (not added) to dst[0..8]: the
-// deterministic backward's per-(pair, wave) partial record, which no other
-// wave writes.  Zero sums are stored too (the record is not cleared).
-__device__ __forceinline__ void wave_sum9_store(const float (&v)[9], float* __restrict__ dst, const Sum9Lane& sl) {
-  const float p01 = swap_sum32(v[0], v[1]);
-  const float p23 = swap_sum32(v[2], v[3]);
-  const float p45 = swap_sum32(v[4], v[5]);
-  const float p67 = swap_sum32(v[6], v[7]);
-  const float p8 = swap_sum32(v[8], 0.f);
-  const float r0 = row_sum16(swap_sum16(p01, p23));
-  const float r1 = row_sum16(swap_sum16(p45, p67));
-  const float r2 = row_sum16(swap_sum16(p8, 0.f));
-  float val = sl.which == 0 ? r0 : (sl.which == 1 ? r1 : r2);
-  asm volatile("" : "+v"(val));  // as in wave_sum9_atomic
-  if (sl.field >= 0) dst[sl.field] = val;
-}
-
-// The nine gradient sums plus the four density-control sums (e w, w, D w
-// and the per-pixel centre-gradient norm) of the same Gaussian: the same
-// folding with fields 9-11 in the rows of r2 that the nine-value form leaves
-// empty (row 2: field 9, row 1: 10, row 3: 11) and field 12 in row 0 of r3;
-// they go to stats[gid][field - 9], one 16-byte slot.
-__device__ __forceinline__ void wave_sum13_atomic(const float (&v)[13], float* __restrict__ dst,
-                                                  float* __restrict__ stats, uint32_t gid, int64_t n,
-                                                  const Sum9Lane& sl) {
-  const float p01 = swap_sum32(v[0], v[1]);
-  const float p23 = swap_sum32(v[2], v[3]);
-  const float p45 = swap_sum32(v[4], v[5]);
-  const float p67 = swap_sum32(v[6], v[7]);
-  const float p89 = swap_sum32(v[8], v[9]);
-  const float pab = swap_sum32(v[10], v[11]);
-  const float pc = swap_sum32(v[12], 0.f);
-  const float r0 = row_sum16(swap_sum16(p01, p23));
-  const float r1 = row_sum16(swap_sum16(p45, p67));
-  const float r2 = row_sum16(swap_sum16(p89, pab));
-  const float r3 = row_sum16(swap_sum16(pc, 0.f));
-  float val = sl.which == 0 ? r0 : (sl.which == 1 ? r1 : (sl.which == 2 ? r2 : r3));
-  asm volatile("" : "+v"(val));  // as in wave_sum9_atomic
-  if (sl.field >= 0 && val != 0.f) {
-    if (sl.field < 9) unsafeAtomicAdd(&dst[sl.field], val);
-    else if (gid < (uint32_t)n) unsafeAtomicAdd(&stats[(int64_t)gid * 4 + (sl.field - 9)], val);
-  }
+// Sum over the quads of a row of 16 lanes: every lane ends with the sum over
+// the row's lanes of its own index modulo 4.
+__device__ __forceinline__ float row_sum_quads(float v) {
+  v += dpp_f<0x128>(0.f, v);  // row_ror:8
+  v += dpp_f<0x124>(0.f, v);  // row_ror:4
+  return v;
 }
 
 // Optional density-control sums in the backward (Sec. 3.8): the replay
@@ -403,12 +334,78 @@ struct DensityArgs {
   int64_t n;
 };
 
-// kDet: the deterministic variant.  Instead of adding each wave's nine sums
-// to g2d[gid] with atomics, it stores them to g2d[(pos * kWaves + wave) * 9]
-// (g2d is then the partial buffer, pos the pair's index in the sorted list);
+// The backward's sums over pixels.
+//
+// Per (Gaussian, pixel) the replay leaves two scalars, q = dL/d opacity at
+// that pixel (G dalpha where alpha is not clamped) and the weight w.  With d =
+// the pixel's offset from the centre, every gradient of the Gaussian is a
+// moment of q or w over the pixels: sum q, sum q d, sum q d d^T and sum w g
+// (g = dL/d colour of the pixel).  Summing nine values across a wave with
+// lane swaps and DPP adds took ~40 of the ~83 vector instructions of a
+// (Gaussian, wave) step, and the walk is bound by vector issue, so the sums
+// run on the matrix cores instead: for four Gaussians at a time, matrices of 4
+// Gaussians x 64 pixels (q dx, q dy, q and w) times 64 pixels x 4 columns (1,
+// x, y; or the colour gradients), as v_mfma_f32_4x4x1 (16 blocks, one pixel
+// per block and instruction, FP32 products and sums).  The x, y columns are
+// relative to the tile's centre, the same for every Gaussian; the offset of
+// the Gaussian's centre is taken off afterwards (sum q dx dx = sum (q dx) x -
+// cx sum q dx): one factor of each product is formed per pixel, so only the
+// linear shift is subtracted from a sum.  Going from a lane per pixel to the
+// matrix operand (a lane per Gaussian and block) is a transposition through
+// LDS private to the wave, whose LDS operations execute in order.  The 16
+// blocks' partial sums are folded with lane swaps and row rotations, 24
+// instructions per four Gaussians, into a table; at the end of a batch a
+// thread per Gaussian combines its row (over the workgroup's waves, in wave
+// order) and consecutive lanes add the nine gradients of consecutive
+// Gaussians (36-byte runs).  46 vector instructions per step; 300k Gaussians,
+// 1296 x 840: 89 -> 78 us at 64 samples per tile, 274 -> 228 us dense (there
+// the waves of a tile also share one set of atomics; plain stores in their
+// place take the same time).  Of the 78 us, 9 are the workgroups' dispatch, 11
+// the loads before the walk; the walk issues vector instructions 90% of its time.
+constexpr int kBwdBatch = TGS_RENDER_CHUNK_LEN;  // Gaussians per batch: one short chunk
+constexpr int kBwdGroup = 4;                     // Gaussians per matrix
+constexpr int kBwdStage = 2 * kBwdBatch;         // Gaussians loaded per round
+static_assert(kBwdBatch == 32, "a round's composited Gaussians are kept as a 32-bit mask");
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Sums of the four rows (Gaussians) of a 16-block accumulator over the
+// blocks: row r of 16 lanes holds Gaussian ((r & 1) << 1) | (r >> 1), lane l
+// of the row column l % 4.
+__device__ __forceinline__ float block_sums(const v4f& c) {
+  return row_sum_quads(swap_sum16(swap_sum32(c[0], c[1]), swap_sum32(c[2], c[3])));
+}
+
+// Two 4 Gaussians x 64 pixels matrices from a lane per pixel (x[u], y[u]:
+// Gaussian u) to the operands of the four instructions s: lane l gets
+// Gaussian l % 4 of pixel 16 s + l / 4.  The buffer is the wave's own and its
+// LDS operations execute in order, so the writes of one call follow the reads
+// of the call before it.
+template <typename F>
+__device__ __forceinline__ void transpose2(float* tr, int lane, const float (&x)[4], const float (&y)[4], F&& f) {
+  float4* tw = reinterpret_cast<float4*>(tr);
+  tw[lane] = make_float4(x[0], x[1], x[2], x[3]);
+  tw[kWave + lane] = make_float4(y[0], y[1], y[2], y[3]);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  float xs[4], ys[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    xs[s] = tr[s * kWave + lane];
+    ys[s] = tr[(4 + s) * kWave + lane];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int s = 0; s < 4; ++s) f(s, xs[s], ys[s]);
+}
+
+// kDet: the deterministic variant.  Instead of adding the pair's nine sums to
+// g2d[gid] with atomics, it stores them to g2d[pos * 9] (g2d is then the
+// partial buffer, pos the pair's index in the sorted list);
 // det_reduce_kernel adds them up per Gaussian in a fixed order.
 template <int kBlock, bool kDense, bool kDensity = false, bool kDet = false>
-__global__ void __launch_bounds__(kBlock) render_bwd_kernel(RasterArgs a,
+__global__ void __launch_bounds__(kBlock, kBlock == 64 ? 6 : 5) render_bwd_kernel(RasterArgs a,
                                                             const float4* __restrict__ out,
                                                             const uint32_t* __restrict__ ncontrib,
                                                             const float4* __restrict__ dL,
@@ -416,27 +413,41 @@ __global__ void __launch_bounds__(kBlock) render_bwd_kernel(RasterArgs a,
                                                             const float4* __restrict__ state,
                                                             uint8_t* __restrict__ touched,
                                                             DensityArgs dens = {}) {
-  __shared__ float4 s_geo[kBlock];
-  __shared__ float4 s_app[kBlock];
-  __shared__ float4 s_con[kBlock];  // conic a, b, c (natural units), blue
-  __shared__ uint32_t s_gid[kBlock];
-  // the last chunk (the rest of the list, the longest walks) is dispatched
-  // first, so its workgroups run beside the fixed-length chunks
+  constexpr int kWaves = kBlock / kWave;
+  constexpr int kCols = kDensity ? 16 : 12; // sums per Gaussian in the table
+  constexpr int kFields = kDensity ? 13 : 9;
+  __shared__ float4 s_geo[kBwdStage];
+  __shared__ float4 s_app[kBwdStage];
+  __shared__ float4 s_con[kBwdStage];  // conic a, b, c (natural units), blue
+  __shared__ uint32_t s_gid[kBwdStage];
+  // a wave's transposition buffer (two matrices at a time); before the walk its pixels' columns
+  __shared__ __align__(16) float s_tr[kWaves][2][kWave * kBwdGroup];
+  __shared__ __align__(16) float s_tab[kWaves][kBwdBatch * kCols];
+  __shared__ uint32_t s_hit[kWaves];  // Gaussians of the batch composited in the wave
+  // the last chunks (the longest walks) are dispatched first, so their
+  // workgroups run beside the short ones
   const int slot = blockIdx.x, chunk = (int)gridDim.y - 1 - (int)blockIdx.y, tid = threadIdx.x;
+  const int lane = lane_id(), wave = tid / kWave;
   const int tile = kDense ? slot : a.valid_tiles[slot];
   const int tx = tile % a.tiles_x, ty = tile / a.tiles_x;
   const TileList L = tile_list(a, tile);
   const uint2 range = make_uint2(0u, L.len);
   // list positions [begin, end) of this chunk (one chunk without a state record)
-  const uint32_t begin = range.x + (uint32_t)(chunk * TGS_RENDER_CHUNK_LEN);
+  const uint32_t begin = range.x + chunk_begin(chunk);
   if (begin >= range.y && chunk > 0) return;  // workgroup-uniform
   const uint32_t end =
-      chunk + 1 == (int)gridDim.y ? range.y : min(range.y, begin + (uint32_t)TGS_RENDER_CHUNK_LEN);
+      chunk + 1 == (int)gridDim.y ? range.y : min(range.y, range.x + chunk_begin(chunk + 1));
+  // a thread of the first 64 stages one Gaussian; the ids of the next round
+  // are loaded ahead, the records are not (holding them over the walk costs
+  // the registers of a wave per SIMD).  The first ids are asked for here,
+  // beside the pixels' contributor counts.
+  const bool stager = tid < kBwdStage;
+  uint32_t g_next = 0;
+  if (stager && begin + tid < end) g_next = list_id(a, L, begin + tid);
   const PixelSlot px = pixel_of<kBlock, kDense>(a, slot, tile, tid);
   const float lx = (float)(px.loc & 15), ly = (float)(px.loc >> 4);
   const float x0 = (float)(tx * kTile), y0 = (float)(ty * kTile);
   const float amin = a.alpha_min, amax = a.alpha_max;
-  const Sum9Lane sl = sum9_lane(kDensity);
   const float hw = 0.5f * (float)a.width, hh = 0.5f * (float)a.height;  // pixel -> NDC units
 
   float Cout0 = 0.f, Cout1 = 0.f, Cout2 = 0.f, g0 = 0.f, g1 = 0.f, g2 = 0.f;
@@ -459,7 +470,7 @@ __global__ void __launch_bounds__(kBlock) render_bwd_kernel(RasterArgs a,
   // and at it), updated as S -= w * sum_c g_c colour_c
   float T = 1.f, acc0 = 0.f, acc1 = 0.f, acc2 = 0.f;
   if (chunk > 0 && !done) {
-    const float4 st = state[((int64_t)slot * (TGS_RENDER_CHUNKS - 1) + chunk - 1) * kBlock + tid];
+    const float4 st = state[((int64_t)slot * (kChunks - 1) + chunk - 1) * kBlock + tid];
     T = st.x;
     acc0 = st.y;
     acc1 = st.z;
@@ -467,87 +478,186 @@ __global__ void __launch_bounds__(kBlock) render_bwd_kernel(RasterArgs a,
   }
   float S = g0 * (Cout0 - acc0) + g1 * (Cout1 - acc1) + g2 * (Cout2 - acc2);
 
-  Staged nxt = {};
-  uint32_t g_after = 0;
-  if (begin + tid < end) nxt = stage_load(a, list_id(a, L, begin + tid), x0, y0);
-  if (begin + kBlock + tid < end) g_after = list_id(a, L, begin + kBlock + tid);
+  auto stage = [&](uint32_t start) {
+    Staged st = {};
+    if (start + tid < end) st = stage_load(a, g_next, x0, y0);
+    if (start + kBwdStage + tid < end) g_next = list_id(a, L, start + kBwdStage + tid);
+    s_geo[tid] = st.geo;
+    s_app[tid] = st.app;
+    s_con[tid] = st.con;
+    s_gid[tid] = st.gid;
+  };
+  if (stager) stage(begin);
 
-  for (uint32_t start = begin; start < end; start += kBlock) {
+  // the pixels' columns as matrix operands: lane l of instruction s holds
+  // column l % 4 of pixel 16 s + l / 4
+  float* const tr = &s_tr[wave][0][0];
+  float* const s_fin = &s_tr[0][0][0];  // the batch's gradients, after the walk
+  static_assert(kBwdBatch * kFields <= 2 * kWave * kBwdGroup, "the gradients fit one wave's buffer");
+  {
+    float4* row = reinterpret_cast<float4*>(tr);
+    row[2 * lane] = make_float4(1.f, lx - 7.5f, ly - 7.5f, 0.f);
+    row[2 * lane + 1] = make_float4(g0, g1, g2, e_pix);
+  }
+  __syncthreads();
+  const int col = lane & 3;
+  float b0[4], bw[4];  // columns 1, x, y, 0 and the colour gradients (and the pixel's error)
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const float* row = tr + (16 * s + (lane >> 2)) * 8;
+    b0[s] = row[col];
+    bw[s] = row[4 + col];
+  }
+  const float e3 = col == 3 ? 1.f : 0.f;  // the fourth column
+
+  for (uint32_t start = begin; start < end; start += kBwdBatch) {
     if (__syncthreads_count(done) == kBlock) break;
-    const bool live = start + tid < end;
-    s_geo[tid] = live ? nxt.geo : make_float4(0.f, 0.f, 0.f, 0.f);
-    s_app[tid] = live ? nxt.app : make_float4(0.f, 0.f, 0.f, 0.f);
-    s_con[tid] = live ? nxt.con : make_float4(0.f, 0.f, 0.f, 0.f);
-    s_gid[tid] = nxt.gid;
-    __syncthreads();
-    const uint32_t i1 = start + kBlock + tid, i2 = start + 2 * kBlock + tid;
-    if (i1 < end) nxt = stage_load(a, g_after, x0, y0);
-    if (i2 < end) g_after = list_id(a, L, i2);
-    const int cnt = (int)min((uint32_t)kBlock, end - start);
+    const int st0 = (int)((start - begin) & (uint32_t)(kBwdStage - 1));  // the batch's first staged entry
+    if (st0 == 0 && start != begin) {
+      if (stager) stage(start);
+      __syncthreads();
+    }
+    const float4* const b_geo = s_geo + st0;
+    const float4* const b_app = s_app + st0;
+    const float4* const b_con = s_con + st0;
+    const uint32_t* const b_gid = s_gid + st0;
+    const int cnt = (int)min((uint32_t)kBwdBatch, end - start);
     const uint32_t pos0 = start - range.x;
-    for (int j = 0; j < cnt; j += kUnrollB) {
-      if (__ballot(!done) == 0ull) break;  // the whole wave has finished
-      float al[kUnrollB], Gv[kUnrollB], pw[kUnrollB], dxv[kUnrollB], dyv[kUnrollB];
-      float pxx[kUnrollB], pxy[kUnrollB], pyy[kUnrollB];
+    uint32_t hit = 0;  // wave-uniform
+    for (int j = 0; j < cnt; j += kBwdGroup) {
+      if (__builtin_amdgcn_ballot_w64(!done) == 0ull) break;  // the whole wave has finished
+      float q[4], qx[4], qy[4], w[4], e2[4];
+      uint32_t some = 0;
 #pragma unroll
-      for (int u = 0; u < kUnrollB; ++u) {
-        const float4 ge = s_geo[j + u];
-        const float4 ap = s_app[j + u];
-        dxv[u] = lx - ge.x;
-        dyv[u] = ly - ge.y;
-        pw[u] = splat_exponent_p(dxv[u], dyv[u], ge.z, ge.w, ap.x, pxx[u], pxy[u], pyy[u]);
-        al[u] = splat_alpha(pw[u], ap.y, amax, Gv[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < kUnrollB; ++u) {
-        if (j + u >= cnt) break;  // uniform
-        const float4 ap = s_app[j + u];
-        const float4 cn = s_con[j + u];
-        const float alpha = al[u];
-        const bool ok = !done && pw[u] <= 0.f && alpha >= amin;
-        const float w = ok ? alpha * T : 0.f;
+      for (int u = 0; u < kBwdGroup; ++u) {
+        const float4 ge = b_geo[j + u];
+        const float4 ap = b_app[j + u];
+        const float blue = b_con[j + u].w;
+        const float dx = lx - ge.x, dy = ly - ge.y;
+        const float p2 = splat_exponent(dx, dy, ge.z, ge.w, ap.x);
+        float G;
+        const float alpha = splat_alpha(p2, ap.y, amax, G);
+        const bool ok = !done && p2 <= 0.f && alpha >= amin && j + u < cnt;
+        w[u] = ok ? alpha * T : 0.f;
         // loss-weighted colour of this Gaussian: sum_c g_c colour_c
-        const float gc = __builtin_fmaf(g2, cn.w, __builtin_fmaf(g1, ap.w, g0 * ap.z));
+        const float gc = __builtin_fmaf(g2, blue, __builtin_fmaf(g1, ap.w, g0 * ap.z));
         const float T_before = T;
         T = ok ? one_minus_times(T, alpha) : T;
-        S = __builtin_fmaf(-w, gc, S);
+        S = __builtin_fmaf(-w[u], gc, S);
         done = done || (pos0 + (uint32_t)(j + u) + 1u >= last);
-        if (__ballot(ok) != 0ull) {  // the gradient terms only where some lane composited
-          const float G = Gv[u], dx = dxv[u], dy = dyv[u];
-          const float inv = __builtin_amdgcn_rcpf(1.f - alpha);
-          // dL/dalpha = T_before sum_c g_c colour_c - S / (1 - alpha)
-          const float dalpha = __builtin_fmaf(T_before, gc, -S * inv);
-          const bool unclamped = ok && ap.y * G < amax;
-          const float dop = unclamped ? G * dalpha : 0.f;
-          const float dpow = ap.y * dop;
-          const float hdp = -0.5f * dpow;
-          float v[9];
-          v[0] = (cn.x * dx + cn.y * dy) * dpow;
-          v[1] = (cn.y * dx + cn.z * dy) * dpow;
-          v[2] = pxx[u] * hdp;
-          v[3] = pxy[u] * (2.f * hdp);
-          v[4] = pyy[u] * hdp;
-          v[5] = dop;
-          v[6] = w * g0;
-          v[7] = w * g1;
-          v[8] = w * g2;
-          const uint32_t gid = __builtin_amdgcn_readfirstlane(s_gid[j + u]);  // uniform
-          if (touched != nullptr && lane_id() == 0) touched[gid] = 1u;  // composited at a sample
-          if constexpr (kDet) {
-            // the pair's index in vals (the deterministic backward takes single-segment lists)
-            const size_t rec = (size_t)(L.b1 + start + (uint32_t)(j + u)) * (kBlock / kWave) + (size_t)(tid / kWave);
-            wave_sum9_store(v, g2d + rec * 9, sl);
-          } else if constexpr (kDensity) {
-            constexpr float kTwoLn2 = 1.3862943611198906f;
-            const float dist = __builtin_sqrtf(fmaxf(-kTwoLn2 * pw[u], 0.f));
-            const float nx = hw * v[0], ny = hh * v[1];
-            const float v13[13] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8],
-                                   e_pix * w, w, dist * w, __builtin_sqrtf(nx * nx + ny * ny)};
-            wave_sum13_atomic(v13, g2d + (size_t)gid * 9, dens.stats, gid, dens.n, sl);
-          } else {
-            wave_sum9_atomic(v, g2d + (size_t)gid * 9, sl);
-          }
+        const float inv = __builtin_amdgcn_rcpf(1.f - alpha);
+        // dL/dalpha = T_before sum_c g_c colour_c - S / (1 - alpha)
+        const float dalpha = __builtin_fmaf(T_before, gc, -S * inv);
+        q[u] = ok && ap.y * G < amax ? G * dalpha : 0.f;  // clamped alphas pass nothing
+        qx[u] = q[u] * dx;
+        qy[u] = q[u] * dy;
+        if constexpr (kDensity) e2[u] = ok ? p2 : 0.f;
+        some |= __builtin_amdgcn_ballot_w64(ok) != 0ull ? 1u << u : 0u;
+      }
+      if (some == 0u) continue;  // wave-uniform: no pixel of the wave composited any of the four
+      hit |= some << j;
+      v4f m0 = {0.f, 0.f, 0.f, 0.f}, m1 = m0, m2 = m0, m3 = m0;
+      transpose2(tr, lane, q, qx, [&](int s, float x, float y) {
+        m0 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, b0[s], m0, 0, 0, 0);
+        m0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, e3, m0, 0, 0, 0);
+      });
+      transpose2(tr, lane, w, qy, [&](int s, float x, float y) {
+        m1 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, b0[s], m1, 0, 0, 0);
+        m2 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, bw[s], m2, 0, 0, 0);
+        if constexpr (kDensity) m1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, e3, m1, 0, 0, 0);
+      });
+      if constexpr (kDensity) {
+        // D w (D = the distance, sqrt(-2 power)) and the norm of the pixel's own centre gradient
+        constexpr float kTwoLn2 = 1.3862943611198906f;
+        float dw[4], nrm[4];
+#pragma unroll
+        for (int u = 0; u < kBwdGroup; ++u) {
+          const float4 cn = b_con[j + u];
+          const float opac = b_app[j + u].y;
+          dw[u] = __builtin_amdgcn_sqrtf(fmaxf(-kTwoLn2 * e2[u], 0.f)) * w[u];
+          const float nx = hw * ((cn.x * qx[u] + cn.y * qy[u]) * opac);
+          const float ny = hh * ((cn.y * qx[u] + cn.z * qy[u]) * opac);
+          nrm[u] = __builtin_amdgcn_sqrtf(nx * nx + ny * ny);
         }
+        transpose2(tr, lane, dw, nrm, [&](int, float x, float y) {
+          m3 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, col == 0 ? 1.f : 0.f, m3, 0, 0, 0);
+          m3 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, col == 1 ? 1.f : 0.f, m3, 0, 0, 0);
+        });
+      }
+      const float r0 = block_sums(m0), r1 = block_sums(m1), r2 = block_sums(m2);
+      const int quad = (lane >> 2) & 3, row = lane >> 4;
+      float val = quad == 0 ? r0 : (quad == 1 ? r1 : r2);
+      if constexpr (kDensity) {
+        const float r3 = block_sums(m3);
+        val = quad == 3 ? r3 : val;
+      }
+      if (kDensity || quad < 3)
+        s_tab[wave][(j + (((row & 1) << 1) | (row >> 1))) * kCols + quad * 4 + col] = val;
+    }
+    if (lane == 0) s_hit[wave] = hit;
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) any |= s_hit[v];
+    if (any == 0u) continue;  // workgroup-uniform
+    if (tid < kBwdBatch && (any >> tid) & 1u) {
+      // row of the table: sum q dx, q dx x, q dx y, q; q dy, q dy x, q dy y, w
+      // (density); w g0, w g1, w g2, w e; w D, |n|, -, -
+      float t[kCols];
+#pragma unroll
+      for (int k = 0; k < kCols; ++k) t[k] = 0.f;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        if (!((s_hit[v] >> tid) & 1u)) continue;
+        const float4* tb = reinterpret_cast<const float4*>(&s_tab[v][tid * kCols]);
+#pragma unroll
+        for (int k = 0; k < kCols / 4; ++k) {
+          const float4 x = tb[k];
+          t[4 * k] += x.x;
+          t[4 * k + 1] += x.y;
+          t[4 * k + 2] += x.z;
+          t[4 * k + 3] += x.w;
+        }
+      }
+      const float4 ge = b_geo[tid], cn = b_con[tid];
+      const float opac = b_app[tid].y;
+      const float cx = ge.x - 7.5f, cy = ge.y - 7.5f;  // centre relative to the tile's
+      const float sx = t[0], sy = t[4];
+      const float sxx = __builtin_fmaf(-cx, sx, t[1]), sxy = __builtin_fmaf(-cy, sx, t[2]);
+      const float syy = __builtin_fmaf(-cy, sy, t[6]);
+      float* fin = s_fin + tid * kFields;
+      fin[0] = opac * __builtin_fmaf(cn.x, sx, cn.y * sy);
+      fin[1] = opac * __builtin_fmaf(cn.y, sx, cn.z * sy);
+      fin[2] = -0.5f * opac * sxx;
+      fin[3] = -opac * sxy;
+      fin[4] = -0.5f * opac * syy;
+      fin[5] = t[3];
+      fin[6] = t[8];
+      fin[7] = t[9];
+      fin[8] = t[10];
+      if constexpr (kDensity) {
+        fin[9] = t[11];
+        fin[10] = t[7];
+        fin[11] = t[12];
+        fin[12] = t[13];
+      }
+      if (touched != nullptr) touched[b_gid[tid]] = 1u;  // composited at a sample
+    }
+    __syncthreads();
+    int e0 = tid;
+    asm volatile("" : "+v"(e0));  // keeps the entries' indices out of the registers that live over the walk
+#pragma unroll 1
+    for (int e = e0; e < kBwdBatch * kFields; e += kBlock) {
+      const int k = e / kFields, f = e - k * kFields;
+      if (!((any >> k) & 1u)) continue;
+      const float val = s_fin[e];
+      const uint32_t gid = b_gid[k];
+      if constexpr (kDet) {
+        // the pair's index in vals (the deterministic backward takes single-segment lists)
+        g2d[(size_t)(L.b1 + start + (uint32_t)k) * 9 + (size_t)f] = val;
+      } else if (val != 0.f) {
+        if (!kDensity || f < 9) unsafeAtomicAdd(&g2d[(size_t)gid * 9 + (size_t)f], val);
+        else if (gid < (uint32_t)dens.n) unsafeAtomicAdd(&dens.stats[(size_t)gid * 4 + (size_t)(f - 9)], val);
       }
     }
   }
@@ -572,17 +682,17 @@ __global__ void __launch_bounds__(kBlock) render_accum_kernel(RasterArgs a, cons
   __shared__ float s_opa[kBlock];
   __shared__ float s_cc[kBlock];
   __shared__ uint32_t s_gid[kBlock];
-  // the last chunk (the rest of the list, the longest walks) is dispatched
-  // first, so its workgroups run beside the fixed-length chunks
+  // the last chunks (the longest walks) are dispatched first, so their
+  // workgroups run beside the short ones
   const int slot = blockIdx.x, chunk = (int)gridDim.y - 1 - (int)blockIdx.y, tid = threadIdx.x;
   const int tile = kDense ? slot : a.valid_tiles[slot];
   const int tx = tile % a.tiles_x, ty = tile / a.tiles_x;
   const TileList L = tile_list(a, tile);
   const uint2 range = make_uint2(0u, L.len);
-  const uint32_t begin = range.x + (uint32_t)(chunk * TGS_RENDER_CHUNK_LEN);
+  const uint32_t begin = range.x + chunk_begin(chunk);
   if (begin >= range.y && chunk > 0) return;  // workgroup-uniform
   const uint32_t end =
-      chunk + 1 == (int)gridDim.y ? range.y : min(range.y, begin + (uint32_t)TGS_RENDER_CHUNK_LEN);
+      chunk + 1 == (int)gridDim.y ? range.y : min(range.y, range.x + chunk_begin(chunk + 1));
   const PixelSlot px = pixel_of<kBlock, kDense>(a, slot, tile, tid);
   const float lx = (float)(px.loc & 15), ly = (float)(px.loc >> 4);
   const float x0 = (float)(tx * kTile), y0 = (float)(ty * kTile);
@@ -600,7 +710,7 @@ __global__ void __launch_bounds__(kBlock) render_accum_kernel(RasterArgs a, cons
   }
   bool done = last <= begin - range.x;  // nothing composited from this chunk on
   float T = 1.f;
-  if (chunk > 0 && !done) T = state[((int64_t)slot * (TGS_RENDER_CHUNKS - 1) + chunk - 1) * kBlock + tid].x;
+  if (chunk > 0 && !done) T = state[((int64_t)slot * (kChunks - 1) + chunk - 1) * kBlock + tid].x;
 
   Staged nxt = {};
   uint32_t g_after = 0;
@@ -662,7 +772,7 @@ template <int kBlock, bool kDense>
 static void launch_bwd(const RasterArgs& a, int grid, const float* out, const uint32_t* ncontrib,
                        const float* dL, float* g2d, const float* state, uint8_t* touched, hipStream_t s,
                        const DensityArgs* dens = nullptr) {
-  const unsigned chunks = state != nullptr ? TGS_RENDER_CHUNKS : 1;
+  const unsigned chunks = state != nullptr ? kChunks : 1;
   if (dens != nullptr)
     hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, true>), dim3(grid, chunks), dim3(kBlock), 0, s, a,
                        (const float4*)out, ncontrib, (const float4*)dL, g2d, (const float4*)state, touched, *dens);
@@ -675,7 +785,7 @@ static void launch_bwd(const RasterArgs& a, int grid, const float* out, const ui
 template <int kBlock, bool kDense>
 static void launch_bwd_det(const RasterArgs& a, int grid, const float* out, const uint32_t* ncontrib,
                            const float* dL, float* partial, const float* state, uint8_t* touched, hipStream_t s) {
-  const unsigned chunks = state != nullptr ? TGS_RENDER_CHUNKS : 1;
+  const unsigned chunks = state != nullptr ? kChunks : 1;
   hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, false, true>), dim3(grid, chunks), dim3(kBlock), 0, s, a,
                      (const float4*)out, ncontrib, (const float4*)dL, partial, (const float4*)state, touched,
                      DensityArgs{});
@@ -689,13 +799,13 @@ __global__ void __launch_bounds__(256) zero_f32_kernel(float* __restrict__ p, in
 // Deterministic reduction of the partial records: a thread per Gaussian
 // visits the tiles of its rectangle in row-major order, finds its pair in
 // the tile's list by binary search on (depth bits, id) (the list's order),
-// and adds the pair's wave records in wave order; the total is added to
-// g2d once.  Any order would do; a fixed one gives the same bits on every
+// and adds the pair's record; the total is added to g2d once.  Any order
+// would do; a fixed one gives the same bits on every
 // run.
 __global__ void __launch_bounds__(256) det_reduce_kernel(const int4* __restrict__ rect, const float* __restrict__ depth,
                                                          const uint32_t* __restrict__ vals,
                                                          const uint2* __restrict__ ranges, int64_t n, int tiles_x,
-                                                         int tiles_y, int waves, const float* __restrict__ partial,
+                                                         int tiles_y, const float* __restrict__ partial,
                                                          float* __restrict__ g2d) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -718,9 +828,8 @@ __global__ void __launch_bounds__(256) det_reduce_kernel(const int4* __restrict_
         else hi = mid;
       }
       if (lo < rg.y && vals[lo] == id) {
-        const float* p = partial + (size_t)lo * waves * 9;
-        for (int w = 0; w < waves; ++w)
-          for (int f = 0; f < 9; ++f) acc[f] += p[w * 9 + f];
+        const float* p = partial + (size_t)lo * 9;
+        for (int f = 0; f < 9; ++f) acc[f] += p[f];
         any = true;
       }
     }
@@ -798,7 +907,7 @@ using namespace tgs;
 
 extern "C" size_t tgs_render_state_size(int32_t n_slots, int32_t max_per_tile) {
   if (n_slots < 0 || max_per_tile < 0 || max_per_tile > kTilePixels) return 0;
-  return (size_t)n_slots * (TGS_RENDER_CHUNKS - 1) * (size_t)raster_block(false, max_per_tile) * sizeof(float4);
+  return (size_t)n_slots * (kChunks - 1) * (size_t)raster_block(false, max_per_tile) * sizeof(float4);
 }
 
 static int32_t render_fwd_launch(const RasterArgs& a, bool dense, int32_t n_st, int32_t max_per_tile, float* out,
@@ -932,8 +1041,8 @@ extern "C" int32_t tgs_render_bwd2(const float* splat, const uint32_t* vals, con
 
 extern "C" size_t tgs_render_bwd_det_workspace_size(int64_t n_pairs, int32_t max_per_tile, int32_t dense) {
   if (n_pairs < 0 || max_per_tile < 0 || max_per_tile > kTilePixels) return 0;
-  const int waves = raster_block(dense != 0, max_per_tile) / kWave;
-  return (size_t)std::max<int64_t>(n_pairs, 1) * (size_t)waves * 9 * sizeof(float);
+  (void)dense;
+  return (size_t)std::max<int64_t>(n_pairs, 1) * 9 * sizeof(float);
 }
 
 extern "C" int32_t tgs_render_bwd_deterministic(const float* splat, const uint32_t* vals, const uint32_t* ranges,
@@ -960,8 +1069,7 @@ extern "C" int32_t tgs_render_bwd_deterministic(const float* splat, const uint32
   TGS_REQUIRE(ws_bytes >= need, "tgs_render_bwd_deterministic: workspace %zu bytes < %zu", ws_bytes, need);
   hipStream_t s = as_stream(stream);
   float* partial = (float*)ws;
-  const int waves = raster_block(dense, max_per_tile) / kWave;
-  const int64_t words = std::max<int64_t>(n_pairs, 1) * waves * 9;
+  const int64_t words = std::max<int64_t>(n_pairs, 1) * 9;
   hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(words, 256), 8192)), dim3(256), 0,
                      s, partial, words);
   if (dense) {
@@ -974,7 +1082,7 @@ extern "C" int32_t tgs_render_bwd_deterministic(const float* splat, const uint32
   }
   if (n > 0)
     hipLaunchKernelGGL(det_reduce_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, (const int4*)rect,
-                       depth, vals, (const uint2*)ranges, n, tiles_x, tiles_y, waves, partial, g2d);
+                       depth, vals, (const uint2*)ranges, n, tiles_x, tiles_y, partial, g2d);
   return hip_status("tgs_render_bwd_deterministic");
 }
 
@@ -1051,7 +1159,7 @@ static int32_t density_accumulate_launch(const RasterArgs& a, const int32_t* val
   TGS_REQUIRE(((uintptr_t)state & 15) == 0, "tgs_density_accumulate: state must be 16-byte aligned");
   hipStream_t s = as_stream(stream);
   if (n == 0) return hip_status("tgs_density_accumulate");
-  const unsigned chunks = state != nullptr ? TGS_RENDER_CHUNKS : 1;
+  const unsigned chunks = state != nullptr ? kChunks : 1;
   const float4* st = (const float4*)state;
 #define TGS_ACCUM(BLK, DENSE, GRID) \
   hipLaunchKernelGGL((render_accum_kernel<BLK, DENSE>), dim3(GRID, chunks), dim3(BLK), 0, s, a, ncontrib, err, n, \
