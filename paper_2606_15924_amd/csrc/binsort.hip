@@ -3,90 +3,45 @@
 // The per-tile Gaussian lists must follow (tile, FP32 depth bits, Gaussian
 // id) and hold only the (Gaussian, tile) pairs whose tile can composite: the
 // tile lies in the Gaussian's 3-sigma rectangle and its pixel-centre
-// rectangle meets the ellipse q(d) <= tau of the stored centre and conic.
+// rectangle meets the ellipse q(d) <= t of the stored centre and conic.
 // Row by row that is an interval of columns (row_span, FP64 with a fixed
 // operation order).  Rather than radix-sorting a 64-bit (tile, depth) key
 // with an id for every pair, the Gaussians are put in (depth, id) order once
-// (a 32-bit sort of n keys) and the pairs are emitted in that order; a
-// stable sort on the tile bits alone then yields the full order.  The pair
-// key is (tile << id_bits) | Gaussian id, usually 32 bits: the id bits only
-// ride along, since a stable sort never compares them.
+// (a 32-bit sort of n keys), and their row intervals, not the pairs, are
+// partitioned by tile row: a record (id, first column, last column) stands
+// for 4-5 pairs.  Each tile row's records, which are in depth order, are then
+// expanded straight into the tiles' lists.
 //
-//   count     a thread per Gaussian over its rectangle rows: kept pairs in
-//             valid tiles, depth key (Gaussians without a kept valid tile
-//             get a key above every depth), touched flag
-//   sort      LSD radix sort of (depth key, id) over n, one kernel per pass:
-//             stable, so ties keep id order; Gaussians with pairs come
-//             first; the last pass gathers rectangles and pair counts into
-//             depth order
-//   scan      exclusive scan of the counts -> pair offsets; the totals are
-//             read back once
-//   emit      a wave per 32 depth-ordered Gaussians walks their rows; each
-//             row's span (its valid columns, with a tile subset) is keyed
-//             and written contiguously after the rows before it
-//   sort      LSD radix sort of the pair keys on the tile bits only; the
-//             last pass writes the ids, the sorted keys and (if asked) the
-//             64-bit keys
-//   ranges    tile boundaries of the sorted keys -> [start, end) per tile
+//   sort      (depth, id) order of the Gaussians with a non-empty rectangle:
+//             LSD radix sort, the others dropped in its first pass (or, for
+//             few Gaussians, ranks by counting)
+//   count     a thread per depth position over its rectangle rows: the row
+//             intervals that hold a valid tile, counted per strip (a tile row,
+//             or 256 columns of one in wider grids) and block
+//   strips    per strip, the prefix of the blocks' counts and the totals; then
+//             the strips' first record, pair and block, and the pair count
+//   rows      the records, written to their strip in depth order
+//   hist      a workgroup per 512 records of one strip: pairs per column
+//             (a difference array, two LDS atomics per record)
+//   offsets   per strip, the prefix over its blocks of every column, from the
+//             tile's first pair on; the tiles' ranges
+//   place     a workgroup per 512 records again: each record's rank among
+//             the earlier records covering the column (a bit mask per column
+//             over the wave's 64 records), the id written to the list
 //
-// A radix pass is a stable counting sort over blocks of 256 x kItems keys:
-// per-block digit histograms, one scan of the digit-major histogram table,
-// and a scatter that ranks the block's keys (peer lanes of a digit found by
-// a ballot match; each wave owns a contiguous quarter of the block),
-// reorders them by digit in LDS and writes runs of equal digits to
-// consecutive addresses.
+// Sorting row records instead of pairs moves 8 bytes per 4-5 pairs through
+// the partition and writes each pair once; the pair-wise form (emit keys, two
+// radix passes with their histograms, find the tile boundaries) moved every
+// pair six times.  300k Gaussians, 1296 x 840, 5.7M pairs: 216 -> 159 us; 1.5M
+// Gaussians, 1600 x 1060, 42M pairs: 745 -> 461 us.
 #include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdint>
-#include <utility>
 
 #include "scan.h"
 
 namespace tgs {
-
-// Zeroes two arrays in one launch: [0, n0) of p0, then [0, n1) of p1.
-__global__ void __launch_bounds__(256) zero2_u32_kernel(uint32_t* __restrict__ p0, int64_t n0,
-                                                        uint32_t* __restrict__ p1, int64_t n1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n0) p0[i] = 0u;
-  else if (i - n0 < n1) p1[i - n0] = 0u;
-}
-
-__global__ void __launch_bounds__(64) copy_counts_kernel(const unsigned long long* __restrict__ src,
-                                                         unsigned long long* __restrict__ dst) {
-  if (threadIdx.x < 2) dst[threadIdx.x] = src[threadIdx.x];
-}
-
-// Sums the count kernel's partial totals (one wave): counts[0] = pairs in
-// valid tiles, counts[1] = all pairs, and the number of pairs the pair sort
-// takes: all of them when they fit the capacity, else none.
-__global__ void __launch_bounds__(64) totals_kernel(const unsigned long long* __restrict__ slots, int64_t capacity,
-                                                    unsigned long long* __restrict__ counts,
-                                                    uint32_t* __restrict__ eff_total) {
-  const int i = threadIdx.x;
-  unsigned long long v = 0, a = 0;
-  for (int q = i; q < TGS_COUNTER_SLOTS; q += 64) {
-    v += slots[q];
-    a += slots[TGS_COUNTER_SLOTS + q];
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    v += __shfl_down(v, o, 64);
-    a += __shfl_down(a, o, 64);
-  }
-  if (i == 0) {
-    counts[0] = v;
-    counts[1] = a;
-    counts[3] = a;  // kept when a depth-prefix call replaces counts[1]
-    *eff_total = a <= (unsigned long long)capacity ? (uint32_t)a : 0u;
-  }
-}
-
-// The prefix call's three counts: lists' length, pairs emitted, whole-list pairs.
-__global__ void __launch_bounds__(64) copy_counts3_kernel(const unsigned long long* __restrict__ src,
-                                                          unsigned long long* __restrict__ dst) {
-  if (threadIdx.x < 3) dst[threadIdx.x] = src[threadIdx.x == 2 ? 3 : threadIdx.x];
-}
 
 // ------------------------------------------------------------------ scans
 template <typename T>
@@ -153,8 +108,6 @@ static void exclusive_scan(const T* in, T* out, int64_t n, T* partials, hipStrea
 void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials, hipStream_t s) {
   exclusive_scan<uint32_t>(in, out, n, partials, s);
 }
-
-
 
 // ------------------------------------------------------------------ row spans
 // Depth key of a Gaussian without pairs: above every finite positive depth bit pattern.
@@ -248,354 +201,13 @@ __device__ __forceinline__ void row_span(const RowEllipse& e, int ty, int rx0, i
   hi = (int)fmin(fmax(h, (double)(rx0 - 1)), (double)(rx1 - 1));
 }
 
-// Inclusive max-scan over the wave (identity -1): DPP shifts inside rows of
-// 16, then the row broadcasts.
-__device__ __forceinline__ int wave_max_scan(int v) {
-  v = max(v, dpp_i<0x111>(-1, v));  // row_shr:1
-  v = max(v, dpp_i<0x112>(-1, v));  // row_shr:2
-  v = max(v, dpp_i<0x114>(-1, v));  // row_shr:4
-  v = max(v, dpp_i<0x118>(-1, v));  // row_shr:8
-  v = max(v, dpp_i<kDppRowBcast15, 0xa>(-1, v));
-  v = max(v, dpp_i<kDppRowBcast31, 0xc>(-1, v));
-  return v;
-}
-
-// ------------------------------------------------------------------ count
-// Depth sort blocks (see depth_pass_kernel): 256 threads x 8 keys, 256 digits.
-constexpr int kDepthItems = 8;
-constexpr int kDepthBlockKeys = 256 * kDepthItems;
-constexpr int kDepthDigits = 256;
-
-// One wave per 64 Gaussians (in index order).  Their rectangle rows are
-// flattened Gaussian by Gaussian and handed out 64 per round, so every lane
-// evaluates a row span whatever the rectangles' heights; a Gaussian whose
-// first row falls in the round marks its slot and an inclusive max-scan
-// carries each owner to the following slots.  Per Gaussian: kept pairs in
-// valid tiles (every kept pair when there is no tile subset), summed by LDS
-// atomics; then the depth key (Gaussians without a kept valid tile get a key
-// above every depth), pair count and touched flag.
-constexpr int kCountBatch = kWave;  // Gaussians per wave (32 measured slower)
-
-struct CountBatch {
-  int4 rect[kWave];
-  uint32_t row0[kWave];  // exclusive prefix of the row counts in the batch
-  RowEllipse ell[kWave];
-  int mark[kWave];
-  uint32_t valid[kWave];
-};
-
-// ids == nullptr: Gaussian i of the index order (rect, depth by index),
-// writing the depth keys.  ids != nullptr: position i of the depth order
-// (rect is then the sorted rectangles, ids the Gaussians), writing only the
-// counts by position (emit_cnt) and the touched flags.
-__global__ void __launch_bounds__(kWave) count_kernel(
-    const int4* __restrict__ rect, const uint32_t* __restrict__ ids, const float4* __restrict__ splat,
-    const float* __restrict__ depth, int64_t n, const int32_t* __restrict__ tile_slot, int tiles_x, int tiles_y,
-    double tau, double lia, uint32_t* __restrict__ dkeys, uint32_t* __restrict__ dvals,
-    uint32_t* __restrict__ emit_cnt, uint8_t* __restrict__ touched, unsigned long long* __restrict__ totals) {
-  __shared__ CountBatch cb;
-  __shared__ uint64_t s_red[1];
-  const int lane = lane_id();
-  const int64_t i = (int64_t)blockIdx.x * kCountBatch + lane;
-  const bool mine = lane < kCountBatch && i < n;
-  int4 r = make_int4(0, 0, 0, 0);
-  uint32_t g = (uint32_t)i;
-  if (mine) {
-    r = clamp_rect(rect[i], tiles_x, tiles_y);
-    if (ids != nullptr) g = ids[i];
-  }
-  const uint32_t rows = r.z > r.x ? (uint32_t)(r.w - r.y) : 0u;
-  const uint32_t incl = wave_inclusive_scan_u32(rows);
-  const uint32_t my_row0 = incl - rows;
-  const uint32_t n_rows = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-  cb.rect[lane] = r;
-  cb.row0[lane] = my_row0;
-  cb.valid[lane] = 0u;
-  if (rows > 0) cb.ell[lane] = load_row_ellipse(splat, g, tau, lia);
-  int carry = -1;
-  for (uint32_t f0 = 0; f0 < n_rows; f0 += kWave) {
-    cb.mark[lane] = -1;
-    __syncthreads();
-    if (rows > 0 && my_row0 >= f0 && my_row0 - f0 < (uint32_t)kWave) cb.mark[my_row0 - f0] = lane;
-    __syncthreads();
-    const int jl = max(wave_max_scan(cb.mark[lane]), carry);
-    carry = __builtin_amdgcn_readlane(jl, kWave - 1);
-    const uint32_t f = f0 + (uint32_t)lane;
-    // jl >= 0 whenever f < n_rows: the first Gaussian with rows starts at row 0
-    if (f < n_rows && jl >= 0) {
-      const int4 rj = cb.rect[jl];
-      const int ty = rj.y + (int)(f - cb.row0[jl]);
-      int lo, hi;
-      row_span(cb.ell[jl], ty, rj.x, rj.z, lo, hi);
-      uint32_t cv = (uint32_t)max(hi - lo + 1, 0);
-      if (tile_slot != nullptr) {
-        cv = 0u;
-        const int32_t* trow = tile_slot + (int64_t)ty * tiles_x;
-        for (int tx = lo; tx <= hi; ++tx) cv += trow[tx] >= 0 ? 1u : 0u;
-      }
-      if (cv > 0) atomicAdd(&cb.valid[jl], cv);
-    }
-    __syncthreads();  // the round's reads and sums before the next round's writes
-  }
-  __syncthreads();
-  const uint32_t valid = cb.valid[lane];
-  if (mine) {
-    if (ids == nullptr) {
-      dkeys[i] = valid > 0 ? __float_as_uint(depth[i]) : kCulledKey;
-      dvals[i] = (uint32_t)i;
-    }
-    emit_cnt[i] = valid;  // only the valid tiles are listed
-    if (touched != nullptr && valid > 0) touched[g] = 1;
-  }
-  // 64-bit totals, spread over slots: [0] pairs in valid tiles, [1] pairs
-  // listed (the same count: the lists hold the valid tiles only)
-  const uint64_t v2[2] = {valid, valid};
-  for (int k = 0; k < 2; ++k) {
-    uint64_t tot;
-    block_exclusive_scan<kWave, uint64_t>(v2[k], s_red, &tot);
-    if (lane == 0 && tot > 0)
-      atomicAdd(&totals[k * TGS_COUNTER_SLOTS + (blockIdx.x & (TGS_COUNTER_SLOTS - 1))], (unsigned long long)tot);
-  }
-}
-
-// Depth keys of the depth-prefix call, before any count: a Gaussian with a
-// non-empty rectangle is keyed by its depth, the others sort last; the
-// number of keyed Gaussians goes to the 64-bit slots of row 2.
-__global__ void __launch_bounds__(256) key_kernel(const int4* __restrict__ rect, const float* __restrict__ depth,
-                                                  int64_t n, int tiles_x, int tiles_y, uint32_t* __restrict__ dkeys,
-                                                  uint32_t* __restrict__ dvals,
-                                                  unsigned long long* __restrict__ totals) {
-  __shared__ uint64_t s_red[1];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  bool keyed = false;
-  if (i < n) {
-    const int4 r = clamp_rect(rect[i], tiles_x, tiles_y);
-    keyed = r.z > r.x && r.w > r.y;
-    dkeys[i] = keyed ? __float_as_uint(depth[i]) : kCulledKey;
-    dvals[i] = (uint32_t)i;
-  }
-  uint64_t tot;
-  block_exclusive_scan<256, uint64_t>(keyed ? 1ull : 0ull, s_red, &tot);
-  if (threadIdx.x == 0 && tot > 0)
-    atomicAdd(&totals[2 * TGS_COUNTER_SLOTS + (blockIdx.x & (TGS_COUNTER_SLOTS - 1))], (unsigned long long)tot);
-}
-
-// The depth-prefix call's counts from the slots: counts[0] = pairs of the
-// prefix in valid tiles, counts[1] = its pairs (the capacity it needs; the
-// sort takes them when they fit), counts[3] = an estimate of the whole
-// lists' pairs for sizing a continuation: the prefix's pairs per Gaussian
-// times the keyed Gaussians (exact when the prefix holds them all; the
-// nearest Gaussians cover the most tiles, so it tends to exceed the count).
-__global__ void __launch_bounds__(64) prefix_totals_kernel(const unsigned long long* __restrict__ slots, int64_t m,
-                                                           int64_t capacity, unsigned long long* __restrict__ counts,
-                                                           uint32_t* __restrict__ eff_total) {
-  const int i = threadIdx.x;
-  unsigned long long v = 0, a = 0, k = 0;
-  for (int q = i; q < TGS_COUNTER_SLOTS; q += 64) {
-    v += slots[q];
-    a += slots[TGS_COUNTER_SLOTS + q];
-    k += slots[2 * TGS_COUNTER_SLOTS + q];
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    v += __shfl_down(v, o, 64);
-    a += __shfl_down(a, o, 64);
-    k += __shfl_down(k, o, 64);
-  }
-  if (i == 0) {
-    counts[0] = v;
-    counts[1] = a;
-    const unsigned long long mk = (unsigned long long)(m < (int64_t)k ? m : (int64_t)k);
-    counts[3] = mk >= k || mk == 0 ? a : (unsigned long long)ceil((double)a * (double)k / (double)mk);
-    *eff_total = a <= (unsigned long long)capacity ? (uint32_t)a : 0u;
-  }
-}
-
-// Per tile row, the running count of flagged tiles: rowc[y * (tiles_x + 1)
-// + x] = flagged tiles among columns < x of row y (a wave per row, 64
-// columns per scan).  Nothing to do when no tile is flagged.
-__global__ void __launch_bounds__(kWave) flag_rows_kernel(const int32_t* __restrict__ flag_slot, int tiles_x,
-                                                          const uint32_t* __restrict__ n_flagged,
-                                                          uint32_t* __restrict__ rowc) {
-  if (n_flagged != nullptr && *n_flagged == 0u) return;
-  const int y = blockIdx.x, lane = lane_id();
-  const int64_t W1 = tiles_x + 1;
-  uint32_t carry = 0;
-  if (lane == 0) rowc[y * W1] = 0u;
-  for (int x0 = 0; x0 < tiles_x; x0 += kWave) {
-    const int x = x0 + lane;
-    const uint32_t f = x < tiles_x && flag_slot[(int64_t)y * tiles_x + x] >= 0 ? 1u : 0u;
-    const uint32_t incl = carry + wave_inclusive_scan_u32(f);
-    if (x < tiles_x) rowc[y * W1 + x + 1] = incl;
-    carry = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-  }
-}
-
-// The summed-area table of the flagged tiles: sat[y * (tiles_x + 1) + x] =
-// flagged tiles in rows < y and columns < x, (tiles_y + 1) x (tiles_x + 1)
-// entries built in LDS by one workgroup (row scans by the waves, then a
-// column pass per thread).  Nothing to do when no tile is flagged.
-constexpr int kSatWords = 12288;  // LDS words: grids up to this many (tiles_x + 1) (tiles_y + 1)
-
-__global__ void __launch_bounds__(1024) flag_sat_kernel(const int32_t* __restrict__ flag_slot, int tiles_x,
-                                                        int tiles_y, const uint32_t* __restrict__ n_flagged,
-                                                        uint32_t* __restrict__ sat) {
-  __shared__ uint32_t t[kSatWords];
-  if (n_flagged != nullptr && *n_flagged == 0u) return;  // workgroup-uniform
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  const int W1 = tiles_x + 1, words = (tiles_y + 1) * W1;
-  for (int x = tid; x < W1; x += 1024) t[x] = 0u;
-  for (int y = wave; y < tiles_y; y += 1024 / kWave) {
-    uint32_t carry = 0;
-    if (lane == 0) t[(y + 1) * W1] = 0u;
-    for (int x0 = 0; x0 < tiles_x; x0 += kWave) {
-      const int x = x0 + lane;
-      const uint32_t f = x < tiles_x && flag_slot[(int64_t)y * tiles_x + x] >= 0 ? 1u : 0u;
-      const uint32_t incl = carry + wave_inclusive_scan_u32(f);
-      if (x < tiles_x) t[(y + 1) * W1 + x + 1] = incl;
-      carry = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-    }
-  }
-  __syncthreads();
-  // column prefix: a wave scans each of its columns, 64 rows at a time
-  for (int x = wave; x < W1; x += 1024 / kWave) {
-    uint32_t carry = 0;
-    for (int y0 = 0; y0 <= tiles_y; y0 += kWave) {
-      const int y = y0 + lane;
-      const uint32_t incl = carry + wave_inclusive_scan_u32(y <= tiles_y ? t[y * W1 + x] : 0u);
-      if (y <= tiles_y) t[y * W1 + x] = incl;
-      carry = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < words; i += 1024) sat[i] = t[i];
-}
-
-// Continuation counts: one wave per 64 Gaussians of the depth order from a
-// given rank on (their rectangles, ids and, when known, first-pass pair
-// counts in that order).  Per Gaussian: its kept pairs in the flagged tiles (tile map
-// entry >= 0), by the same row spans.  Gaussians without pairs in the first
-// pass, or whose rectangle holds no flagged tile (four reads of the
-// summed-area table, or two reads of the row counts per rectangle row, when
-// given), are skipped before their splat is read; the whole call is skipped
-// when no tile is flagged (every count 0).
-// The sum goes to the 64-bit totals (both slots).
-__global__ void __launch_bounds__(kWave) count_cont_kernel(
-    const int4* __restrict__ rect_sorted, const uint32_t* __restrict__ ids_sorted,
-    const uint32_t* __restrict__ cnt_sorted, int64_t m, const float4* __restrict__ splat,
-    const int32_t* __restrict__ flag_slot, const uint32_t* __restrict__ n_flagged,
-    const uint32_t* __restrict__ rowc, const uint32_t* __restrict__ sat, int tiles_x, int tiles_y, double tau,
-    double lia, uint32_t* __restrict__ cnt, unsigned long long* __restrict__ totals) {
-  __shared__ CountBatch cb;
-  __shared__ uint64_t s_red[1];
-  const int lane = lane_id();
-  const int64_t k = (int64_t)blockIdx.x * kCountBatch + lane;
-  if (n_flagged != nullptr && *n_flagged == 0u) {  // workgroup-uniform
-    if (k < m) cnt[k] = 0u;
-    return;
-  }
-  bool mine = k < m && (cnt_sorted == nullptr || cnt_sorted[k] > 0);
-  int4 r = make_int4(0, 0, 0, 0);
-  uint32_t g = 0;
-  if (mine) {
-    r = clamp_rect(rect_sorted[k], tiles_x, tiles_y);
-    if (sat != nullptr || rowc != nullptr) {
-      const int64_t W1 = tiles_x + 1;
-      uint32_t f = 0u;
-      if (sat != nullptr)
-        f = (sat[r.w * W1 + r.z] - sat[r.y * W1 + r.z]) - (sat[r.w * W1 + r.x] - sat[r.y * W1 + r.x]);
-      else
-        for (int y = r.y; y < r.w && f == 0u; ++y) f = rowc[y * W1 + r.z] - rowc[y * W1 + r.x];
-      if (f == 0u) {
-        mine = false;
-        r = make_int4(0, 0, 0, 0);
-      }
-    }
-    if (mine) g = ids_sorted[k];
-  }
-  const uint32_t rows = r.z > r.x ? (uint32_t)(r.w - r.y) : 0u;
-  const uint32_t incl = wave_inclusive_scan_u32(rows);
-  const uint32_t my_row0 = incl - rows;
-  const uint32_t n_rows = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-  cb.rect[lane] = r;
-  cb.row0[lane] = my_row0;
-  cb.valid[lane] = 0u;
-  if (rows > 0) cb.ell[lane] = load_row_ellipse(splat, g, tau, lia);
-  int carry = -1;
-  for (uint32_t f0 = 0; f0 < n_rows; f0 += kWave) {
-    cb.mark[lane] = -1;
-    __syncthreads();
-    if (rows > 0 && my_row0 >= f0 && my_row0 - f0 < (uint32_t)kWave) cb.mark[my_row0 - f0] = lane;
-    __syncthreads();
-    const int jl = max(wave_max_scan(cb.mark[lane]), carry);
-    carry = __builtin_amdgcn_readlane(jl, kWave - 1);
-    const uint32_t f = f0 + (uint32_t)lane;
-    if (f < n_rows && jl >= 0) {
-      const int4 rj = cb.rect[jl];
-      const int ty = rj.y + (int)(f - cb.row0[jl]);
-      int lo, hi;
-      row_span(cb.ell[jl], ty, rj.x, rj.z, lo, hi);
-      uint32_t cv = 0u;
-      const int32_t* trow = flag_slot + (int64_t)ty * tiles_x;
-      for (int tx = lo; tx <= hi; ++tx) cv += trow[tx] >= 0 ? 1u : 0u;
-      if (cv > 0) atomicAdd(&cb.valid[jl], cv);
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-  const uint32_t valid = cb.valid[lane];
-  if (k < m) cnt[k] = valid;
-  uint64_t tot;
-  block_exclusive_scan<kWave, uint64_t>((uint64_t)valid, s_red, &tot);
-  if (lane == 0 && tot > 0)
-    for (int q = 0; q < 2; ++q)
-      atomicAdd(&totals[q * TGS_COUNTER_SLOTS + (blockIdx.x & (TGS_COUNTER_SLOTS - 1))], (unsigned long long)tot);
-}
-
-// ------------------------------------------------------------------ ranges
-// A workgroup takes 256 x kRangeItems consecutive sorted pairs: their tile
-// ids are loaded coalesced into LDS (with the one before the block), then
-// each position is compared with its predecessor.  A tile boundary writes
-// the start of the new tile and the end of the previous one, the last pair
-// the end of its tile (a tile id >= n_t, which no list emits, would write
-// nothing); empty tiles keep the [0, 0) of the fill.
-constexpr int kRangeItems = 8;
-constexpr int kRangeBlock = 256 * kRangeItems;
-
-template <typename K>
-__global__ void __launch_bounds__(256) ranges_kernel(const K* __restrict__ keys, uint32_t total_arg,
-                                                     const uint32_t* __restrict__ total_dev, int id_bits,
-                                                     uint32_t n_t, uint2* __restrict__ ranges) {
-  const uint32_t total = total_dev != nullptr ? *total_dev : total_arg;  // the device count when given
-  __shared__ uint32_t s_t[kRangeBlock + 1];  // s_t[0]: the pair before the block
-  const uint32_t b0 = blockIdx.x * (uint32_t)kRangeBlock;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < kRangeItems; ++k) {
-    const uint32_t i = b0 + (uint32_t)(k * 256 + tid);
-    s_t[1 + k * 256 + tid] = i < total ? (uint32_t)(keys[i] >> id_bits) : 0xffffffffu;
-  }
-  if (tid == 0) s_t[0] = b0 > 0 ? (uint32_t)(keys[b0 - 1] >> id_bits) : 0xffffffffu;
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kRangeItems; ++k) {
-    const int l = k * 256 + tid;
-    const uint32_t i = b0 + (uint32_t)l;
-    if (i >= total) break;
-    const uint32_t t = s_t[1 + l], tp = s_t[l];
-    if (i == 0 || t != tp) {
-      if (t < n_t) ranges[t].x = i;
-      if (i > 0 && tp < n_t) ranges[tp].y = i;
-    }
-    if (i == total - 1 && t < n_t) ranges[t].y = total;
-  }
-}
-
-// ------------------------------------------------------------------ radix sort
+// ------------------------------------------------------------------ depth sort
+// Blocks of 256 threads x 8 keys, 256 digits.
 constexpr int kSortThreads = 256;
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kPairItems = 16;  // keys per thread of the pair sort
-
-static int64_t sort_blocks(int64_t n, int items) { return ceil_div(n, (int64_t)kSortThreads * items); }
+constexpr int kDepthItems = 8;
+constexpr int kDepthBlockKeys = kSortThreads * kDepthItems;
+constexpr int kDepthDigits = 256;
 
 __device__ __forceinline__ uint64_t lanes_below() {
   const int lane = lane_id();
@@ -617,34 +229,60 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid, uint64_t
   return peers;
 }
 
-// Per-block histogram: block b covers keys [b * 256 * kItems, ...), wave w
-// the contiguous quarter w of it, 64 keys per round.
-template <typename K, int kBits, int kItems>
-__global__ void __launch_bounds__(kSortThreads) radix_hist_kernel(const K* __restrict__ keys, uint32_t n_arg,
-                                                                 const uint32_t* __restrict__ n_dev, int shift,
-                                                                 int nblocks, uint32_t* __restrict__ hist) {
-  const uint32_t n = n_dev != nullptr ? *n_dev : n_arg;  // the device count when given
-  // blocks past the count (a grid sized by the capacity) leave their entries
-  // unwritten: the scan and the scatter stop at the last block that holds keys
-  if (n_dev != nullptr && (int64_t)blockIdx.x * kSortThreads * kItems >= (int64_t)n) return;
-  constexpr int kDigits = 1 << kBits;
-  __shared__ uint32_t h[kDigits];
-  for (int i = threadIdx.x; i < kDigits; i += kSortThreads) h[i] = 0;
-  const int lane = lane_id(), wave = threadIdx.x / kWave;
-  const int64_t wbase = (int64_t)blockIdx.x * kSortThreads * kItems + (int64_t)wave * kWave * kItems;
-  K key[kItems];
+// Depth key of Gaussian i: its depth bits when its rectangle holds a tile
+// (below kCulledKey also for a NaN depth), else kCulledKey.
+__device__ __forceinline__ uint32_t depth_key(int4 r, float depth) {
+  if (!(r.z > r.x && r.w > r.y)) return kCulledKey;
+  return min(__float_as_uint(depth), kCulledKey - 1u);
+}
+
+// The depth keys, the first pass's digit counts of every block (culled
+// Gaussians left out), and, when rects is given, the clamped rectangles (a
+// depth-prefix call keeps them for its continuation).
+__global__ void __launch_bounds__(kSortThreads) key_kernel(const int4* __restrict__ rect,
+                                                           const float* __restrict__ depth, uint32_t n, int tiles_x,
+                                                           int tiles_y, int stride, uint32_t* __restrict__ dkeys,
+                                                           uint32_t* __restrict__ hist, int4* __restrict__ rects) {
+  __shared__ uint32_t h[kDepthDigits];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+  const int64_t b0 = (int64_t)blockIdx.x * kDepthBlockKeys;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t i = wbase + k * kWave + lane;
-    key[k] = i < n ? keys[i] : (K)0;
+  for (int k = 0; k < kDepthItems; ++k) {
+    const int64_t i = b0 + k * kSortThreads + threadIdx.x;
+    if (i >= (int64_t)n) continue;
+    const int4 r = clamp_rect(rect[i], tiles_x, tiles_y);
+    const uint32_t key = depth_key(r, depth[i]);
+    dkeys[i] = key;
+    if (rects != nullptr) rects[i] = r;
+    if (key != kCulledKey) atomicAdd(&h[key & (kDepthDigits - 1u)], 1u);
+  }
+  __syncthreads();
+  hist[(int64_t)threadIdx.x * stride + blockIdx.x] = h[threadIdx.x];
+}
+
+// Digit counts of every block of the later passes (over the *n keys left).
+__global__ void __launch_bounds__(kSortThreads) depth_hist_kernel(const uint32_t* __restrict__ keys,
+                                                                  const uint32_t* __restrict__ n_dev, int shift,
+                                                                  int stride, uint32_t* __restrict__ hist) {
+  const uint32_t n = *n_dev;
+  const int64_t b0 = (int64_t)blockIdx.x * kDepthBlockKeys;
+  if (b0 >= (int64_t)n) return;  // the scan and the scatter stop at the last block that holds keys
+  __shared__ uint32_t h[kDepthDigits];
+  h[threadIdx.x] = 0u;
+  uint32_t key[kDepthItems];
+#pragma unroll
+  for (int k = 0; k < kDepthItems; ++k) {
+    const int64_t i = b0 + k * kSortThreads + threadIdx.x;
+    key[k] = i < (int64_t)n ? keys[i] : 0u;
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kItems; ++k)
-    if (wbase + k * kWave + lane < n) atomicAdd(&h[(uint32_t)(key[k] >> shift) & (kDigits - 1u)], 1u);
+  for (int k = 0; k < kDepthItems; ++k)
+    if (b0 + k * kSortThreads + threadIdx.x < (int64_t)n)
+      atomicAdd(&h[(key[k] >> shift) & (kDepthDigits - 1u)], 1u);
   __syncthreads();
-  for (int dg = threadIdx.x; dg < kDigits; dg += kSortThreads)
-    hist[(int64_t)dg * nblocks + blockIdx.x] = h[dg];
+  hist[(int64_t)threadIdx.x * stride + blockIdx.x] = h[threadIdx.x];
 }
 
 // One workgroup per digit: exclusive prefix of the digit's per-block counts
@@ -669,145 +307,19 @@ __global__ void __launch_bounds__(1024) digit_scan_kernel(const uint32_t* __rest
   if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
 }
 
-// Output of a scatter pass: the keys (and values) for the next pass; in the
-// last pass of the pair sort also the Gaussian ids carried in the low key
-// bits and optionally the 64-bit (tile << 32) | depth-bits keys.
-struct ScatterOut {
-  void* keys;
-  uint32_t* vals;
-  int id_bits;           // final pass: key = (tile << id_bits) | id
-  const float* depth;    // final pass, for keys64
-  uint64_t* keys64;      // final pass, nullable
-};
-
-template <typename K, bool kVals, bool kFinal, int kBits, int kItems>
-__global__ void __launch_bounds__(kSortThreads) radix_scatter_kernel(
-    const K* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t n_arg,
-    const uint32_t* __restrict__ n_dev, int shift, int nblocks, const uint32_t* __restrict__ offs,
-    const uint32_t* __restrict__ dtot, ScatterOut o) {
-  const uint32_t n = n_dev != nullptr ? *n_dev : n_arg;  // the device count when given
-  constexpr int kDigits = 1 << kBits;
-  constexpr int kBlockKeys = kSortThreads * kItems;
-  if ((int64_t)blockIdx.x * kBlockKeys >= (int64_t)n) return;  // past the keys: nothing to place
-  __shared__ uint32_t s_cnt[kSortWaves][kDigits];  // per-wave digit counts, then block-local offsets
-  __shared__ uint32_t s_gbase[kDigits];            // global position of block-local position 0 of the digit
-  __shared__ K s_keys[kBlockKeys];
-  __shared__ uint32_t s_vals[kVals ? kBlockKeys : 1];
-  __shared__ uint32_t s_red[kSortWaves];
-  __shared__ uint64_t s_mask[kSortWaves][kDigits];
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  for (int i = tid; i < kSortWaves * kDigits; i += kSortThreads) (&s_cnt[0][0])[i] = 0;
-  const int64_t blk0 = (int64_t)blockIdx.x * kBlockKeys;
-  const int64_t wbase = blk0 + (int64_t)wave * kWave * kItems;
-  K key[kItems];
-  uint32_t val[kItems];
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int64_t i = wbase + k * kWave + lane;
-    key[k] = i < n ? keys_in[i] : (K)0;
-    if (kVals) val[k] = i < n ? vals_in[i] : 0u;
-  }
-  __syncthreads();
-  // rank of each key among the wave's keys of the same digit (stable: by
-  // round, then lane); the wave's running counts live in s_cnt[wave]
-  const uint64_t below = lanes_below();
-  uint32_t rank[kItems];
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const bool valid = wbase + k * kWave + lane < n;
-    const uint32_t d = (uint32_t)(key[k] >> shift) & (kDigits - 1u);
-    const uint64_t peers = digit_peers(d, valid, s_mask[wave]);
-    const uint32_t r = (uint32_t)__popcll(peers & below);
-    const uint32_t before = valid ? s_cnt[wave][d] : 0u;
-    rank[k] = before + r;
-    if (valid && r == 0) s_cnt[wave][d] = before + (uint32_t)__popcll(peers);
-  }
-  __syncthreads();
-  // block-local start of each (digit, wave) and the digit's global base
-  uint32_t pre[kSortWaves];
-  uint32_t tot = 0;
-  if (tid < kDigits)
-    for (int w = 0; w < kSortWaves; ++w) {
-      pre[w] = tot;
-      tot += s_cnt[w][tid];
-    }
-  uint32_t all;
-  const uint32_t lstart = block_exclusive_scan<kSortThreads, uint32_t>(tid < kDigits ? tot : 0u, s_red, &all);
-  const uint32_t gstart =
-      block_exclusive_scan<kSortThreads, uint32_t>(tid < kDigits ? dtot[tid] : 0u, s_red, &all);
-  if (tid < kDigits) {
-    for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = lstart + pre[w];
-    s_gbase[tid] = gstart + offs[(int64_t)tid * nblocks + blockIdx.x] - lstart;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    if (wbase + k * kWave + lane < n) {
-      const uint32_t d = (uint32_t)(key[k] >> shift) & (kDigits - 1u);
-      const uint32_t lp = s_cnt[wave][d] + rank[k];
-      if (lp < (uint32_t)kBlockKeys) {  // always (ranks are a permutation); a safeguard
-        s_keys[lp] = key[k];
-        if (kVals) s_vals[lp] = val[k];
-      }
-    }
-  }
-  __syncthreads();
-  // runs of equal digits go to consecutive addresses
-  const int count = (int)min((int64_t)kBlockKeys, (int64_t)n - blk0);
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const int lp = k * kSortThreads + tid;
-    if (lp < count) {
-      const K kk = s_keys[lp];
-      const uint32_t dst = s_gbase[(uint32_t)(kk >> shift) & (kDigits - 1u)] + (uint32_t)lp;
-      if (dst >= n) continue;  // never taken for a consistent table; keeps every write in bounds
-      ((K*)o.keys)[dst] = kk;
-      if (kFinal) {
-        // the Gaussian id: the payload, or the low key bits when it rides in the key
-        const uint32_t g = kVals ? s_vals[lp] : (uint32_t)(kk & (((K)1 << o.id_bits) - 1));
-        o.vals[dst] = g;
-        if (o.keys64 != nullptr)
-          o.keys64[dst] = ((uint64_t)(kk >> o.id_bits) << 32) | (uint64_t)__float_as_uint(o.depth[g]);
-      } else if (kVals) {
-        o.vals[dst] = s_vals[lp];
-      }
-    }
-  }
-}
-
-// ------------------------------------------------------------------ depth sort
-// The depth sort (four 8-bit passes over n keys with ids) takes three
-// kernels per pass: the per-block digit counts (the table hist[digit][block],
-// row stride hstride), one workgroup per digit scanning its row (each
-// block's exclusive offset within the digit, and the digit's total), then
-// the scatter.  (Letting every scatter block add up its offsets from the
-// raw table instead reads the whole table once per block, which grows with
-// the square of the block count: 70-100 us per pass at 1.5M Gaussians.)
-// The last pass writes the ids and gathers each Gaussian's rectangle and
-// pair count into depth order instead of writing keys.
-static_assert(kDepthBlockKeys == kSortThreads * kDepthItems && kDepthDigits == kSortThreads,
-              "a depth pass block: one thread per digit");
-
-static int64_t depth_blocks(int64_t n) { return ceil_div(n, (int64_t)kDepthBlockKeys); }
-static int64_t depth_hstride(int64_t n) { return ceil_div(std::max<int64_t>(depth_blocks(n), 1), 4) * 4; }
-
-struct DepthPassOut {
-  uint32_t* keys;             // not last: keys and ids
-  uint32_t* vals;
-  uint32_t* ids_sorted;       // last: ids, rectangles and pair counts in depth order
-  const int4* rect;
-  const uint32_t* emit_cnt;
-  int4* rect_sorted;
-  uint32_t* cnt_sorted;
-  int tiles_x, tiles_y;
-};
-
-template <bool kLast>
+// One pass of the depth sort: ranks a block's keys by digit (stable: by wave,
+// round, lane), reorders them in LDS and writes runs of equal digits to
+// consecutive addresses.  kFirst: the ids are the indices, culled keys are
+// left out and the number kept goes to *n_dev, which the later passes read.
+// kLast: only the ids are written.
+template <bool kFirst, bool kLast>
 __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t* __restrict__ keys_in,
-                                                                  const uint32_t* __restrict__ vals_in, uint32_t n,
-                                                                  int shift, int hstride,
+                                                                  const uint32_t* __restrict__ vals_in, uint32_t n_arg,
+                                                                  uint32_t* __restrict__ n_dev, int shift, int stride,
                                                                   const uint32_t* __restrict__ hoffs,
-                                                                  const uint32_t* __restrict__ dtot, DepthPassOut o) {
+                                                                  const uint32_t* __restrict__ dtot,
+                                                                  uint32_t* __restrict__ keys_out,
+                                                                  uint32_t* __restrict__ vals_out) {
   constexpr int kItems = kDepthItems, kBlockKeys = kDepthBlockKeys, kDigits = kDepthDigits;
   __shared__ uint32_t s_cnt[kSortWaves][kDigits];  // per-wave digit counts, then block-local offsets
   __shared__ uint32_t s_gbase[kDigits];            // global position of block-local position 0 of the digit
@@ -815,25 +327,28 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
   __shared__ uint32_t s_vals[kBlockKeys];
   __shared__ uint32_t s_red[kSortWaves];
   __shared__ uint64_t s_mask[kSortWaves][kDigits];
+  const uint32_t n = kFirst ? n_arg : *n_dev;
+  const int64_t blk0 = (int64_t)blockIdx.x * kBlockKeys;
+  if (blk0 >= (int64_t)n) return;  // workgroup-uniform
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   for (int i = tid; i < kSortWaves * kDigits; i += kSortThreads) (&s_cnt[0][0])[i] = 0;
   // keys of digit tid in the earlier blocks, and in all blocks
-  const uint32_t before = hoffs[(int64_t)tid * hstride + blockIdx.x], all_d = dtot[tid];
-  const int64_t blk0 = (int64_t)blockIdx.x * kBlockKeys;
+  const uint32_t before = hoffs[(int64_t)tid * stride + blockIdx.x], all_d = dtot[tid];
   const int64_t wbase = blk0 + (int64_t)wave * kWave * kItems;
   uint32_t key[kItems], val[kItems];
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
     const int64_t i = wbase + k * kWave + lane;
-    key[k] = i < n ? keys_in[i] : 0u;
-    val[k] = i < n ? vals_in[i] : 0u;
+    key[k] = i < n ? keys_in[i] : kCulledKey;
+    val[k] = kFirst ? (uint32_t)i : (i < n ? vals_in[i] : 0u);
   }
+  auto have = [&](int k) { return kFirst ? key[k] != kCulledKey : wbase + k * kWave + lane < n; };
   __syncthreads();
   const uint64_t below = lanes_below();
   uint32_t rank[kItems];
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    const bool valid = wbase + k * kWave + lane < n;
+    const bool valid = have(k);
     const uint32_t d = (key[k] >> shift) & (kDigits - 1u);
     const uint64_t peers = digit_peers(d, valid, s_mask[wave]);
     const uint32_t r = (uint32_t)__popcll(peers & below);
@@ -848,15 +363,16 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
     pre[w] = tot;
     tot += s_cnt[w][tid];
   }
-  uint32_t all;
-  const uint32_t lstart = block_exclusive_scan<kSortThreads, uint32_t>(tot, s_red, &all);
+  uint32_t count, all;
+  const uint32_t lstart = block_exclusive_scan<kSortThreads, uint32_t>(tot, s_red, &count);
   const uint32_t dstart = block_exclusive_scan<kSortThreads, uint32_t>(all_d, s_red, &all);
   for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = lstart + pre[w];
   s_gbase[tid] = dstart + before - lstart;
+  if (kFirst && blockIdx.x == 0 && tid == 0) *n_dev = all;
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    if (wbase + k * kWave + lane < n) {
+    if (have(k)) {
       const uint32_t d = (key[k] >> shift) & (kDigits - 1u);
       const uint32_t lp = s_cnt[wave][d] + rank[k];
       if (lp < (uint32_t)kBlockKeys) {  // always (ranks are a permutation); a safeguard
@@ -866,252 +382,697 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
     }
   }
   __syncthreads();
-  const int count = (int)min((int64_t)kBlockKeys, (int64_t)n - blk0);
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    const int lp = k * kSortThreads + tid;
+    const uint32_t lp = (uint32_t)(k * kSortThreads + tid);
     if (lp < count) {
-      const uint32_t kk = s_keys[lp], g = s_vals[lp];
-      const uint32_t dst = s_gbase[(kk >> shift) & (kDigits - 1u)] + (uint32_t)lp;
-      if (dst >= n || g >= n) continue;  // never taken for a consistent table; keeps every access in bounds
-      if (kLast) {
-        o.ids_sorted[dst] = g;
-        o.rect_sorted[dst] = clamp_rect(o.rect[g], o.tiles_x, o.tiles_y);
-        if (o.emit_cnt != nullptr) o.cnt_sorted[dst] = o.emit_cnt[g];
-      } else {
-        o.keys[dst] = kk;
-        o.vals[dst] = g;
-      }
+      const uint32_t kk = s_keys[lp];
+      const uint32_t dst = s_gbase[(kk >> shift) & (kDigits - 1u)] + lp;
+      if (dst >= n_arg) continue;  // never taken for a consistent table; keeps every write in bounds
+      if (!kLast) keys_out[dst] = kk;
+      vals_out[dst] = s_vals[lp];
     }
   }
 }
 
-// One radix pass over n keys on bits [shift, shift + kBits); the histogram
-// table is taken here unless the caller already wrote it (hist_ready).
-template <typename K, bool kVals, bool kFinal, int kBits, int kItems>
-static void radix_pass(const K* keys, const uint32_t* vals, uint32_t n, const uint32_t* n_dev, int shift,
-                       uint32_t* hist, uint32_t* hoffs, uint32_t* dtot, const ScatterOut& o, hipStream_t s) {
-  // n bounds the keys (the grid); n_dev, when given, holds the actual count on the device
-  const int nblocks = (int)sort_blocks(n, kItems);
-  hipLaunchKernelGGL((radix_hist_kernel<K, kBits, kItems>), dim3(nblocks), dim3(kSortThreads), 0, s, keys, n, n_dev,
-                     shift, nblocks, hist);
-  hipLaunchKernelGGL(digit_scan_kernel, dim3(1 << kBits), dim3(1024), 0, s, hist, nblocks, nblocks, hoffs, dtot, n_dev,
-                     kSortThreads * kItems);
-  hipLaunchKernelGGL((radix_scatter_kernel<K, kVals, kFinal, kBits, kItems>), dim3(nblocks), dim3(kSortThreads),
-                     0, s, keys, vals, n, n_dev, shift, nblocks, hoffs, dtot, o);
+// Few Gaussians: the rank of every key by counting the keys before it.  The
+// twelve launches above take ~5 us each whatever n is (57 us in all); n^2
+// comparisons spread over the chip take 18 us at 10,000 Gaussians, a sort
+// in one workgroup's LDS 47 us.  The comparisons overtake the passes at some
+// 30,000.
+//
+// rank: 256 Gaussians against 256 others per workgroup.  Keys tie-break by
+// index, so a chunk of others before the workgroup's Gaussians counts its
+// equal keys and one after them does not; only the chunk holding them compares
+// the indices.
+constexpr int64_t kSmallSort = 16384;
+constexpr int kRankThreads = 256;
+constexpr int kRankChunk = kRankThreads;
+
+__global__ void __launch_bounds__(kRankThreads) rank_kernel(const int4* __restrict__ rect,
+                                                            const float* __restrict__ depth, uint32_t n, int tiles_x,
+                                                            int tiles_y, uint32_t* __restrict__ part,
+                                                            uint32_t* __restrict__ kept, int4* __restrict__ rects) {
+  __shared__ __align__(16) uint32_t s_key[kRankChunk];
+  __shared__ uint32_t s_kept;
+  const int tid = threadIdx.x;
+  const uint32_t i = blockIdx.x * (uint32_t)kRankThreads + tid, j0 = blockIdx.y * (uint32_t)kRankChunk;
+  if (tid == 0) s_kept = 0u;
+  __syncthreads();
+  {
+    const uint32_t j = j0 + tid;
+    uint32_t other = kCulledKey;  // past the end: before no key
+    if (j < n) other = depth_key(clamp_rect(rect[j], tiles_x, tiles_y), depth[j]);
+    s_key[tid] = other;
+    const uint64_t have = ballot(other != kCulledKey);
+    if (blockIdx.x == 0 && lane_id() == 0) atomicAdd(&s_kept, (uint32_t)__popcll(have));
+  }
+  uint32_t key = kCulledKey;
+  if (i < n) {
+    const int4 r = clamp_rect(rect[i], tiles_x, tiles_y);
+    key = depth_key(r, depth[i]);
+    if (rects != nullptr && blockIdx.y == 0) rects[i] = r;
+  }
+  __syncthreads();
+  uint32_t rank = 0;
+  const uint4* const k4 = reinterpret_cast<const uint4*>(s_key);
+  // workgroup-uniform branches
+  if (blockIdx.y < blockIdx.x) {
+#pragma unroll 8
+    for (int q = 0; q < kRankChunk / 4; ++q) {
+      const uint4 o = k4[q];
+      rank += (o.x <= key ? 1u : 0u) + (o.y <= key ? 1u : 0u) + (o.z <= key ? 1u : 0u) + (o.w <= key ? 1u : 0u);
+    }
+  } else if (blockIdx.y > blockIdx.x) {
+#pragma unroll 8
+    for (int q = 0; q < kRankChunk / 4; ++q) {
+      const uint4 o = k4[q];
+      rank += (o.x < key ? 1u : 0u) + (o.y < key ? 1u : 0u) + (o.z < key ? 1u : 0u) + (o.w < key ? 1u : 0u);
+    }
+  } else {
+#pragma unroll 8
+    for (int q = 0; q < kRankChunk / 4; ++q) {
+      const uint4 o = k4[q];
+      const int l = tid - 4 * q;  // others before this Gaussian: o.x for l > 0, o.y for l > 1, ...
+      rank += (l > 0 ? o.x <= key : o.x < key) ? 1u : 0u;
+      rank += (l > 1 ? o.y <= key : o.y < key) ? 1u : 0u;
+      rank += (l > 2 ? o.z <= key : o.z < key) ? 1u : 0u;
+      rank += (l > 3 ? o.w <= key : o.w < key) ? 1u : 0u;
+    }
+  }
+  if (i < n) part[(int64_t)blockIdx.y * n + i] = key == kCulledKey ? ~0u : rank;
+  if (blockIdx.x == 0 && tid == 0) kept[blockIdx.y] = s_kept;
 }
 
-template <typename K, bool kVals, bool kFinal, int kItems>
-static void radix_pass_bits(int bits, const K* keys, const uint32_t* vals, uint32_t n, const uint32_t* n_dev,
-                            int shift, uint32_t* hist, uint32_t* hoffs, uint32_t* dtot, const ScatterOut& o,
-                            hipStream_t s) {
-  switch (bits) {
-#define TGS_PASS(B) \
-  case B: radix_pass<K, kVals, kFinal, B, kItems>(keys, vals, n, n_dev, shift, hist, hoffs, dtot, o, s); break;
-    TGS_PASS(1) TGS_PASS(2) TGS_PASS(3) TGS_PASS(4) TGS_PASS(5) TGS_PASS(6) TGS_PASS(7)
-    default: radix_pass<K, kVals, kFinal, 8, kItems>(keys, vals, n, n_dev, shift, hist, hoffs, dtot, o, s);
-#undef TGS_PASS
+__global__ void __launch_bounds__(kRankThreads) rank_place_kernel(const uint32_t* __restrict__ part,
+                                                                  const uint32_t* __restrict__ kept, uint32_t n,
+                                                                  int chunks, uint32_t* __restrict__ ids_out,
+                                                                  uint32_t* __restrict__ n_out) {
+  const uint32_t i = blockIdx.x * (uint32_t)kRankThreads + threadIdx.x;
+  if (i < n && part[i] != ~0u) {
+    uint32_t r = 0;
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) r += part[(int64_t)c * n + i];
+    if (r < n) ids_out[r] = i;  // always (the ranks are a permutation); a safeguard
+  }
+  if (i == 0) {
+    uint32_t t = 0;
+    for (int c = 0; c < chunks; ++c) t += kept[c];
+    *n_out = t;
   }
 }
 
-// Passes of at most 8 bits over [lo, lo + bits), split evenly.
-static int pass_count(int bits) { return (bits + 7) / 8; }
-static int pass_bits(int bits, int p) {
-  const int per = (bits + pass_count(bits) - 1) / pass_count(bits);
-  return std::min(per, bits - p * per);
+// ------------------------------------------------------------------ valid tiles
+// One bit per tile, wpr 64-bit words per tile row: the tiles whose map entry
+// is >= 0.  A wave per row.
+__global__ void __launch_bounds__(kWave) tile_bits_kernel(const int32_t* __restrict__ tile_slot, int tiles_x, int wpr,
+                                                          uint64_t* __restrict__ bits) {
+  const int64_t y = blockIdx.x;
+  for (int w = 0; w < wpr; ++w) {
+    const int x = w * kWave + lane_id();
+    const uint64_t b = ballot(x < tiles_x && tile_slot[y * tiles_x + x] >= 0);
+    if (lane_id() == 0) bits[y * wpr + w] = b;
+  }
 }
 
-// ------------------------------------------------------------------ emit
-// Per-wave LDS slice of a batch of up to 64 depth-ordered Gaussians.
-struct RowBatch {
-  int4 rect[kWave];
-  uint32_t row0[kWave];  // exclusive prefix of the row counts in the batch
-  RowEllipse ell[kWave];
-  uint32_t id[kWave];
-  int mark[kWave];
-  // a round's row spans: first column, tile id of the row's column 0, id,
-  // first output (exclusive prefix of the span lengths)
-  int lo[kWave], hi[kWave];
-  uint32_t trow[kWave], gid[kWave], ex[kWave];
+// Set bits of the columns [lo, hi] of a row of bits.
+__device__ __forceinline__ uint32_t valid_in(const uint64_t* __restrict__ row, int lo, int hi) {
+  uint32_t c = 0;
+  for (int w = lo >> 6; lo <= hi && w <= hi >> 6; ++w) {
+    uint64_t b = row[w];
+    if (w == lo >> 6) b &= ~0ull << (lo & 63);
+    if (w == hi >> 6) b &= ~0ull >> (63 - (hi & 63));
+    c += (uint32_t)__popcll(b);
+  }
+  return c;
+}
+
+// ------------------------------------------------------------------ row records
+// Strips: a tile row, cut into pieces of kStripCols columns when it has more
+// (strip (y, c) holds the tiles of row y with x / kStripCols = c), in tile
+// order.  The row stages keep a counter per strip in LDS, so grids of more
+// than kGroup strips are taken in groups of kGroup, one after the other.
+constexpr int kStripCols = 256;  // a record's columns within its strip are 8 bits each
+constexpr int kGroup = 256;
+constexpr int kRowThreads = 256;  // depth positions per block of the row stages
+constexpr int kRowWaves = kRowThreads / kWave;
+constexpr int kSpanRows = 12 * kRowThreads;  // rows per block whose intervals the count keeps for the records
+constexpr int kRecThreads = 256;
+constexpr int kRecItems = 2;
+constexpr int kRecBlock = kRecThreads * kRecItems;  // records per block of the pair stages
+
+struct BinArgs {
+  const uint32_t* n_keyed;    // Gaussians in the depth order (device)
+  int64_t pos0, pos_end;      // the depth positions taken: [pos0, min(pos_end, *n_keyed))
+  const uint32_t* ids;        // Gaussians in depth order
+  const int4* rect;           // by Gaussian
+  const float4* splat;
+  const uint64_t* bits;       // valid tiles (nullptr: all)
+  const uint32_t* n_flagged;  // nullable: nothing is listed when it is 0
+  int tiles_x, tiles_y, wpr;
+  int sc;                     // strips per tile row
+  int s0, sn;                 // the group: strips [s0, s0 + sn)
+  double tau, lia;
+  int64_t kb;                 // blocks of depth positions: row stride of the tables
+  uint32_t* rows_tab;         // [sn][kb] records per strip and block, then their prefix
+  uint32_t* pairs_tab;        // [sn][kb] pairs
+  uint16_t* spans;            // [blocks][kSpanRows] the block's rows' intervals, position after position
+  int2* rowinfo;              // [positions] first tile row, rows
+  uint8_t* touched;
+  // per strip (all groups)
+  unsigned long long* row_tot;
+  unsigned long long* pair_tot;
+  uint32_t* row_base;         // [S + 1]
+  uint32_t* pair_base;
+  uint32_t* blk_base;
+  uint32_t* eff_total;        // all pairs when they fit the capacity, else 0
+  uint2* rec;                 // [capacity] records: id, first column | last column << 8
+  uint32_t* hist;             // [blocks of the group][cols] pairs per column, then first list positions
+  int cols;                   // its row length: columns per strip
+  uint32_t* vals;
+  uint64_t* keys64;           // nullable
+  const float* depth;         // for keys64
+  uint2* ranges;
 };
 
-constexpr int kEmitThreads = kWave;  // one wave per workgroup: __syncthreads is a wave barrier
-constexpr int kEmitBatch = 32;       // Gaussians per wave: more waves, fewer rounds each (64 measured slower)
-// The continuation's emission runs over every Gaussian past the prefix, few
-// of which have pairs in the marked tiles: 64 per wave halves the waves
-// that only find an empty batch.
-// What a row emits: every kept column; its columns with a map entry >= 0,
-// compacted by a ballot over the sub-round's outputs (a tile subset, where
-// a good share of the columns is valid); or its flagged columns found by a
-// walk over the row (the continuation, where few are).
-constexpr int kEmitAll = 0, kEmitCompact = 1, kEmitWalk = 2;
-template <int kMode>
-constexpr int emit_batch() { return kMode == kEmitWalk ? kWave : kEmitBatch; }
+__device__ __forceinline__ int64_t bin_end(const BinArgs& a) { return min(a.pos_end, (int64_t)*a.n_keyed); }
+__device__ __forceinline__ bool bin_nothing(const BinArgs& a) { return a.n_flagged != nullptr && *a.n_flagged == 0u; }
 
-// A wave per kEmitBatch depth-ordered Gaussians.  Their rectangle rows are
-// flattened Gaussian by Gaussian and handed out 64 per round; a Gaussian
-// whose first row falls in the round marks its slot and an inclusive
-// max-scan carries each owner to the following slots, so a lane finds its
-// Gaussian without a search.  Each lane takes its row's span; a wave scan of
-// the span lengths places the row's keys after those of the rows before it,
-// starting from the batch's first pair offset (pairs are emitted Gaussian by
-// Gaussian, row by row, columns ascending).
-//
-// kEmitCompact, kEmitWalk: only the tiles whose map entry is >= 0 are
-// emitted.  Compact hands out every kept column as above and writes the
-// valid ones at the ballot prefix of the sub-round's valid outputs; Walk
-// (the continuation lists) counts a row's flagged columns and hands out only
-// those, each output lane walking the row's span to its column.
-template <typename K, int kMode>
-__global__ void __launch_bounds__(kEmitThreads) emit_kernel(
-    const int4* __restrict__ rect_sorted, const uint32_t* __restrict__ off, const uint32_t* __restrict__ ids_sorted,
-    int64_t n, const float4* __restrict__ splat, const int32_t* __restrict__ tile_slot, int tiles_x, uint32_t n_t,
-    int id_bits, double tau, double lia, const uint32_t* __restrict__ total_dev, K* __restrict__ keys,
-    uint32_t* __restrict__ pay) {
-  const uint32_t total = *total_dev;  // pairs to emit (0 when they exceed the capacity)
-  __shared__ RowBatch rb;
-  const int lane = lane_id();
-  constexpr int kBatch = emit_batch<kMode>();
-  const int64_t b0 = (int64_t)blockIdx.x * kBatch;
-  const int64_t j = b0 + lane;
-  int4 r = make_int4(0, 0, 0, 0);
-  uint32_t g = 0, rows = 0;
-  if (total == 0) return;  // workgroup-uniform
-  if (lane < kBatch && j < n && off[j + 1] > off[j]) {
-    r = rect_sorted[j];
-    g = ids_sorted[j];
-    rows = (uint32_t)(r.w - r.y);
+// Kept tiles of row ty, a piece per strip of the group: f(strip in the group,
+// first column, last column, valid tiles) for each piece with a valid tile.
+template <bool kWide, typename F>
+__device__ __forceinline__ void row_pieces(const BinArgs& a, int ty, int lo, int hi, F&& f) {
+  if (lo > hi) return;
+  const uint64_t* brow = a.bits != nullptr ? a.bits + (int64_t)ty * a.wpr : nullptr;
+  if (!kWide) {
+    const uint32_t c = brow != nullptr ? valid_in(brow, lo, hi) : (uint32_t)(hi - lo + 1);
+    if (c > 0) f(ty - a.s0, lo, hi, c);
+    return;
   }
-  const uint32_t incl = wave_inclusive_scan_u32(rows);
-  const uint32_t my_row0 = incl - rows;
-  const uint32_t n_rows = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-  if (n_rows == 0) return;  // wave-uniform: no Gaussian of the batch has pairs
-  rb.rect[lane] = r;
-  rb.row0[lane] = my_row0;
-  rb.id[lane] = g;
-  if (rows > 0) rb.ell[lane] = load_row_ellipse(splat, g, tau, lia);
-  const uint32_t base = off[b0];  // pair offset of the batch's first Gaussian
-  uint32_t written = 0;           // wave-uniform
-  int carry = -1;
-  for (uint32_t f0 = 0; f0 < n_rows; f0 += kWave) {
-    rb.mark[lane] = -1;
-    __syncthreads();
-    if (rows > 0 && my_row0 >= f0 && my_row0 - f0 < (uint32_t)kWave) rb.mark[my_row0 - f0] = lane;
-    __syncthreads();
-    const int jl = max(wave_max_scan(rb.mark[lane]), carry);
-    carry = __builtin_amdgcn_readlane(jl, kWave - 1);
-    const uint32_t f = f0 + (uint32_t)lane;
-    // jl >= 0 whenever f < n_rows: the first Gaussian with rows starts at row 0
-    const bool in = f < n_rows && jl >= 0;
-    int lo = 0, hi = -1, ty = 0;
-    uint32_t gid = 0;
-    if (in) {
-      const int4 rj = rb.rect[jl];
-      ty = rj.y + (int)(f - rb.row0[jl]);
-      gid = rb.id[jl];
-      row_span(rb.ell[jl], ty, rj.x, rj.z, lo, hi);
+  for (int q = lo / kStripCols; q <= hi / kStripCols; ++q) {
+    const int l = max(lo, q * kStripCols), h = min(hi, q * kStripCols + kStripCols - 1);
+    const uint32_t c = brow != nullptr ? valid_in(brow, l, h) : (uint32_t)(h - l + 1);
+    if (c > 0) f((int)((int64_t)ty * a.sc + q - a.s0), l - q * kStripCols, h - q * kStripCols, c);
+  }
+}
+
+// The rows of the rectangle that the ellipse can meet: rows of pixel centres
+// 16 ty .. 16 ty + 15 with 16 ty + 15 >= cy - ym and 16 ty <= cy + ym, widened
+// by far more than FP64 rounds (row_span decides; this only saves it the rows
+// past the ellipse, two of seven on average).
+__device__ __forceinline__ void ellipse_rows(const RowEllipse& e, int4 r, int& y0, int& y1) {
+  y0 = r.y;
+  y1 = r.w;
+  if (!e.pd) return;
+  const double cy = e.yi + e.yf, eps = 1e-9 * (fabs(cy) + e.ym) + 1e-6;
+  const double f = ceil((cy - e.ym - (double)(kTile - 1) - eps) * (1.0 / kTile));
+  const double l = floor((cy + e.ym + eps) * (1.0 / kTile));
+  y0 = (int)fmin(fmax(f, (double)r.y), (double)r.w);
+  y1 = (int)fmin(fmax(l + 1.0, (double)y0), (double)r.w);
+}
+
+// Count.  Bound by the gathers of rectangle and record in depth order and by
+// the divergence of the row loop; FP64 itself runs at the FP32 rate.  Handing
+// the rows of 64 Gaussians out one per lane keeps every lane busy, but costs a
+// prefix sum, two exchanges through LDS and their barriers per 64 rows, which
+// took longer than the idle lanes do.
+template <bool kWide>
+__global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinArgs a) {
+  __shared__ uint32_t s_rows[kGroup], s_pairs[kGroup];
+  __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
+  __shared__ uint32_t s_red[kRowWaves];
+  if (bin_nothing(a)) return;
+  const int tid = threadIdx.x;
+  const int64_t end = bin_end(a), p0 = a.pos0 + (int64_t)blockIdx.x * kRowThreads, p = p0 + tid;
+  if (p0 >= end) return;  // workgroup-uniform
+  static_assert(kGroup == kRowThreads, "a thread per strip counter");
+  s_rows[tid] = 0u;
+  s_pairs[tid] = 0u;
+  int4 r = make_int4(0, 0, 0, 0);
+  uint32_t g = 0;
+  if (p < end) {
+    g = a.ids[p];
+    r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
+  }
+  bool some = r.z > r.x && r.w > r.y;
+  if (a.bits != nullptr && some) {
+    // a rectangle without a valid tile is done before its record is read
+    some = false;
+    for (int y = r.y; y < r.w && !some; ++y) some = valid_in(a.bits + (int64_t)y * a.wpr, r.x, r.z - 1) > 0;
+  }
+  RowEllipse e = {};
+  int y0 = 0, y1 = 0;
+  if (some) {
+    e = load_row_ellipse(a.splat, g, a.tau, a.lia);
+    ellipse_rows(e, r, y0, y1);
+  }
+  uint32_t total;
+  const uint32_t at = block_exclusive_scan<kRowThreads, uint32_t>((uint32_t)(y1 - y0), s_red, &total);
+  bool any = false;
+  for (int y = y0; y < y1; ++y) {
+    int lo, hi;
+    row_span(e, y, r.x, r.z, lo, hi);
+    uint32_t span = 0xffu;  // first column 255, last 0: empty
+    row_pieces<kWide>(a, y, lo, hi, [&](int s, int l, int h, uint32_t c) {
+      any = true;
+      span = (uint32_t)l | ((uint32_t)h << 8);
+      if (s >= 0 && s < a.sn) {
+        atomicAdd(&s_rows[s], 1u);
+        atomicAdd(&s_pairs[s], c);
+      }
+    });
+    const uint32_t q = at + (uint32_t)(y - y0);
+    if (!kWide && q < (uint32_t)kSpanRows) s_span[q] = (uint16_t)span;
+  }
+  if (p < end) {
+    if (any && a.touched != nullptr) a.touched[g] = 1;
+    a.rowinfo[p - a.pos0] = make_int2(y0, y1 - y0);
+  }
+  __syncthreads();
+  if (!kWide) {
+    const uint32_t words = (min(total, (uint32_t)kSpanRows) + 1u) / 2u;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(a.spans + (int64_t)blockIdx.x * kSpanRows);
+    for (uint32_t i = tid; i < words; i += kRowThreads) dst[i] = reinterpret_cast<const uint32_t*>(s_span)[i];
+  }
+  if (tid < a.sn) {
+    a.rows_tab[(int64_t)tid * a.kb + blockIdx.x] = s_rows[tid];
+    a.pairs_tab[(int64_t)tid * a.kb + blockIdx.x] = s_pairs[tid];
+  }
+}
+
+// A workgroup per strip of the group: the prefix of its records over the
+// blocks (in place), its records and its pairs.
+__global__ void __launch_bounds__(1024) strip_scan_kernel(BinArgs a) {
+  __shared__ uint32_t lds[1024 / kWave];
+  __shared__ unsigned long long lds64[1024 / kWave];
+  const int64_t end = bin_end(a);
+  const int64_t nb = bin_nothing(a) || end <= a.pos0 ? 0 : ceil_div(end - a.pos0, kRowThreads);
+  uint32_t* rows = a.rows_tab + (int64_t)blockIdx.x * a.kb;
+  const uint32_t* pairs = a.pairs_tab + (int64_t)blockIdx.x * a.kb;
+  unsigned long long np = 0;
+  uint32_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
+    const int64_t b = b0 + threadIdx.x;
+    const uint32_t v = b < nb ? rows[b] : 0u;
+    if (b < nb) np += pairs[b];
+    uint32_t tot;
+    const uint32_t ex = block_exclusive_scan<1024, uint32_t>(v, lds, &tot);
+    if (b < nb) rows[b] = carry + ex;
+    carry += tot;
+  }
+  unsigned long long all;
+  (void)block_exclusive_scan<1024, unsigned long long>(np, lds64, &all);
+  if (threadIdx.x == 0) {
+    a.row_tot[a.s0 + blockIdx.x] = carry;
+    a.pair_tot[a.s0 + blockIdx.x] = all;
+  }
+}
+
+// One workgroup: every strip's first record, pair and pair-stage block, and
+// the counts.  out (nullable) receives counts[0] = counts[1] = pairs; with
+// m > 0 (a depth-prefix call over m positions) also an estimate of the whole
+// lists' pairs: the prefix's pairs per Gaussian times the keyed Gaussians
+// (exact when the prefix holds them all; the nearest Gaussians cover the most
+// tiles, so it tends to exceed the count).
+__global__ void __launch_bounds__(1024) strip_base_kernel(BinArgs a, int64_t strips, int64_t m, int64_t capacity,
+                                                          unsigned long long* __restrict__ counts,
+                                                          unsigned long long* __restrict__ out) {
+  __shared__ unsigned long long lds[1024 / kWave];
+  unsigned long long rows = 0, pairs = 0, blks = 0;  // before the strips of this round
+  for (int64_t s0 = 0; s0 < strips; s0 += 1024) {
+    const int64_t s = s0 + threadIdx.x;
+    const unsigned long long r = s < strips ? a.row_tot[s] : 0ull, p = s < strips ? a.pair_tot[s] : 0ull;
+    unsigned long long tr, tp, tb;
+    const unsigned long long er = block_exclusive_scan<1024, unsigned long long>(r, lds, &tr);
+    const unsigned long long ep = block_exclusive_scan<1024, unsigned long long>(p, lds, &tp);
+    const unsigned long long eb =
+        block_exclusive_scan<1024, unsigned long long>((r + kRecBlock - 1) / kRecBlock, lds, &tb);
+    if (s < strips) {  // they wrap only past 2^32 pairs, where nothing reads them
+      a.row_base[s] = (uint32_t)(rows + er);
+      a.pair_base[s] = (uint32_t)(pairs + ep);
+      a.blk_base[s] = (uint32_t)(blks + eb);
     }
-    uint32_t c = (uint32_t)max(hi - lo + 1, 0);
-    if (kMode == kEmitWalk && c > 0) {
-      const int32_t* tr = tile_slot + (int64_t)ty * tiles_x;
-      uint32_t cf = 0u;
-      for (int tx = lo; tx <= hi; ++tx) cf += tr[tx] >= 0 ? 1u : 0u;
-      c = cf;
+    rows += tr;
+    pairs += tp;
+    blks += tb;
+  }
+  if (threadIdx.x == 0) {
+    a.row_base[strips] = (uint32_t)rows;
+    a.pair_base[strips] = (uint32_t)pairs;
+    a.blk_base[strips] = (uint32_t)blks;
+    counts[0] = pairs;
+    counts[1] = pairs;
+    *a.eff_total = pairs <= (unsigned long long)capacity ? (uint32_t)pairs : 0u;
+    if (out != nullptr) {
+      out[0] = pairs;
+      out[1] = pairs;
+      if (m >= 0) {
+        const unsigned long long k = *a.n_keyed, mk = (unsigned long long)m < k ? (unsigned long long)m : k;
+        out[2] = mk >= k || mk == 0 ? pairs : (unsigned long long)ceil((double)pairs * (double)k / (double)mk);
+      }
     }
-    const uint32_t ci = wave_inclusive_scan_u32(c);
-    const uint32_t n_out = (uint32_t)__builtin_amdgcn_readlane((int)ci, kWave - 1);
-    // the round's rows write n_out consecutive pairs from base + written; they
-    // are handed out 64 per sub-round, lane q taking output q, so every store
-    // covers consecutive addresses: the row owning an output is found like
-    // the rows' owners above (its first output marked, a max-scan carries it)
-    rb.lo[lane] = lo;
-    rb.hi[lane] = hi;
-    rb.trow[lane] = in ? (uint32_t)ty * (uint32_t)tiles_x : 0u;
-    rb.gid[lane] = gid;
-    rb.ex[lane] = ci - c;
-    int ocarry = -1;
-    for (uint32_t q0 = 0; q0 < n_out; q0 += kWave) {
-      rb.mark[lane] = -1;
-      __syncthreads();
-      if (c > 0 && ci - c >= q0 && ci - c - q0 < (uint32_t)kWave) rb.mark[ci - c - q0] = lane;
-      __syncthreads();
-      const int own = max(wave_max_scan(rb.mark[lane]), ocarry);
-      ocarry = __builtin_amdgcn_readlane(own, kWave - 1);
-      const uint32_t q = q0 + (uint32_t)lane;
-      // own >= 0 whenever q < n_out: output 0 belongs to the first row with pairs
-      bool out = q < n_out && own >= 0;
-      uint32_t tile = 0;
-      if (out) {
-        if (kMode == kEmitWalk) {  // the (q - ex)-th flagged column of the row (there are c of them)
-          int left = (int)(q - rb.ex[own]), tx = rb.lo[own];
-          const uint32_t tr = rb.trow[own];
-          for (; tx < rb.hi[own]; ++tx) {
-            if (tile_slot[tr + (uint32_t)tx] >= 0) {
-              if (left == 0) break;
-              --left;
-            }
-          }
-          tile = tr + (uint32_t)tx;
-        } else {
-          tile = rb.trow[own] + (uint32_t)(rb.lo[own] + (int)(q - rb.ex[own]));
+  }
+}
+
+// Records.  Per wave a 64-bit mask per strip collects which of its 64 depth
+// positions have a record there; a record's place is the strip's first one,
+// plus the earlier blocks', the earlier waves' and the earlier lanes' records.
+template <bool kWide>
+__global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinArgs a) {
+  __shared__ uint64_t s_mask[kRowWaves][kGroup];
+  __shared__ uint32_t s_pos[kRowWaves][kGroup];
+  __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
+  __shared__ uint32_t s_red[kRowWaves];
+  if (bin_nothing(a)) return;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int64_t end = bin_end(a), p0 = a.pos0 + (int64_t)blockIdx.x * kRowThreads, p = p0 + tid;
+  if (p0 >= end || *a.eff_total == 0u) return;  // workgroup-uniform
+#pragma unroll
+  for (int w = 0; w < kRowWaves; ++w) s_mask[w][tid] = 0ull;
+  int2 info = make_int2(0, 0);
+  uint32_t g = 0;
+  if (p < end) {
+    info = a.rowinfo[p - a.pos0];
+    g = a.ids[p];
+  }
+  uint32_t total;
+  const uint32_t at = block_exclusive_scan<kRowThreads, uint32_t>((uint32_t)info.y, s_red, &total);
+  if (!kWide) {
+    const uint32_t words = (min(total, (uint32_t)kSpanRows) + 1u) / 2u;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.spans + (int64_t)blockIdx.x * kSpanRows);
+    for (uint32_t i = tid; i < words; i += kRowThreads) reinterpret_cast<uint32_t*>(s_span)[i] = src[i];
+  }
+  RowEllipse e = {};
+  int4 r = make_int4(0, 0, 0, 0);
+  if (info.y > 0 && (kWide || at + (uint32_t)info.y > (uint32_t)kSpanRows)) {  // rows not kept: evaluated again
+    r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
+    e = load_row_ellipse(a.splat, g, a.tau, a.lia);
+  }
+  __syncthreads();
+  auto each = [&](auto&& f) {
+    for (int k = 0; k < info.y; ++k) {
+      if (!kWide && at + (uint32_t)k < (uint32_t)kSpanRows) {
+        const uint32_t c = s_span[at + (uint32_t)k];
+        const int s = info.x + k - a.s0;
+        if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c);
+      } else {
+        int lo, hi;
+        row_span(e, info.x + k, r.x, r.z, lo, hi);
+        row_pieces<kWide>(a, info.x + k, lo, hi, [&](int s, int l, int h, uint32_t) {
+          if (s >= 0 && s < a.sn) f(s, (uint32_t)l | ((uint32_t)h << 8));
+        });
+      }
+    }
+  };
+  each([&](int s, uint32_t) {
+    __hip_atomic_fetch_or(&s_mask[wave][s], 1ull << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  });
+  __syncthreads();
+  if (tid < a.sn) {
+    uint32_t q = a.row_base[a.s0 + tid] + a.rows_tab[(int64_t)tid * a.kb + blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) {
+      s_pos[w][tid] = q;
+      q += (uint32_t)__popcll(s_mask[w][tid]);
+    }
+  }
+  __syncthreads();
+  const uint64_t below = lanes_below();
+  const uint32_t rows_all = *a.eff_total;  // a record holds a pair, so there are no more records than pairs
+  each([&](int s, uint32_t c) {
+    const uint32_t q = s_pos[wave][s] + (uint32_t)__popcll(s_mask[wave][s] & below);
+    if (q < rows_all) a.rec[q] = make_uint2(g, c);  // always; a safeguard
+  });
+}
+
+// The pair stages' blocks of the group are known on the device only (the host
+// knows the capacity, some six times the records), so a fixed grid strides over
+// them: a workgroup launched for nothing costs 0.4 ns, and there would be tens
+// of thousands of them.
+constexpr int64_t kPairGrid = 8192;
+
+__device__ __forceinline__ uint32_t group_blocks(const BinArgs& a) {
+  return a.blk_base[a.s0 + a.sn] - a.blk_base[a.s0];
+}
+
+// The strip of the group (and the first record and record count within it)
+// that block b of the pair stages belongs to.
+struct RecSpan {
+  int strip;
+  uint32_t first, count;
+};
+
+__device__ __forceinline__ RecSpan rec_span(const BinArgs& a, uint32_t b, int* s_strip) {
+  if (threadIdx.x == 0) *s_strip = 0;
+  __syncthreads();
+  if ((int)threadIdx.x < a.sn) {
+    const uint32_t f = a.blk_base[a.s0];
+    if (a.blk_base[a.s0 + threadIdx.x] - f <= b && b < a.blk_base[a.s0 + threadIdx.x + 1] - f) *s_strip = threadIdx.x;
+  }
+  __syncthreads();
+  RecSpan q{*s_strip, 0u, 0u};
+  const int s = a.s0 + q.strip;
+  const uint32_t seg = b - (a.blk_base[s] - a.blk_base[a.s0]);
+  q.first = a.row_base[s] + seg * kRecBlock;
+  q.count = min((uint32_t)kRecBlock, a.row_base[s + 1] - q.first);
+  return q;
+}
+
+// Pairs per column of 512 records: a difference array, then its prefix.
+__global__ void __launch_bounds__(kRecThreads) bin_hist_kernel(BinArgs a) {
+  __shared__ int s_diff[kStripCols + 1];
+  __shared__ int s_red[kRecThreads / kWave];
+  __shared__ int s_strip;
+  if (*a.eff_total == 0u) return;
+  static_assert(kRecThreads == kStripCols && kRecThreads >= kGroup, "a thread per column and per strip");
+  const int tid = threadIdx.x;
+  const uint32_t blocks = group_blocks(a);
+  for (uint32_t b = blockIdx.x; b < blocks; b += gridDim.x) {
+    const RecSpan q = rec_span(a, b, &s_strip);
+    s_diff[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRecItems; ++k) {
+      const uint32_t i = (uint32_t)(k * kRecThreads + tid);
+      if (i < q.count) {
+        const uint32_t c = a.rec[q.first + i].y;
+        atomicAdd(&s_diff[c & 0xffu], 1);
+        atomicAdd(&s_diff[(c >> 8) + 1u], -1);
+      }
+    }
+    __syncthreads();
+    const int d = s_diff[tid];
+    int tot;
+    const int ex = block_exclusive_scan<kRecThreads, int>(d, s_red, &tot);
+    if (tid < a.cols) a.hist[(int64_t)b * a.cols + tid] = (uint32_t)(ex + d);
+  }
+}
+
+// A workgroup per strip of the group, 256 threads over its columns in each of
+// four quarters of its blocks: the columns' pairs, the tiles' ranges, and the
+// first list position of every (block, column).
+__global__ void __launch_bounds__(1024) bin_offsets_kernel(BinArgs a) {
+  __shared__ uint32_t s_part[4][kStripCols];
+  __shared__ uint32_t s_red[1024 / kWave];
+  const int tid = threadIdx.x, col = tid & (kStripCols - 1), part = tid / kStripCols;
+  const int64_t s = (int64_t)a.s0 + blockIdx.x;
+  const int64_t ty = s / a.sc;
+  const int tx = (int)(s % a.sc) * kStripCols + col;
+  const bool in = col < a.cols && tx < a.tiles_x;
+  const bool valid = in && (a.bits == nullptr || (a.bits[ty * a.wpr + (tx >> 6)] >> (tx & 63)) & 1ull);
+  const bool none = *a.eff_total == 0u;
+  const uint32_t b0 = a.blk_base[s] - a.blk_base[a.s0], nb = none ? 0u : a.blk_base[s + 1] - a.blk_base[s];
+  const uint32_t per = (nb + 3u) / 4u, f = min(nb, part * per), l = min(nb, f + per);
+  uint32_t* h = a.hist + (int64_t)b0 * a.cols + col;
+  uint32_t sum = 0;
+  if (valid)
+#pragma unroll 8
+    for (uint32_t b = f; b < l; ++b) sum += h[(int64_t)b * a.cols];
+  s_part[part][col] = sum;
+  __syncthreads();
+  uint32_t tot = 0;
+  if (part == 0) tot = s_part[0][col] + s_part[1][col] + s_part[2][col] + s_part[3][col];
+  uint32_t all;
+  uint32_t run = block_exclusive_scan<1024, uint32_t>(tot, s_red, &all);
+  if (part == 0) {
+    run += a.pair_base[s];
+    if (in) a.ranges[ty * a.tiles_x + tx] = !none && tot > 0 ? make_uint2(run, run + tot) : make_uint2(0u, 0u);
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t c = s_part[q][col];
+      s_part[q][col] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  run = s_part[part][col];
+  if (valid)
+#pragma unroll 8
+    for (uint32_t b = f; b < l; ++b) {
+      const uint32_t c = h[(int64_t)b * a.cols];
+      h[(int64_t)b * a.cols] = run;
+      run += c;
+    }
+}
+
+// Lists.  A wave takes 64 consecutive records at a time: each sets its bit in
+// the masks of its columns, then its rank in a column's list is the mask's
+// earlier bits.  The masks and running positions are the wave's own, and a
+// wave's LDS operations execute in order, so the rounds need no barrier.  The
+// ids go to LDS, column after column, and from there to the lists in runs (512
+// records put ~30 ids in each list): written to the lists one by one they were
+// 4-byte requests to as many cache lines, which bound the kernel at the L2
+// (42M pairs: 229 us, now 141).  A block with more ids than the buffer holds writes them one by
+// one.
+constexpr int kPlaceIds = 4096;
+
+template <int kCols>
+__global__ void __launch_bounds__(kRecThreads) bin_place_kernel(BinArgs a) {
+  constexpr int kWaves = kRecThreads / kWave;
+  __shared__ uint64_t s_mask[kWaves][kCols];
+  __shared__ uint32_t s_run[kWaves][kCols];
+  __shared__ uint32_t s_first[kCols];  // list position of a column's first id, less its place in the buffer
+  __shared__ uint32_t s_ids[kPlaceIds];
+  __shared__ uint8_t s_col[kPlaceIds];
+  __shared__ uint32_t s_red[kWaves];
+  __shared__ int s_strip;
+  static_assert(kWaves * (kCols + 1) <= kPlaceIds, "the difference arrays fit the id buffer");
+  int* const diff = reinterpret_cast<int*>(s_ids);  // [kWaves][kCols + 1], before the ids
+  const uint32_t total = *a.eff_total;
+  if (total == 0u) return;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const uint32_t blocks = group_blocks(a);
+  for (uint32_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+    const RecSpan q = rec_span(a, blk, &s_strip);
+    const int64_t s = (int64_t)a.s0 + q.strip;
+    const int64_t ty = s / a.sc;
+    const int x0 = (int)(s % a.sc) * kStripCols;
+    const uint64_t* brow = a.bits != nullptr ? a.bits + ty * a.wpr + (x0 >> 6) : nullptr;
+    auto listed = [&](int x) { return brow == nullptr || (brow[x >> 6] >> (x & 63)) & 1ull; };
+    for (int i = tid; i < kWaves * kCols; i += kRecThreads) (&s_mask[0][0])[i] = 0ull;
+    for (int i = tid; i < kWaves * (kCols + 1); i += kRecThreads) diff[i] = 0;
+    __syncthreads();
+    // each wave takes 64 kRecItems consecutive records
+    uint2 rec[kRecItems];
+#pragma unroll
+    for (int k = 0; k < kRecItems; ++k) {
+      const uint32_t i = (uint32_t)((wave * kRecItems + k) * kWave + lane);
+      rec[k] = i < q.count ? a.rec[q.first + i] : make_uint2(0u, 0xffu);  // past the end: an empty interval
+      if (i < q.count) {
+        atomicAdd(&diff[wave * (kCols + 1) + (int)(rec[k].y & 0xffu)], 1);
+        atomicAdd(&diff[wave * (kCols + 1) + (int)(rec[k].y >> 8) + 1], -1);
+      }
+    }
+    __syncthreads();
+    {
+      // the wave's ids per column
+      constexpr int kPer = kCols / kWave;
+      int d[kPer], sum = 0;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        d[k] = diff[wave * (kCols + 1) + lane * kPer + k];
+        sum += d[k];
+      }
+      int run = wave_inclusive_scan_i_dpp(sum) - sum;
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        run += d[k];
+        s_run[wave][lane * kPer + k] = (uint32_t)run;
+      }
+    }
+    __syncthreads();
+    uint32_t ids = 0;
+    if (tid < a.cols && listed(tid))
+      for (int w = 0; w < kWaves; ++w) ids += s_run[w][tid];
+    uint32_t block_ids;
+    uint32_t run = block_exclusive_scan<kRecThreads, uint32_t>(ids, s_red, &block_ids);
+    if (tid < a.cols) {
+      s_first[tid] = a.hist[(int64_t)blk * a.cols + tid] - run;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_run[w][tid];
+        s_run[w][tid] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+    const bool buffered = block_ids <= (uint32_t)kPlaceIds;  // workgroup-uniform
+    auto put = [&](uint32_t pos, int x, uint32_t id) {
+      if (pos >= total) return;  // never; a safeguard
+      a.vals[pos] = id;
+      if (a.keys64 != nullptr)
+        a.keys64[pos] = ((uint64_t)(ty * a.tiles_x + x0 + x) << 32) | (uint64_t)__float_as_uint(a.depth[id]);
+    };
+    const uint64_t below = lanes_below();
+    uint64_t* const mask = s_mask[wave];
+    uint32_t* const base = s_run[wave];
+#pragma unroll
+    for (int k = 0; k < kRecItems; ++k) {
+      const int xl = (int)(rec[k].y & 0xffu), xh = (int)(rec[k].y >> 8);
+      for (int x = xl; x <= xh; ++x)
+        __hip_atomic_fetch_or(&mask[x], 1ull << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int x = xl; x <= xh; ++x) {
+        if (!listed(x)) continue;
+        const uint32_t lp = base[x] + (uint32_t)__popcll(mask[x] & below);
+        if (!buffered) {
+          put(s_first[x] + lp, x, rec[k].x);
+        } else if (lp < (uint32_t)kPlaceIds) {  // always (the counts are the masks'); a safeguard
+          s_ids[lp] = rec[k].x;
+          s_col[lp] = (uint8_t)x;
         }
       }
-      uint32_t pos = base + written + q;
-      if (kMode == kEmitCompact) {
-        out = out && tile_slot[tile] >= 0;
-        const uint64_t vb = __ballot(out);
-        pos = base + written +
-              __builtin_amdgcn_mbcnt_hi((uint32_t)(vb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vb, 0u));
-        written += (uint32_t)__popcll(vb);  // wave-uniform
-      }
-      if (out && pos < total) {  // pos < total always holds; the bound is a safeguard
-        if (pay != nullptr) {  // the id as a separate payload, the key is the tile alone
-          keys[pos] = (K)tile;
-          pay[pos] = rb.gid[own];
-        } else {
-          keys[pos] = ((K)tile << id_bits) | (K)rb.gid[own];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int x = lane; x < kCols; x += kWave) {
+        const uint64_t m = mask[x];
+        if (m != 0ull) {
+          base[x] += (uint32_t)__popcll(m);
+          mask[x] = 0ull;
         }
       }
-      __syncthreads();  // the sub-round's mark reads before the next one's writes
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    if (kMode != kEmitCompact) written += n_out;
-    __syncthreads();  // the round's mark reads before the next round's writes
+    __syncthreads();
+    if (buffered)
+      for (uint32_t i = tid; i < block_ids; i += kRecThreads) put(s_first[s_col[i]] + i, s_col[i], s_ids[i]);
+    __syncthreads();  // before the next block clears the masks and the difference arrays
   }
 }
 
 // ------------------------------------------------------------------ workspace
 struct SortWs {
-  unsigned long long* scalars;  // [2][TGS_COUNTER_SLOTS] partial totals: valid pairs, pairs
-  uint32_t* dhist[4];           // [256][hstride] per-block digit counts of each depth pass
-  uint32_t* dhoffs;             // [256][hstride] their exclusive prefix per digit (the pass being run)
-  uint32_t* ddtot;              // [256] digit totals of the pass being run
-  uint32_t* zeroed;             // scalars and dhist: one region, cleared at the start
-  int64_t zeroed_words;         // its size in 32-bit words
-  int hstride;                  // row stride of the depth tables
-  uint32_t* emit_cnt;           // [n] pairs each Gaussian emits
-  int4* rect_sorted;            // [n] rectangles in depth order
-  uint32_t* cnt_sorted;         // [n] pair counts in depth order
-  uint32_t* ids_sorted;         // [n] Gaussian ids in depth order
-  uint32_t* off;                // [n + 1] exclusive prefix of the counts: pair offsets
+  unsigned long long* counts;   // [2] pairs (blocking call's readback)
+  uint32_t* eff_total;          // all pairs when they fit the capacity, else 0
+  uint32_t* n_keyed;            // Gaussians with a non-empty rectangle
+  uint32_t* dhist;              // [256][hstride] per-block digit counts of the depth pass being run
+  uint32_t* dhoffs;             // [256][hstride] their prefix per digit
+  uint32_t* ddtot;              // [256] digit totals
+  int hstride;
   uint32_t* dkeys[2];           // [n] depth keys (ping-pong)
   uint32_t* dvals[2];           // [n] ids
-  uint32_t* partials;           // scan block sums, digit totals
-  uint32_t* hist;               // [256 * max_blocks]
-  uint32_t* hoffs;              // [256 * max_blocks]
-  void* pkeys[2];               // [capacity] x 8 bytes each: pair keys (u32), or u16/u32 tile keys then u32 ids
-  int64_t cap;                  // pairs each ping-pong buffer holds
-  unsigned long long* counts;   // [2] pairs in valid tiles, all pairs (the call's device result)
-  uint32_t* eff_total;          // all pairs when they fit the capacity, else 0 (what the pair sort sorts)
+  uint32_t* ids_sorted;         // [n] Gaussians in depth order
+  uint32_t* part;               // few Gaussians: [chunks][n] partial ranks
+  int4* rects;                  // [n] clamped rectangles (kept by a depth-prefix call)
+  uint16_t* spans;              // [kb][kSpanRows]
+  int2* rowinfo;                // [n]
+  int64_t kb;                   // blocks of depth positions
+  uint32_t* rows_tab;           // [min(n_tiles, kGroup)][kb]
+  uint32_t* pairs_tab;
+  unsigned long long* row_tot;  // [n_tiles] (at most a strip per tile)
+  unsigned long long* pair_tot;
+  uint32_t* row_base;           // [n_tiles + 1]
+  uint32_t* pair_base;
+  uint32_t* blk_base;
+  uint64_t* bits;               // [at most n_tiles] words
+  uint2* rec;                   // [capacity]
+  uint32_t* hist;               // [capacity / kRecBlock + kGroup][columns]
   size_t bytes;
 };
 
-static SortWs layout(void* ws, int64_t n, int64_t capacity) {
-  const int64_t cap = std::max<int64_t>(capacity, 1), nn = std::max<int64_t>(n, 1);
-  const int64_t m = std::max(cap, nn);
-  // blocks of any sort of up to m keys: 1024-key blocks below 2^20 keys, 4096-key blocks above
-  const int64_t max_blocks = std::max<int64_t>(1024, sort_blocks(m, kPairItems)) + 1;
-  const int64_t hist_n = 256 * max_blocks;
-  const int64_t part_n = std::max<int64_t>(256, scan_partials(nn + 1)) + 1;
+static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
+  const int64_t cap = std::max<int64_t>(capacity, 1), nn = std::max<int64_t>(n, 1), nt = std::max<int64_t>(n_tiles, 1);
   size_t o = 0;
   char* b = (char*)ws;
   auto take = [&](size_t bytes) {
@@ -1120,113 +1081,149 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity) {
     return (void*)p;
   };
   SortWs w;
-  w.hstride = (int)depth_hstride(nn);
-  const int64_t table_words = (int64_t)kDepthDigits * w.hstride;
-  const int64_t scalar_words = 3 * 2 * TGS_COUNTER_SLOTS;  // three rows of 64-bit slots
-  w.zeroed_words = scalar_words + 4 * table_words;
-  w.zeroed = (uint32_t*)take(sizeof(uint32_t) * w.zeroed_words);
-  w.scalars = (unsigned long long*)w.zeroed;
-  for (int k = 0; k < 4; ++k) w.dhist[k] = w.zeroed ? w.zeroed + scalar_words + k * table_words : nullptr;
   w.counts = (unsigned long long*)take(4 * sizeof(unsigned long long));
   w.eff_total = (uint32_t*)(w.counts ? w.counts + 2 : nullptr);
-  w.dhoffs = (uint32_t*)take(sizeof(uint32_t) * table_words);
+  w.n_keyed = (uint32_t*)(w.counts ? w.counts + 3 : nullptr);
+  w.hstride = (int)(ceil_div(ceil_div(nn, kDepthBlockKeys), 4) * 4);
+  w.dhist = (uint32_t*)take(sizeof(uint32_t) * kDepthDigits * w.hstride);
+  w.dhoffs = (uint32_t*)take(sizeof(uint32_t) * kDepthDigits * w.hstride);
   w.ddtot = (uint32_t*)take(sizeof(uint32_t) * kDepthDigits);
-  w.emit_cnt = (uint32_t*)take(sizeof(uint32_t) * nn);
-  w.rect_sorted = (int4*)take(sizeof(int4) * nn);
-  w.cnt_sorted = (uint32_t*)take(sizeof(uint32_t) * nn);
-  w.ids_sorted = (uint32_t*)take(sizeof(uint32_t) * nn);
-  w.off = (uint32_t*)take(sizeof(uint32_t) * (nn + 1));
   for (int k = 0; k < 2; ++k) {
     w.dkeys[k] = (uint32_t*)take(sizeof(uint32_t) * nn);
     w.dvals[k] = (uint32_t*)take(sizeof(uint32_t) * nn);
   }
-  w.partials = (uint32_t*)take(sizeof(uint32_t) * part_n);
-  w.hist = (uint32_t*)take(sizeof(uint32_t) * hist_n);
-  w.hoffs = (uint32_t*)take(sizeof(uint32_t) * hist_n);
-  w.cap = cap;
-  // 8 bytes per pair: a u32 key, or (16-byte aligned halves) a u16/u32 tile key and a u32 id
-  for (int k = 0; k < 2; ++k) w.pkeys[k] = take(align_up(sizeof(uint32_t) * cap, 256) + sizeof(uint32_t) * cap);
+  w.ids_sorted = w.dvals[0];  // the last pass's target
+  w.part = (uint32_t*)take(nn <= kSmallSort ? sizeof(uint32_t) * nn * ceil_div(nn, kRankChunk) : 0);
+  w.rects = (int4*)take(sizeof(int4) * nn);
+  w.kb = ceil_div(nn, kRowThreads);
+  w.spans = (uint16_t*)take(sizeof(uint16_t) * kSpanRows * w.kb);
+  w.rowinfo = (int2*)take(sizeof(int2) * nn);
+  const int64_t gs = std::min<int64_t>(nt, kGroup);
+  w.rows_tab = (uint32_t*)take(sizeof(uint32_t) * gs * w.kb);
+  w.pairs_tab = (uint32_t*)take(sizeof(uint32_t) * gs * w.kb);
+  w.row_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
+  w.pair_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
+  w.row_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
+  w.pair_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
+  w.blk_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
+  w.bits = (uint64_t*)take(sizeof(uint64_t) * nt);
+  w.rec = (uint2*)take(sizeof(uint2) * cap);
+  w.hist = (uint32_t*)take(sizeof(uint32_t) * (cap / kRecBlock + gs + 1) * std::min<int64_t>(nt, kStripCols));
   w.bytes = o;
   return w;
 }
 
-static int bits_for(uint64_t max_value) {  // bits needed to represent 0..max_value
-  int b = 0;
-  while (b < 64 && (max_value >> b) != 0) ++b;
-  return b;
-}
-
-// Stable LSD sort of the n depth keys with their ids (the count kernel has
-// filled the first pass's table); the last pass writes ids, rectangles and
-// pair counts in depth order.
-static void sort_depth(const SortWs& w, uint32_t n, const int4* rect, int tiles_x, int tiles_y, hipStream_t s,
-                       bool gather_counts = true) {
-  const unsigned nb = (unsigned)depth_blocks(n);
-  int cur = 0;
+// The depth order of the Gaussians with a non-empty rectangle; rects, when
+// given, receives the clamped rectangles.
+static void sort_depth(const SortWs& w, int64_t n, const int4* rect, const float* depth, int tiles_x, int tiles_y,
+                       int4* rects, hipStream_t s) {
+  if (n <= kSmallSort) {
+    const int chunks = (int)ceil_div(n, kRankChunk);
+    const unsigned blocks = (unsigned)ceil_div(n, kRankThreads);
+    hipLaunchKernelGGL(rank_kernel, dim3(blocks, (unsigned)chunks), dim3(kRankThreads), 0, s, rect, depth, (uint32_t)n,
+                       tiles_x, tiles_y, w.part, w.ddtot, rects);
+    hipLaunchKernelGGL(rank_place_kernel, dim3(blocks), dim3(kRankThreads), 0, s, (const uint32_t*)w.part,
+                       (const uint32_t*)w.ddtot, (uint32_t)n, chunks, w.ids_sorted, w.n_keyed);
+    return;
+  }
+  const int nb = (int)ceil_div(n, kDepthBlockKeys);
+  const dim3 grid((unsigned)nb), block(kSortThreads);
+  hipLaunchKernelGGL(key_kernel, grid, block, 0, s, rect, depth, (uint32_t)n, tiles_x, tiles_y, w.hstride, w.dkeys[0],
+                     w.dhist, rects);
   for (int p = 0; p < 4; ++p) {
-    // rows of hstride entries (the padding stays zero from the start-of-call fill)
-    hipLaunchKernelGGL((radix_hist_kernel<uint32_t, 8, kDepthItems>), dim3(nb), dim3(kSortThreads), 0, s,
-                       w.dkeys[cur], n, (const uint32_t*)nullptr, 8 * p, w.hstride, w.dhist[p]);
-    hipLaunchKernelGGL(digit_scan_kernel, dim3(kDepthDigits), dim3(1024), 0, s, w.dhist[p], (int)nb, w.hstride,
-                       w.dhoffs, w.ddtot, (const uint32_t*)nullptr, kDepthBlockKeys);
-    DepthPassOut o{};
-    if (p < 3) {
-      o.keys = w.dkeys[cur ^ 1];
-      o.vals = w.dvals[cur ^ 1];
-      hipLaunchKernelGGL(depth_pass_kernel<false>, dim3(nb), dim3(kSortThreads), 0, s, w.dkeys[cur], w.dvals[cur],
-                         n, 8 * p, w.hstride, w.dhoffs, w.ddtot, o);
-    } else {
-      o.ids_sorted = w.ids_sorted;
-      o.rect = rect;
-      o.emit_cnt = gather_counts ? w.emit_cnt : nullptr;
-      o.rect_sorted = w.rect_sorted;
-      o.cnt_sorted = w.cnt_sorted;
-      o.tiles_x = tiles_x;
-      o.tiles_y = tiles_y;
-      hipLaunchKernelGGL(depth_pass_kernel<true>, dim3(nb), dim3(kSortThreads), 0, s, w.dkeys[cur], w.dvals[cur],
-                         n, 8 * p, w.hstride, w.dhoffs, w.ddtot, o);
-    }
-    cur ^= 1;
+    const uint32_t* kin = w.dkeys[p & 1];
+    const uint32_t* vin = w.dvals[p & 1];
+    uint32_t* kout = w.dkeys[(p & 1) ^ 1];
+    uint32_t* vout = w.dvals[(p & 1) ^ 1];  // ids_sorted after the last pass
+    if (p > 0)
+      hipLaunchKernelGGL(depth_hist_kernel, grid, block, 0, s, kin, (const uint32_t*)w.n_keyed, 8 * p, w.hstride,
+                         w.dhist);
+    hipLaunchKernelGGL(digit_scan_kernel, dim3(kDepthDigits), dim3(1024), 0, s, w.dhist, nb, w.hstride, w.dhoffs,
+                       w.ddtot, p > 0 ? (const uint32_t*)w.n_keyed : (const uint32_t*)nullptr, kDepthBlockKeys);
+    if (p == 0)
+      hipLaunchKernelGGL((depth_pass_kernel<true, false>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed, 0,
+                         w.hstride, w.dhoffs, w.ddtot, kout, vout);
+    else if (p < 3)
+      hipLaunchKernelGGL((depth_pass_kernel<false, false>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed,
+                         8 * p, w.hstride, w.dhoffs, w.ddtot, kout, vout);
+    else
+      hipLaunchKernelGGL((depth_pass_kernel<false, true>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed,
+                         8 * p, w.hstride, w.dhoffs, w.ddtot, kout, vout);
   }
 }
 
-// kPay false: the key is (tile << id_bits) | id (32 bits when they fit).
-// kPay true: the key is the tile alone (16 bits) and the id travels as a
-// 32-bit payload; used when tile and id bits together exceed 32, where a
-// 64-bit key would move 16 bytes per pair and pass instead of 12.
-// bound: the capacity (host), sizing every grid; the pair count itself is
-// read on the device (w.eff_total), so nothing here waits for the host.
-template <typename K, bool kPay, int kMode = kEmitAll>
-static void sort_pairs(const SortWs& w, const uint32_t* ids, int64_t n, uint32_t bound, const float4* splat,
-                       const int32_t* tile_slot, int tiles_x, uint32_t n_t, int id_bits, int tbits, double tau, double lia,
-                       const float* depth, uint32_t* vals, uint64_t* keys64, uint32_t* ranges, hipStream_t s) {
-  // each ping-pong buffer (8 bytes per pair of capacity) holds the keys and, after them, the payload
-  K* kb[2] = {(K*)w.pkeys[0], (K*)w.pkeys[1]};
-  uint32_t* pb[2] = {nullptr, nullptr};
-  if (kPay)
-    for (int k = 0; k < 2; ++k) pb[k] = (uint32_t*)((char*)w.pkeys[k] + align_up(sizeof(K) * (size_t)w.cap, 256));
-  const int key_id_bits = kPay ? 0 : id_bits;
-  hipLaunchKernelGGL((emit_kernel<K, kMode>), dim3((unsigned)std::max<int64_t>(ceil_div(n, emit_batch<kMode>()), 1)),
-                     dim3(kEmitThreads), 0, s,
-                     w.rect_sorted, w.off, ids, n, splat, tile_slot, tiles_x, n_t, key_id_bits, tau, lia, w.eff_total,
-                     kb[0], pb[0]);
-  const int passes = pass_count(tbits);
-  int cur = 0, shift = key_id_bits;
-  for (int p = 0; p < passes; ++p) {
-    const int b = pass_bits(tbits, p);
-    // non-final passes carry the payload to the other buffer; the last writes the ids
-    const ScatterOut o = {kb[cur ^ 1], p == passes - 1 ? vals : pb[cur ^ 1], key_id_bits, depth, keys64};
-    if (p == passes - 1)
-      radix_pass_bits<K, kPay, true, kPairItems>(b, kb[cur], pb[cur], bound, w.eff_total, shift, w.hist, w.hoffs,
-                                                 w.partials, o, s);
-    else
-      radix_pass_bits<K, kPay, false, kPairItems>(b, kb[cur], pb[cur], bound, w.eff_total, shift, w.hist, w.hoffs,
-                                                  w.partials, o, s);
-    cur ^= 1;
-    shift += b;
+// The lists of the depth positions that a describes (a.pos0 .. a.pos_end of
+// at most `positions`), with the tables and buffers of w.  m as in
+// strip_base_kernel (-1: not a depth-prefix call).
+template <bool kWide>
+static void list_pairs(BinArgs a, const SortWs& w, int64_t positions, int64_t capacity, int64_t m,
+                       unsigned long long* out, hipStream_t s) {
+  const int64_t strips = (int64_t)a.sc * a.tiles_y;
+  const unsigned kb = (unsigned)ceil_div(positions, kRowThreads);
+  auto group = [&](int64_t s0) {
+    a.s0 = (int)s0;
+    a.sn = (int)std::min<int64_t>(kGroup, strips - s0);
+  };
+  auto count = [&] {
+    if (kb > 0) hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb), dim3(kRowThreads), 0, s, a);
+    hipLaunchKernelGGL(strip_scan_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
+  };
+  for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
+    group(s0);
+    count();
   }
-  hipLaunchKernelGGL((ranges_kernel<K>), dim3((unsigned)std::max<int64_t>(ceil_div(bound, kRangeBlock), 1)),
-                     dim3(256), 0, s, kb[cur], bound, w.eff_total, key_id_bits, n_t, (uint2*)ranges);
+  hipLaunchKernelGGL(strip_base_kernel, dim3(1), dim3(1024), 0, s, a, strips, m, capacity, w.counts, out);
+  for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
+    group(s0);
+    if (strips > kGroup) count();  // the tables hold one group
+    if (kb > 0 && capacity > 0) {
+      const unsigned nb = (unsigned)std::min<int64_t>(capacity / kRecBlock + a.sn, kPairGrid);
+      hipLaunchKernelGGL(bin_rows_kernel<kWide>, dim3(kb), dim3(kRowThreads), 0, s, a);
+      hipLaunchKernelGGL(bin_hist_kernel, dim3(nb), dim3(kRecThreads), 0, s, a);
+      hipLaunchKernelGGL(bin_offsets_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
+      if (a.cols <= kStripCols / 2)  // half the LDS: more workgroups per compute unit
+        hipLaunchKernelGGL(bin_place_kernel<kStripCols / 2>, dim3(nb), dim3(kRecThreads), 0, s, a);
+      else
+        hipLaunchKernelGGL(bin_place_kernel<kStripCols>, dim3(nb), dim3(kRecThreads), 0, s, a);
+    } else {
+      hipLaunchKernelGGL(bin_offsets_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
+    }
+  }
+}
+
+// What both calls share of BinArgs; tile_slot (nullable) becomes the bits.
+static BinArgs bin_args(const SortWs& w, const float* splat, const int32_t* tile_slot, int tiles_x, int tiles_y,
+                        float alpha_min, uint32_t* vals, uint32_t* ranges, hipStream_t s) {
+  BinArgs a{};
+  a.splat = (const float4*)splat;
+  a.tiles_x = tiles_x;
+  a.tiles_y = tiles_y;
+  a.wpr = (int)ceil_div(tiles_x, kWave);
+  a.sc = (int)ceil_div(tiles_x, kStripCols);
+  a.cols = std::min(tiles_x, kStripCols);
+  // 2 ln(1/alpha_min) with a 0.1 % margin, rounded up to a multiple of 1/64
+  a.lia = std::log(1.0 / (double)alpha_min);
+  a.tau = std::ceil(128.0 * a.lia * 1.001) / 64.0;
+  a.kb = w.kb;
+  a.rows_tab = w.rows_tab;
+  a.pairs_tab = w.pairs_tab;
+  a.spans = w.spans;
+  a.rowinfo = w.rowinfo;
+  a.row_tot = w.row_tot;
+  a.pair_tot = w.pair_tot;
+  a.row_base = w.row_base;
+  a.pair_base = w.pair_base;
+  a.blk_base = w.blk_base;
+  a.eff_total = w.eff_total;
+  a.rec = w.rec;
+  a.hist = w.hist;
+  a.vals = vals;
+  a.ranges = (uint2*)ranges;
+  if (tile_slot != nullptr) {
+    hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)tiles_y), dim3(kWave), 0, s, tile_slot, tiles_x, a.wpr, w.bits);
+    a.bits = w.bits;
+  }
+  return a;
 }
 
 }  // namespace tgs
@@ -1234,128 +1231,60 @@ static void sort_pairs(const SortWs& w, const uint32_t* ids, int64_t n, uint32_t
 using namespace tgs;
 
 extern "C" size_t tgs_bin_sort_workspace_size(int64_t n, int64_t capacity, int32_t n_tiles) {
-  (void)n_tiles;
   if (n < 0 || capacity < 0) return 0;
-  return layout(nullptr, n, capacity).bytes;
+  return layout(nullptr, n, capacity, n_tiles).bytes;
 }
 
 // Everything after the argument checks: queued on the stream, no host wait.
 // prefix >= 0: the lists hold the pairs of the first `prefix` Gaussians in
-// (depth, id) order only (every Gaussian when prefix >= n), and the counts
-// are the prefix call's (w.counts[3] = the whole lists' pairs); -1: whole
-// lists with the plain counts.
+// (depth, id) order only (every Gaussian when prefix >= n) and out[2] is the
+// prefix call's estimate; -1: whole lists.  out nullable.
 static int32_t bin_sort_queue(const int32_t* rect, const float* splat, const float* depth, int64_t n,
                               const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
                               uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges, uint8_t* touched,
-                              const SortWs& w, hipStream_t s, const char* who, int64_t prefix = -1) {
-  const uint32_t n_t = (uint32_t)tiles_x * (uint32_t)tiles_y;
-  // 2 ln(1/alpha_min) with a 0.1 % margin, rounded up to a multiple of 1/64
-  const double lia = std::log(1.0 / (double)alpha_min);
-  const double tau = std::ceil(128.0 * lia * 1.001) / 64.0;
-  // empty ranges and the zeroed workspace region (counters, table padding)
-  hipLaunchKernelGGL(zero2_u32_kernel, dim3((unsigned)ceil_div(2 * (int64_t)n_t + w.zeroed_words, 256)), dim3(256),
-                     0, s, ranges, 2 * (int64_t)n_t, w.zeroed, w.zeroed_words);
-  if (n == 0) {  // zero counts and pair total
-    hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(64), 0, s, w.scalars, capacity, w.counts, w.eff_total);
-    return hip_status(who);
-  }
-  const bool pre = prefix >= 0;
-  const int64_t m = pre ? std::min(prefix, n) : n;
-  if (!pre) {
-    hipLaunchKernelGGL(count_kernel, dim3((unsigned)ceil_div(n, kCountBatch)), dim3(kWave), 0, s,
-                       (const int4*)rect, (const uint32_t*)nullptr, (const float4*)splat, depth, n, tile_slot,
-                       tiles_x, tiles_y, tau, lia, w.dkeys[0], w.dvals[0], w.emit_cnt, touched, w.scalars);
-    hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(64), 0, s, w.scalars, capacity, w.counts, w.eff_total);
-    // (depth, id) order; Gaussians without pairs last
-    sort_depth(w, (uint32_t)n, (const int4*)rect, tiles_x, tiles_y, s);
-    // pair offsets (they wrap only past 2^32 pairs, where the capacity check has already set the total to 0)
-    exclusive_scan<uint32_t>(w.cnt_sorted, w.off, n, w.partials, s);
-  } else {
-    // depth-prefix lists: (depth, id) order of the Gaussians with a
-    // rectangle (the others last), then the counts of the first m only
-    hipLaunchKernelGGL(key_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, (const int4*)rect, depth, n,
-                       tiles_x, tiles_y, w.dkeys[0], w.dvals[0], w.scalars);
-    sort_depth(w, (uint32_t)n, (const int4*)rect, tiles_x, tiles_y, s, false);
-    if (m > 0)
-      hipLaunchKernelGGL(count_kernel, dim3((unsigned)ceil_div(m, kCountBatch)), dim3(kWave), 0, s,
-                         (const int4*)w.rect_sorted, (const uint32_t*)w.ids_sorted, (const float4*)splat, depth, m,
-                         tile_slot, tiles_x, tiles_y, tau, lia, (uint32_t*)nullptr, (uint32_t*)nullptr,
-                         w.cnt_sorted, touched, w.scalars);
-    hipLaunchKernelGGL(prefix_totals_kernel, dim3(1), dim3(64), 0, s, w.scalars, m, capacity, w.counts,
-                       w.eff_total);
-    exclusive_scan<uint32_t>(w.cnt_sorted, w.off, m, w.partials, s);
-  }
-  if (capacity == 0) return hip_status(who);
-  const uint32_t bound = (uint32_t)capacity;
-  const int id_bits = std::max(1, bits_for((uint64_t)n - 1));
-  const int tbits = bits_for(n_t);
-  // with a tile subset only its tiles are emitted
-  auto sort_all = [&](auto filter) {
-    constexpr int kF = decltype(filter)::value ? kEmitCompact : kEmitAll;
-    if (id_bits + tbits <= 32)
-      sort_pairs<uint32_t, false, kF>(w, w.ids_sorted, m, bound, (const float4*)splat, tile_slot, tiles_x, n_t,
-                                      id_bits, tbits, tau, lia, depth, vals, keys, ranges, s);
-    else if (tbits <= 16)
-      sort_pairs<uint16_t, true, kF>(w, w.ids_sorted, m, bound, (const float4*)splat, tile_slot, tiles_x, n_t,
-                                     id_bits, tbits, tau, lia, depth, vals, keys, ranges, s);
-    else
-      sort_pairs<uint32_t, true, kF>(w, w.ids_sorted, m, bound, (const float4*)splat, tile_slot, tiles_x, n_t,
-                                     id_bits, tbits, tau, lia, depth, vals, keys, ranges, s);
-  };
-  if (tile_slot != nullptr)
-    sort_all(std::true_type{});
+                              const SortWs& w, hipStream_t s, const char* who, unsigned long long* out,
+                              int64_t prefix = -1) {
+  BinArgs a = bin_args(w, splat, tile_slot, tiles_x, tiles_y, alpha_min, vals, ranges, s);
+  if (n > 0)
+    sort_depth(w, n, (const int4*)rect, depth, tiles_x, tiles_y, prefix >= 0 ? w.rects : nullptr, s);
   else
-    sort_all(std::false_type{});
+    hipLaunchKernelGGL(set_kernel<uint32_t>, dim3(1), dim3(64), 0, s, w.n_keyed, 0u);
+  const int64_t m = prefix >= 0 ? std::min(prefix, n) : n;
+  a.n_keyed = w.n_keyed;
+  a.pos0 = 0;
+  a.pos_end = m;
+  a.ids = w.ids_sorted;
+  a.rect = (const int4*)rect;
+  a.touched = touched;
+  a.keys64 = keys;
+  a.depth = depth;
+  if (a.sc > 1)
+    list_pairs<true>(a, w, m, capacity, prefix >= 0 ? m : -1, out, s);
+  else
+    list_pairs<false>(a, w, m, capacity, prefix >= 0 ? m : -1, out, s);
   return hip_status(who);
 }
 
 // The continuation of depth-prefix lists: the pairs of the Gaussians from
-// depth rank `prefix` on in the flagged tiles, from the depth order that
-// the prefix call left in its workspace w1, sorted by tile (each tile's
-// list in depth order) with the scratch and pair buffers of w2.
+// depth rank `prefix` on in the flagged tiles, from the depth order and the
+// rectangles that the prefix call left in its workspace w1, with the tables
+// and buffers of w2.
 static int32_t continue_queue(const float* splat, int64_t n, const int32_t* flag_slot, const uint32_t* n_flagged,
                               int32_t tiles_x, int32_t tiles_y, float alpha_min, int64_t prefix, uint32_t* vals2,
                               int64_t capacity2, uint32_t* ranges2, const SortWs& w1, const SortWs& w2,
-                              hipStream_t s, const char* who) {
-  const uint32_t n_t = (uint32_t)tiles_x * (uint32_t)tiles_y;
-  const double lia = std::log(1.0 / (double)alpha_min);
-  const double tau = std::ceil(128.0 * lia * 1.001) / 64.0;
-  hipLaunchKernelGGL(zero2_u32_kernel, dim3((unsigned)ceil_div(2 * (int64_t)n_t + w2.zeroed_words, 256)), dim3(256),
-                     0, s, ranges2, 2 * (int64_t)n_t, w2.zeroed, w2.zeroed_words);
-  const int64_t m = n - std::min(prefix, n);
-  // the flagged tiles' summed-area table (or, for larger grids, per-row
-  // running counts) in the pair-sort histogram (free until the sort)
-  const int64_t sat_words = (int64_t)(tiles_x + 1) * (tiles_y + 1);
-  const int64_t rc_words = (int64_t)(tiles_x + 1) * tiles_y;
-  uint32_t* sat = sat_words <= kSatWords ? w2.hist : nullptr;
-  uint32_t* rowc = sat == nullptr && rc_words <= 256 * 1024 ? w2.hist : nullptr;
-  if (m > 0 && sat != nullptr)
-    hipLaunchKernelGGL(flag_sat_kernel, dim3(1), dim3(1024), 0, s, flag_slot, tiles_x, tiles_y, n_flagged, sat);
-  if (m > 0 && rowc != nullptr)
-    hipLaunchKernelGGL(flag_rows_kernel, dim3((unsigned)tiles_y), dim3(kWave), 0, s, flag_slot, tiles_x, n_flagged,
-                       rowc);
-  if (m > 0)
-    hipLaunchKernelGGL(count_cont_kernel, dim3((unsigned)ceil_div(m, kCountBatch)), dim3(kWave), 0, s,
-                       w1.rect_sorted + prefix, w1.ids_sorted + prefix, (const uint32_t*)nullptr, m,
-                       (const float4*)splat, flag_slot, n_flagged, (const uint32_t*)rowc, (const uint32_t*)sat,
-                       tiles_x, tiles_y, tau, lia, w2.emit_cnt, w2.scalars);
-  hipLaunchKernelGGL(totals_kernel, dim3(1), dim3(64), 0, s, w2.scalars, capacity2, w2.counts, w2.eff_total);
-  if (m == 0 || capacity2 == 0) return hip_status(who);
-  exclusive_scan<uint32_t>(w2.emit_cnt, w2.off, m, w2.partials, s);
-  SortWs wc = w2;
-  wc.rect_sorted = w1.rect_sorted + prefix;
-  const uint32_t bound = (uint32_t)capacity2;
-  const int id_bits = std::max(1, bits_for((uint64_t)n - 1));
-  const int tbits = bits_for(n_t);
-  if (id_bits + tbits <= 32)
-    sort_pairs<uint32_t, false, kEmitWalk>(wc, w1.ids_sorted + prefix, m, bound, (const float4*)splat, flag_slot, tiles_x,
-                                      n_t, id_bits, tbits, tau, lia, nullptr, vals2, nullptr, ranges2, s);
-  else if (tbits <= 16)
-    sort_pairs<uint16_t, true, kEmitWalk>(wc, w1.ids_sorted + prefix, m, bound, (const float4*)splat, flag_slot, tiles_x,
-                                     n_t, id_bits, tbits, tau, lia, nullptr, vals2, nullptr, ranges2, s);
+                              unsigned long long* out, hipStream_t s, const char* who) {
+  BinArgs a = bin_args(w2, splat, flag_slot, tiles_x, tiles_y, alpha_min, vals2, ranges2, s);
+  const int64_t p0 = std::min(prefix, n);
+  a.n_keyed = w1.n_keyed;
+  a.pos0 = p0;
+  a.pos_end = n;
+  a.ids = w1.ids_sorted;
+  a.rect = w1.rects;
+  a.n_flagged = n_flagged;
+  if (a.sc > 1)
+    list_pairs<true>(a, w2, n - p0, capacity2, -1, out, s);
   else
-    sort_pairs<uint32_t, true, kEmitWalk>(wc, w1.ids_sorted + prefix, m, bound, (const float4*)splat, flag_slot, tiles_x,
-                                     n_t, id_bits, tbits, tau, lia, nullptr, vals2, nullptr, ranges2, s);
+    list_pairs<false>(a, w2, n - p0, capacity2, -1, out, s);
   return hip_status(who);
 }
 
@@ -1374,23 +1303,23 @@ static int32_t bin_sort_check(const int32_t* rect, const float* splat, const flo
   return TGS_OK;
 }
 
+// Tiles of a grid for the layout, 0 for a grid that the checks refuse.
+static int64_t grid_tiles(int32_t tiles_x, int32_t tiles_y) {
+  return tiles_x > 0 && tiles_y > 0 ? (int64_t)tiles_x * tiles_y : 0;
+}
+
 extern "C" int32_t tgs_bin_sort_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,
                                       const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
                                       uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges,
                                       uint8_t* touched, int64_t* counts, void* ws, size_t ws_bytes, void* stream) {
-  const SortWs w = layout(ws, n, capacity);
+  const SortWs w = layout(ws, n, capacity, grid_tiles(tiles_x, tiles_y));
   if (int32_t e = bin_sort_check(rect, splat, depth, n, tiles_x, tiles_y, alpha_min, vals, capacity, ranges, ws,
                                  ws_bytes, w, "tgs_bin_sort_async"))
     return e;
   TGS_REQUIRE(counts != nullptr && ((uintptr_t)counts & 7) == 0,
               "tgs_bin_sort_async: counts must be an 8-byte aligned device pointer");
-  hipStream_t s = as_stream(stream);
-  if (int32_t e = bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
-                                 ranges, touched, w, s, "tgs_bin_sort_async"))
-    return e;
-  hipLaunchKernelGGL(copy_counts_kernel, dim3(1), dim3(64), 0, s, (const unsigned long long*)w.counts,
-                     (unsigned long long*)counts);
-  return hip_status("tgs_bin_sort_async");
+  return bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
+                        touched, w, as_stream(stream), "tgs_bin_sort_async", (unsigned long long*)counts);
 }
 
 extern "C" int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,
@@ -1398,20 +1327,15 @@ extern "C" int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* s
                                              float alpha_min, int64_t prefix, uint64_t* keys, uint32_t* vals,
                                              int64_t capacity, uint32_t* ranges, uint8_t* touched, int64_t* counts,
                                              void* ws, size_t ws_bytes, void* stream) {
-  const SortWs w = layout(ws, n, capacity);
+  const SortWs w = layout(ws, n, capacity, grid_tiles(tiles_x, tiles_y));
   if (int32_t e = bin_sort_check(rect, splat, depth, n, tiles_x, tiles_y, alpha_min, vals, capacity, ranges, ws,
                                  ws_bytes, w, "tgs_bin_sort_prefix_async"))
     return e;
   TGS_REQUIRE(prefix >= 0, "tgs_bin_sort_prefix_async: negative prefix");
   TGS_REQUIRE(counts != nullptr && ((uintptr_t)counts & 7) == 0,
               "tgs_bin_sort_prefix_async: counts must be an 8-byte aligned device pointer");
-  hipStream_t s = as_stream(stream);
-  if (int32_t e = bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
-                                 ranges, touched, w, s, "tgs_bin_sort_prefix_async", prefix))
-    return e;
-  hipLaunchKernelGGL(copy_counts3_kernel, dim3(1), dim3(64), 0, s, (const unsigned long long*)w.counts,
-                     (unsigned long long*)counts);
-  return hip_status("tgs_bin_sort_prefix_async");
+  return bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
+                        touched, w, as_stream(stream), "tgs_bin_sort_prefix_async", (unsigned long long*)counts, prefix);
 }
 
 extern "C" int32_t tgs_bin_sort_continue_async(const float* splat, int64_t n, const int32_t* flag_slot,
@@ -1429,16 +1353,12 @@ extern "C" int32_t tgs_bin_sort_continue_async(const float* splat, int64_t n, co
   TGS_REQUIRE(((uintptr_t)splat & 15) == 0 && ((uintptr_t)ws & 15) == 0 && ((uintptr_t)ws2 & 15) == 0 &&
                   ((uintptr_t)counts2 & 7) == 0,
               "%s: splat, ws and ws2 must be 16-byte, counts2 8-byte aligned", who);
-  const SortWs w1 = layout((void*)ws, n, capacity);
-  const SortWs w2 = layout(ws2, n, capacity2);
+  const int64_t n_t = grid_tiles(tiles_x, tiles_y);
+  const SortWs w1 = layout((void*)ws, n, capacity, n_t);
+  const SortWs w2 = layout(ws2, n, capacity2, n_t);
   TGS_REQUIRE(ws_bytes >= w1.bytes && ws2_bytes >= w2.bytes, "%s: workspace too small", who);
-  hipStream_t s = as_stream(stream);
-  if (int32_t e = continue_queue(splat, n, flag_slot, n_flagged, tiles_x, tiles_y, alpha_min, prefix, vals2, capacity2,
-                                 ranges2, w1, w2, s, who))
-    return e;
-  hipLaunchKernelGGL(copy_counts_kernel, dim3(1), dim3(64), 0, s, (const unsigned long long*)w2.counts,
-                     (unsigned long long*)counts2);
-  return hip_status(who);
+  return continue_queue(splat, n, flag_slot, n_flagged, tiles_x, tiles_y, alpha_min, prefix, vals2, capacity2, ranges2,
+                        w1, w2, (unsigned long long*)counts2, as_stream(stream), who);
 }
 
 extern "C" int32_t tgs_bin_sort(const int32_t* rect, const float* splat, const float* depth, int64_t n,
@@ -1446,14 +1366,14 @@ extern "C" int32_t tgs_bin_sort(const int32_t* rect, const float* splat, const f
                                 uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges,
                                 uint8_t* touched, int64_t* n_pairs, void* ws, size_t ws_bytes,
                                 void* stream) {
-  const SortWs w = layout(ws, n, capacity);
+  const SortWs w = layout(ws, n, capacity, grid_tiles(tiles_x, tiles_y));
   if (int32_t e = bin_sort_check(rect, splat, depth, n, tiles_x, tiles_y, alpha_min, vals, capacity, ranges, ws,
                                  ws_bytes, w, "tgs_bin_sort"))
     return e;
   TGS_REQUIRE(n_pairs != nullptr, "tgs_bin_sort: null n_pairs");
   hipStream_t s = as_stream(stream);
   if (int32_t e = bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
-                                 ranges, touched, w, s, "tgs_bin_sort"))
+                                 ranges, touched, w, s, "tgs_bin_sort", nullptr))
     return e;
   // the one synchronisation: the two counts, read back when the stream has run the call
   unsigned long long host[2] = {0, 0};
