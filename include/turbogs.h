@@ -163,6 +163,17 @@ int32_t tgs_project(const float* params, int64_t n, const tgs_camera* cam,
                     int32_t* radius, int32_t* rect, uint8_t* clamp, float* g2d_clear,
                     void* stream);
 
+/* tgs_project of several views in one pass over the parameters (each
+ * Gaussian's parameters are read once for every eight views); the outputs
+ * equal tgs_project's bit for bit.
+ *   cams     [n_views] host array of the views' cameras (n_views >= 0)
+ *   splat, depth, radius, rect, clamp, g2d_clear  host arrays of n_views
+ *            device pointers (g2d_clear nullable, and so is each entry) */
+int32_t tgs_project_views(const float* params, int64_t n, int32_t n_views, const tgs_camera* cams,
+                          const tgs_raster_params* rp, float* const* splat, float* const* depth,
+                          int32_t* const* radius, int32_t* const* rect, uint8_t* const* clamp,
+                          float* const* g2d_clear, void* stream);
+
 /* Tile-wise error/age pixel sampling (Sec. 3.5, Eq. pix_prob_err and
  * Eq. pix_topk_age, plus the mixed remainder of the hyper-parameter table).
  *   E, A        [H][W] uint16: half-precision error bits, age (read)

@@ -110,6 +110,8 @@ PROTOTYPES = {
     "tgs_sample_tile_count": (_I32, [_I32, _I32, ctypes.POINTER(tgs_sample_params)]),
     "tgs_project": (_I32, [_P, _I64, ctypes.POINTER(tgs_camera), ctypes.POINTER(tgs_raster_params),
                            _P, _P, _P, _P, _P, _P, _P]),
+    "tgs_project_views": (_I32, [_P, _I64, _I32, ctypes.POINTER(tgs_camera), ctypes.POINTER(tgs_raster_params),
+                                 _P, _P, _P, _P, _P, _P, _P]),
     "tgs_sample_workspace_size": (_SZ, [_I32, _I32]),
     "tgs_sample": (_I32, [_P, _P, _I32, _I32, ctypes.POINTER(tgs_sample_params), _P, _P, _P, _P, _P, _P,
                           _P, _SZ, _P]),
@@ -281,6 +283,15 @@ def tgs_project(params, n, cam: tgs_camera, rp: tgs_raster_params, splat, depth,
                 g2d_clear=None):
     _check(lib().tgs_project(_ptr(params), n, ctypes.byref(cam), ctypes.byref(rp), _ptr(splat), _ptr(depth),
                              _ptr(radius), _ptr(rect), _ptr(clamp), _ptr(g2d_clear), _stream()), "tgs_project")
+
+
+def tgs_project_views(params, n, cams, rp: tgs_raster_params, splat, depth, radius, rect, clamp, g2d_clear):
+    """tgs_project of several views in one launch; cams and the outputs are
+    per-view lists (tgs_camera records, device tensors)."""
+    k = len(cams)
+    ptrs = [(ctypes.c_void_p * k)(*[_ptr(t) for t in xs]) for xs in (splat, depth, radius, rect, clamp, g2d_clear)]
+    _check(lib().tgs_project_views(_ptr(params), n, k, (tgs_camera * k)(*cams), ctypes.byref(rp), *ptrs, _stream()),
+           "tgs_project_views")
 
 
 def tgs_project_f64(params, n, cam: tgs_camera, rp: tgs_raster_params, rec64, splat, depth, radius, rect, clamp):

@@ -120,18 +120,11 @@ struct Geom {
   int rect[4];
 };
 
+// The part that no camera enters: mean, scales, rotation and 3D covariance.
 template <typename PT>
-__device__ __forceinline__ void geometry(const PT* __restrict__ params, int64_t n, int64_t i,
-                                         const CamArgs& cam, double z_near, double dil, Geom& g) {
+__device__ __forceinline__ void shape_geometry(const PT* __restrict__ params, int64_t n, int64_t i, Geom& g) {
 #pragma clang fp contract(off)
   for (int k = 0; k < 3; ++k) g.mu[k] = (double)params[(int64_t)k * n + i];
-  for (int r = 0; r < 3; ++r)
-    g.t[r] = ((cam.R[r * 3 + 0] * g.mu[0] + cam.R[r * 3 + 1] * g.mu[1]) + cam.R[r * 3 + 2] * g.mu[2]) +
-             cam.t[r];
-  const double tx = g.t[0], ty = g.t[1], tz = g.t[2];
-  const bool in_front = tz > z_near;
-  const double tzs = in_front ? tz : 1.0;
-
   for (int k = 0; k < 3; ++k) g.s[k] = exp((double)params[(int64_t)(3 + k) * n + i]);
   const double qw = params[6 * n + i], qx = params[7 * n + i], qy = params[8 * n + i],
                qz = params[9 * n + i];
@@ -152,7 +145,17 @@ __device__ __forceinline__ void geometry(const PT* __restrict__ params, int64_t 
   for (int r = 0; r < 3; ++r)
     for (int k = 0; k < 3; ++k)
       g.Sigma[r][k] = (g.M[r][0] * g.M[k][0] + g.M[r][1] * g.M[k][1]) + g.M[r][2] * g.M[k][2];
+}
 
+// The camera's part, from the shape.
+__device__ __forceinline__ void view_geometry(const CamArgs& cam, double z_near, double dil, Geom& g) {
+#pragma clang fp contract(off)
+  for (int r = 0; r < 3; ++r)
+    g.t[r] = ((cam.R[r * 3 + 0] * g.mu[0] + cam.R[r * 3 + 1] * g.mu[1]) + cam.R[r * 3 + 2] * g.mu[2]) +
+             cam.t[r];
+  const double tx = g.t[0], ty = g.t[1], tz = g.t[2];
+  const bool in_front = tz > z_near;
+  const double tzs = in_front ? tz : 1.0;
   g.J00 = cam.fx / tzs;
   g.J02 = -(cam.fx * tx) / (tzs * tzs);
   g.J11 = cam.fy / tzs;
@@ -193,6 +196,13 @@ __device__ __forceinline__ void geometry(const PT* __restrict__ params, int64_t 
   g.rect[3] = tclamp(((g.py + r) + 15.0) / 16.0, cam.tiles_y);
   const int area = (g.rect[2] - g.rect[0]) * (g.rect[3] - g.rect[1]);
   g.visible = in_front && ok_det && area > 0;
+}
+
+template <typename PT>
+__device__ __forceinline__ void geometry(const PT* __restrict__ params, int64_t n, int64_t i,
+                                         const CamArgs& cam, double z_near, double dil, Geom& g) {
+  shape_geometry(params, n, i, g);
+  view_geometry(cam, z_near, dil, g);
 }
 
 

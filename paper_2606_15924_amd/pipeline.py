@@ -5,6 +5,7 @@ of the path runs in the HIP library through the C ABI.
 A view's work, in order:
   tgs_sample -> tgs_project -> tgs_bin_sort -> tgs_render_fwd -> tgs_loss
   -> tgs_ema_age_update -> tgs_render_bwd -> tgs_project_bwd
+(steps of several views project them all in one launch, tgs_project_views)
 and once per step the optimizer update, fused with the last view's
 projection backward (tgs_project_bwd_optimizer_step).  The sampler of every view runs first
 because the loss normalises by the step's total sample and tile counts.
@@ -553,36 +554,43 @@ class Trainer:
                 while len(self._done) <= k:
                     self._done.append(torch.cuda.Event())
                 out.append((vs, self._view_chain(k, used[k], views[k], self.cams[views[k]], sampled, prefix_n, vs,
-                                                 self._done[k])))
+                                                 self._done[k], projected=together)))
             return out
 
-        def advance(chains, once=False):
+        def advance(chains):
             while chains:
                 for c in list(chains):
                     with torch.cuda.stream(c[0]):
                         if next(c[1], StopIteration) is StopIteration:
                             chains.remove(c)
-                if once:
-                    return
 
-        first = []
+        def project_all():
+            # every view's projection in one pass over the parameters
+            with st("project"):
+                B.tgs_project_views(self.params, self.n, [self.cams[v] for v in views], self.rp,
+                                    [vb.splat for vb in used], [vb.depth for vb in used], [vb.radius for vb in used],
+                                    [vb.rect for vb in used], [vb.clamp for vb in used], [vb.g2d for vb in used])
+
+        together = len(used) > 1
         if par:
+            if together:
+                project_all()
             if self._cleared is None:
                 self._cleared = torch.cuda.Event()
             self._cleared.record(main)
-            # the first views' projections are queued before the samplers
-            first = chains_of(0)
-            advance(first, once=True)
         for k, (vb, v) in enumerate(zip(used, views)):
             if vb.dense:
                 sampled.append(None)
                 continue
             # views side by side: a sampler over every tile is short and runs
-            # on main (idle until the first backward) beside the projections;
+            # on main (idle until the first backward) beside the views' binning;
             # drawing a tile subset is one long workgroup per view, so those
-            # run on the view streams (after the view's projection), side by side
+            # run on the view streams, side by side
             if par:
-                ss = self._view_stream(k) if self.cfg.n_tiles_sel > 0 else main
+                ss = main
+                if self.cfg.n_tiles_sel > 0:
+                    ss = self._view_stream(k)
+                    ss.wait_event(self._cleared)
             else:
                 ss = self._sample_stream(k)
                 ss.wait_stream(main)
@@ -607,15 +615,16 @@ class Trainer:
             # enqueued breadth first, a stage of every view in turn, so each
             # stream has work queued soon after the step starts (views that
             # share a stream go in consecutive rounds)
-            advance(first)
-            for g0 in range(S, len(used), S):
+            for g0 in range(0, len(used), S):
                 advance(chains_of(g0))
+        elif together:
+            project_all()
         for k, (vb, v) in enumerate(zip(used, views)):
             cam = self.cams[v]
             if par:
                 main.wait_event(self._done[k])
             else:
-                for _ in self._view_chain(k, vb, v, cam, sampled, prefix_n, main):
+                for _ in self._view_chain(k, vb, v, cam, sampled, prefix_n, main, projected=together):
                     pass
             with st("render_bwd"):
                 # g2d was cleared by the projection; the density sums of sparse
@@ -655,18 +664,19 @@ class Trainer:
         self._queue_count_check(used)
         return used
 
-    def _view_chain(self, k, vb, v, cam, sampled, prefix_n, vs, done=None):
-        """Projection, binning, forward and loss of the step's k-th view on
-        stream ``vs`` (the current stream).  With ``done`` (views side by
+    def _view_chain(self, k, vb, v, cam, sampled, prefix_n, vs, done=None, projected=False):
+        """Projection (unless ``projected``), binning, forward and loss of the
+        step's k-th view on stream ``vs`` (the current stream).  With ``done`` (views side by
         side) the event is recorded after the loss and the error maps'
         update follows on ``vs`` itself: a wait queued on the side stream
         would hold up whatever view stream shares its hardware queue.  A
         generator: it yields after each stage, with the stream set by the
         caller around every resumption."""
         st = self._stage
-        with st("project"):
-            vb.project(self.params, cam, self.rp)
-        yield
+        if not projected:
+            with st("project"):
+                vb.project(self.params, cam, self.rp)
+            yield
         if sampled[k] is not None and vb.bin_sort_needs_samples():
             vs.wait_event(sampled[k])   # binning keeps the sampled tiles only
         with st("bin_sort"):
