@@ -62,6 +62,7 @@ extern "C" {
 #define TGS_COUNTER_SLOTS 64 /* slots per counter of tgs_render_fwd */
 #define TGS_RENDER_CHUNKS 8      /* equal chunks of a tile's list in the backward when the forward keeps state */
 #define TGS_RENDER_CHUNK_LEN 32  /* their list positions */
+#define TGS_VIEW_BATCH 4         /* views per launch of the calls over several views */
 #define TGS_RENDER_LONG_CHUNKS 4 /* chunks after them: 2, 4, 8 times as long, the last takes the rest */
 
 enum {
@@ -295,6 +296,31 @@ int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* splat, const
                                   int64_t prefix, uint64_t* keys, uint32_t* vals, int64_t capacity,
                                   uint32_t* ranges, uint8_t* touched, int64_t* counts, void* ws, size_t ws_bytes,
                                   void* stream);
+
+/* tgs_bin_sort_async (prefix = -1) or tgs_bin_sort_prefix_async
+ * (prefix >= 0) of several views of one set of Gaussians, each kernel
+ * launched once for up to TGS_VIEW_BATCH views; the lists and counts are
+ * those calls'.
+ *   views  [n_views] host array (n_views >= 0): each view's arguments as of
+ *          the single-view calls, the output arrays and workspaces distinct
+ *          (touched may be shared) */
+typedef struct tgs_bin_view {
+  const int32_t* rect;
+  const float* splat;
+  const float* depth;
+  const int32_t* tile_slot;
+  uint64_t* keys;
+  uint32_t* vals;
+  int64_t capacity;
+  uint32_t* ranges;
+  uint8_t* touched;
+  int64_t* counts;
+  void* ws;
+  size_t ws_bytes;
+  int32_t tiles_x, tiles_y;
+} tgs_bin_view;
+int32_t tgs_bin_sort_views_async(const tgs_bin_view* views, int32_t n_views, int64_t n, float alpha_min,
+                                 int64_t prefix, void* stream);
 
 /* The continuation of depth-prefix lists: for every tile with
  * flag_slot[tile] >= 0, the pairs of the Gaussians from depth rank `prefix`

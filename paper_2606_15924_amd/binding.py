@@ -40,6 +40,14 @@ class tgs_raster_params(ctypes.Structure):
                 ("bg", ctypes.c_float * 3)]
 
 
+class tgs_bin_view(ctypes.Structure):
+    _fields_ = [("rect", ctypes.c_void_p), ("splat", ctypes.c_void_p), ("depth", ctypes.c_void_p),
+                ("tile_slot", ctypes.c_void_p), ("keys", ctypes.c_void_p), ("vals", ctypes.c_void_p),
+                ("capacity", ctypes.c_int64), ("ranges", ctypes.c_void_p), ("touched", ctypes.c_void_p),
+                ("counts", ctypes.c_void_p), ("ws", ctypes.c_void_p), ("ws_bytes", ctypes.c_size_t),
+                ("tiles_x", ctypes.c_int32), ("tiles_y", ctypes.c_int32)]
+
+
 class tgs_sample_params(ctypes.Structure):
     _fields_ = [("n_pix", ctypes.c_int32), ("hard_permille", ctypes.c_int32),
                 ("stable_permille", ctypes.c_int32), ("n_tiles_sel", ctypes.c_int32),
@@ -83,6 +91,7 @@ PROTOTYPES = {
                                   _SZ, _P]),
     "tgs_bin_sort_prefix_async": (_I32, [_P, _P, _P, _I64, _P, _I32, _I32, ctypes.c_float, _I64, _P, _P, _I64, _P,
                                          _P, _P, _P, _SZ, _P]),
+    "tgs_bin_sort_views_async": (_I32, [_P, _I32, _I64, ctypes.c_float, _I64, _P]),
     "tgs_bin_sort_continue_async": (_I32, [_P, _I64, _P, _P, _I32, _I32, ctypes.c_float, _I64, _I64, _P, _SZ, _P,
                                            _I64, _P, _P, _P, _SZ, _P]),
     "tgs_render_fwd_prefix": (_I32, [_P, _P, _P, _I32, _I32, _I32, _I32, _P, _P, _P, _I32, _I32,
@@ -374,6 +383,18 @@ def tgs_bin_sort_prefix_async(rect, splat, depth, n, tile_slot, tiles_x, tiles_y
                                            _ptr(ranges), _ptr(touched), _ptr(counts), _ptr(ws),
                                            ws.numel() * ws.element_size(), _stream()),
            "tgs_bin_sort_prefix_async")
+
+
+def tgs_bin_sort_views_async(views, n, alpha_min, prefix):
+    """tgs_bin_sort_async (prefix -1) or tgs_bin_sort_prefix_async of several
+    views in one call; views: tgs_bin_view records (see bin_view)."""
+    _check(lib().tgs_bin_sort_views_async((tgs_bin_view * len(views))(*views), len(views), n, alpha_min, prefix,
+                                          _stream()), "tgs_bin_sort_views_async")
+
+
+def bin_view(rect, splat, depth, tile_slot, tiles_x, tiles_y, keys, vals, capacity, ranges, touched, counts, ws):
+    return tgs_bin_view(_ptr(rect), _ptr(splat), _ptr(depth), _ptr(tile_slot), _ptr(keys), _ptr(vals), capacity,
+                        _ptr(ranges), _ptr(touched), _ptr(counts), _ptr(ws), ws.numel(), tiles_x, tiles_y)
 
 
 def tgs_bin_sort_continue_async(splat, n, flag_slot, tiles_x, tiles_y, alpha_min, prefix, capacity, ws, vals2,

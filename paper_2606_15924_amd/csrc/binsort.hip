@@ -229,6 +229,26 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid, uint64_t
   return peers;
 }
 
+// A view's depth sort.  The views of a step go through every kernel together,
+// one per grid layer: the short launches (scans, counts) are latency-bound, so
+// three views in one take about as long as one.
+struct DepthArgs {
+  const int4* rect;
+  const float* depth;
+  uint32_t n;
+  int tiles_x, tiles_y;
+  int stride;          // row stride of the digit tables
+  uint32_t* keys[2];
+  uint32_t* vals[2];
+  uint32_t* hist;      // [256][stride]
+  uint32_t* hoffs;
+  uint32_t* dtot;      // [256]
+  uint32_t* n_keyed;
+  int4* rects;         // nullable
+  uint32_t* part;      // few Gaussians: partial ranks
+};
+using DepthBatch = Batch<DepthArgs>;
+
 // Depth key of Gaussian i: its depth bits when its rectangle holds a tile
 // (below kCulledKey also for a NaN depth), else kCulledKey.
 __device__ __forceinline__ uint32_t depth_key(int4 r, float depth) {
@@ -239,10 +259,8 @@ __device__ __forceinline__ uint32_t depth_key(int4 r, float depth) {
 // The depth keys, the first pass's digit counts of every block (culled
 // Gaussians left out), and, when rects is given, the clamped rectangles (a
 // depth-prefix call keeps them for its continuation).
-__global__ void __launch_bounds__(kSortThreads) key_kernel(const int4* __restrict__ rect,
-                                                           const float* __restrict__ depth, uint32_t n, int tiles_x,
-                                                           int tiles_y, int stride, uint32_t* __restrict__ dkeys,
-                                                           uint32_t* __restrict__ hist, int4* __restrict__ rects) {
+__global__ void __launch_bounds__(kSortThreads) key_kernel(DepthBatch batch) {
+  const DepthArgs& a = batch.v[blockIdx.z];
   __shared__ uint32_t h[kDepthDigits];
   h[threadIdx.x] = 0u;
   __syncthreads();
@@ -250,22 +268,23 @@ __global__ void __launch_bounds__(kSortThreads) key_kernel(const int4* __restric
 #pragma unroll
   for (int k = 0; k < kDepthItems; ++k) {
     const int64_t i = b0 + k * kSortThreads + threadIdx.x;
-    if (i >= (int64_t)n) continue;
-    const int4 r = clamp_rect(rect[i], tiles_x, tiles_y);
-    const uint32_t key = depth_key(r, depth[i]);
-    dkeys[i] = key;
-    if (rects != nullptr) rects[i] = r;
+    if (i >= (int64_t)a.n) continue;
+    const int4 r = clamp_rect(a.rect[i], a.tiles_x, a.tiles_y);
+    const uint32_t key = depth_key(r, a.depth[i]);
+    a.keys[0][i] = key;
+    if (a.rects != nullptr) a.rects[i] = r;
     if (key != kCulledKey) atomicAdd(&h[key & (kDepthDigits - 1u)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * stride + blockIdx.x] = h[threadIdx.x];
+  a.hist[(int64_t)threadIdx.x * a.stride + blockIdx.x] = h[threadIdx.x];
 }
 
 // Digit counts of every block of the later passes (over the *n keys left).
-__global__ void __launch_bounds__(kSortThreads) depth_hist_kernel(const uint32_t* __restrict__ keys,
-                                                                  const uint32_t* __restrict__ n_dev, int shift,
-                                                                  int stride, uint32_t* __restrict__ hist) {
-  const uint32_t n = *n_dev;
+__global__ void __launch_bounds__(kSortThreads) depth_hist_kernel(DepthBatch batch, int pass) {
+  const DepthArgs& a = batch.v[blockIdx.z];
+  const uint32_t* const keys = a.keys[pass & 1];
+  const uint32_t n = *a.n_keyed;
+  const int shift = 8 * pass;
   const int64_t b0 = (int64_t)blockIdx.x * kDepthBlockKeys;
   if (b0 >= (int64_t)n) return;  // the scan and the scatter stop at the last block that holds keys
   __shared__ uint32_t h[kDepthDigits];
@@ -282,44 +301,43 @@ __global__ void __launch_bounds__(kSortThreads) depth_hist_kernel(const uint32_t
     if (b0 + k * kSortThreads + threadIdx.x < (int64_t)n)
       atomicAdd(&h[(key[k] >> shift) & (kDepthDigits - 1u)], 1u);
   __syncthreads();
-  hist[(int64_t)threadIdx.x * stride + blockIdx.x] = h[threadIdx.x];
+  a.hist[(int64_t)threadIdx.x * a.stride + blockIdx.x] = h[threadIdx.x];
 }
 
 // One workgroup per digit: exclusive prefix of the digit's per-block counts
-// (a contiguous row of the digit-major table) and the digit's total.
-__global__ void __launch_bounds__(1024) digit_scan_kernel(const uint32_t* __restrict__ hist, int nblocks,
-                                                          int stride, uint32_t* __restrict__ hoffs,
-                                                          uint32_t* __restrict__ dtot,
-                                                          const uint32_t* __restrict__ n_dev, int block_keys) {
+// (a contiguous row of the digit-major table) and the digit's total.  Only the
+// blocks that hold keys have table entries.
+__global__ void __launch_bounds__(1024) digit_scan_kernel(DepthBatch batch, int pass) {
+  const DepthArgs& a = batch.v[blockIdx.z];
   __shared__ uint32_t lds[1024 / kWave];
-  // with a device count, only the blocks that hold keys have table entries
-  if (n_dev != nullptr) nblocks = (int)min<int64_t>(nblocks, ceil_div((int64_t)*n_dev, (int64_t)block_keys));
-  const int64_t row = (int64_t)blockIdx.x * stride;
+  const int64_t n = pass == 0 ? a.n : *a.n_keyed;
+  const int nblocks = (int)ceil_div(n, kDepthBlockKeys);
+  const int64_t row = (int64_t)blockIdx.x * a.stride;
   uint32_t carry = 0;
   for (int b0 = 0; b0 < nblocks; b0 += 1024) {
     const int b = b0 + (int)threadIdx.x;
-    const uint32_t v = b < nblocks ? hist[row + b] : 0u;
+    const uint32_t v = b < nblocks ? a.hist[row + b] : 0u;
     uint32_t tot;
     const uint32_t ex = block_exclusive_scan<1024, uint32_t>(v, lds, &tot);
-    if (b < nblocks) hoffs[row + b] = carry + ex;
+    if (b < nblocks) a.hoffs[row + b] = carry + ex;
     carry += tot;
   }
-  if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
+  if (threadIdx.x == 0) a.dtot[blockIdx.x] = carry;
 }
 
 // One pass of the depth sort: ranks a block's keys by digit (stable: by wave,
 // round, lane), reorders them in LDS and writes runs of equal digits to
 // consecutive addresses.  kFirst: the ids are the indices, culled keys are
-// left out and the number kept goes to *n_dev, which the later passes read.
+// left out and the number kept goes to *n_keyed, which the later passes read.
 // kLast: only the ids are written.
 template <bool kFirst, bool kLast>
-__global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t* __restrict__ keys_in,
-                                                                  const uint32_t* __restrict__ vals_in, uint32_t n_arg,
-                                                                  uint32_t* __restrict__ n_dev, int shift, int stride,
-                                                                  const uint32_t* __restrict__ hoffs,
-                                                                  const uint32_t* __restrict__ dtot,
-                                                                  uint32_t* __restrict__ keys_out,
-                                                                  uint32_t* __restrict__ vals_out) {
+__global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(DepthBatch batch, int pass) {
+  const DepthArgs& a = batch.v[blockIdx.z];
+  const uint32_t* const keys_in = a.keys[pass & 1];
+  const uint32_t* const vals_in = a.vals[pass & 1];
+  uint32_t* const keys_out = a.keys[(pass & 1) ^ 1];
+  uint32_t* const vals_out = a.vals[(pass & 1) ^ 1];
+  const int shift = 8 * pass;
   constexpr int kItems = kDepthItems, kBlockKeys = kDepthBlockKeys, kDigits = kDepthDigits;
   __shared__ uint32_t s_cnt[kSortWaves][kDigits];  // per-wave digit counts, then block-local offsets
   __shared__ uint32_t s_gbase[kDigits];            // global position of block-local position 0 of the digit
@@ -327,13 +345,13 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
   __shared__ uint32_t s_vals[kBlockKeys];
   __shared__ uint32_t s_red[kSortWaves];
   __shared__ uint64_t s_mask[kSortWaves][kDigits];
-  const uint32_t n = kFirst ? n_arg : *n_dev;
+  const uint32_t n = kFirst ? a.n : *a.n_keyed;
   const int64_t blk0 = (int64_t)blockIdx.x * kBlockKeys;
   if (blk0 >= (int64_t)n) return;  // workgroup-uniform
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   for (int i = tid; i < kSortWaves * kDigits; i += kSortThreads) (&s_cnt[0][0])[i] = 0;
   // keys of digit tid in the earlier blocks, and in all blocks
-  const uint32_t before = hoffs[(int64_t)tid * stride + blockIdx.x], all_d = dtot[tid];
+  const uint32_t before = a.hoffs[(int64_t)tid * a.stride + blockIdx.x], all_d = a.dtot[tid];
   const int64_t wbase = blk0 + (int64_t)wave * kWave * kItems;
   uint32_t key[kItems], val[kItems];
 #pragma unroll
@@ -368,7 +386,7 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
   const uint32_t dstart = block_exclusive_scan<kSortThreads, uint32_t>(all_d, s_red, &all);
   for (int w = 0; w < kSortWaves; ++w) s_cnt[w][tid] = lstart + pre[w];
   s_gbase[tid] = dstart + before - lstart;
-  if (kFirst && blockIdx.x == 0 && tid == 0) *n_dev = all;
+  if (kFirst && blockIdx.x == 0 && tid == 0) *a.n_keyed = all;
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
@@ -388,7 +406,7 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(const uint32_t
     if (lp < count) {
       const uint32_t kk = s_keys[lp];
       const uint32_t dst = s_gbase[(kk >> shift) & (kDigits - 1u)] + lp;
-      if (dst >= n_arg) continue;  // never taken for a consistent table; keeps every write in bounds
+      if (dst >= a.n) continue;  // never taken for a consistent table; keeps every write in bounds
       if (!kLast) keys_out[dst] = kk;
       vals_out[dst] = s_vals[lp];
     }
@@ -409,10 +427,9 @@ constexpr int64_t kSmallSort = 16384;
 constexpr int kRankThreads = 256;
 constexpr int kRankChunk = kRankThreads;
 
-__global__ void __launch_bounds__(kRankThreads) rank_kernel(const int4* __restrict__ rect,
-                                                            const float* __restrict__ depth, uint32_t n, int tiles_x,
-                                                            int tiles_y, uint32_t* __restrict__ part,
-                                                            uint32_t* __restrict__ kept, int4* __restrict__ rects) {
+__global__ void __launch_bounds__(kRankThreads) rank_kernel(DepthBatch batch) {
+  const DepthArgs& a = batch.v[blockIdx.z];
+  const uint32_t n = a.n;
   __shared__ __align__(16) uint32_t s_key[kRankChunk];
   __shared__ uint32_t s_kept;
   const int tid = threadIdx.x;
@@ -422,16 +439,16 @@ __global__ void __launch_bounds__(kRankThreads) rank_kernel(const int4* __restri
   {
     const uint32_t j = j0 + tid;
     uint32_t other = kCulledKey;  // past the end: before no key
-    if (j < n) other = depth_key(clamp_rect(rect[j], tiles_x, tiles_y), depth[j]);
+    if (j < n) other = depth_key(clamp_rect(a.rect[j], a.tiles_x, a.tiles_y), a.depth[j]);
     s_key[tid] = other;
     const uint64_t have = ballot(other != kCulledKey);
     if (blockIdx.x == 0 && lane_id() == 0) atomicAdd(&s_kept, (uint32_t)__popcll(have));
   }
   uint32_t key = kCulledKey;
   if (i < n) {
-    const int4 r = clamp_rect(rect[i], tiles_x, tiles_y);
-    key = depth_key(r, depth[i]);
-    if (rects != nullptr && blockIdx.y == 0) rects[i] = r;
+    const int4 r = clamp_rect(a.rect[i], a.tiles_x, a.tiles_y);
+    key = depth_key(r, a.depth[i]);
+    if (a.rects != nullptr && blockIdx.y == 0) a.rects[i] = r;
   }
   __syncthreads();
   uint32_t rank = 0;
@@ -460,41 +477,27 @@ __global__ void __launch_bounds__(kRankThreads) rank_kernel(const int4* __restri
       rank += (l > 3 ? o.w <= key : o.w < key) ? 1u : 0u;
     }
   }
-  if (i < n) part[(int64_t)blockIdx.y * n + i] = key == kCulledKey ? ~0u : rank;
-  if (blockIdx.x == 0 && tid == 0) kept[blockIdx.y] = s_kept;
+  if (i < n) a.part[(int64_t)blockIdx.y * n + i] = key == kCulledKey ? ~0u : rank;
+  if (blockIdx.x == 0 && tid == 0) a.dtot[blockIdx.y] = s_kept;
 }
 
-__global__ void __launch_bounds__(kRankThreads) rank_place_kernel(const uint32_t* __restrict__ part,
-                                                                  const uint32_t* __restrict__ kept, uint32_t n,
-                                                                  int chunks, uint32_t* __restrict__ ids_out,
-                                                                  uint32_t* __restrict__ n_out) {
-  const uint32_t i = blockIdx.x * (uint32_t)kRankThreads + threadIdx.x;
-  if (i < n && part[i] != ~0u) {
+__global__ void __launch_bounds__(kRankThreads) rank_place_kernel(DepthBatch batch, int chunks) {
+  const DepthArgs& a = batch.v[blockIdx.z];
+  const uint32_t n = a.n, i = blockIdx.x * (uint32_t)kRankThreads + threadIdx.x;
+  if (i < n && a.part[i] != ~0u) {
     uint32_t r = 0;
 #pragma unroll 8
-    for (int c = 0; c < chunks; ++c) r += part[(int64_t)c * n + i];
-    if (r < n) ids_out[r] = i;  // always (the ranks are a permutation); a safeguard
+    for (int c = 0; c < chunks; ++c) r += a.part[(int64_t)c * n + i];
+    if (r < n) a.vals[0][r] = i;  // always (the ranks are a permutation); a safeguard
   }
   if (i == 0) {
     uint32_t t = 0;
-    for (int c = 0; c < chunks; ++c) t += kept[c];
-    *n_out = t;
+    for (int c = 0; c < chunks; ++c) t += a.dtot[c];
+    *a.n_keyed = t;
   }
 }
 
 // ------------------------------------------------------------------ valid tiles
-// One bit per tile, wpr 64-bit words per tile row: the tiles whose map entry
-// is >= 0.  A wave per row.
-__global__ void __launch_bounds__(kWave) tile_bits_kernel(const int32_t* __restrict__ tile_slot, int tiles_x, int wpr,
-                                                          uint64_t* __restrict__ bits) {
-  const int64_t y = blockIdx.x;
-  for (int w = 0; w < wpr; ++w) {
-    const int x = w * kWave + lane_id();
-    const uint64_t b = ballot(x < tiles_x && tile_slot[y * tiles_x + x] >= 0);
-    if (lane_id() == 0) bits[y * wpr + w] = b;
-  }
-}
-
 // Set bits of the columns [lo, hi] of a row of bits.
 __device__ __forceinline__ uint32_t valid_in(const uint64_t* __restrict__ row, int lo, int hi) {
   uint32_t c = 0;
@@ -527,7 +530,7 @@ struct BinArgs {
   const uint32_t* ids;        // Gaussians in depth order
   const int4* rect;           // by Gaussian
   const float4* splat;
-  const uint64_t* bits;       // valid tiles (nullptr: all)
+  uint64_t* bits;             // valid tiles (nullptr: all)
   const uint32_t* n_flagged;  // nullable: nothing is listed when it is 0
   int tiles_x, tiles_y, wpr;
   int sc;                     // strips per tile row
@@ -553,7 +556,25 @@ struct BinArgs {
   uint64_t* keys64;           // nullable
   const float* depth;         // for keys64
   uint2* ranges;
+  const int32_t* tile_slot;   // nullable: the bits are made from it
+  int64_t m, capacity;        // m >= 0: a depth-prefix call over m positions
+  unsigned long long* counts; // the call's counts in its workspace
+  unsigned long long* out;    // nullable: the caller's
 };
+using BinBatch = Batch<BinArgs>;
+
+// One bit per tile, wpr 64-bit words per tile row: the tiles whose map entry
+// is >= 0.  A wave per row.
+__global__ void __launch_bounds__(kWave) tile_bits_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
+  const int64_t y = blockIdx.x;
+  if (a.tile_slot == nullptr || y >= a.tiles_y) return;
+  for (int w = 0; w < a.wpr; ++w) {
+    const int x = w * kWave + lane_id();
+    const uint64_t b = ballot(x < a.tiles_x && a.tile_slot[y * a.tiles_x + x] >= 0);
+    if (lane_id() == 0) a.bits[y * a.wpr + w] = b;
+  }
+}
 
 __device__ __forceinline__ int64_t bin_end(const BinArgs& a) { return min(a.pos_end, (int64_t)*a.n_keyed); }
 __device__ __forceinline__ bool bin_nothing(const BinArgs& a) { return a.n_flagged != nullptr && *a.n_flagged == 0u; }
@@ -597,7 +618,8 @@ __device__ __forceinline__ void ellipse_rows(const RowEllipse& e, int4 r, int& y
 // prefix sum, two exchanges through LDS and their barriers per 64 rows, which
 // took longer than the idle lanes do.
 template <bool kWide>
-__global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinArgs a) {
+__global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
   __shared__ uint32_t s_rows[kGroup], s_pairs[kGroup];
   __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
   __shared__ uint32_t s_red[kRowWaves];
@@ -662,7 +684,9 @@ __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinArgs a) {
 
 // A workgroup per strip of the group: the prefix of its records over the
 // blocks (in place), its records and its pairs.
-__global__ void __launch_bounds__(1024) strip_scan_kernel(BinArgs a) {
+__global__ void __launch_bounds__(1024) strip_scan_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
+  if ((int)blockIdx.x >= a.sn) return;  // the grid is sized for the view of the most strips
   __shared__ uint32_t lds[1024 / kWave];
   __shared__ unsigned long long lds64[1024 / kWave];
   const int64_t end = bin_end(a);
@@ -690,13 +714,13 @@ __global__ void __launch_bounds__(1024) strip_scan_kernel(BinArgs a) {
 
 // One workgroup: every strip's first record, pair and pair-stage block, and
 // the counts.  out (nullable) receives counts[0] = counts[1] = pairs; with
-// m > 0 (a depth-prefix call over m positions) also an estimate of the whole
+// m >= 0 (a depth-prefix call over m positions) also an estimate of the whole
 // lists' pairs: the prefix's pairs per Gaussian times the keyed Gaussians
 // (exact when the prefix holds them all; the nearest Gaussians cover the most
 // tiles, so it tends to exceed the count).
-__global__ void __launch_bounds__(1024) strip_base_kernel(BinArgs a, int64_t strips, int64_t m, int64_t capacity,
-                                                          unsigned long long* __restrict__ counts,
-                                                          unsigned long long* __restrict__ out) {
+__global__ void __launch_bounds__(1024) strip_base_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
+  const int64_t strips = (int64_t)a.sc * a.tiles_y;
   __shared__ unsigned long long lds[1024 / kWave];
   unsigned long long rows = 0, pairs = 0, blks = 0;  // before the strips of this round
   for (int64_t s0 = 0; s0 < strips; s0 += 1024) {
@@ -720,15 +744,15 @@ __global__ void __launch_bounds__(1024) strip_base_kernel(BinArgs a, int64_t str
     a.row_base[strips] = (uint32_t)rows;
     a.pair_base[strips] = (uint32_t)pairs;
     a.blk_base[strips] = (uint32_t)blks;
-    counts[0] = pairs;
-    counts[1] = pairs;
-    *a.eff_total = pairs <= (unsigned long long)capacity ? (uint32_t)pairs : 0u;
-    if (out != nullptr) {
-      out[0] = pairs;
-      out[1] = pairs;
-      if (m >= 0) {
-        const unsigned long long k = *a.n_keyed, mk = (unsigned long long)m < k ? (unsigned long long)m : k;
-        out[2] = mk >= k || mk == 0 ? pairs : (unsigned long long)ceil((double)pairs * (double)k / (double)mk);
+    a.counts[0] = pairs;
+    a.counts[1] = pairs;
+    *a.eff_total = pairs <= (unsigned long long)a.capacity ? (uint32_t)pairs : 0u;
+    if (a.out != nullptr) {
+      a.out[0] = pairs;
+      a.out[1] = pairs;
+      if (a.m >= 0) {
+        const unsigned long long k = *a.n_keyed, mk = (unsigned long long)a.m < k ? (unsigned long long)a.m : k;
+        a.out[2] = mk >= k || mk == 0 ? pairs : (unsigned long long)ceil((double)pairs * (double)k / (double)mk);
       }
     }
   }
@@ -738,7 +762,8 @@ __global__ void __launch_bounds__(1024) strip_base_kernel(BinArgs a, int64_t str
 // positions have a record there; a record's place is the strip's first one,
 // plus the earlier blocks', the earlier waves' and the earlier lanes' records.
 template <bool kWide>
-__global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinArgs a) {
+__global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
   __shared__ uint64_t s_mask[kRowWaves][kGroup];
   __shared__ uint32_t s_pos[kRowWaves][kGroup];
   __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
@@ -839,7 +864,8 @@ __device__ __forceinline__ RecSpan rec_span(const BinArgs& a, uint32_t b, int* s
 }
 
 // Pairs per column of 512 records: a difference array, then its prefix.
-__global__ void __launch_bounds__(kRecThreads) bin_hist_kernel(BinArgs a) {
+__global__ void __launch_bounds__(kRecThreads) bin_hist_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
   __shared__ int s_diff[kStripCols + 1];
   __shared__ int s_red[kRecThreads / kWave];
   __shared__ int s_strip;
@@ -871,7 +897,9 @@ __global__ void __launch_bounds__(kRecThreads) bin_hist_kernel(BinArgs a) {
 // A workgroup per strip of the group, 256 threads over its columns in each of
 // four quarters of its blocks: the columns' pairs, the tiles' ranges, and the
 // first list position of every (block, column).
-__global__ void __launch_bounds__(1024) bin_offsets_kernel(BinArgs a) {
+__global__ void __launch_bounds__(1024) bin_offsets_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
+  if ((int)blockIdx.x >= a.sn) return;  // as in strip_scan_kernel
   __shared__ uint32_t s_part[4][kStripCols];
   __shared__ uint32_t s_red[1024 / kWave];
   const int tid = threadIdx.x, col = tid & (kStripCols - 1), part = tid / kStripCols;
@@ -926,7 +954,8 @@ __global__ void __launch_bounds__(1024) bin_offsets_kernel(BinArgs a) {
 constexpr int kPlaceIds = 4096;
 
 template <int kCols>
-__global__ void __launch_bounds__(kRecThreads) bin_place_kernel(BinArgs a) {
+__global__ void __launch_bounds__(kRecThreads) bin_place_kernel(BinBatch batch) {
+  const BinArgs& a = batch.v[blockIdx.z];
   constexpr int kWaves = kRecThreads / kWave;
   __shared__ uint64_t s_mask[kWaves][kCols];
   __shared__ uint32_t s_run[kWaves][kCols];
@@ -1113,87 +1142,108 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
   return w;
 }
 
-// The depth order of the Gaussians with a non-empty rectangle; rects, when
-// given, receives the clamped rectangles.
-static void sort_depth(const SortWs& w, int64_t n, const int4* rect, const float* depth, int tiles_x, int tiles_y,
-                       int4* rects, hipStream_t s) {
+// The depth orders of the views' Gaussians with a non-empty rectangle.
+static void sort_depth(const DepthBatch& d, int views, int64_t n, hipStream_t s) {
+  const unsigned nv = (unsigned)views;
   if (n <= kSmallSort) {
     const int chunks = (int)ceil_div(n, kRankChunk);
     const unsigned blocks = (unsigned)ceil_div(n, kRankThreads);
-    hipLaunchKernelGGL(rank_kernel, dim3(blocks, (unsigned)chunks), dim3(kRankThreads), 0, s, rect, depth, (uint32_t)n,
-                       tiles_x, tiles_y, w.part, w.ddtot, rects);
-    hipLaunchKernelGGL(rank_place_kernel, dim3(blocks), dim3(kRankThreads), 0, s, (const uint32_t*)w.part,
-                       (const uint32_t*)w.ddtot, (uint32_t)n, chunks, w.ids_sorted, w.n_keyed);
+    hipLaunchKernelGGL(rank_kernel, dim3(blocks, (unsigned)chunks, nv), dim3(kRankThreads), 0, s, d);
+    hipLaunchKernelGGL(rank_place_kernel, dim3(blocks, 1, nv), dim3(kRankThreads), 0, s, d, chunks);
     return;
   }
-  const int nb = (int)ceil_div(n, kDepthBlockKeys);
-  const dim3 grid((unsigned)nb), block(kSortThreads);
-  hipLaunchKernelGGL(key_kernel, grid, block, 0, s, rect, depth, (uint32_t)n, tiles_x, tiles_y, w.hstride, w.dkeys[0],
-                     w.dhist, rects);
-  for (int p = 0; p < 4; ++p) {
-    const uint32_t* kin = w.dkeys[p & 1];
-    const uint32_t* vin = w.dvals[p & 1];
-    uint32_t* kout = w.dkeys[(p & 1) ^ 1];
-    uint32_t* vout = w.dvals[(p & 1) ^ 1];  // ids_sorted after the last pass
-    if (p > 0)
-      hipLaunchKernelGGL(depth_hist_kernel, grid, block, 0, s, kin, (const uint32_t*)w.n_keyed, 8 * p, w.hstride,
-                         w.dhist);
-    hipLaunchKernelGGL(digit_scan_kernel, dim3(kDepthDigits), dim3(1024), 0, s, w.dhist, nb, w.hstride, w.dhoffs,
-                       w.ddtot, p > 0 ? (const uint32_t*)w.n_keyed : (const uint32_t*)nullptr, kDepthBlockKeys);
+  const dim3 grid((unsigned)ceil_div(n, kDepthBlockKeys), 1, nv), block(kSortThreads);
+  hipLaunchKernelGGL(key_kernel, grid, block, 0, s, d);
+  for (int p = 0; p < 4; ++p) {  // the ids end in vals[0]
+    if (p > 0) hipLaunchKernelGGL(depth_hist_kernel, grid, block, 0, s, d, p);
+    hipLaunchKernelGGL(digit_scan_kernel, dim3(kDepthDigits, 1, nv), dim3(1024), 0, s, d, p);
     if (p == 0)
-      hipLaunchKernelGGL((depth_pass_kernel<true, false>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed, 0,
-                         w.hstride, w.dhoffs, w.ddtot, kout, vout);
+      hipLaunchKernelGGL((depth_pass_kernel<true, false>), grid, block, 0, s, d, p);
     else if (p < 3)
-      hipLaunchKernelGGL((depth_pass_kernel<false, false>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed,
-                         8 * p, w.hstride, w.dhoffs, w.ddtot, kout, vout);
+      hipLaunchKernelGGL((depth_pass_kernel<false, false>), grid, block, 0, s, d, p);
     else
-      hipLaunchKernelGGL((depth_pass_kernel<false, true>), grid, block, 0, s, kin, vin, (uint32_t)n, w.n_keyed,
-                         8 * p, w.hstride, w.dhoffs, w.ddtot, kout, vout);
+      hipLaunchKernelGGL((depth_pass_kernel<false, true>), grid, block, 0, s, d, p);
   }
 }
 
-// The lists of the depth positions that a describes (a.pos0 .. a.pos_end of
-// at most `positions`), with the tables and buffers of w.  m as in
-// strip_base_kernel (-1: not a depth-prefix call).
+static int64_t strips_of(const BinArgs& a) { return (int64_t)a.sc * a.tiles_y; }
+
+// The lists of the depth positions that each view's arguments describe
+// (pos0 .. pos_end).
 template <bool kWide>
-static void list_pairs(BinArgs a, const SortWs& w, int64_t positions, int64_t capacity, int64_t m,
-                       unsigned long long* out, hipStream_t s) {
-  const int64_t strips = (int64_t)a.sc * a.tiles_y;
+static void list_pairs(BinBatch& b, int views, hipStream_t s) {
+  const unsigned nv = (unsigned)views;
+  int64_t strips = 0, positions = 0, capacity = 0;
+  int rows = 0, cols = 0;
+  bool subset = false;
+  for (int k = 0; k < views; ++k) {
+    strips = std::max(strips, strips_of(b.v[k]));
+    positions = std::max(positions, b.v[k].pos_end - b.v[k].pos0);
+    capacity = std::max(capacity, b.v[k].capacity);
+    rows = std::max(rows, b.v[k].tiles_y);
+    cols = std::max(cols, b.v[k].cols);
+    subset = subset || b.v[k].tile_slot != nullptr;
+  }
   const unsigned kb = (unsigned)ceil_div(positions, kRowThreads);
+  unsigned sn = 0;
   auto group = [&](int64_t s0) {
-    a.s0 = (int)s0;
-    a.sn = (int)std::min<int64_t>(kGroup, strips - s0);
+    sn = 0;
+    for (int k = 0; k < views; ++k) {
+      BinArgs& a = b.v[k];
+      a.s0 = (int)s0;
+      a.sn = (int)std::min<int64_t>(kGroup, strips_of(a) - s0);
+      sn = std::max(sn, (unsigned)a.sn);
+    }
   };
   auto count = [&] {
-    if (kb > 0) hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb), dim3(kRowThreads), 0, s, a);
-    hipLaunchKernelGGL(strip_scan_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
+    if (kb > 0) hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads), 0, s, b);
+    hipLaunchKernelGGL(strip_scan_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
   };
+  if (subset) hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)rows, 1, nv), dim3(kWave), 0, s, b);
   for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
     group(s0);
     count();
   }
-  hipLaunchKernelGGL(strip_base_kernel, dim3(1), dim3(1024), 0, s, a, strips, m, capacity, w.counts, out);
+  hipLaunchKernelGGL(strip_base_kernel, dim3(1, 1, nv), dim3(1024), 0, s, b);
   for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
     group(s0);
     if (strips > kGroup) count();  // the tables hold one group
     if (kb > 0 && capacity > 0) {
-      const unsigned nb = (unsigned)std::min<int64_t>(capacity / kRecBlock + a.sn, kPairGrid);
-      hipLaunchKernelGGL(bin_rows_kernel<kWide>, dim3(kb), dim3(kRowThreads), 0, s, a);
-      hipLaunchKernelGGL(bin_hist_kernel, dim3(nb), dim3(kRecThreads), 0, s, a);
-      hipLaunchKernelGGL(bin_offsets_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
-      if (a.cols <= kStripCols / 2)  // half the LDS: more workgroups per compute unit
-        hipLaunchKernelGGL(bin_place_kernel<kStripCols / 2>, dim3(nb), dim3(kRecThreads), 0, s, a);
+      const unsigned nb = (unsigned)std::min<int64_t>(capacity / kRecBlock + sn, kPairGrid);
+      hipLaunchKernelGGL(bin_rows_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads), 0, s, b);
+      hipLaunchKernelGGL(bin_hist_kernel, dim3(nb, 1, nv), dim3(kRecThreads), 0, s, b);
+      hipLaunchKernelGGL(bin_offsets_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
+      if (cols <= kStripCols / 2)  // half the LDS: more workgroups per compute unit
+        hipLaunchKernelGGL(bin_place_kernel<kStripCols / 2>, dim3(nb, 1, nv), dim3(kRecThreads), 0, s, b);
       else
-        hipLaunchKernelGGL(bin_place_kernel<kStripCols>, dim3(nb), dim3(kRecThreads), 0, s, a);
+        hipLaunchKernelGGL(bin_place_kernel<kStripCols>, dim3(nb, 1, nv), dim3(kRecThreads), 0, s, b);
     } else {
-      hipLaunchKernelGGL(bin_offsets_kernel, dim3((unsigned)a.sn), dim3(1024), 0, s, a);
+      hipLaunchKernelGGL(bin_offsets_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
     }
   }
 }
 
-// What both calls share of BinArgs; tile_slot (nullable) becomes the bits.
+// Views of more strips than one group, or of strips cut by columns, go one by
+// one; the others together.
+static void list_all(BinBatch& b, int views, hipStream_t s) {
+  bool together = true;
+  for (int k = 0; k < views; ++k) together = together && b.v[k].sc == 1 && strips_of(b.v[k]) <= kGroup;
+  if (together) {
+    list_pairs<false>(b, views, s);
+    return;
+  }
+  for (int k = 0; k < views; ++k) {
+    BinBatch one{};
+    one.v[0] = b.v[k];
+    if (one.v[0].sc > 1) list_pairs<true>(one, 1, s);
+    else list_pairs<false>(one, 1, s);
+  }
+}
+
+// What both calls share of BinArgs; tile_slot nullable.
 static BinArgs bin_args(const SortWs& w, const float* splat, const int32_t* tile_slot, int tiles_x, int tiles_y,
-                        float alpha_min, uint32_t* vals, uint32_t* ranges, hipStream_t s) {
+                        float alpha_min, uint32_t* vals, uint32_t* ranges, int64_t capacity,
+                        unsigned long long* out) {
   BinArgs a{};
   a.splat = (const float4*)splat;
   a.tiles_x = tiles_x;
@@ -1219,10 +1269,12 @@ static BinArgs bin_args(const SortWs& w, const float* splat, const int32_t* tile
   a.hist = w.hist;
   a.vals = vals;
   a.ranges = (uint2*)ranges;
-  if (tile_slot != nullptr) {
-    hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)tiles_y), dim3(kWave), 0, s, tile_slot, tiles_x, a.wpr, w.bits);
-    a.bits = w.bits;
-  }
+  a.tile_slot = tile_slot;
+  a.bits = tile_slot != nullptr ? w.bits : nullptr;
+  a.m = -1;
+  a.capacity = capacity;
+  a.counts = w.counts;
+  a.out = out;
   return a;
 }
 
@@ -1235,57 +1287,82 @@ extern "C" size_t tgs_bin_sort_workspace_size(int64_t n, int64_t capacity, int32
   return layout(nullptr, n, capacity, n_tiles).bytes;
 }
 
-// Everything after the argument checks: queued on the stream, no host wait.
+// One view's call, after its argument checks: what goes into the batches.
 // prefix >= 0: the lists hold the pairs of the first `prefix` Gaussians in
 // (depth, id) order only (every Gaussian when prefix >= n) and out[2] is the
 // prefix call's estimate; -1: whole lists.  out nullable.
-static int32_t bin_sort_queue(const int32_t* rect, const float* splat, const float* depth, int64_t n,
-                              const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
-                              uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges, uint8_t* touched,
-                              const SortWs& w, hipStream_t s, const char* who, unsigned long long* out,
-                              int64_t prefix = -1) {
-  BinArgs a = bin_args(w, splat, tile_slot, tiles_x, tiles_y, alpha_min, vals, ranges, s);
-  if (n > 0)
-    sort_depth(w, n, (const int4*)rect, depth, tiles_x, tiles_y, prefix >= 0 ? w.rects : nullptr, s);
-  else
-    hipLaunchKernelGGL(set_kernel<uint32_t>, dim3(1), dim3(64), 0, s, w.n_keyed, 0u);
-  const int64_t m = prefix >= 0 ? std::min(prefix, n) : n;
+static void bin_sort_view(DepthArgs& d, BinArgs& a, const int32_t* rect, const float* splat, const float* depth,
+                          int64_t n, const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
+                          uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges, uint8_t* touched,
+                          const SortWs& w, unsigned long long* out, int64_t prefix) {
+  d.rect = (const int4*)rect;
+  d.depth = depth;
+  d.n = (uint32_t)n;
+  d.tiles_x = tiles_x;
+  d.tiles_y = tiles_y;
+  d.stride = w.hstride;
+  for (int k = 0; k < 2; ++k) {
+    d.keys[k] = w.dkeys[k];
+    d.vals[k] = w.dvals[k];
+  }
+  d.hist = w.dhist;
+  d.hoffs = w.dhoffs;
+  d.dtot = w.ddtot;
+  d.n_keyed = w.n_keyed;
+  d.rects = prefix >= 0 ? w.rects : nullptr;
+  d.part = w.part;
+  a = bin_args(w, splat, tile_slot, tiles_x, tiles_y, alpha_min, vals, ranges, capacity, out);
   a.n_keyed = w.n_keyed;
   a.pos0 = 0;
-  a.pos_end = m;
+  a.pos_end = prefix >= 0 ? std::min(prefix, n) : n;
+  a.m = prefix >= 0 ? a.pos_end : -1;
   a.ids = w.ids_sorted;
   a.rect = (const int4*)rect;
   a.touched = touched;
   a.keys64 = keys;
   a.depth = depth;
-  if (a.sc > 1)
-    list_pairs<true>(a, w, m, capacity, prefix >= 0 ? m : -1, out, s);
+}
+
+// Queued on the stream, no host wait.
+static int32_t bin_sort_queue(const DepthBatch& d, BinBatch& b, int views, int64_t n, hipStream_t s,
+                              const char* who) {
+  if (n > 0)
+    sort_depth(d, views, n, s);
   else
-    list_pairs<false>(a, w, m, capacity, prefix >= 0 ? m : -1, out, s);
+    for (int k = 0; k < views; ++k)
+      hipLaunchKernelGGL(set_kernel<uint32_t>, dim3(1), dim3(64), 0, s, d.v[k].n_keyed, 0u);
+  list_all(b, views, s);
   return hip_status(who);
+}
+
+static int32_t bin_sort_one(const int32_t* rect, const float* splat, const float* depth, int64_t n,
+                            const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
+                            uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges, uint8_t* touched,
+                            const SortWs& w, hipStream_t s, const char* who, unsigned long long* out,
+                            int64_t prefix = -1) {
+  DepthBatch d{};
+  BinBatch b{};
+  bin_sort_view(d.v[0], b.v[0], rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
+                ranges, touched, w, out, prefix);
+  return bin_sort_queue(d, b, 1, n, s, who);
 }
 
 // The continuation of depth-prefix lists: the pairs of the Gaussians from
 // depth rank `prefix` on in the flagged tiles, from the depth order and the
 // rectangles that the prefix call left in its workspace w1, with the tables
 // and buffers of w2.
-static int32_t continue_queue(const float* splat, int64_t n, const int32_t* flag_slot, const uint32_t* n_flagged,
-                              int32_t tiles_x, int32_t tiles_y, float alpha_min, int64_t prefix, uint32_t* vals2,
-                              int64_t capacity2, uint32_t* ranges2, const SortWs& w1, const SortWs& w2,
-                              unsigned long long* out, hipStream_t s, const char* who) {
-  BinArgs a = bin_args(w2, splat, flag_slot, tiles_x, tiles_y, alpha_min, vals2, ranges2, s);
-  const int64_t p0 = std::min(prefix, n);
+static BinArgs continue_view(const float* splat, int64_t n, const int32_t* flag_slot, const uint32_t* n_flagged,
+                             int32_t tiles_x, int32_t tiles_y, float alpha_min, int64_t prefix, uint32_t* vals2,
+                             int64_t capacity2, uint32_t* ranges2, const SortWs& w1, const SortWs& w2,
+                             unsigned long long* out) {
+  BinArgs a = bin_args(w2, splat, flag_slot, tiles_x, tiles_y, alpha_min, vals2, ranges2, capacity2, out);
   a.n_keyed = w1.n_keyed;
-  a.pos0 = p0;
+  a.pos0 = std::min(prefix, n);
   a.pos_end = n;
   a.ids = w1.ids_sorted;
   a.rect = w1.rects;
   a.n_flagged = n_flagged;
-  if (a.sc > 1)
-    list_pairs<true>(a, w2, n - p0, capacity2, -1, out, s);
-  else
-    list_pairs<false>(a, w2, n - p0, capacity2, -1, out, s);
-  return hip_status(who);
+  return a;
 }
 
 static int32_t bin_sort_check(const int32_t* rect, const float* splat, const float* depth, int64_t n,
@@ -1318,8 +1395,8 @@ extern "C" int32_t tgs_bin_sort_async(const int32_t* rect, const float* splat, c
     return e;
   TGS_REQUIRE(counts != nullptr && ((uintptr_t)counts & 7) == 0,
               "tgs_bin_sort_async: counts must be an 8-byte aligned device pointer");
-  return bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
-                        touched, w, as_stream(stream), "tgs_bin_sort_async", (unsigned long long*)counts);
+  return bin_sort_one(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
+                      touched, w, as_stream(stream), "tgs_bin_sort_async", (unsigned long long*)counts);
 }
 
 extern "C" int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,
@@ -1334,8 +1411,39 @@ extern "C" int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* s
   TGS_REQUIRE(prefix >= 0, "tgs_bin_sort_prefix_async: negative prefix");
   TGS_REQUIRE(counts != nullptr && ((uintptr_t)counts & 7) == 0,
               "tgs_bin_sort_prefix_async: counts must be an 8-byte aligned device pointer");
-  return bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
-                        touched, w, as_stream(stream), "tgs_bin_sort_prefix_async", (unsigned long long*)counts, prefix);
+  return bin_sort_one(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
+                      touched, w, as_stream(stream), "tgs_bin_sort_prefix_async", (unsigned long long*)counts, prefix);
+}
+
+// The views in batches, each kernel launched once for up to kBatch of them.
+extern "C" int32_t tgs_bin_sort_views_async(const tgs_bin_view* views, int32_t n_views, int64_t n, float alpha_min,
+                                            int64_t prefix, void* stream) {
+  const char* who = "tgs_bin_sort_views_async";
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "%s: bad view list", who);
+  TGS_REQUIRE(prefix >= -1, "%s: prefix below -1", who);
+  for (int k = 0; k < n_views; ++k) {
+    const tgs_bin_view& v = views[k];
+    const SortWs w = layout(v.ws, n, v.capacity, grid_tiles(v.tiles_x, v.tiles_y));
+    if (int32_t e = bin_sort_check(v.rect, v.splat, v.depth, n, v.tiles_x, v.tiles_y, alpha_min, v.vals, v.capacity,
+                                   v.ranges, v.ws, v.ws_bytes, w, who))
+      return e;
+    TGS_REQUIRE(v.counts != nullptr && ((uintptr_t)v.counts & 7) == 0,
+                "%s: counts must be an 8-byte aligned device pointer", who);
+  }
+  for (int k0 = 0; k0 < n_views; k0 += kBatch) {
+    const int nv = std::min(kBatch, n_views - k0);
+    DepthBatch d{};
+    BinBatch b{};
+    for (int k = 0; k < nv; ++k) {
+      const tgs_bin_view& v = views[k0 + k];
+      bin_sort_view(d.v[k], b.v[k], v.rect, v.splat, v.depth, n, v.tile_slot, v.tiles_x, v.tiles_y, alpha_min, v.keys,
+                    v.vals, v.capacity, v.ranges, v.touched,
+                    layout(v.ws, n, v.capacity, grid_tiles(v.tiles_x, v.tiles_y)), (unsigned long long*)v.counts,
+                    prefix);
+    }
+    if (int32_t e = bin_sort_queue(d, b, nv, n, as_stream(stream), who)) return e;
+  }
+  return TGS_OK;
 }
 
 extern "C" int32_t tgs_bin_sort_continue_async(const float* splat, int64_t n, const int32_t* flag_slot,
@@ -1357,8 +1465,11 @@ extern "C" int32_t tgs_bin_sort_continue_async(const float* splat, int64_t n, co
   const SortWs w1 = layout((void*)ws, n, capacity, n_t);
   const SortWs w2 = layout(ws2, n, capacity2, n_t);
   TGS_REQUIRE(ws_bytes >= w1.bytes && ws2_bytes >= w2.bytes, "%s: workspace too small", who);
-  return continue_queue(splat, n, flag_slot, n_flagged, tiles_x, tiles_y, alpha_min, prefix, vals2, capacity2, ranges2,
-                        w1, w2, (unsigned long long*)counts2, as_stream(stream), who);
+  BinBatch b{};
+  b.v[0] = continue_view(splat, n, flag_slot, n_flagged, tiles_x, tiles_y, alpha_min, prefix, vals2, capacity2, ranges2,
+                         w1, w2, (unsigned long long*)counts2);
+  list_all(b, 1, as_stream(stream));
+  return hip_status(who);
 }
 
 extern "C" int32_t tgs_bin_sort(const int32_t* rect, const float* splat, const float* depth, int64_t n,
@@ -1372,8 +1483,8 @@ extern "C" int32_t tgs_bin_sort(const int32_t* rect, const float* splat, const f
     return e;
   TGS_REQUIRE(n_pairs != nullptr, "tgs_bin_sort: null n_pairs");
   hipStream_t s = as_stream(stream);
-  if (int32_t e = bin_sort_queue(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
-                                 ranges, touched, w, s, "tgs_bin_sort", nullptr))
+  if (int32_t e = bin_sort_one(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
+                               ranges, touched, w, s, "tgs_bin_sort", nullptr))
     return e;
   // the one synchronisation: the two counts, read back when the stream has run the call
   unsigned long long host[2] = {0, 0};

@@ -30,6 +30,15 @@ __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + 
 
 __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// ---------------------------------------------------------------- batches
+// Arguments of one launch over the views of a training step, view k in grid
+// layer z = k.  They travel as kernel arguments (at most 4 KB).
+constexpr int kBatch = TGS_VIEW_BATCH;
+template <typename A>
+struct Batch {
+  A v[kBatch];
+};
+
 // ---------------------------------------------------------------- wave-level
 // DPP control words of the GFX9 family (CDNA).
 constexpr int kDppQuadPerm1032 = 0xB1;  // quad_perm [1, 0, 3, 2]

@@ -195,6 +195,17 @@ class ViewBuffers:
         self.two_part = False
         self._n_pairs = None
 
+    def bin_view(self, prefix: int | None) -> B.tgs_bin_view:
+        """This view's part of a bin_sort of several views (no host wait);
+        ``prefix``: the nearest Gaussians only, as in bin_sort_prefix."""
+        self.two_part = prefix is not None
+        if self.two_part:
+            self.prefix = int(min(prefix, self.n))
+        self._n_pairs = None
+        return B.bin_view(self.rect, self.splat, self.depth, self.tile_slot if self.bin_sort_needs_samples() else None,
+                          self.tiles_x, self.tiles_y, self.keys, self.vals, self.capacity, self.ranges, None,
+                          self.counts, self.sort_ws)
+
     # ---- depth-prefix lists
     def _alloc_cont(self, capacity2: int):
         dev = self.splat.device
@@ -571,7 +582,22 @@ class Trainer:
                                     [vb.splat for vb in used], [vb.depth for vb in used], [vb.radius for vb in used],
                                     [vb.rect for vb in used], [vb.clamp for vb in used], [vb.g2d for vb in used])
 
+        def bin_all():
+            # every view's lists, each kernel launched once for all of them
+            for k, vb in enumerate(used):
+                if vb.bin_sort_needs_samples():
+                    main.wait_event(sampled[k])   # binning keeps the sampled tiles only
+            with st("bin_sort"):
+                B.tgs_bin_sort_views_async([vb.bin_view(prefix_n) for vb in used], self.n, self.rp.alpha_min,
+                                           -1 if prefix_n is None else min(prefix_n, self.n))
+
         together = len(used) > 1
+        # one stream: the views' lists in one call (at 10k Gaussians, four
+        # 256x256 views, a step took 803 us with a call per view, 681 us with
+        # one; side by side at 5M the views' binning overlaps their samplers
+        # and forwards instead: 3337 us, and 3413 us with one call), but the
+        # first step of a slot waits to size its arrays
+        binned = together and not par and all(vb.sized for vb in used)
         if par:
             if together:
                 project_all()
@@ -619,12 +645,15 @@ class Trainer:
                 advance(chains_of(g0))
         elif together:
             project_all()
+            if binned:
+                bin_all()
         for k, (vb, v) in enumerate(zip(used, views)):
             cam = self.cams[v]
             if par:
                 main.wait_event(self._done[k])
             else:
-                for _ in self._view_chain(k, vb, v, cam, sampled, prefix_n, main, projected=together):
+                for _ in self._view_chain(k, vb, v, cam, sampled, prefix_n, main, projected=together,
+                                          binned=binned):
                     pass
             with st("render_bwd"):
                 # g2d was cleared by the projection; the density sums of sparse
@@ -664,30 +693,31 @@ class Trainer:
         self._queue_count_check(used)
         return used
 
-    def _view_chain(self, k, vb, v, cam, sampled, prefix_n, vs, done=None, projected=False):
-        """Projection (unless ``projected``), binning, forward and loss of the
-        step's k-th view on stream ``vs`` (the current stream).  With ``done`` (views side by
-        side) the event is recorded after the loss and the error maps'
-        update follows on ``vs`` itself: a wait queued on the side stream
-        would hold up whatever view stream shares its hardware queue.  A
-        generator: it yields after each stage, with the stream set by the
-        caller around every resumption."""
+    def _view_chain(self, k, vb, v, cam, sampled, prefix_n, vs, done=None, projected=False, binned=False):
+        """Projection (unless ``projected``), binning (unless ``binned``),
+        forward and loss of the step's k-th view on stream ``vs`` (the
+        current stream).  With ``done`` (views side by side) the event is
+        recorded after the loss and the error maps' update follows on ``vs``
+        itself: a wait queued on the side stream would hold up whatever view
+        stream shares its hardware queue.  A generator: it yields after each
+        stage, with the stream set by the caller around every resumption."""
         st = self._stage
         if not projected:
             with st("project"):
                 vb.project(self.params, cam, self.rp)
             yield
-        if sampled[k] is not None and vb.bin_sort_needs_samples():
-            vs.wait_event(sampled[k])   # binning keeps the sampled tiles only
-        with st("bin_sort"):
-            if prefix_n is not None:
-                # the nearest Gaussians only; the first step of a slot waits to size its arrays
-                vb.bin_sort_prefix(prefix_n, None, self.rp.alpha_min, wait=not vb.sized)
-            elif vb.sized:
-                vb.bin_sort_async(None, self.rp.alpha_min)   # no host wait
-            else:
-                vb.bin_sort(None, self.rp.alpha_min)         # sizes the pair arrays once per slot
-        yield
+        if not binned:
+            if sampled[k] is not None and vb.bin_sort_needs_samples():
+                vs.wait_event(sampled[k])   # binning keeps the sampled tiles only
+            with st("bin_sort"):
+                if prefix_n is not None:
+                    # the nearest Gaussians only; the first step of a slot waits to size its arrays
+                    vb.bin_sort_prefix(prefix_n, None, self.rp.alpha_min, wait=not vb.sized)
+                elif vb.sized:
+                    vb.bin_sort_async(None, self.rp.alpha_min)   # no host wait
+                else:
+                    vb.bin_sort(None, self.rp.alpha_min)         # sizes the pair arrays once per slot
+            yield
         if sampled[k] is not None:
             vs.wait_event(sampled[k])   # the forward renders this view's samples
         if vb.two_part:
