@@ -56,10 +56,9 @@ __device__ __forceinline__ uint64_t mulhi64(uint64_t a, uint64_t b) { return __u
 
 // E * 2^24 for a half bit pattern; negative, infinite and NaN values weigh 0.
 __device__ __forceinline__ uint64_t half_weight(uint16_t h) {
-  const uint32_t sign = h >> 15, ex = (h >> 10) & 0x1f, man = h & 0x3ff;
-  if (sign || ex == 0x1f) return 0;
-  if (ex == 0) return man;
-  return (uint64_t)(1024u + man) << (ex - 1);
+  const uint32_t ex = (h >> 10) & 0x1f, man = h & 0x3ff;
+  const uint64_t v = (uint64_t)(ex != 0 ? 1024u + man : man) << (max(ex, 1u) - 1u);  // no branch
+  return h < 0x7c00 ? v : 0;
 }
 
 // Lane l's value of a 64-bit register (l uniform).
@@ -123,7 +122,9 @@ __global__ void __launch_bounds__(64) tile_keys_kernel(const uint16_t* __restric
     for (int k = 0; k < kTilePixels / kKeyTiles; ++k) {
       const int loc = sub + kKeyTiles * k;
       const int x = tx * kTile + (loc & 15), y = ty * kTile + (loc >> 4);
-      if (x < W && y < H) s += half_weight(E[(int64_t)y * W + x]);
+      // a clamped address, so that no load waits behind a branch
+      const uint64_t w = half_weight(E[(int64_t)min(y, H - 1) * W + min(x, W - 1)]);
+      s += x < W && y < H ? w : 0;
     }
   }
 #pragma unroll
@@ -315,6 +316,12 @@ __global__ void __launch_bounds__(kSelectThreads) tile_select_kernel(
 // ------------------------------------------------------------------ tile pixels
 __device__ __forceinline__ int split_round(int permille, int n) { return (permille * n + 500) / 1000; }
 
+// One wave per tile.  Bound by the chain of draws (each needs the weight that
+// the last one left) of the few waves that a view gives a SIMD: the draws
+// update running sums without a branch, the counts are ballots, the loads
+// wait for nothing.  4,293 tiles of 64 samples (1296x840): 23 us; with the
+// in-lane search in a branch, 24 counting steps by lane sums for the ages and
+// loads behind the image bounds it took 47 us.  6,120 tiles of 51: 21 us.
 __global__ void __launch_bounds__(64) tile_pixels_kernel(
     const uint16_t* __restrict__ E, const uint16_t* __restrict__ A, int H, int W, int tiles_x,
     int n_st, int n_pix, int hard_pm, int stable_pm, uint64_t seed, uint64_t step, uint64_t view,
@@ -323,7 +330,7 @@ __global__ void __launch_bounds__(64) tile_pixels_kernel(
   const int slot = blockIdx.x;
   if (slot >= n_st) return;
   const int lane = threadIdx.x;
-  const int t = valid_tiles[slot];
+  const int t = valid_tiles[slot], out = tile_off[slot];
   const int tx = t % tiles_x, ty = t / tiles_x;
   const int n_valid = tile_valid_w(tx, W) * tile_valid_h(ty, H);
   const int n = min(n_pix, n_valid);
@@ -332,126 +339,144 @@ __global__ void __launch_bounds__(64) tile_pixels_kernel(
   if (n_hard + n_stable > n) n_stable = n - n_hard;
   int n_mixed = n - n_hard - n_stable;
 
+  // The lane's four pixels are consecutive in a row.  Out-of-image pixels
+  // load a clamped address, so that no load waits behind a branch.
   uint64_t w[4];
-  uint32_t age[4];
+  int age[4];
   bool valid[4];
-  for (int k = 0; k < 4; ++k) {
-    const int loc = lane * 4 + k;
-    const int x = tx * kTile + (loc & 15), y = ty * kTile + (loc >> 4);
-    valid[k] = x < W && y < H;
-    const int64_t idx = (int64_t)y * W + x;
-    w[k] = valid[k] ? half_weight(E[idx]) : 0;
-    age[k] = valid[k] ? A[idx] : 0;
+  {
+    const int x0 = tx * kTile + (lane & 3) * 4, y = ty * kTile + (lane >> 2);
+    const int64_t row = (int64_t)min(y, H - 1) * W;
+    uint16_t e[4], g[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t idx = row + min(x0 + k, W - 1);
+      e[k] = E[idx];
+      g[k] = A[idx];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      valid[k] = x0 + k < W && y < H;
+      w[k] = valid[k] ? half_weight(e[k]) : 0;
+      age[k] = g[k];
+    }
   }
   uint32_t picked = 0;  // bit k: local index lane*4+k chosen
   const uint64_t key = stream_key(seed, step, view, (uint64_t)t);
 
   // --- hard: sequential error-weighted draws without replacement.  The
   // draws' random words are hashed up front, lane l holding draw l + 64 q
-  // in uh[q].  The wave prefix sum of the lanes' unpicked weight is taken
-  // once and kept up to date: a draw lands in the first lane whose
-  // inclusive sum exceeds r, and removing the picked weight lowers the sums
-  // of that lane and the lanes after it.
+  // in uh[q].  c[k] is the running weight, over the whole tile, up to and
+  // with pixel k: a draw r picks the first pixel with c > r, and taking its
+  // weight away lowers exactly the sums that exceed r.  A picked pixel's sum
+  // then equals its predecessor's, so it is never the first above a draw
+  // again, and after the draws the pixels of positive weight whose sum
+  // equals their predecessor's are the picked ones.
   int n_hard_done = 0;
   {
     uint64_t uh[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) uh[q] = kWave * q < n_hard ? absorb(key, (uint64_t)(lane + kWave * q)) : 0;
-    uint64_t ls = w[0] + w[1] + w[2] + w[3];
-    uint64_t incl = wave_inclusive_scan_u64(ls);
-    uint64_t total = readlane_u64(incl, kWave - 1);
+    const uint64_t ls = w[0] + w[1] + w[2] + w[3];
+    uint64_t c[4];
+    c[3] = wave_inclusive_scan_u64_dpp(ls);
+    c[2] = c[3] - w[3];
+    c[1] = c[2] - w[2];
+    c[0] = c[1] - w[1];
+    uint64_t total = readlane_u64(c[3], kWave - 1);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       for (int jj = 0; jj < kWave && n_hard_done < n_hard && total != 0; ++jj) {
         const uint64_t r = mulhi64(readlane_u64(uh[q], jj), total);
-        const int pl = (int)__builtin_ctzll(__ballot(incl > r));  // incl of lane 63 = total > r
-        uint64_t wp = 0;
-        if (lane == pl) {
-          uint64_t run = incl - ls;
-          for (int k = 0; k < 4; ++k) {
-            if ((picked >> k) & 1u) continue;
-            run += w[k];
-            if (run > r) {
-              picked |= 1u << k;
-              wp = w[k];
-              break;
-            }
-          }
-          ls -= wp;
-        }
-        wp = readlane_u64(wp, pl);
-        if (lane >= pl) incl -= wp;
+        const bool above0 = c[0] > r, above1 = c[1] > r, above2 = c[2] > r, above3 = c[3] > r;
+        const int pl = (int)__builtin_ctzll(ballot(above3));  // c[3] of lane 63 = total > r
+        const uint64_t wp = readlane_u64(above0 ? w[0] : above1 ? w[1] : above2 ? w[2] : w[3], pl);
+        c[0] -= above0 ? wp : 0;
+        c[1] -= above1 ? wp : 0;
+        c[2] -= above2 ? wp : 0;
+        c[3] -= above3 ? wp : 0;
         total -= wp;
         ++n_hard_done;
       }
     }
+    const uint32_t plo = (uint32_t)__shfl_up((int)(uint32_t)c[3], 1, kWave);
+    const uint32_t phi = (uint32_t)__shfl_up((int)(uint32_t)(c[3] >> 32), 1, kWave);
+    uint64_t prev = lane == 0 ? 0 : ((uint64_t)phi << 32) | plo;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (w[k] != 0 && c[k] == prev) picked |= 1u << k;
+      prev = c[k];
+    }
   }
   n_mixed += n_hard - n_hard_done;
 
-  // --- stable: TopK age among the rest; key (age << 8) | (255 - loc) is
-  // unique and orders by age, then by lower index.  The K-th largest key is
-  // found by bisection on counts.
+  // --- stable: TopK age among the rest, ties to the lower index.  The K-th
+  // largest age is built bit by bit on counts.
   if (n_stable > 0) {
-    uint32_t kk[4];
-    bool elig[4];
-    for (int k = 0; k < 4; ++k) {
-      elig[k] = valid[k] && !((picked >> k) & 1u);
-      kk[k] = (age[k] << 8) | (uint32_t)(255 - (lane * 4 + k));
-    }
-    uint32_t lo = 0, hi = 1u << 24;  // count(key >= lo) >= n_stable > count(key >= hi)
-    while (hi - lo > 1) {
-      const uint32_t mid = lo + (hi - lo) / 2;
-      int c = 0;
-      for (int k = 0; k < 4; ++k) c += (elig[k] && kk[k] >= mid) ? 1 : 0;
-      c = wave_sum_i(c);
-      if (c >= n_stable) lo = mid; else hi = mid;
-    }
+#pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (elig[k] && kk[k] >= lo) picked |= 1u << k;
+      if (!valid[k] || ((picked >> k) & 1u)) age[k] = -1;
+    auto count = [&](int a) {  // pixels of at least age a
+      int c = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c += __builtin_popcountll(ballot(age[k] >= a));
+      return c;
+    };
+    int kth = 0;
+    for (int bit = count(256) >= n_stable ? 1 << 15 : 1 << 7; bit > 0; bit >>= 1)
+      if (count(kth | bit) >= n_stable) kth |= bit;
+    const int ties = n_stable - count(kth + 1);  // to take among those of the K-th age
+    int lt = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) lt += age[k] == kth ? 1 : 0;
+    int before = wave_inclusive_scan_i_dpp(lt) - lt;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (age[k] > kth || (age[k] == kth && before++ < ties)) picked |= 1u << k;
   }
 
-  // --- mixed: uniform without replacement over the rest, ascending order
-  // (the r-th remaining pixel; words hashed up front and the count prefix
-  // kept up to date as above)
+  // --- mixed: uniform without replacement over the rest: a draw picks the
+  // r-th remaining pixel in ascending order.  c[k] counts the remaining
+  // pixels up to and with pixel k and is kept up to date as above; each draw
+  // takes one pixel, so every r is known up front.
   {
-    uint64_t um[4];
+    int c[4], lc = 0;
+    bool rest[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      um[q] = kWave * q < n_mixed ? absorb(key, (uint64_t)(256 + lane + kWave * q)) : 0;
-    int lc = 0;
-    for (int k = 0; k < 4; ++k) lc += (valid[k] && !((picked >> k) & 1u)) ? 1 : 0;
-    int ic = wave_inclusive_scan_i(lc);
-    int nrem = __builtin_amdgcn_readlane(ic, kWave - 1);
-    int done = 0;
+    for (int k = 0; k < 4; ++k) {
+      rest[k] = valid[k] && !((picked >> k) & 1u);
+      lc += rest[k] ? 1 : 0;
+    }
+    c[3] = wave_inclusive_scan_i_dpp(lc);
+    c[2] = c[3] - (rest[3] ? 1 : 0);
+    c[1] = c[2] - (rest[2] ? 1 : 0);
+    c[0] = c[1] - (rest[1] ? 1 : 0);
+    const int nrem = __builtin_amdgcn_readlane(c[3], kWave - 1);
+    const int draws = min(n_mixed, nrem);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      // nrem == 0: nothing left, every later draw picks nothing
-      for (int jj = 0; jj < kWave && done < n_mixed && nrem > 0; ++jj) {
-        const int r = (int)mulhi64(readlane_u64(um[q], jj), (uint64_t)nrem);
-        const int pl = (int)__builtin_ctzll(__ballot(ic > r));
-        if (lane == pl) {
-          int c = ic - lc;
-          for (int k = 0; k < 4; ++k) {
-            if (!valid[k] || ((picked >> k) & 1u)) continue;
-            if (c == r) {
-              picked |= 1u << k;
-              break;
-            }
-            ++c;
-          }
-          --lc;
-        }
-        if (lane >= pl) --ic;
-        --nrem;
-        ++done;
+      if (kWave * q >= draws) continue;  // uniform
+      const int j = lane + kWave * q;
+      const int rj = (int)mulhi64(absorb(key, (uint64_t)(256 + j)), (uint64_t)max(nrem - j, 0));
+      for (int jj = 0; jj < min(kWave, draws - kWave * q); ++jj) {
+        const int r = __builtin_amdgcn_readlane(rj, jj);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] -= c[k] > r ? 1 : 0;
       }
+    }
+    int prev = __shfl_up(c[3], 1, kWave);
+    if (lane == 0) prev = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (rest[k] && c[k] == prev) picked |= 1u << k;
+      prev = c[k];
     }
   }
 
   // --- write the sorted local indices
   const int lc = __builtin_popcount(picked);
-  const int ic = wave_inclusive_scan_i(lc);
-  int pos = tile_off[slot] + ic - lc;
+  const int ic = wave_inclusive_scan_i_dpp(lc);
+  int pos = out + ic - lc;
   for (int k = 0; k < 4; ++k)
     if ((picked >> k) & 1u) pix[pos++] = (uint8_t)(lane * 4 + k);
 }
