@@ -182,134 +182,289 @@ __global__ void __launch_bounds__(256) tile_list_all_kernel(int H, int W, int ti
   }
 }
 
-// A subset: one workgroup.  An MSB-first radix select over the race keys (8
-// bits a pass, LDS histogram, keys staged in LDS when they fit) finds the
-// n_sel-th smallest key thr and how many of the keys equal to it are taken
-// (krem, the lowest tile indices first); then the whole workgroup lists the
-// chosen tiles in ascending order with their sample counts and prefix
-// offsets.
-constexpr int kSelectThreads = 1024;
+// A subset: one workgroup.  A radix select over the race keys (11 bits a
+// pass from the highest bit in which any two keys differ, LDS histogram)
+// narrows the n_sel-th smallest key down to a few candidates, which are
+// ranked against each other; thr is that key and krem how many of the keys
+// equal to it are taken (the lowest tile indices first).  Then the whole
+// workgroup lists the chosen tiles in ascending order with their sample
+// counts and prefix offsets, a tile per thread and round.
+//
+// Bound by the instructions that one compute unit issues and by barriers, so
+// the keys stay in registers (kRegs: all rounds at once; a grid of more
+// tiles than the largest such variant reads them again from memory in each
+// pass), and a grid of few tiles takes a small workgroup: 8,160 tiles 13 us,
+// 256 tiles 5.5 us.  With the keys in LDS, 8-bit passes from bit 63 on and a
+// contiguous run of tiles per thread in the listing: 25 and 7 us; the same
+// 11-bit passes with keys in LDS and 1024 threads throughout: 23 and 11 us.
+constexpr int kSelectBits = 11;
+constexpr int kSelectBins = 1 << kSelectBits;
+constexpr int kRankCandidates = 128;
 
-__global__ void __launch_bounds__(kSelectThreads) tile_select_kernel(
-    const uint64_t* __restrict__ keys, int H, int W, int tiles_x, int n_t, int n_sel, int n_pix,
-    int32_t* __restrict__ valid_tiles, int32_t* __restrict__ tile_off, int32_t* __restrict__ tile_slot,
-    int64_t* __restrict__ totals, int lds_tiles) {
-  extern __shared__ uint64_t s_keys[];  // [n_t] when n_t <= lds_tiles
-  __shared__ uint32_t hist[256];
-  __shared__ uint64_t s_thr;
-  __shared__ int s_krem, s_done;
-  const int tid = threadIdx.x, lane = lane_id();
-  const bool in_lds = n_t <= lds_tiles;  // 0 <= n_sel < n_t here
-  if (in_lds)
-    for (int t = tid; t < n_t; t += kSelectThreads) s_keys[t] = keys[t];
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
+  uint32_t w[2] = {(uint32_t)v, (uint32_t)(v >> 32)};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    int x = (int)w[k];
+    x |= dpp_i<kDppQuadPerm1032>(0, x);
+    x |= dpp_i<kDppQuadPerm2301>(0, x);
+    x |= dpp_i<kDppRowHalfMirror>(0, x);
+    x |= dpp_i<kDppRowMirror>(0, x);
+    x |= dpp_i<kDppRowBcast15, 0xa>(0, x);
+    x |= dpp_i<kDppRowBcast31, 0xc>(0, x);
+    w[k] = (uint32_t)__builtin_amdgcn_readlane(x, 63);
+  }
+  return (uint64_t)w[1] << 32 | w[0];
+}
+
+// Exclusive prefix over the workgroup of a value per thread (in lds, kThreads
+// / 64 entries), the sum in *total.  Barriers before and after lds is used.
+template <int kThreads>
+__device__ __forceinline__ uint64_t select_scan(uint64_t v, uint64_t* lds, uint64_t* total) {
+  constexpr int kWaves = kThreads / kWave;
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint64_t incl = wave_inclusive_scan_u64_dpp(v);
+  if (lane == kWave - 1) lds[wave] = incl;
   __syncthreads();
-  const uint64_t* kk = in_lds ? s_keys : keys;
-  uint64_t thr = 0;  // n_sel = 0: no key is below 0 and none is taken at it
+  const uint64_t w = lane < kWaves ? lds[lane] : 0;
+  const uint64_t wi = wave_inclusive_scan_u64_dpp(w);
+  *total = readlane_u64(wi, kWaves - 1);
+  const uint64_t before = readlane_u64(wi - w, __builtin_amdgcn_readfirstlane(wave));
+  __syncthreads();
+  return before + incl - v;
+}
+
+template <int kThreads, int kItems, bool kRegs>
+__global__ void __launch_bounds__(kThreads) tile_select_kernel(
+    const uint64_t* __restrict__ keys, int H, int W, int tiles_x, int tiles_y, int n_sel, int n_pix,
+    int32_t* __restrict__ valid_tiles, int32_t* __restrict__ tile_off, int32_t* __restrict__ tile_slot,
+    int64_t* __restrict__ totals) {
+  constexpr int kWaves = kThreads / kWave;
+  constexpr int kStep = kThreads * kItems;
+  static_assert(kItems * kWaves <= kThreads && kItems <= 32, "a count per wave and round");
+  __shared__ uint32_t hist[kSelectBins];
+  __shared__ uint64_t lds[kWaves], s_or[2 * kWaves];
+  __shared__ uint64_t s_n[kItems * kWaves];  // tiles above, samples below bit 32
+  __shared__ uint64_t s_cand[kRankCandidates];
+  __shared__ uint64_t s_thr;
+  __shared__ int s_krem, s_in_bin, s_cands;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int n_t = tiles_x * tiles_y;  // 0 <= n_sel < n_t; at most kStep when kRegs
+  uint64_t k[kItems];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int t = t0 + i * kThreads + tid;
+      k[i] = keys[min(t, n_t - 1)];
+    }
+  };
+  auto is_tile = [&](int t0, int i) { return t0 + i * kThreads + tid < n_t; };
+  if (kRegs) load(0);
+  uint64_t thr = 0;
   int krem = 0;
-  int fs = 0;  // keys are compared on their bits from fs up
+  int fs = 0;             // keys are compared on their bits from fs up
+  bool all_ties = false;  // every key equal to thr on those bits is chosen
   if (n_sel > 0) {
+    // the bits in which the keys differ: set in some key and clear in another
+    uint64_t any = 0, none = 0;
+    for (int t0 = 0; t0 < n_t; t0 += kStep) {
+      if (!kRegs) load(t0);
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {  // past the end: the last tile's key again
+        any |= k[i];
+        none |= ~k[i];
+      }
+    }
+    any = wave_or_u64(any);
+    none = wave_or_u64(none);
+    if (lane == 0) {
+      s_or[wave] = any;
+      s_or[kWaves + wave] = none;
+    }
+    if (tid == 0) s_cands = 0;
+    __syncthreads();
+    any = wave_or_u64(lane < kWaves ? s_or[lane] : 0);
+    none = wave_or_u64(lane < kWaves ? s_or[kWaves + lane] : 0);
+    const uint64_t differ = any & none;
+    int top = differ != 0 ? 64 - __clzll((long long)differ) : 0;  // bits still open: [0, top)
+    thr = any & ~(top < 64 ? (1ull << top) - 1 : ~0ull);          // the bits above, which every key shares
     krem = n_sel;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-      if (tid < 256) hist[tid] = 0;
+    int in_bin = n_t;  // keys that share thr's bits from top up
+    while (top > 0 && in_bin != krem && in_bin > kRankCandidates) {
+      const int shift = max(top - kSelectBits, 0);
+      const uint32_t dmask = (1u << (top - shift)) - 1u;
+      for (int b = tid; b < kSelectBins; b += kThreads) hist[b] = 0;
       __syncthreads();
-      const uint64_t hmask = shift == 56 ? 0ull : ~0ull << (shift + 8);  // bits already fixed
-      for (int t0 = 0; t0 < n_t; t0 += kSelectThreads) {
-        const int t = t0 + tid;
-        const uint64_t k = t < n_t ? kk[t] : 0ull;
-        const bool act = t < n_t && ((k ^ thr) & hmask) == 0;
-        const uint32_t d = (uint32_t)(k >> shift) & 255u;
-        const uint64_t am = __ballot(act);
-        if (am != 0ull) {
-          // one atomic for the wave when its candidates share a digit (the
-          // leading passes, where every key has the same exponent bits)
-          const int o = __ffsll((unsigned long long)am) - 1;
-          const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, o);
-          if (__ballot(act && d == d0) == am) {
-            if (lane == o) atomicAdd(&hist[d0], (uint32_t)__popcll(am));
-          } else if (act) {
-            atomicAdd(&hist[d], 1u);
-          }
-        }
+      const uint64_t hmask = top == 64 ? 0ull : ~0ull << top;  // bits already fixed
+      for (int t0 = 0; t0 < n_t; t0 += kStep) {
+        if (!kRegs) load(t0);
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+          if (is_tile(t0, i) && ((k[i] ^ thr) & hmask) == 0) atomicAdd(&hist[(uint32_t)(k[i] >> shift) & dmask], 1u);
       }
       __syncthreads();
-      if (tid < kWave) {
-        uint32_t h[4], sum = 0;
+      // the bin in which the running count reaches krem (the candidates
+      // number at least krem)
+      constexpr int kBins = kSelectBins / kThreads;
+      uint32_t h[kBins], sum = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          h[i] = hist[lane * 4 + i];
-          sum += h[i];
-        }
-        const uint32_t incl = wave_inclusive_scan_t<uint32_t>(sum);
-        // the candidates number at least krem, so some lane's sum reaches it
-        const int o = __ffsll((unsigned long long)__ballot(incl >= (uint32_t)krem)) - 1;
-        if (lane == o) {
-          uint32_t below = incl - sum;  // candidates in the bins before this lane's
-          int b = -1;
+      for (int i = 0; i < kBins; ++i) {
+        h[i] = hist[tid * kBins + i];
+        sum += h[i];
+      }
+      uint64_t all;
+      uint32_t below = (uint32_t)select_scan<kThreads>(sum, lds, &all);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (b < 0) {
-              if (below + h[i] >= (uint32_t)krem) b = i;
-              else below += h[i];
-            }
-          }
-          s_thr = thr | ((uint64_t)(lane * 4 + b) << shift);
+      for (int i = 0; i < kBins; ++i) {
+        if (below < (uint32_t)krem && below + h[i] >= (uint32_t)krem) {
+          s_thr = thr | ((uint64_t)(tid * kBins + i) << shift);
           s_krem = krem - (int)below;
-          // the bin holds exactly the keys still to take: every key with
-          // this prefix is chosen and the lower bits decide nothing
-          s_done = (int)h[b] == krem - (int)below;
+          s_in_bin = (int)h[i];
+        }
+        below += h[i];
+      }
+      __syncthreads();
+      thr = s_thr;
+      krem = s_krem;
+      in_bin = s_in_bin;
+      top = shift;
+    }
+    fs = top;
+    if (in_bin == krem) {
+      all_ties = true;  // every key with this prefix is chosen: the lower bits decide nothing
+    } else if (top > 0) {
+      // few candidates: the one with fewer than krem below it and krem or
+      // more up to and with it is thr
+      const uint64_t hmask = top == 64 ? 0ull : ~0ull << top;
+      for (int t0 = 0; t0 < n_t; t0 += kStep) {
+        if (!kRegs) load(t0);
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+          if (is_tile(t0, i) && ((k[i] ^ thr) & hmask) == 0) {
+            const int at = atomicAdd(&s_cands, 1);
+            if (at < kRankCandidates) s_cand[at] = k[i];  // always: in_bin candidates
+          }
+      }
+      __syncthreads();
+      const int cands = min(s_cands, kRankCandidates);
+      if (tid < cands) {
+        const uint64_t mine = s_cand[tid];
+        int less = 0, equal = 0;
+#pragma unroll 4
+        for (int c = 0; c < cands; ++c) {
+          less += s_cand[c] < mine ? 1 : 0;
+          equal += s_cand[c] == mine ? 1 : 0;
+        }
+        if (less < krem && less + equal >= krem) {  // equal keys write the same
+          s_thr = mine;
+          s_krem = krem - less;
+          s_in_bin = equal;
         }
       }
       __syncthreads();
       thr = s_thr;
       krem = s_krem;
-      if (s_done) {  // workgroup-uniform
-        fs = shift;
-        break;
+      all_ties = s_in_bin == krem;
+      fs = 0;
+    }
+  }
+  // the list of the chosen tiles: keys below thr, and the first krem tiles
+  // whose key equals thr, both on the bits from fs up.  One count per wave
+  // and round, scanned together.  A tile has pf samples, fewer in the last
+  // column (dc more, negative) and the last row (dr); the corner (both) is
+  // the last tile, and its own difference dk is in no other tile's offset.
+  const uint64_t thr_s = thr >> fs;
+  const int w0 = tiles_x > 1 ? kTile : W, h0 = tiles_y > 1 ? kTile : H;
+  const int w1 = tile_valid_w(tiles_x - 1, W), h1 = tile_valid_h(tiles_y - 1, H);
+  const int pf = min(n_pix, w0 * h0), dc = min(n_pix, w1 * h0) - pf, dr = min(n_pix, w0 * h1) - pf;
+  const int dk = min(n_pix, w1 * h1) - pf - dc - dr;
+  const bool ragged = (dc | dr | dk) != 0;
+  // exclusive prefixes of s_n; returns the sum
+  auto scan_counts = [&] {
+    __syncthreads();
+    uint64_t all;
+    const uint64_t ex = select_scan<kThreads>(tid < kItems * kWaves ? s_n[tid] : 0ull, lds, &all);
+    if (tid < kItems * kWaves) s_n[tid] = ex;
+    __syncthreads();
+    return all;
+  };
+  uint32_t ties_before = 0;
+  uint64_t done = 0;  // as s_n
+  for (int t0 = 0; t0 < n_t; t0 += kStep) {
+    if (!kRegs) load(t0);
+    uint32_t chosen = 0, tied = 0;  // bit i: this thread's tile of round i
+    if (n_sel > 0) {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const uint64_t ks = k[i] >> fs;
+        if (is_tile(t0, i) && ks < thr_s) chosen |= 1u << i;
+        if (is_tile(t0, i) && ks == thr_s) tied |= 1u << i;
+      }
+      if (all_ties) {
+        chosen |= tied;
+      } else {  // equal 64-bit keys, not all of them taken
+        for (int i = 0; i < kItems; ++i) {
+          const uint64_t m = ballot((tied >> i) & 1u);
+          if (lane == 0) s_n[i * kWaves + wave] = (uint64_t)__popcll(m);
+        }
+        const uint64_t all = scan_counts();
+        for (int i = 0; i < kItems; ++i) {
+          const bool tie = (tied >> i) & 1u;
+          const uint64_t m = ballot(tie);
+          const uint32_t rank = ties_before + (uint32_t)s_n[i * kWaves + wave] + (uint32_t)mask_rank(m);
+          if (tie && rank < (uint32_t)krem) chosen |= 1u << i;
+        }
+        ties_before += (uint32_t)all;
+        __syncthreads();  // s_n is written again below
       }
     }
-  }
-  // ascending list of the chosen tiles (keys below thr, and the first krem
-  // tiles whose key equals thr, both on the bits from fs up) with their
-  // sample counts
-  __shared__ uint32_t lds[kSelectThreads / kWave];
-  const int chunk = (n_t + kSelectThreads - 1) / kSelectThreads;
-  const int c0 = min(n_t, tid * chunk), c1 = min(n_t, c0 + chunk);
-  uint32_t lties = 0;
-  const uint64_t thr_s = thr >> fs;
-  for (int t = c0; t < c1; ++t) lties += kk[t] >> fs == thr_s ? 1u : 0u;
-  uint32_t n_ties;
-  const uint32_t tie0 = block_exclusive_scan<kSelectThreads, uint32_t>(lties, lds, &n_ties);
-  uint32_t lcount = 0, lpix = 0;
-  uint32_t tie = tie0;
-  for (int t = c0; t < c1; ++t) {
-    const uint64_t k = kk[t] >> fs;
-    const bool ch = k < thr_s || (k == thr_s && tie++ < (uint32_t)krem);
-    if (ch) {
-      ++lcount;
-      lpix += (uint32_t)min(n_pix, tile_valid_w(t % tiles_x, W) * tile_valid_h(t / tiles_x, H));
+    uint32_t last_col = 0, last_row = 0;  // bits as chosen, of the chosen tiles
+    if (ragged) {
+#pragma unroll
+      for (int i = 0; i < kItems; ++i) {
+        const int t = t0 + i * kThreads + tid;
+        if ((t + 1) % tiles_x == 0) last_col |= 1u << i;
+        if (t >= n_t - tiles_x) last_row |= 1u << i;
+      }
+      last_col &= chosen;
+      last_row &= chosen;
     }
-  }
-  uint32_t n_chosen, P;
-  int slot = (int)block_exclusive_scan<kSelectThreads, uint32_t>(lcount, lds, &n_chosen);
-  int off = (int)block_exclusive_scan<kSelectThreads, uint32_t>(lpix, lds, &P);
-  tie = tie0;
-  for (int t = c0; t < c1; ++t) {
-    const uint64_t k = kk[t] >> fs;
-    const bool ch = k < thr_s || (k == thr_s && tie++ < (uint32_t)krem);
-    if (ch) {
-      valid_tiles[slot] = t;
-      tile_off[slot] = off;
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int n = __popcll(ballot((chosen >> i) & 1u));
+      int p = n * pf;
+      if (ragged) {
+        const uint64_t mc = ballot((last_col >> i) & 1u), mr = ballot((last_row >> i) & 1u);
+        const bool corner = ballot(((chosen >> i) & 1u) && t0 + i * kThreads + tid == n_t - 1) != 0;
+        p += __popcll(mc) * dc + __popcll(mr) * dr + (corner ? dk : 0);
+      }
+      if (lane == 0) s_n[i * kWaves + wave] = (uint64_t)n << 32 | (uint32_t)p;
+    }
+    const uint64_t all = scan_counts();
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) {
+      const int t = t0 + i * kThreads + tid;
+      const bool ch = (chosen >> i) & 1u;
+      const int rank = mask_rank(ballot(ch));
+      int p = rank * pf;
+      if (ragged)
+        p += mask_rank(ballot((last_col >> i) & 1u)) * dc + mask_rank(ballot((last_row >> i) & 1u)) * dr;
+      const uint64_t before = done + s_n[i * kWaves + wave];
+      const int slot = ch ? (int)(before >> 32) + rank : -1;
+      if (t >= n_t) continue;
+      if (ch) {
+        valid_tiles[slot] = t;
+        tile_off[slot] = (int32_t)(uint32_t)before + p;
+      }
       tile_slot[t] = slot;
-      off += min(n_pix, tile_valid_w(t % tiles_x, W) * tile_valid_h(t / tiles_x, H));
-      ++slot;
-    } else {
-      tile_slot[t] = -1;
     }
+    done += all;
+    if (!kRegs) __syncthreads();
   }
   if (tid == 0) {
-    tile_off[n_chosen] = (int32_t)P;
-    atomicAdd((unsigned long long*)&totals[0], (unsigned long long)P);
-    atomicAdd((unsigned long long*)&totals[1], (unsigned long long)n_chosen);
+    tile_off[done >> 32] = (int32_t)(uint32_t)done;
+    atomicAdd((unsigned long long*)&totals[0], (unsigned long long)(uint32_t)done);
+    atomicAdd((unsigned long long*)&totals[1], (unsigned long long)(done >> 32));
   }
 }
 
@@ -491,33 +646,6 @@ extern "C" size_t tgs_sample_workspace_size(int32_t height, int32_t width) {
   return align_up(n_t * sizeof(uint64_t), 256);
 }
 
-// Tiles whose race keys the select can stage in LDS on the current device:
-// the workgroup's LDS limit (160 KiB on gfx950) less the kernel's static
-// arrays, 8 bytes per tile.  Queried, and the kernel's dynamic LDS limit
-// raised, once per device.
-static int select_lds_tiles() {
-  constexpr int kMaxDevices = 64;
-  static std::mutex mu;
-  static int cache[kMaxDevices];
-  static bool known[kMaxDevices];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!known[dev]) {
-    int bytes = 0;
-    if (hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) bytes = 0;
-    int dyn = bytes - 2048;  // static LDS of the kernel (histogram, scan partials) with margin
-    if (dyn > 65536 && hipFuncSetAttribute((const void*)tile_select_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess) {
-      (void)hipGetLastError();
-      dyn = 65536 - 2048;
-    }
-    cache[dev] = max(0, dyn / (int)sizeof(uint64_t));
-    known[dev] = true;
-  }
-  return cache[dev];
-}
-
 static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height, int32_t width,
                            const tgs_sample_params* sp, const float* tile_pred, int32_t* valid_tiles,
                            int32_t* tile_off, uint8_t* pix, int32_t* tile_slot, int64_t* totals, void* ws,
@@ -551,11 +679,15 @@ static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height,
     hipLaunchKernelGGL(tile_list_all_kernel, dim3((unsigned)ceil_div(n_t + 1, 256)), dim3(256), 0, s, height, width,
                        tiles_x, tiles_y, sp->n_pix, valid_tiles, tile_off, tile_slot, totals);
   } else {
-    const int lds_tiles = select_lds_tiles();
-    const size_t sel_lds = n_t <= lds_tiles ? (size_t)n_t * sizeof(uint64_t) : 0;
-    hipLaunchKernelGGL(tile_select_kernel, dim3(1), dim3(kSelectThreads), sel_lds, s, keys, height, width,
-                       tiles_x, n_t, sp->n_tiles_sel, sp->n_pix, valid_tiles, tile_off, tile_slot, totals,
-                       lds_tiles);
+    auto select = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, keys, height, width, tiles_x, tiles_y, sp->n_tiles_sel,
+                         sp->n_pix, valid_tiles, tile_off, tile_slot, totals);
+    };
+    // the smallest variant that keeps every key in registers
+    if (n_t <= 256 * 4) select(tile_select_kernel<256, 4, true>, 256);
+    else if (n_t <= 1024 * 8) select(tile_select_kernel<1024, 8, true>, 1024);
+    else if (n_t <= 1024 * 16) select(tile_select_kernel<1024, 16, true>, 1024);
+    else select(tile_select_kernel<1024, 16, false>, 1024);
   }
   if (n_st > 0)
     hipLaunchKernelGGL(tile_pixels_kernel, dim3(n_st), dim3(64), 0, s, E, A, height, width, tiles_x,
