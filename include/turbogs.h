@@ -785,6 +785,54 @@ int32_t tgs_tile_mlp_train_step(float* params, float* m, float* v, const float* 
                                 int64_t step, float lr, float* grad, void* ws, size_t ws_bytes,
                                 void* stream);
 
+/* ---- several views of a step in one call --------------------------------
+ * The stages of a training step for several views at once: each kernel is
+ * launched once for up to TGS_VIEW_BATCH views of one kind, which a step of
+ * small views needs to fill the device.  Every view's results are those of
+ * the single-view call.  A record holds a view's buffers as of the
+ * single-view calls (only the fields that a call reads or writes need to be
+ * set; valid_tiles null: a dense view, null tile_off, pix and tile_slot).
+ * Output buffers are distinct, the maps E and A too where they are written.
+ * All views are checked before anything is queued. */
+typedef struct tgs_view {
+  const float* splat;      /* render */
+  const uint32_t* vals;
+  const uint32_t* ranges;
+  int32_t* valid_tiles;    /* samples */
+  int32_t* tile_off;
+  int32_t* tile_slot;
+  uint8_t* pix;
+  float* out;              /* forward */
+  uint32_t* ncontrib;
+  float* state;            /* nullable, in all views or none */
+  const float* gt;         /* loss */
+  float* dL_dout;
+  float* err;
+  float* lambda;
+  float* tile_loss;
+  float* g2d;              /* backward */
+  uint16_t* E;             /* maps */
+  uint16_t* A;
+  const float* tile_pred;  /* nullable */
+  void* sample_ws;
+  size_t sample_ws_bytes;
+  int32_t tiles_x, tiles_y, width, height;
+  int32_t n_st, max_per_tile;
+  int32_t view;            /* the view's index in the sampler's draws (sp->view is not read) */
+} tgs_view;
+
+int32_t tgs_sample_views(const tgs_view* views, int32_t n_views, const tgs_sample_params* sp, int64_t* totals,
+                         void* stream);
+int32_t tgs_render_fwd_views(const tgs_view* views, int32_t n_views, const tgs_raster_params* rp,
+                             uint64_t* counters, void* stream);
+int32_t tgs_loss_views(const tgs_view* views, int32_t n_views, const int64_t* totals, const tgs_loss_params* lp,
+                       void* stream);
+int32_t tgs_ema_age_update_views(const tgs_view* views, int32_t n_views, float beta, void* stream);
+/* stats nullable: with it the density-control sums of n Gaussians, as
+ * tgs_render_bwd_density; touched nullable */
+int32_t tgs_render_bwd_views(const tgs_view* views, int32_t n_views, const tgs_raster_params* rp, uint8_t* touched,
+                             int64_t n, float* stats, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

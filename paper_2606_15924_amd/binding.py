@@ -48,6 +48,14 @@ class tgs_bin_view(ctypes.Structure):
                 ("tiles_x", ctypes.c_int32), ("tiles_y", ctypes.c_int32)]
 
 
+class tgs_view(ctypes.Structure):
+    _fields_ = ([(f, ctypes.c_void_p) for f in (
+        "splat", "vals", "ranges", "valid_tiles", "tile_off", "tile_slot", "pix", "out", "ncontrib", "state", "gt",
+        "dL_dout", "err", "lam", "tile_loss", "g2d", "E", "A", "tile_pred", "sample_ws")] +
+        [("sample_ws_bytes", ctypes.c_size_t)] +
+        [(f, ctypes.c_int32) for f in ("tiles_x", "tiles_y", "width", "height", "n_st", "max_per_tile", "view")])
+
+
 class tgs_sample_params(ctypes.Structure):
     _fields_ = [("n_pix", ctypes.c_int32), ("hard_permille", ctypes.c_int32),
                 ("stable_permille", ctypes.c_int32), ("n_tiles_sel", ctypes.c_int32),
@@ -91,6 +99,11 @@ PROTOTYPES = {
                                   _SZ, _P]),
     "tgs_bin_sort_prefix_async": (_I32, [_P, _P, _P, _I64, _P, _I32, _I32, ctypes.c_float, _I64, _P, _P, _I64, _P,
                                          _P, _P, _P, _SZ, _P]),
+    "tgs_sample_views": (_I32, [_P, _I32, ctypes.POINTER(tgs_sample_params), _P, _P]),
+    "tgs_render_fwd_views": (_I32, [_P, _I32, ctypes.POINTER(tgs_raster_params), _P, _P]),
+    "tgs_loss_views": (_I32, [_P, _I32, _P, ctypes.POINTER(tgs_loss_params), _P]),
+    "tgs_ema_age_update_views": (_I32, [_P, _I32, ctypes.c_float, _P]),
+    "tgs_render_bwd_views": (_I32, [_P, _I32, ctypes.POINTER(tgs_raster_params), _P, _I64, _P, _P]),
     "tgs_bin_sort_views_async": (_I32, [_P, _I32, _I64, ctypes.c_float, _I64, _P]),
     "tgs_bin_sort_continue_async": (_I32, [_P, _I64, _P, _P, _I32, _I32, ctypes.c_float, _I64, _I64, _P, _SZ, _P,
                                            _I64, _P, _P, _P, _SZ, _P]),
@@ -383,6 +396,33 @@ def tgs_bin_sort_prefix_async(rect, splat, depth, n, tile_slot, tiles_x, tiles_y
                                            _ptr(ranges), _ptr(touched), _ptr(counts), _ptr(ws),
                                            ws.numel() * ws.element_size(), _stream()),
            "tgs_bin_sort_prefix_async")
+
+
+def views_array(records):
+    """The host array of tgs_view records that the calls over several views take."""
+    return (tgs_view * len(records))(*records)
+
+
+def tgs_sample_views(views, sp: tgs_sample_params, totals):
+    _check(lib().tgs_sample_views(views, len(views), ctypes.byref(sp), _ptr(totals), _stream()), "tgs_sample_views")
+
+
+def tgs_render_fwd_views(views, rp: tgs_raster_params, counters):
+    _check(lib().tgs_render_fwd_views(views, len(views), ctypes.byref(rp), _ptr(counters), _stream()),
+           "tgs_render_fwd_views")
+
+
+def tgs_loss_views(views, totals, lp: tgs_loss_params):
+    _check(lib().tgs_loss_views(views, len(views), _ptr(totals), ctypes.byref(lp), _stream()), "tgs_loss_views")
+
+
+def tgs_ema_age_update_views(views, beta):
+    _check(lib().tgs_ema_age_update_views(views, len(views), beta, _stream()), "tgs_ema_age_update_views")
+
+
+def tgs_render_bwd_views(views, rp: tgs_raster_params, touched, n, stats):
+    _check(lib().tgs_render_bwd_views(views, len(views), ctypes.byref(rp), _ptr(touched), n, _ptr(stats), _stream()),
+           "tgs_render_bwd_views")
 
 
 def tgs_bin_sort_views_async(views, n, alpha_min, prefix):

@@ -18,13 +18,36 @@ namespace tgs {
 constexpr float kSsimC1 = 1e-4f;
 constexpr float kSsimC2 = 9e-4f;
 
+// A view's arguments; the views of a step share a launch, one per grid layer.
+struct LossArgs {
+  const float4* out;
+  const float* gt;
+  const int32_t* valid_tiles;
+  const int32_t* tile_off;
+  const uint8_t* pix;
+  float4* dL;
+  float* err;
+  float* lambda_out;
+  float2* tile_loss;
+  int H, W, tiles_x;
+  int grid;  // the view's workgroups; the launch's grid is the largest view's
+};
+
 template <bool kDense, bool kSsim = false>
-__global__ void __launch_bounds__(64) loss_kernel(
-    const float4* __restrict__ out, const float* __restrict__ gt, int H, int W, int tiles_x,
-    const int32_t* __restrict__ valid_tiles, const int32_t* __restrict__ tile_off,
-    const uint8_t* __restrict__ pix, const int64_t* __restrict__ totals, float eps_c2,
-    float eps_n, float eps_l, float4* __restrict__ dL, float* __restrict__ err,
-    float* __restrict__ lambda_out, float2* __restrict__ tile_loss) {
+__global__ void __launch_bounds__(64) loss_kernel(Batch<LossArgs> batch, const int64_t* __restrict__ totals,
+                                                  float eps_c2, float eps_n, float eps_l) {
+  const LossArgs& v = batch.v[blockIdx.z];
+  if ((int)blockIdx.x >= v.grid) return;
+  const float4* __restrict__ const out = v.out;
+  const float* __restrict__ const gt = v.gt;
+  const int32_t* __restrict__ const valid_tiles = v.valid_tiles;
+  const int32_t* __restrict__ const tile_off = v.tile_off;
+  const uint8_t* __restrict__ const pix = v.pix;
+  float4* __restrict__ const dL = v.dL;
+  float* __restrict__ const err = v.err;
+  float* __restrict__ const lambda_out = v.lambda_out;
+  float2* __restrict__ const tile_loss = v.tile_loss;
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x;
   const int slot = blockIdx.x, lane = threadIdx.x;
   const int tile = kDense ? slot : valid_tiles[slot];
   const int tx = tile % tiles_x, ty = tile / tiles_x;
@@ -158,13 +181,26 @@ __device__ __forceinline__ uint16_t ema_half(uint16_t e_bits, float e, float bet
 // age 0 and its error blended, every other pixel age + 1 (saturating).
 constexpr int kEmaTiles = 8;
 
-__global__ void __launch_bounds__(256) ema_age_kernel(uint16_t* __restrict__ E, uint16_t* __restrict__ A,
-                                                      int H, int W, int tiles_x,
-                                                      const int32_t* __restrict__ tile_slot,
-                                                      const int32_t* __restrict__ tile_off,
-                                                      const uint8_t* __restrict__ pix,
-                                                      const float* __restrict__ err, float beta,
-                                                      float omb) {
+struct EmaArgs {
+  uint16_t* E;
+  uint16_t* A;
+  const int32_t* tile_slot;
+  const int32_t* tile_off;
+  const uint8_t* pix;
+  const float* err;
+  int H, W, tiles_x, tiles_y;
+};
+
+__global__ void __launch_bounds__(256) ema_age_kernel(Batch<EmaArgs> batch, float beta, float omb) {
+  const EmaArgs& v = batch.v[blockIdx.z];
+  if ((int)blockIdx.x * kEmaTiles >= v.tiles_x || (int)blockIdx.y >= v.tiles_y) return;
+  uint16_t* __restrict__ const E = v.E;
+  uint16_t* __restrict__ const A = v.A;
+  const int32_t* __restrict__ const tile_slot = v.tile_slot;
+  const int32_t* __restrict__ const tile_off = v.tile_off;
+  const uint8_t* __restrict__ const pix = v.pix;
+  const float* __restrict__ const err = v.err;
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x;
   __shared__ int pos[kEmaTiles][kTilePixels];
   const int tid = threadIdx.x, ty = blockIdx.y, tx0 = blockIdx.x * kEmaTiles;
   for (int k = 0; k < kEmaTiles; ++k) pos[k][tid] = -1;
@@ -187,8 +223,8 @@ __global__ void __launch_bounds__(256) ema_age_kernel(uint16_t* __restrict__ E, 
   uint16_t a[8];
   const bool vec = (W & 7) == 0 && x0 + 8 <= W;  // 16-byte aligned and inside the row
   if (vec) {
-    const uint4 v = *reinterpret_cast<const uint4*>(A + i0);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const uint4 q = *reinterpret_cast<const uint4*>(A + i0);
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
     for (int j = 0; j < 4; ++j) {
       a[2 * j] = (uint16_t)(w[j] & 0xffffu);
       a[2 * j + 1] = (uint16_t)(w[j] >> 16);
@@ -206,12 +242,12 @@ __global__ void __launch_bounds__(256) ema_age_kernel(uint16_t* __restrict__ E, 
     }
   }
   if (vec) {
-    uint4 v;
-    v.x = (uint32_t)a[0] | ((uint32_t)a[1] << 16);
-    v.y = (uint32_t)a[2] | ((uint32_t)a[3] << 16);
-    v.z = (uint32_t)a[4] | ((uint32_t)a[5] << 16);
-    v.w = (uint32_t)a[6] | ((uint32_t)a[7] << 16);
-    *reinterpret_cast<uint4*>(A + i0) = v;
+    uint4 q;
+    q.x = (uint32_t)a[0] | ((uint32_t)a[1] << 16);
+    q.y = (uint32_t)a[2] | ((uint32_t)a[3] << 16);
+    q.z = (uint32_t)a[4] | ((uint32_t)a[5] << 16);
+    q.w = (uint32_t)a[6] | ((uint32_t)a[7] << 16);
+    *reinterpret_cast<uint4*>(A + i0) = q;
   } else {
     for (int j = 0; j < 8; ++j)
       if (x0 + j < W) A[i0 + j] = a[j];
@@ -236,54 +272,134 @@ __global__ void __launch_bounds__(256) error_init_kernel(const float4* __restric
 
 using namespace tgs;
 
+static int32_t loss_params_check(const tgs_loss_params* lp, const int64_t* totals, const char* who) {
+  TGS_REQUIRE(lp != nullptr, "%s: null params", who);
+  TGS_REQUIRE(totals != nullptr, "%s: null pointer", who);
+  TGS_REQUIRE(lp->structure == TGS_STRUCTURE_NCC || lp->structure == TGS_STRUCTURE_SSIM,
+              "%s: unknown structure term %d", who, lp->structure);
+  return TGS_OK;
+}
+
+static int32_t loss_args(LossArgs& v, const float* out, const float* gt, int32_t height, int32_t width,
+                         const int32_t* valid_tiles, const int32_t* tile_off, const uint8_t* pix, int32_t n_st,
+                         float* dL_dout, float* err, float* lambda, float* tile_loss, const char* who) {
+  TGS_REQUIRE(height > 0 && width > 0, "%s: bad image size", who);
+  TGS_REQUIRE(out && gt && dL_dout && err && lambda && tile_loss, "%s: null pointer", who);
+  TGS_REQUIRE(((uintptr_t)out & 15) == 0 && ((uintptr_t)dL_dout & 15) == 0,
+              "%s: out and dL_dout must be 16-byte aligned", who);
+  const int tiles_x = (int)ceil_div(width, kTile), tiles_y = (int)ceil_div(height, kTile);
+  if (valid_tiles != nullptr) {
+    TGS_REQUIRE(tile_off && pix, "%s: null tile_off/pix", who);
+    TGS_REQUIRE(n_st >= 0 && n_st <= tiles_x * tiles_y, "%s: bad n_st %d", who, n_st);
+  }
+  v = LossArgs{(const float4*)out, gt, valid_tiles, tile_off, pix, (float4*)dL_dout, err, lambda, (float2*)tile_loss,
+               height, width, tiles_x, valid_tiles == nullptr ? tiles_x * tiles_y : n_st};
+  return TGS_OK;
+}
+
+// Views that are all dense or all sparse.
+static void loss_launch(const Batch<LossArgs>& b, int views, const int64_t* totals, const tgs_loss_params* lp,
+                        hipStream_t s) {
+  int grid = 0;
+  for (int k = 0; k < views; ++k) grid = max(grid, b.v[k].grid);
+  if (grid == 0) return;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid, 1, (unsigned)views), dim3(64), 0, s, b, totals,
+                       lp->eps_charb * lp->eps_charb, lp->eps_ncc, lp->eps_lambda);
+  };
+  const bool ssim = lp->structure == TGS_STRUCTURE_SSIM;
+  if (b.v[0].valid_tiles == nullptr) {
+    if (ssim) launch(loss_kernel<true, true>);
+    else launch(loss_kernel<true, false>);
+  } else {
+    if (ssim) launch(loss_kernel<false, true>);
+    else launch(loss_kernel<false, false>);
+  }
+}
+
 extern "C" int32_t tgs_loss(const float* out, const float* gt, int32_t height, int32_t width,
                             const int32_t* valid_tiles, const int32_t* tile_off, const uint8_t* pix,
                             int32_t n_st, const int64_t* totals, const tgs_loss_params* lp,
                             float* dL_dout, float* err, float* lambda, float* tile_loss,
                             void* stream) {
-  TGS_REQUIRE(height > 0 && width > 0, "tgs_loss: bad image size");
-  TGS_REQUIRE(lp != nullptr, "tgs_loss: null params");
-  TGS_REQUIRE(out && gt && totals && dL_dout && err && lambda && tile_loss, "tgs_loss: null pointer");
-  TGS_REQUIRE(((uintptr_t)out & 15) == 0 && ((uintptr_t)dL_dout & 15) == 0,
-              "tgs_loss: out and dL_dout must be 16-byte aligned");
-  const int tiles_x = (int)ceil_div(width, kTile), tiles_y = (int)ceil_div(height, kTile);
-  hipStream_t s = as_stream(stream);
-  TGS_REQUIRE(lp->structure == TGS_STRUCTURE_NCC || lp->structure == TGS_STRUCTURE_SSIM,
-              "tgs_loss: unknown structure term %d", lp->structure);
-  const float eps_c2 = lp->eps_charb * lp->eps_charb;
-  const bool ssim = lp->structure == TGS_STRUCTURE_SSIM;
-#define TGS_LOSS(DENSE, SSIM, GRID)                                                                              \
-  hipLaunchKernelGGL((loss_kernel<DENSE, SSIM>), dim3(GRID), dim3(64), 0, s, (const float4*)out, gt, height,     \
-                     width, tiles_x, valid_tiles, tile_off, pix, totals, eps_c2, lp->eps_ncc, lp->eps_lambda,    \
-                     (float4*)dL_dout, err, lambda, (float2*)tile_loss)
-  if (valid_tiles == nullptr) {
-    if (ssim) TGS_LOSS(true, true, tiles_x * tiles_y);
-    else TGS_LOSS(true, false, tiles_x * tiles_y);
-  } else {
-    TGS_REQUIRE(tile_off && pix, "tgs_loss: null tile_off/pix");
-    TGS_REQUIRE(n_st >= 0 && n_st <= tiles_x * tiles_y, "tgs_loss: bad n_st %d", n_st);
-    if (n_st > 0) {
-      if (ssim) TGS_LOSS(false, true, n_st);
-      else TGS_LOSS(false, false, n_st);
-    }
-  }
-#undef TGS_LOSS
+  if (int32_t e = loss_params_check(lp, totals, "tgs_loss")) return e;
+  Batch<LossArgs> b{};
+  if (int32_t e = loss_args(b.v[0], out, gt, height, width, valid_tiles, tile_off, pix, n_st, dL_dout, err, lambda,
+                            tile_loss, "tgs_loss"))
+    return e;
+  loss_launch(b, 1, totals, lp, as_stream(stream));
   return hip_status("tgs_loss");
+}
+
+extern "C" int32_t tgs_loss_views(const tgs_view* views, int32_t n_views, const int64_t* totals,
+                                  const tgs_loss_params* lp, void* stream) {
+  const char* who = "tgs_loss_views";
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "%s: bad view list", who);
+  if (int32_t e = loss_params_check(lp, totals, who)) return e;
+  for (int pass = 0; pass < 2; ++pass)  // every view is checked before any is launched
+    for (int32_t k = 0, end; k < n_views; k = end) {
+      Batch<LossArgs> b{};
+      for (end = k; end < n_views && end - k < kBatch; ++end) {
+        const tgs_view& v = views[end];
+        if ((v.valid_tiles == nullptr) != (views[k].valid_tiles == nullptr)) break;
+        if (int32_t e = loss_args(b.v[end - k], v.out, v.gt, v.height, v.width, v.valid_tiles, v.tile_off, v.pix,
+                                  v.n_st, v.dL_dout, v.err, v.lambda, v.tile_loss, who))
+          return e;
+      }
+      if (pass == 1) loss_launch(b, end - k, totals, lp, as_stream(stream));
+    }
+  return hip_status(who);
+}
+
+static int32_t ema_args(EmaArgs& v, uint16_t* E, uint16_t* A, int32_t height, int32_t width, const int32_t* tile_slot,
+                        const int32_t* tile_off, const uint8_t* pix, const float* err, const char* who) {
+  TGS_REQUIRE(height > 0 && width > 0, "%s: bad image size", who);
+  TGS_REQUIRE(E && A && tile_slot && tile_off && pix && err, "%s: null pointer", who);
+  TGS_REQUIRE((width & 7) != 0 || ((uintptr_t)A & 15) == 0,
+              "%s: A must be 16-byte aligned when the width is a multiple of 8", who);
+  v = EmaArgs{E,   A,      tile_slot, tile_off, pix, err, height, width, (int)ceil_div(width, kTile),
+              (int)ceil_div(height, kTile)};
+  return TGS_OK;
+}
+
+static void ema_launch(const Batch<EmaArgs>& b, int views, float beta, hipStream_t s) {
+  int tx = 0, ty = 0;
+  for (int k = 0; k < views; ++k) {
+    tx = max(tx, b.v[k].tiles_x);
+    ty = max(ty, b.v[k].tiles_y);
+  }
+  hipLaunchKernelGGL(ema_age_kernel, dim3((unsigned)ceil_div(tx, kEmaTiles), (unsigned)ty, (unsigned)views), dim3(256),
+                     0, s, b, beta, 1.0f - beta);
 }
 
 extern "C" int32_t tgs_ema_age_update(uint16_t* E, uint16_t* A, int32_t height, int32_t width,
                                       const int32_t* tile_slot, const int32_t* tile_off,
                                       const uint8_t* pix, const float* err, float beta,
                                       void* stream) {
-  TGS_REQUIRE(height > 0 && width > 0, "tgs_ema_age_update: bad image size");
-  TGS_REQUIRE(E && A && tile_slot && tile_off && pix && err, "tgs_ema_age_update: null pointer");
-  const int tiles_x = (int)ceil_div(width, kTile), tiles_y = (int)ceil_div(height, kTile);
-  const float omb = 1.0f - beta;
-  TGS_REQUIRE((width & 7) != 0 || ((uintptr_t)A & 15) == 0,
-              "tgs_ema_age_update: A must be 16-byte aligned when the width is a multiple of 8");
-  hipLaunchKernelGGL(ema_age_kernel, dim3((unsigned)ceil_div(tiles_x, kEmaTiles), (unsigned)tiles_y), dim3(256), 0,
-                     as_stream(stream), E, A, height, width, tiles_x, tile_slot, tile_off, pix, err, beta, omb);
+  Batch<EmaArgs> b{};
+  if (int32_t e = ema_args(b.v[0], E, A, height, width, tile_slot, tile_off, pix, err, "tgs_ema_age_update")) return e;
+  ema_launch(b, 1, beta, as_stream(stream));
   return hip_status("tgs_ema_age_update");
+}
+
+extern "C" int32_t tgs_ema_age_update_views(const tgs_view* views, int32_t n_views, float beta, void* stream) {
+  const char* who = "tgs_ema_age_update_views";
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "%s: bad view list", who);
+  for (int32_t i = 0; i < n_views; ++i)
+    for (int32_t j = 0; j < i; ++j)
+      TGS_REQUIRE(views[i].E != views[j].E && views[i].A != views[j].A, "%s: views %d and %d share a map", who, j, i);
+  for (int pass = 0; pass < 2; ++pass)
+    for (int32_t k = 0; k < n_views; k += kBatch) {
+      const int nv = min(kBatch, n_views - k);
+      Batch<EmaArgs> b{};
+      for (int i = 0; i < nv; ++i) {
+        const tgs_view& v = views[k + i];
+        if (int32_t e = ema_args(b.v[i], v.E, v.A, v.height, v.width, v.tile_slot, v.tile_off, v.pix, v.err, who))
+          return e;
+      }
+      if (pass == 1) ema_launch(b, nv, beta, as_stream(stream));
+    }
+  return hip_status(who);
 }
 
 extern "C" int32_t tgs_error_init(const float* out_dense, const float* gt, int32_t height,

@@ -186,10 +186,10 @@ __device__ __forceinline__ Staged stage_load(const RasterArgs& a, uint32_t gid, 
 }
 
 template <int kBlock, bool kDense>
-__global__ void __launch_bounds__(kBlock) render_fwd_kernel(RasterArgs a, float4* __restrict__ out,
-                                                            uint32_t* __restrict__ ncontrib,
-                                                            unsigned long long* __restrict__ counters,
-                                                            float4* __restrict__ state) {
+__device__ __forceinline__ void render_fwd_view(const RasterArgs& a, float4* __restrict__ out,
+                                                uint32_t* __restrict__ ncontrib,
+                                                unsigned long long* __restrict__ counters,
+                                                float4* __restrict__ state) {
   __shared__ float4 s_geo[kBlock];
   __shared__ float4 s_app[kBlock];
   __shared__ float s_blue[kBlock];
@@ -294,6 +294,25 @@ __global__ void __launch_bounds__(kBlock) render_fwd_kernel(RasterArgs a, float4
     atomicAdd(&counters[cs], (unsigned long long)n_eval);
     atomicAdd(&counters[TGS_COUNTER_SLOTS + cs], (unsigned long long)n_blend);
   }
+}
+
+// The views of a step in one launch, view k in grid layer z = k: a small view
+// has fewer workgroups than the device holds.  Four 256x256 views of 64 tiles
+// each take 39 us together, 4 x 36 us one by one (the backward 15 us, 4 x 12).
+struct FwdArgs {
+  RasterArgs a;
+  float4* out;
+  uint32_t* ncontrib;
+  unsigned long long* counters;
+  float4* state;
+  int grid;  // the view's workgroups; the launch's grid is the largest view's
+};
+
+template <int kBlock, bool kDense>
+__global__ void __launch_bounds__(kBlock) render_fwd_kernel(Batch<FwdArgs> b) {
+  const FwdArgs& v = b.v[blockIdx.z];
+  if ((int)blockIdx.x >= v.grid) return;
+  render_fwd_view<kBlock, kDense>(v.a, v.out, v.ncontrib, v.counters, v.state);
 }
 
 __device__ __forceinline__ float swap_sum32(float x, float y) {
@@ -405,14 +424,11 @@ __device__ __forceinline__ void transpose2(float* tr, int lane, const float (&x)
 // partial buffer, pos the pair's index in the sorted list);
 // det_reduce_kernel adds them up per Gaussian in a fixed order.
 template <int kBlock, bool kDense, bool kDensity = false, bool kDet = false>
-__global__ void __launch_bounds__(kBlock, kBlock == 64 ? 6 : 5) render_bwd_kernel(RasterArgs a,
-                                                            const float4* __restrict__ out,
-                                                            const uint32_t* __restrict__ ncontrib,
-                                                            const float4* __restrict__ dL,
-                                                            float* __restrict__ g2d,
-                                                            const float4* __restrict__ state,
-                                                            uint8_t* __restrict__ touched,
-                                                            DensityArgs dens = {}) {
+__device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float4* __restrict__ out,
+                                                const uint32_t* __restrict__ ncontrib,
+                                                const float4* __restrict__ dL, float* __restrict__ g2d,
+                                                const float4* __restrict__ state, uint8_t* __restrict__ touched,
+                                                const DensityArgs& dens) {
   constexpr int kWaves = kBlock / kWave;
   constexpr int kCols = kDensity ? 16 : 12; // sums per Gaussian in the table
   constexpr int kFields = kDensity ? 13 : 9;
@@ -663,6 +679,25 @@ __global__ void __launch_bounds__(kBlock, kBlock == 64 ? 6 : 5) render_bwd_kerne
   }
 }
 
+struct BwdArgs {
+  RasterArgs a;
+  const float4* out;
+  const uint32_t* ncontrib;
+  const float4* dL;
+  float* g2d;
+  const float4* state;
+  uint8_t* touched;
+  DensityArgs dens;
+  int grid;  // as in FwdArgs
+};
+
+template <int kBlock, bool kDense, bool kDensity, bool kDet>
+__global__ void __launch_bounds__(kBlock, kBlock == 64 ? 6 : 5) render_bwd_kernel(Batch<BwdArgs> b) {
+  const BwdArgs& v = b.v[blockIdx.z];
+  if ((int)blockIdx.x >= v.grid) return;
+  render_bwd_view<kBlock, kDense, kDensity, kDet>(v.a, v.out, v.ncontrib, v.dL, v.g2d, v.state, v.touched, v.dens);
+}
+
 // Back-projection of per-pixel statistics onto the Gaussians (Sec. 3.8,
 // Eq. gauss_err_accum): the forward walk is replayed with the same alpha
 // decisions, bounded by the forward's contributor count, and every
@@ -762,33 +797,21 @@ __global__ void __launch_bounds__(kBlock) render_accum_kernel(RasterArgs a, cons
 }
 
 template <int kBlock, bool kDense>
-static void launch_fwd(const RasterArgs& a, int grid, float* out, uint32_t* ncontrib,
-                       uint64_t* counters, float* state, hipStream_t s) {
-  hipLaunchKernelGGL((render_fwd_kernel<kBlock, kDense>), dim3(grid), dim3(kBlock), 0, s, a,
-                     (float4*)out, ncontrib, (unsigned long long*)counters, (float4*)state);
+static void launch_fwd(const Batch<FwdArgs>& b, int views, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((render_fwd_kernel<kBlock, kDense>), dim3((unsigned)grid, 1, (unsigned)views), dim3(kBlock), 0, s,
+                     b);
 }
 
-template <int kBlock, bool kDense>
-static void launch_bwd(const RasterArgs& a, int grid, const float* out, const uint32_t* ncontrib,
-                       const float* dL, float* g2d, const float* state, uint8_t* touched, hipStream_t s,
-                       const DensityArgs* dens = nullptr) {
-  const unsigned chunks = state != nullptr ? kChunks : 1;
-  if (dens != nullptr)
-    hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, true>), dim3(grid, chunks), dim3(kBlock), 0, s, a,
-                       (const float4*)out, ncontrib, (const float4*)dL, g2d, (const float4*)state, touched, *dens);
+// One chunk per tile without the forward's state record, of any view.
+template <int kBlock, bool kDense, bool kDet>
+static void launch_bwd(const Batch<BwdArgs>& b, int views, int grid, bool density, hipStream_t s) {
+  const dim3 g((unsigned)grid, b.v[0].state != nullptr ? kChunks : 1, (unsigned)views);
+  if constexpr (kDet)
+    hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, false, true>), g, dim3(kBlock), 0, s, b);
+  else if (density)
+    hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, true, false>), g, dim3(kBlock), 0, s, b);
   else
-    hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense>), dim3(grid, chunks), dim3(kBlock), 0, s, a,
-                       (const float4*)out, ncontrib, (const float4*)dL, g2d, (const float4*)state, touched,
-                       DensityArgs{});
-}
-
-template <int kBlock, bool kDense>
-static void launch_bwd_det(const RasterArgs& a, int grid, const float* out, const uint32_t* ncontrib,
-                           const float* dL, float* partial, const float* state, uint8_t* touched, hipStream_t s) {
-  const unsigned chunks = state != nullptr ? kChunks : 1;
-  hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, false, true>), dim3(grid, chunks), dim3(kBlock), 0, s, a,
-                     (const float4*)out, ncontrib, (const float4*)dL, partial, (const float4*)state, touched,
-                     DensityArgs{});
+    hipLaunchKernelGGL((render_bwd_kernel<kBlock, kDense, false, false>), g, dim3(kBlock), 0, s, b);
 }
 
 __global__ void __launch_bounds__(256) zero_f32_kernel(float* __restrict__ p, int64_t n) {
@@ -910,19 +933,42 @@ extern "C" size_t tgs_render_state_size(int32_t n_slots, int32_t max_per_tile) {
   return (size_t)n_slots * (kChunks - 1) * (size_t)raster_block(false, max_per_tile) * sizeof(float4);
 }
 
-static int32_t render_fwd_launch(const RasterArgs& a, bool dense, int32_t n_st, int32_t max_per_tile, float* out,
-                                 uint32_t* ncontrib, uint64_t* counters, float* state, hipStream_t s,
-                                 const char* who) {
+// The workgroups of a view, 0 when it has no tile to render.
+static int view_grid(const RasterArgs& a, int32_t n_st) {
+  return a.valid_tiles == nullptr ? a.tiles_x * a.tiles_y : n_st;
+}
+
+static int32_t fwd_args(FwdArgs& v, const RasterArgs& a, int32_t n_st, float* out, uint32_t* ncontrib,
+                        uint64_t* counters, float* state, const char* who) {
   TGS_REQUIRE(out && ncontrib, "%s: null output", who);
   TGS_REQUIRE(((uintptr_t)out & 15) == 0 && ((uintptr_t)state & 15) == 0, "%s: out and state must be 16-byte aligned",
               who);
-  if (dense) {
-    launch_fwd<256, true>(a, a.tiles_x * a.tiles_y, out, ncontrib, counters, state, s);
-  } else if (n_st > 0) {
-    if (max_per_tile <= 64) launch_fwd<64, false>(a, n_st, out, ncontrib, counters, state, s);
-    else if (max_per_tile <= 128) launch_fwd<128, false>(a, n_st, out, ncontrib, counters, state, s);
-    else launch_fwd<256, false>(a, n_st, out, ncontrib, counters, state, s);
-  }
+  v.a = a;
+  v.out = (float4*)out;
+  v.ncontrib = ncontrib;
+  v.counters = (unsigned long long*)counters;
+  v.state = (float4*)state;
+  v.grid = view_grid(a, n_st);
+  return TGS_OK;
+}
+
+// Views of one kind (dense, or sparse with the same workgroup size).
+static void fwd_launch(const Batch<FwdArgs>& b, int views, int32_t max_per_tile, hipStream_t s) {
+  int grid = 0;
+  for (int k = 0; k < views; ++k) grid = std::max(grid, b.v[k].grid);
+  if (grid == 0) return;
+  if (b.v[0].a.valid_tiles == nullptr) launch_fwd<256, true>(b, views, grid, s);
+  else if (max_per_tile <= 64) launch_fwd<64, false>(b, views, grid, s);
+  else if (max_per_tile <= 128) launch_fwd<128, false>(b, views, grid, s);
+  else launch_fwd<256, false>(b, views, grid, s);
+}
+
+static int32_t render_fwd_launch(const RasterArgs& a, int32_t n_st, int32_t max_per_tile, float* out,
+                                 uint32_t* ncontrib, uint64_t* counters, float* state, hipStream_t s,
+                                 const char* who) {
+  Batch<FwdArgs> b{};
+  if (int32_t e = fwd_args(b.v[0], a, n_st, out, ncontrib, counters, state, who)) return e;
+  fwd_launch(b, 1, max_per_tile, s);
   return hip_status(who);
 }
 
@@ -936,7 +982,7 @@ extern "C" int32_t tgs_render_fwd(const float* splat, const uint32_t* vals, cons
   if (int32_t e = make_args(splat, vals, ranges, tiles_x, tiles_y, width, height, valid_tiles,
                             tile_off, pix, n_st, max_per_tile, rp, "tgs_render_fwd", a))
     return e;
-  return render_fwd_launch(a, valid_tiles == nullptr, n_st, max_per_tile, out, ncontrib, counters, state,
+  return render_fwd_launch(a, n_st, max_per_tile, out, ncontrib, counters, state,
                            as_stream(stream), "tgs_render_fwd");
 }
 
@@ -960,7 +1006,7 @@ extern "C" int32_t tgs_render_fwd_prefix(const float* splat, const uint32_t* val
   const int64_t n_t = (int64_t)tiles_x * tiles_y;
   hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)ceil_div(n_t, 256)), dim3(256), 0, s, cont_slot, n_t, -1,
                      cont_count);
-  return render_fwd_launch(a, valid_tiles == nullptr, n_st, max_per_tile, out, ncontrib, counters, state, s, who);
+  return render_fwd_launch(a, n_st, max_per_tile, out, ncontrib, counters, state, s, who);
 }
 
 extern "C" int32_t tgs_render_fwd_cont(const float* splat, const uint32_t* vals, const uint32_t* ranges,
@@ -980,25 +1026,46 @@ extern "C" int32_t tgs_render_fwd_cont(const float* splat, const uint32_t* vals,
   a.mode = 2;
   a.cont_list = (uint32_t*)cont_list;
   a.cont_count = (uint32_t*)cont_count;
-  return render_fwd_launch(a, valid_tiles == nullptr, n_st, max_per_tile, out, ncontrib, counters, state,
+  return render_fwd_launch(a, n_st, max_per_tile, out, ncontrib, counters, state,
                            as_stream(stream), who);
 }
 
-static int32_t render_bwd_launch(const RasterArgs& a, bool dense, int32_t n_st, int32_t max_per_tile,
-                                 const float* out, const uint32_t* ncontrib, const float* dL_dout, float* g2d,
-                                 const float* state, uint8_t* touched, const DensityArgs* dens, hipStream_t s,
-                                 const char* who) {
+static int32_t bwd_args(BwdArgs& v, const RasterArgs& a, int32_t n_st, const float* out, const uint32_t* ncontrib,
+                        const float* dL_dout, float* g2d, const float* state, uint8_t* touched,
+                        const DensityArgs* dens, const char* who) {
   TGS_REQUIRE(out && ncontrib && dL_dout && g2d, "%s: null pointer", who);
   TGS_REQUIRE(((uintptr_t)out & 15) == 0 && ((uintptr_t)dL_dout & 15) == 0 && ((uintptr_t)state & 15) == 0,
               "%s: out, dL_dout and state must be 16-byte aligned", who);
-  if (dense) {
-    launch_bwd<256, true>(a, a.tiles_x * a.tiles_y, out, ncontrib, dL_dout, g2d, state, touched, s, dens);
-  } else if (n_st > 0) {
-    if (max_per_tile <= 64) launch_bwd<64, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, dens);
-    else if (max_per_tile <= 128)
-      launch_bwd<128, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, dens);
-    else launch_bwd<256, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, dens);
-  }
+  v.a = a;
+  v.out = (const float4*)out;
+  v.ncontrib = ncontrib;
+  v.dL = (const float4*)dL_dout;
+  v.g2d = g2d;
+  v.state = (const float4*)state;
+  v.touched = touched;
+  v.dens = dens != nullptr ? *dens : DensityArgs{};
+  v.grid = view_grid(a, n_st);
+  return TGS_OK;
+}
+
+// Views of one kind, as in fwd_launch; all with the state record or none.
+template <bool kDet = false>
+static void bwd_launch(const Batch<BwdArgs>& b, int views, int32_t max_per_tile, bool density, hipStream_t s) {
+  int grid = 0;
+  for (int k = 0; k < views; ++k) grid = std::max(grid, b.v[k].grid);
+  if (grid == 0) return;
+  if (b.v[0].a.valid_tiles == nullptr) launch_bwd<256, true, kDet>(b, views, grid, density, s);
+  else if (max_per_tile <= 64) launch_bwd<64, false, kDet>(b, views, grid, density, s);
+  else if (max_per_tile <= 128) launch_bwd<128, false, kDet>(b, views, grid, density, s);
+  else launch_bwd<256, false, kDet>(b, views, grid, density, s);
+}
+
+static int32_t render_bwd_launch(const RasterArgs& a, int32_t n_st, int32_t max_per_tile, const float* out,
+                                 const uint32_t* ncontrib, const float* dL_dout, float* g2d, const float* state,
+                                 uint8_t* touched, const DensityArgs* dens, hipStream_t s, const char* who) {
+  Batch<BwdArgs> b{};
+  if (int32_t e = bwd_args(b.v[0], a, n_st, out, ncontrib, dL_dout, g2d, state, touched, dens, who)) return e;
+  bwd_launch(b, 1, max_per_tile, dens != nullptr, s);
   return hip_status(who);
 }
 
@@ -1013,7 +1080,7 @@ extern "C" int32_t tgs_render_bwd(const float* splat, const uint32_t* vals, cons
   if (int32_t e = make_args(splat, vals, ranges, tiles_x, tiles_y, width, height, valid_tiles,
                             tile_off, pix, n_st, max_per_tile, rp, "tgs_render_bwd", a))
     return e;
-  return render_bwd_launch(a, valid_tiles == nullptr, n_st, max_per_tile, out, ncontrib, dL_dout, g2d, state,
+  return render_bwd_launch(a, n_st, max_per_tile, out, ncontrib, dL_dout, g2d, state,
                            touched, nullptr, as_stream(stream), "tgs_render_bwd");
 }
 
@@ -1035,7 +1102,7 @@ extern "C" int32_t tgs_render_bwd2(const float* splat, const uint32_t* vals, con
     TGS_REQUIRE(err != nullptr && n > 0 && n < (1ll << 31), "%s: density sums need err and n", who);
     TGS_REQUIRE(((uintptr_t)stats & 15) == 0, "%s: stats must be 16-byte aligned", who);
   }
-  return render_bwd_launch(a, valid_tiles == nullptr, n_st, max_per_tile, out, ncontrib, dL_dout, g2d, state,
+  return render_bwd_launch(a, n_st, max_per_tile, out, ncontrib, dL_dout, g2d, state,
                            touched, stats != nullptr ? &d : nullptr, as_stream(stream), who);
 }
 
@@ -1072,14 +1139,11 @@ extern "C" int32_t tgs_render_bwd_deterministic(const float* splat, const uint32
   const int64_t words = std::max<int64_t>(n_pairs, 1) * 9;
   hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(words, 256), 8192)), dim3(256), 0,
                      s, partial, words);
-  if (dense) {
-    launch_bwd_det<256, true>(a, tiles_x * tiles_y, out, ncontrib, dL_dout, partial, state, touched, s);
-  } else if (n_st > 0) {
-    if (max_per_tile <= 64) launch_bwd_det<64, false>(a, n_st, out, ncontrib, dL_dout, partial, state, touched, s);
-    else if (max_per_tile <= 128)
-      launch_bwd_det<128, false>(a, n_st, out, ncontrib, dL_dout, partial, state, touched, s);
-    else launch_bwd_det<256, false>(a, n_st, out, ncontrib, dL_dout, partial, state, touched, s);
-  }
+  Batch<BwdArgs> b{};
+  if (int32_t e = bwd_args(b.v[0], a, n_st, out, ncontrib, dL_dout, partial, state, touched, nullptr,
+                           "tgs_render_bwd_deterministic"))
+    return e;
+  bwd_launch<true>(b, 1, max_per_tile, false, s);
   if (n > 0)
     hipLaunchKernelGGL(det_reduce_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, (const int4*)rect,
                        depth, vals, (const uint2*)ranges, n, tiles_x, tiles_y, partial, g2d);
@@ -1105,14 +1169,10 @@ extern "C" int32_t tgs_render_bwd_density(const float* splat, const uint32_t* va
               "tgs_render_bwd_density: out, dL_dout and state must be 16-byte aligned");
   hipStream_t s = as_stream(stream);
   const DensityArgs d{err, stats, n};
-  if (valid_tiles == nullptr) {
-    launch_bwd<256, true>(a, tiles_x * tiles_y, out, ncontrib, dL_dout, g2d, state, touched, s, &d);
-  } else if (n_st > 0) {
-    if (max_per_tile <= 64) launch_bwd<64, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, &d);
-    else if (max_per_tile <= 128)
-      launch_bwd<128, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, &d);
-    else launch_bwd<256, false>(a, n_st, out, ncontrib, dL_dout, g2d, state, touched, s, &d);
-  }
+  Batch<BwdArgs> b{};
+  if (int32_t e = bwd_args(b.v[0], a, n_st, out, ncontrib, dL_dout, g2d, state, touched, &d, "tgs_render_bwd_density"))
+    return e;
+  bwd_launch(b, 1, max_per_tile, true, s);
   return hip_status("tgs_render_bwd_density");
 }
 
@@ -1173,4 +1233,71 @@ static int32_t density_accumulate_launch(const RasterArgs& a, const int32_t* val
   }
 #undef TGS_ACCUM
   return hip_status("tgs_density_accumulate");
+}
+
+// ------------------------------------------------------------------ several views
+// A view's raster arguments; its kind decides which views share a launch.
+static int32_t view_args(const tgs_view& v, const tgs_raster_params* rp, const char* who, RasterArgs& a) {
+  return make_args(v.splat, v.vals, v.ranges, v.tiles_x, v.tiles_y, v.width, v.height, v.valid_tiles, v.tile_off,
+                   v.pix, v.n_st, v.max_per_tile, rp, who, a);
+}
+
+static bool same_kind(const tgs_view& a, const tgs_view& b) {
+  const bool dense = a.valid_tiles == nullptr;
+  return dense == (b.valid_tiles == nullptr) && (a.state == nullptr) == (b.state == nullptr) &&
+         raster_block(dense, a.max_per_tile) == raster_block(dense, b.max_per_tile);
+}
+
+// Views [k, end) that share a launch.
+static int32_t kind_end(const tgs_view* views, int32_t n_views, int32_t k) {
+  int32_t end = k + 1;
+  while (end < n_views && end - k < kBatch && same_kind(views[k], views[end])) ++end;
+  return end;
+}
+
+extern "C" int32_t tgs_render_fwd_views(const tgs_view* views, int32_t n_views, const tgs_raster_params* rp,
+                                        uint64_t* counters, void* stream) {
+  const char* who = "tgs_render_fwd_views";
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "%s: bad view list", who);
+  for (int pass = 0; pass < 2; ++pass)  // every view is checked before any is launched
+    for (int32_t k = 0, end; k < n_views; k = end) {
+      end = kind_end(views, n_views, k);
+      Batch<FwdArgs> b{};
+      for (int32_t i = k; i < end; ++i) {
+        RasterArgs a;
+        if (int32_t e = view_args(views[i], rp, who, a)) return e;
+        if (int32_t e = fwd_args(b.v[i - k], a, views[i].n_st, views[i].out, views[i].ncontrib, counters,
+                                 views[i].state, who))
+          return e;
+      }
+      if (pass == 1) fwd_launch(b, end - k, views[k].max_per_tile, as_stream(stream));
+    }
+  return hip_status(who);
+}
+
+extern "C" int32_t tgs_render_bwd_views(const tgs_view* views, int32_t n_views, const tgs_raster_params* rp,
+                                        uint8_t* touched, int64_t n, float* stats, void* stream) {
+  const char* who = "tgs_render_bwd_views";
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "%s: bad view list", who);
+  if (stats != nullptr) {
+    TGS_REQUIRE(n > 0 && n < (1ll << 31), "%s: n out of range", who);
+    TGS_REQUIRE(((uintptr_t)stats & 15) == 0, "%s: stats must be 16-byte aligned", who);
+  }
+  for (int pass = 0; pass < 2; ++pass)
+    for (int32_t k = 0, end; k < n_views; k = end) {
+      end = kind_end(views, n_views, k);
+      Batch<BwdArgs> b{};
+      for (int32_t i = k; i < end; ++i) {
+        const tgs_view& v = views[i];
+        RasterArgs a;
+        if (int32_t e = view_args(v, rp, who, a)) return e;
+        TGS_REQUIRE(stats == nullptr || v.err != nullptr, "%s: density sums need err", who);
+        const DensityArgs d{v.err, stats, n};
+        if (int32_t e = bwd_args(b.v[i - k], a, v.n_st, v.out, v.ncontrib, v.dL_dout, v.g2d, v.state, touched,
+                                 stats != nullptr ? &d : nullptr, who))
+          return e;
+      }
+      if (pass == 1) bwd_launch(b, end - k, views[k].max_per_tile, stats != nullptr, as_stream(stream));
+    }
+  return hip_status(who);
 }

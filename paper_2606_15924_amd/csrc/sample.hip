@@ -71,6 +71,30 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
 __device__ __forceinline__ int tile_valid_w(int tx, int W) { return min(kTile, W - tx * kTile); }
 __device__ __forceinline__ int tile_valid_h(int ty, int H) { return min(kTile, H - ty * kTile); }
 
+// ------------------------------------------------------------------ arguments
+// A view's arguments; the views of a step share the launches, one per grid
+// layer.
+struct SampleArgs {
+  const uint16_t* E;
+  const uint16_t* A;
+  const float* pred;  // nullable
+  uint64_t* keys;
+  int32_t* valid_tiles;
+  int32_t* tile_off;
+  int32_t* tile_slot;
+  uint8_t* pix;
+  int H, W, tiles_x, tiles_y;
+  int n_st;
+  uint64_t view;
+};
+
+// What the views share.
+struct SampleCommon {
+  int n_sel, n_pix, hard_pm, stable_pm;
+  uint64_t seed, step;
+  int64_t* totals;
+};
+
 // ------------------------------------------------------------------ race keys
 constexpr int kLogFrac = 47;  // fractional bits of a race time: 64 * 2^47 = 2^53 is exact in a double
 
@@ -109,9 +133,10 @@ __device__ __forceinline__ uint64_t race_key(uint64_t w, uint64_t u) {
 // parallel per wave.
 constexpr int kKeyTiles = 8;
 
-__global__ void __launch_bounds__(64) tile_keys_kernel(const uint16_t* __restrict__ E, int H, int W,
-                                                       int tiles_x, int n_t, uint64_t seed, uint64_t step,
-                                                       uint64_t view, uint64_t* __restrict__ keys) {
+__global__ void __launch_bounds__(64) tile_keys_kernel(Batch<SampleArgs> batch, SampleCommon c) {
+  const SampleArgs& v = batch.v[blockIdx.z];
+  const uint16_t* __restrict__ const E = v.E;
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x, n_t = v.tiles_x * v.tiles_y;
   const int lane = threadIdx.x;
   const int sub = lane & (kKeyTiles - 1);
   const int t = blockIdx.x * kKeyTiles + lane / kKeyTiles;
@@ -134,23 +159,23 @@ __global__ void __launch_bounds__(64) tile_keys_kernel(const uint16_t* __restric
     s += ((uint64_t)hi << 32) | lo;
   }
   if (t < n_t && sub == 0)
-    keys[t] = race_key(s, absorb(stream_key(seed, step, view, (uint64_t)n_t), (uint64_t)t));
+    v.keys[t] = race_key(s, absorb(stream_key(c.seed, c.step, v.view, (uint64_t)n_t), (uint64_t)t));
 }
 
 // Keys from predicted mean tile errors: weight floor(clamp(p, 0, 65504) *
 // in-image pixels * 2^24), the units of the error-map sums; exact in FP64 (a
 // float times a count up to 256 times a power of two).
-__global__ void __launch_bounds__(256) tile_pred_keys_kernel(const float* __restrict__ pred, int H, int W,
-                                                            int tiles_x, int n_t, uint64_t seed, uint64_t step,
-                                                            uint64_t view, uint64_t* __restrict__ keys) {
+__global__ void __launch_bounds__(256) tile_pred_keys_kernel(Batch<SampleArgs> batch, SampleCommon c) {
+  const SampleArgs& v = batch.v[blockIdx.z];
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x, n_t = v.tiles_x * v.tiles_y;
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= n_t) return;
   const int tx = t % tiles_x, ty = t / tiles_x;
   const int nx = min(kTile, W - tx * kTile), ny = min(kTile, H - ty * kTile);
-  const float p = pred[t];
+  const float p = v.pred[t];
   const double q = p > 0.f ? (double)fminf(p, 65504.f) : 0.0;  // NaN and negatives give 0
   const uint64_t w = (uint64_t)floor(q * (double)(nx * ny) * 16777216.0);
-  keys[t] = race_key(w, absorb(stream_key(seed, step, view, (uint64_t)n_t), (uint64_t)t));
+  v.keys[t] = race_key(w, absorb(stream_key(c.seed, c.step, v.view, (uint64_t)n_t), (uint64_t)t));
 }
 
 // ------------------------------------------------------------------ tile select
@@ -158,11 +183,9 @@ __global__ void __launch_bounds__(256) tile_pred_keys_kernel(const float* __rest
 // closed form (every tile column but the last is 16 pixels wide, every row
 // but the last 16 high), so no single-workgroup pass has to wait for a free
 // compute unit while other streams' kernels fill the device.
-__global__ void __launch_bounds__(256) tile_list_all_kernel(int H, int W, int tiles_x, int tiles_y, int n_pix,
-                                                            int32_t* __restrict__ valid_tiles,
-                                                            int32_t* __restrict__ tile_off,
-                                                            int32_t* __restrict__ tile_slot,
-                                                            int64_t* __restrict__ totals) {
+__global__ void __launch_bounds__(256) tile_list_all_kernel(Batch<SampleArgs> batch, SampleCommon c) {
+  const SampleArgs& v = batch.v[blockIdx.z];
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x, tiles_y = v.tiles_y, n_pix = c.n_pix;
   const int n_t = tiles_x * tiles_y;
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t > n_t) return;
@@ -172,13 +195,13 @@ __global__ void __launch_bounds__(256) tile_list_all_kernel(int H, int W, int ti
   int64_t off = (int64_t)min(ty, tiles_y - 1) * row16;
   if (ty == tiles_y) off += (int64_t)(tiles_x - 1) * min(n_pix, kTile * hl) + min(n_pix, wl * hl);
   else off += (int64_t)tx * min(n_pix, kTile * (ty == tiles_y - 1 ? hl : kTile));
-  tile_off[t] = (int32_t)off;
+  v.tile_off[t] = (int32_t)off;
   if (t < n_t) {
-    valid_tiles[t] = t;
-    tile_slot[t] = t;
+    v.valid_tiles[t] = t;
+    v.tile_slot[t] = t;
   } else {
-    atomicAdd((unsigned long long*)&totals[0], (unsigned long long)off);
-    atomicAdd((unsigned long long*)&totals[1], (unsigned long long)n_t);
+    atomicAdd((unsigned long long*)&c.totals[0], (unsigned long long)off);
+    atomicAdd((unsigned long long*)&c.totals[1], (unsigned long long)n_t);
   }
 }
 
@@ -235,10 +258,14 @@ __device__ __forceinline__ uint64_t select_scan(uint64_t v, uint64_t* lds, uint6
 }
 
 template <int kThreads, int kItems, bool kRegs>
-__global__ void __launch_bounds__(kThreads) tile_select_kernel(
-    const uint64_t* __restrict__ keys, int H, int W, int tiles_x, int tiles_y, int n_sel, int n_pix,
-    int32_t* __restrict__ valid_tiles, int32_t* __restrict__ tile_off, int32_t* __restrict__ tile_slot,
-    int64_t* __restrict__ totals) {
+__global__ void __launch_bounds__(kThreads) tile_select_kernel(Batch<SampleArgs> batch, SampleCommon common) {
+  const SampleArgs& v = batch.v[blockIdx.z];
+  const uint64_t* __restrict__ const keys = v.keys;
+  int32_t* __restrict__ const valid_tiles = v.valid_tiles;
+  int32_t* __restrict__ const tile_off = v.tile_off;
+  int32_t* __restrict__ const tile_slot = v.tile_slot;
+  int64_t* __restrict__ const totals = common.totals;
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x, tiles_y = v.tiles_y, n_sel = common.n_sel, n_pix = common.n_pix;
   constexpr int kWaves = kThreads / kWave;
   constexpr int kStep = kThreads * kItems;
   static_assert(kItems * kWaves <= kThreads && kItems <= 32, "a count per wave and round");
@@ -477,11 +504,15 @@ __device__ __forceinline__ int split_round(int permille, int n) { return (permil
 // wait for nothing.  4,293 tiles of 64 samples (1296x840): 23 us; with the
 // in-lane search in a branch, 24 counting steps by lane sums for the ages and
 // loads behind the image bounds it took 47 us.  6,120 tiles of 51: 21 us.
-__global__ void __launch_bounds__(64) tile_pixels_kernel(
-    const uint16_t* __restrict__ E, const uint16_t* __restrict__ A, int H, int W, int tiles_x,
-    int n_st, int n_pix, int hard_pm, int stable_pm, uint64_t seed, uint64_t step, uint64_t view,
-    const int32_t* __restrict__ valid_tiles, const int32_t* __restrict__ tile_off,
-    uint8_t* __restrict__ pix) {
+__global__ void __launch_bounds__(64) tile_pixels_kernel(Batch<SampleArgs> batch, SampleCommon common) {
+  const SampleArgs& v = batch.v[blockIdx.z];
+  const uint16_t* __restrict__ const E = v.E;
+  const uint16_t* __restrict__ const A = v.A;
+  const int32_t* __restrict__ const valid_tiles = v.valid_tiles;
+  const int32_t* __restrict__ const tile_off = v.tile_off;
+  uint8_t* __restrict__ const pix = v.pix;
+  const int H = v.H, W = v.W, tiles_x = v.tiles_x, n_st = v.n_st, n_pix = common.n_pix;
+  const int hard_pm = common.hard_pm, stable_pm = common.stable_pm;
   const int slot = blockIdx.x;
   if (slot >= n_st) return;
   const int lane = threadIdx.x;
@@ -517,7 +548,7 @@ __global__ void __launch_bounds__(64) tile_pixels_kernel(
     }
   }
   uint32_t picked = 0;  // bit k: local index lane*4+k chosen
-  const uint64_t key = stream_key(seed, step, view, (uint64_t)t);
+  const uint64_t key = stream_key(common.seed, common.step, v.view, (uint64_t)t);
 
   // --- hard: sequential error-weighted draws without replacement.  The
   // draws' random words are hashed up front, lane l holding draw l + 64 q
@@ -646,10 +677,10 @@ extern "C" size_t tgs_sample_workspace_size(int32_t height, int32_t width) {
   return align_up(n_t * sizeof(uint64_t), 256);
 }
 
-static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height, int32_t width,
-                           const tgs_sample_params* sp, const float* tile_pred, int32_t* valid_tiles,
-                           int32_t* tile_off, uint8_t* pix, int32_t* tile_slot, int64_t* totals, void* ws,
-                           size_t ws_bytes, void* stream) {
+static int32_t sample_args(SampleArgs& v, const uint16_t* E, const uint16_t* A, int32_t height, int32_t width,
+                           const tgs_sample_params* sp, int32_t view, const float* tile_pred, int32_t* valid_tiles,
+                           int32_t* tile_off, uint8_t* pix, int32_t* tile_slot, const int64_t* totals, void* ws,
+                           size_t ws_bytes) {
   TGS_REQUIRE(height > 0 && width > 0, "tgs_sample: bad image size %d x %d", width, height);
   TGS_REQUIRE(sp != nullptr, "tgs_sample: null params");
   TGS_REQUIRE(sp->n_pix >= 1 && sp->n_pix <= kTilePixels, "tgs_sample: n_pix %d not in 1..256",
@@ -657,31 +688,42 @@ static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height,
   TGS_REQUIRE(sp->hard_permille >= 0 && sp->stable_permille >= 0 &&
                   sp->hard_permille + sp->stable_permille <= 1000,
               "tgs_sample: bad hard/stable ratios");
-  TGS_REQUIRE(sp->view >= 0, "tgs_sample: negative view index");
+  TGS_REQUIRE(view >= 0, "tgs_sample: negative view index");
   TGS_REQUIRE(E && A && valid_tiles && tile_off && pix && tile_slot && totals && ws,
               "tgs_sample: null pointer");
   TGS_REQUIRE(ws_bytes >= tgs_sample_workspace_size(height, width),
               "tgs_sample: workspace %zu bytes < %zu", ws_bytes,
               tgs_sample_workspace_size(height, width));
-  const int tiles_x = (int)ceil_div(width, kTile), tiles_y = (int)ceil_div(height, kTile);
-  const int n_t = tiles_x * tiles_y;
-  const int n_st = tgs_sample_tile_count(height, width, sp);
-  uint64_t* keys = (uint64_t*)ws;
-  hipStream_t s = as_stream(stream);
-  const bool all_tiles = sp->n_tiles_sel < 0 || sp->n_tiles_sel >= n_t;
-  if (!all_tiles && tile_pred != nullptr)
-    hipLaunchKernelGGL(tile_pred_keys_kernel, dim3((unsigned)ceil_div(n_t, 256)), dim3(256), 0, s, tile_pred,
-                       height, width, tiles_x, n_t, sp->seed, sp->step, (uint64_t)sp->view, keys);
-  else if (!all_tiles)
-    hipLaunchKernelGGL(tile_keys_kernel, dim3((unsigned)ceil_div(n_t, kKeyTiles)), dim3(64), 0, s, E, height, width,
-                       tiles_x, n_t, sp->seed, sp->step, (uint64_t)sp->view, keys);
-  if (all_tiles) {
-    hipLaunchKernelGGL(tile_list_all_kernel, dim3((unsigned)ceil_div(n_t + 1, 256)), dim3(256), 0, s, height, width,
-                       tiles_x, tiles_y, sp->n_pix, valid_tiles, tile_off, tile_slot, totals);
+  v = SampleArgs{E,    A,      tile_pred, (uint64_t*)ws, valid_tiles, tile_off, tile_slot, pix, height, width,
+                 (int)ceil_div(width, kTile), (int)ceil_div(height, kTile), tgs_sample_tile_count(height, width, sp),
+                 (uint64_t)view};
+  return TGS_OK;
+}
+
+static bool all_tiles(const SampleArgs& v, const tgs_sample_params* sp) {
+  return sp->n_tiles_sel < 0 || sp->n_tiles_sel >= v.tiles_x * v.tiles_y;
+}
+
+// Views whose tiles are drawn the same way: all of them, by the error map or
+// by the predictions.
+static void sample_launch(const Batch<SampleArgs>& b, int views, const tgs_sample_params* sp, int64_t* totals,
+                          hipStream_t s) {
+  const SampleCommon c{sp->n_tiles_sel, sp->n_pix, sp->hard_permille, sp->stable_permille, sp->seed, sp->step, totals};
+  const unsigned nv = (unsigned)views;
+  int n_t = 0, n_st = 0;
+  for (int k = 0; k < views; ++k) {
+    n_t = max(n_t, b.v[k].tiles_x * b.v[k].tiles_y);
+    n_st = max(n_st, b.v[k].n_st);
+  }
+  if (all_tiles(b.v[0], sp)) {
+    hipLaunchKernelGGL(tile_list_all_kernel, dim3((unsigned)ceil_div(n_t + 1, 256), 1, nv), dim3(256), 0, s, b, c);
   } else {
+    if (b.v[0].pred != nullptr)
+      hipLaunchKernelGGL(tile_pred_keys_kernel, dim3((unsigned)ceil_div(n_t, 256), 1, nv), dim3(256), 0, s, b, c);
+    else
+      hipLaunchKernelGGL(tile_keys_kernel, dim3((unsigned)ceil_div(n_t, kKeyTiles), 1, nv), dim3(64), 0, s, b, c);
     auto select = [&](auto kernel, int threads) {
-      hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, keys, height, width, tiles_x, tiles_y, sp->n_tiles_sel,
-                         sp->n_pix, valid_tiles, tile_off, tile_slot, totals);
+      hipLaunchKernelGGL(kernel, dim3(1, 1, nv), dim3(threads), 0, s, b, c);
     };
     // the smallest variant that keeps every key in registers
     if (n_t <= 256 * 4) select(tile_select_kernel<256, 4, true>, 256);
@@ -690,10 +732,40 @@ static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height,
     else select(tile_select_kernel<1024, 16, false>, 1024);
   }
   if (n_st > 0)
-    hipLaunchKernelGGL(tile_pixels_kernel, dim3(n_st), dim3(64), 0, s, E, A, height, width, tiles_x,
-                       n_st, sp->n_pix, sp->hard_permille, sp->stable_permille, sp->seed, sp->step,
-                       (uint64_t)sp->view, valid_tiles, tile_off, pix);
+    hipLaunchKernelGGL(tile_pixels_kernel, dim3((unsigned)n_st, 1, nv), dim3(64), 0, s, b, c);
+}
+
+static int32_t sample_impl(const uint16_t* E, const uint16_t* A, int32_t height, int32_t width,
+                           const tgs_sample_params* sp, const float* tile_pred, int32_t* valid_tiles,
+                           int32_t* tile_off, uint8_t* pix, int32_t* tile_slot, int64_t* totals, void* ws,
+                           size_t ws_bytes, void* stream) {
+  Batch<SampleArgs> b{};
+  if (int32_t e = sample_args(b.v[0], E, A, height, width, sp, sp != nullptr ? sp->view : 0, tile_pred, valid_tiles,
+                              tile_off, pix, tile_slot, totals, ws, ws_bytes))
+    return e;
+  sample_launch(b, 1, sp, totals, as_stream(stream));
   return hip_status("tgs_sample");
+}
+
+extern "C" int32_t tgs_sample_views(const tgs_view* views, int32_t n_views, const tgs_sample_params* sp,
+                                    int64_t* totals, void* stream) {
+  TGS_REQUIRE(n_views >= 0 && (n_views == 0 || views != nullptr), "tgs_sample_views: bad view list");
+  for (int pass = 0; pass < 2; ++pass)  // every view is checked before any is launched
+    for (int32_t k = 0, end; k < n_views; k = end) {
+      Batch<SampleArgs> b{};
+      for (end = k; end < n_views && end - k < kBatch; ++end) {
+        const tgs_view& v = views[end];
+        SampleArgs a{};
+        if (int32_t e = sample_args(a, v.E, v.A, v.height, v.width, sp, v.view, v.tile_pred, v.valid_tiles, v.tile_off,
+                                    v.pix, v.tile_slot, totals, v.sample_ws, v.sample_ws_bytes))
+          return e;
+        if (end > k && (all_tiles(a, sp) != all_tiles(b.v[0], sp) || (a.pred == nullptr) != (b.v[0].pred == nullptr)))
+          break;
+        b.v[end - k] = a;
+      }
+      if (pass == 1) sample_launch(b, end - k, sp, totals, as_stream(stream));
+    }
+  return hip_status("tgs_sample_views");
 }
 
 extern "C" int32_t tgs_sample(const uint16_t* E, const uint16_t* A, int32_t height, int32_t width,

@@ -157,9 +157,12 @@ class ViewBuffers:
                                    dtype=torch.uint8, device=dev)
 
     # ---- the steps of one view
+    def sample_params(self, cfg: StepConfig, step: int, view: int):
+        return B.sample_params(self.n_pix, cfg.hard_permille, cfg.stable_permille, cfg.n_tiles_sel, cfg.seed, step,
+                               view)
+
     def sample(self, E, A, cfg: StepConfig, step: int, view: int, totals, tile_pred=None):
-        sp = B.sample_params(self.n_pix, cfg.hard_permille, cfg.stable_permille, cfg.n_tiles_sel,
-                             cfg.seed, step, view)
+        sp = self.sample_params(cfg, step, view)
         B.tgs_sample(E, A, self.height, self.width, sp, self.valid_tiles, self.tile_off, self.pix,
                      self.tile_slot, totals, self.sample_ws, tile_pred=tile_pred)
 
@@ -205,6 +208,16 @@ class ViewBuffers:
         return B.bin_view(self.rect, self.splat, self.depth, self.tile_slot if self.bin_sort_needs_samples() else None,
                           self.tiles_x, self.tiles_y, self.keys, self.vals, self.capacity, self.ranges, None,
                           self.counts, self.sort_ws)
+
+    def record(self, view: int, gt, E, A, tile_pred=None) -> B.tgs_view:
+        """This view's part of the calls over several views (whole lists)."""
+        p = B._ptr
+        ws = None if self.dense else self.sample_ws
+        return B.tgs_view(p(self.splat), p(self.vals), p(self.ranges), p(self.valid_tiles), p(self.tile_off),
+                          p(self.tile_slot), p(self.pix), p(self.out), p(self.ncontrib), p(self.state), p(gt),
+                          p(self.dL), p(self.err), p(self.lam), p(self.tile_loss), p(self.g2d), p(E), p(A),
+                          p(tile_pred), p(ws), 0 if ws is None else ws.numel(), self.tiles_x, self.tiles_y,
+                          self.width, self.height, self.n_st, self.n_pix, view)
 
     # ---- depth-prefix lists
     def _alloc_cont(self, capacity2: int):
@@ -582,11 +595,15 @@ class Trainer:
                                     [vb.splat for vb in used], [vb.depth for vb in used], [vb.radius for vb in used],
                                     [vb.rect for vb in used], [vb.clamp for vb in used], [vb.g2d for vb in used])
 
+        def records():
+            return B.views_array([vb.record(v, self.gts[v], None if self.E is None else self.E[v],
+                                            None if self.A is None else self.A[v], pred)
+                                  for vb, v, pred in zip(used, views, preds)])
+
         def bin_all():
             # every view's lists, each kernel launched once for all of them
-            for k, vb in enumerate(used):
-                if vb.bin_sort_needs_samples():
-                    main.wait_event(sampled[k])   # binning keeps the sampled tiles only
+            for ev in {id(sampled[k]): sampled[k] for k, vb in enumerate(used) if vb.bin_sort_needs_samples()}.values():
+                main.wait_event(ev)   # binning keeps the sampled tiles only
             with st("bin_sort"):
                 B.tgs_bin_sort_views_async([vb.bin_view(prefix_n) for vb in used], self.n, self.rp.alpha_min,
                                            -1 if prefix_n is None else min(prefix_n, self.n))
@@ -598,15 +615,33 @@ class Trainer:
         # and forwards instead: 3337 us, and 3413 us with one call), but the
         # first step of a slot waits to size its arrays
         binned = together and not par and all(vb.sized for vb in used)
+        # and with whole lists every other stage in one call as well (the same
+        # step: 651 us view by view, 368 us so)
+        stacked = binned and prefix_n is None
+        preds = [None] * len(used)
         if par:
             if together:
                 project_all()
             if self._cleared is None:
                 self._cleared = torch.cuda.Event()
             self._cleared.record(main)
+        if stacked and not used[0].dense:
+            ss = self._sample_stream(0)
+            ss.wait_stream(main)
+            with torch.cuda.stream(ss):
+                if self.tiles is not None:
+                    preds = [self.tiles.predict(k, v, self.E[v], self.A[v], vb, self.cams[v])
+                             for k, (vb, v) in enumerate(zip(used, views))]
+                with st("sample"):
+                    B.tgs_sample_views(records(), used[0].sample_params(self.cfg, t, 0), self.totals)
+                if not self._sampled:
+                    self._sampled.append(torch.cuda.Event())
+                self._sampled[0].record(ss)
+            sampled = [self._sampled[0]] * len(used)
         for k, (vb, v) in enumerate(zip(used, views)):
-            if vb.dense:
-                sampled.append(None)
+            if vb.dense or stacked:
+                if vb.dense:
+                    sampled.append(None)
                 continue
             # views side by side: a sampler over every tile is short and runs
             # on main (idle until the first backward) beside the views' binning;
@@ -647,19 +682,22 @@ class Trainer:
             project_all()
             if binned:
                 bin_all()
+            if stacked:
+                self._stacked_stages(used, views, records(), sampled)
         for k, (vb, v) in enumerate(zip(used, views)):
             cam = self.cams[v]
             if par:
                 main.wait_event(self._done[k])
-            else:
+            elif not stacked:
                 for _ in self._view_chain(k, vb, v, cam, sampled, prefix_n, main, projected=together,
                                           binned=binned):
                     pass
-            with st("render_bwd"):
-                # g2d was cleared by the projection; the density sums of sparse
-                # views join the backward's reduction
-                vb.render_bwd(self.rp, zero=False, stats=None if vb.dense else self.dstats, touched=self.touched,
-                              deterministic=self.cfg.deterministic)
+            if not stacked or self.cfg.deterministic:
+                with st("render_bwd"):
+                    # g2d was cleared by the projection; the density sums of sparse
+                    # views join the backward's reduction
+                    vb.render_bwd(self.rp, zero=False, stats=None if vb.dense else self.dstats, touched=self.touched,
+                                  deterministic=self.cfg.deterministic)
             if self.gstats is not None:
                 B.tgs_grad_screen_accumulate(vb.g2d, vb.radius, self.n, cam.width, cam.height, self.gstats)
             if views_fused:
@@ -692,6 +730,38 @@ class Trainer:
                 main.wait_stream(vs)   # their error-map updates, before the next step samples
         self._queue_count_check(used)
         return used
+
+    def _stacked_stages(self, used, views, rec, sampled):
+        """Forward, loss, error maps and (unless it is the deterministic one)
+        backward of a step's views, a call per stage, on the current stream;
+        the maps' update on the side stream."""
+        st, main = self._stage, torch.cuda.current_stream()
+        sparse = not used[0].dense
+        if sparse:
+            main.wait_event(sampled[0])   # one event for all the views' samples
+        with st("render_fwd"):
+            B.tgs_render_fwd_views(rec, self.rp, self.counters)
+        with st("loss"):
+            B.tgs_loss_views(rec, self.totals, self.lp)
+        if sparse:
+            if not self._lossed:
+                self._lossed.append(torch.cuda.Event())
+            self._lossed[0].record(main)
+            self.side.wait_event(self._lossed[0])
+            with torch.cuda.stream(self.side):
+                distinct = len(set(views)) == len(views)   # else a view's maps are updated in turn
+                if distinct:
+                    with st("ema_age"):
+                        B.tgs_ema_age_update_views(rec, self.cfg.beta)
+                for k, (vb, v) in enumerate(zip(used, views)):
+                    if not distinct:
+                        with st("ema_age"):
+                            vb.ema_age(self.E[v], self.A[v], self.cfg.beta)
+                    if self.tiles is not None:
+                        self.tiles.learn(k, v, self.E[v], self.A[v], vb, self.cams[v])
+        if not self.cfg.deterministic:
+            with st("render_bwd"):
+                B.tgs_render_bwd_views(rec, self.rp, self.touched, self.n, self.dstats if sparse else None)
 
     def _view_chain(self, k, vb, v, cam, sampled, prefix_n, vs, done=None, projected=False, binned=False):
         """Projection (unless ``projected``), binning (unless ``binned``),
