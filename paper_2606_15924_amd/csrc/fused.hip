@@ -19,6 +19,7 @@
 // its order (the DC term contributes an exact zero), and both paths share
 // the update functions.
 #include <algorithm>
+#include <type_traits>
 
 #include "optimizer.h"
 #include "projection.h"
@@ -222,11 +223,21 @@ struct ViewSet {
 // order) and gives each wave lane one listed Gaussian, 64 at a time.  The
 // window's rows span 16 cache lines each, so its loads touch the lines a
 // streaming pass would, with a fraction of the waves.
-constexpr int kWindow = 512;
+//
+// A window's groups of 64 run one after the other, each a chain of FP64 work
+// and loads, so few windows leave the device idle: the window is the
+// smallest of 64, 256 and 512 with at most kMaxWindows windows (four to a
+// compute unit).  SH and geometry kernel, four views that touch most of the
+// Gaussians: 10k 12 + 11 us with 64, 63 + 58 with 512; 65k 21 + 14, 33 + 29
+// with 256, 50 + 48 with 512; 131k 36 + 25 with 256, 41 + 35 with 512.  One
+// view that touches few of 300k: 50 + 33 with 64, 33 + 15 with 256, 31 + 14
+// with 512; three views of 1.5M: 283 + 166, 141 + 75, 141 + 76.
+constexpr int64_t kMaxWindows = 1024;
 
 // The touched Gaussians of [w0, w0 + kWindow) as offsets from w0, in
 // order, into lds[0..c); returns c (wave-uniform).  Every Gaussian when
 // touched is null.  Called by one whole wave.
+template <int kWindow>
 __device__ __forceinline__ int window_list(const uint8_t* __restrict__ touched, int64_t n, int64_t w0,
                                            uint16_t* __restrict__ lds) {
   const int lane = lane_id();
@@ -304,7 +315,7 @@ __device__ __forceinline__ void sh_group_views(float* params, int64_t n, const V
   }
 }
 
-template <int kDeg>
+template <int kDeg, int kWindow>
 __global__ void __launch_bounds__(kShGroups * kWave) sh_rest_views_kernel(float* params, int64_t n, ViewSet vs,
                                                                            float* __restrict__ m,
                                                                            float* __restrict__ v,
@@ -315,7 +326,7 @@ __global__ void __launch_bounds__(kShGroups * kWave) sh_rest_views_kernel(float*
   const int grp = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int lane = (int)(threadIdx.x % kWave);
   const int64_t w0 = (int64_t)blockIdx.x * kWindow;
-  const int c = window_list(touched, n, w0, wl[grp]);  // the same count in every wave
+  const int c = window_list<kWindow>(touched, n, w0, wl[grp]);  // the same count in every wave
   for (int g = 0; g < c; g += kWave) {
     // untouched Gaussians are not listed: their parameters and moments stay
     const bool live = g + lane < c;
@@ -492,13 +503,14 @@ __device__ __forceinline__ void geom_lm_views_one(float* params, int64_t n, cons
                                                   float* __restrict__ m, float* __restrict__ v, const OptArgs& o,
                                                   const double* __restrict__ dmu_sh, int64_t i);
 
+template <int kWindow>
 __global__ void __launch_bounds__(64) geom_lm_views_kernel(float* params, int64_t n, ViewSet vs, double dil,
                                                            float* __restrict__ m, float* __restrict__ v,
                                                            const uint8_t* __restrict__ touched, OptArgs o,
                                                            const double* __restrict__ dmu_sh) {
   __shared__ uint16_t wl[kWindow];
   const int64_t w0 = (int64_t)blockIdx.x * kWindow;
-  const int c = window_list(touched, n, w0, wl);
+  const int c = window_list<kWindow>(touched, n, w0, wl);
   for (int g = 0; g < c; g += kWave)
     if (g + (int)threadIdx.x < c) geom_lm_views_one(params, n, vs, dil, m, v, o, dmu_sh, w0 + wl[g + threadIdx.x]);
 }
@@ -593,19 +605,24 @@ extern "C" int32_t tgs_project_bwd_optimizer_step_views(float* params, int64_t n
   TGS_REQUIRE(ws_bytes >= need, "%s: workspace %zu bytes < %zu", who, ws_bytes, need);
   TGS_REQUIRE(((uintptr_t)ws & 7) == 0, "%s: workspace must be 8-byte aligned", who);
   hipStream_t s = as_stream(stream);
-  const dim3 grid((unsigned)ceil_div(n, kWindow));
-#define TGS_SH_VIEWS(D)                                                                                        \
-  hipLaunchKernelGGL(sh_rest_views_kernel<D>, grid, dim3(kShGroups * kWave), 0, s, params, n, vs, m, v, touched, \
-                     o, (double*)ws)
-  switch (rp->sh_degree) {
-    case 0: TGS_SH_VIEWS(0); break;
-    case 1: TGS_SH_VIEWS(1); break;
-    case 2: TGS_SH_VIEWS(2); break;
-    default: TGS_SH_VIEWS(3); break;
-  }
-#undef TGS_SH_VIEWS
-  hipLaunchKernelGGL(geom_lm_views_kernel, grid, dim3(kWave), 0, s, params, n, vs, (double)rp->dilation, m, v,
-                     touched, o, (const double*)ws);
+  auto update = [&](auto window) {
+    constexpr int kWindow = decltype(window)::value;
+    const dim3 grid((unsigned)ceil_div(n, kWindow));
+    auto sh = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kShGroups * kWave), 0, s, params, n, vs, m, v, touched, o, (double*)ws);
+    };
+    switch (rp->sh_degree) {
+      case 0: sh(sh_rest_views_kernel<0, kWindow>); break;
+      case 1: sh(sh_rest_views_kernel<1, kWindow>); break;
+      case 2: sh(sh_rest_views_kernel<2, kWindow>); break;
+      default: sh(sh_rest_views_kernel<3, kWindow>); break;
+    }
+    hipLaunchKernelGGL(geom_lm_views_kernel<kWindow>, grid, dim3(kWave), 0, s, params, n, vs, (double)rp->dilation, m,
+                       v, touched, o, (const double*)ws);
+  };
+  if (n <= 64 * kMaxWindows) update(std::integral_constant<int, 64>{});
+  else if (n <= 256 * kMaxWindows) update(std::integral_constant<int, 256>{});
+  else update(std::integral_constant<int, 512>{});
   return hip_status(who);
 }
 
