@@ -71,7 +71,8 @@ class ViewBuffers:
     """Per-view device buffers for one image size and sampling rate."""
 
     def __init__(self, n: int, width: int, height: int, n_pix: int | None, n_tiles_sel: int,
-                 device, capacity: int | None = None, keep_keys: bool = False):
+                 device, capacity: int | None = None, keep_keys: bool = False,
+                 counts: torch.Tensor | None = None):
         self.n, self.width, self.height = n, width, height
         self.keep_keys = keep_keys
         self.tiles_x, self.tiles_y = (width + TILE - 1) // TILE, (height + TILE - 1) // TILE
@@ -109,12 +110,13 @@ class ViewBuffers:
         # per-pixel (T, colour) at the backward's chunk starts, kept by the forward
         n_state = B.tgs_render_state_size(self.n_st, self.n_pix) // 4
         self.state = torch.empty(max(n_state, 4), dtype=torch.float32, device=dev)
-        # (list length, capacity needed[, whole-list pairs after a depth-prefix call])
-        self.counts = torch.zeros(3, dtype=torch.int64, device=dev)
+        # (list length, capacity needed[, whole-list pairs after a depth-prefix
+        # call]) and the continuation's, in one row that the caller may give
+        row = torch.zeros(5, dtype=torch.int64, device=dev) if counts is None else counts.zero_()
+        self.counts, self.counts2 = row[:3], row[3:]
         # depth-prefix lists: the continuation's lists and the marked tiles
         self.two_part = False
         self.prefix = self.n
-        self.counts2 = torch.zeros(2, dtype=torch.int64, device=dev)
         self.capacity2 = 0
         self.vals2 = self.ranges2 = self.sort_ws2 = None
         self.cont_slot = self.cont_list = self.cont_count = None
@@ -212,12 +214,16 @@ class ViewBuffers:
     def record(self, view: int, gt, E, A, tile_pred=None) -> B.tgs_view:
         """This view's part of the calls over several views (whole lists)."""
         p = B._ptr
-        ws = None if self.dense else self.sample_ws
-        return B.tgs_view(p(self.splat), p(self.vals), p(self.ranges), p(self.valid_tiles), p(self.tile_off),
-                          p(self.tile_slot), p(self.pix), p(self.out), p(self.ncontrib), p(self.state), p(gt),
-                          p(self.dL), p(self.err), p(self.lam), p(self.tile_loss), p(self.g2d), p(E), p(A),
-                          p(tile_pred), p(ws), 0 if ws is None else ws.numel(), self.tiles_x, self.tiles_y,
-                          self.width, self.height, self.n_st, self.n_pix, view)
+        r = B.tgs_view(self.splat.data_ptr(), self.vals.data_ptr(), self.ranges.data_ptr(), None, None, None, None,
+                       self.out.data_ptr(), self.ncontrib.data_ptr(), self.state.data_ptr(), p(gt), self.dL.data_ptr(),
+                       self.err.data_ptr(), self.lam.data_ptr(), self.tile_loss.data_ptr(), self.g2d.data_ptr(), p(E),
+                       p(A), p(tile_pred), None, 0, self.tiles_x, self.tiles_y, self.width, self.height, self.n_st,
+                       self.n_pix, view)
+        if not self.dense:
+            r.valid_tiles, r.tile_off = self.valid_tiles.data_ptr(), self.tile_off.data_ptr()
+            r.tile_slot, r.pix = self.tile_slot.data_ptr(), self.pix.data_ptr()
+            r.sample_ws, r.sample_ws_bytes = self.sample_ws.data_ptr(), self.sample_ws.numel()
+        return r
 
     # ---- depth-prefix lists
     def _alloc_cont(self, capacity2: int):
@@ -453,6 +459,7 @@ class Trainer:
         self.totals = torch.zeros(2, dtype=torch.int64, device=self.dev)
         self.step_count = 0
         self._bufs: dict = {}
+        self._counts = torch.zeros((64, 5), dtype=torch.int64, device=self.dev)   # pair counts of the first slots
         self.counters = torch.zeros((2, B.COUNTER_SLOTS), dtype=torch.int64, device=self.dev)
         self.side = torch.cuda.Stream(device=self.dev)  # default priority
         self.fused_ws = torch.empty(B.tgs_project_bwd_optimizer_workspace_size(self.n), dtype=torch.uint8,
@@ -519,9 +526,11 @@ class Trainer:
         cap = old.capacity if old is not None and old.n == self.n else None
         if old is not None:
             torch.cuda.synchronize(self.dev)   # its arrays may be in use on a view stream
+            old.counts, old.counts2 = old.counts.clone(), old.counts2.clone()   # its row goes to the new set
             del self._bufs[key]
+        row = self._counts[key] if isinstance(key, int) and 0 <= key < len(self._counts) else None
         self._bufs[key] = ViewBuffers(self.n, cam.width, cam.height, n_pix, self.cfg.n_tiles_sel, self.dev,
-                                      capacity=cap)
+                                      capacity=cap, counts=row)
         return self._bufs[key]
 
     def init_error_maps(self, views):
@@ -618,7 +627,7 @@ class Trainer:
         # and with whole lists every other stage in one call as well (the same
         # step: 651 us view by view, 368 us so)
         stacked = binned and prefix_n is None
-        preds = [None] * len(used)
+        preds, rec = [None] * len(used), None
         if par:
             if together:
                 project_all()
@@ -632,8 +641,9 @@ class Trainer:
                 if self.tiles is not None:
                     preds = [self.tiles.predict(k, v, self.E[v], self.A[v], vb, self.cams[v])
                              for k, (vb, v) in enumerate(zip(used, views))]
+                rec = records()
                 with st("sample"):
-                    B.tgs_sample_views(records(), used[0].sample_params(self.cfg, t, 0), self.totals)
+                    B.tgs_sample_views(rec, used[0].sample_params(self.cfg, t, 0), self.totals)
                 if not self._sampled:
                     self._sampled.append(torch.cuda.Event())
                 self._sampled[0].record(ss)
@@ -683,7 +693,7 @@ class Trainer:
             if binned:
                 bin_all()
             if stacked:
-                self._stacked_stages(used, views, records(), sampled)
+                self._stacked_stages(used, views, rec if rec is not None else records(), sampled)
         for k, (vb, v) in enumerate(zip(used, views)):
             cam = self.cams[v]
             if par:
@@ -737,7 +747,7 @@ class Trainer:
         the maps' update on the side stream."""
         st, main = self._stage, torch.cuda.current_stream()
         sparse = not used[0].dense
-        if sparse:
+        if sparse and not any(vb.bin_sort_needs_samples() for vb in used):   # else the binning waited for them
             main.wait_event(sampled[0])   # one event for all the views' samples
         with st("render_fwd"):
             B.tgs_render_fwd_views(rec, self.rp, self.counters)
@@ -852,11 +862,12 @@ class Trainer:
     def _queue_count_check(self, used):
         if not used:
             return
-        host = torch.zeros((len(used), 5), dtype=torch.int64, pin_memory=True)
-        for k, vb in enumerate(used):
+        host = torch.empty((len(used), 5), dtype=torch.int64, pin_memory=True)
+        rows = min(len(used), len(self._counts))   # slot k's counts are row k: one copy
+        host[:rows].copy_(self._counts[:rows], non_blocking=True)
+        for k, vb in enumerate(used[rows:], rows):
             host[k, :3].copy_(vb.counts, non_blocking=True)
-            if vb.two_part:
-                host[k, 3:].copy_(vb.counts2, non_blocking=True)
+            host[k, 3:].copy_(vb.counts2, non_blocking=True)
         ev = torch.cuda.Event()
         ev.record()
         self._pending.append((ev, host, [(vb, vb.capacity, vb.capacity2, vb.two_part) for vb in used]))
