@@ -557,14 +557,17 @@ int32_t tgs_density_score(const float* stats, int64_t n, float lambda_base, floa
  * pruning by percentile thresholds of the scores): the k-th largest
  * (1 <= k <= n) of values[n] in the total order of the IEEE bit patterns
  * (-0 below +0, NaN above +inf), written to out (one device float) by an
- * exact MSB-first radix select that stays on the device (nine small
- * launches, no host synchronisation).
+ * exact MSB-first radix select that stays on the device (five small
+ * launches, no host synchronisation).  tgs_select_kth_largest2 finds the
+ * k0-th and the k1-th largest with the same reads, out[0] and out[1].
  *   ws  tgs_select_workspace_size() bytes, 16-byte aligned, device memory
  *       (fully rewritten by every call; calls that share it must not overlap)
  * Errors: n < 1, k outside [1, n], a short workspace. */
 size_t tgs_select_workspace_size(void);
 int32_t tgs_select_kth_largest(const float* values, int64_t n, int64_t k, float* out, void* ws,
                                size_t ws_bytes, void* stream);
+int32_t tgs_select_kth_largest2(const float* values, int64_t n, int64_t k0, int64_t k1, float* out, void* ws,
+                                size_t ws_bytes, void* stream);
 
 /* mask[i] = 1 when values[i] >= *thr in the order above (thr is a device
  * pointer, e.g. the tgs_select_kth_largest output), else 0. */

@@ -164,6 +164,7 @@ PROTOTYPES = {
     "tgs_view_error_sums": (_I32, [_P, _I32, _I64, _P, _P]),
     "tgs_select_workspace_size": (_SZ, []),
     "tgs_select_kth_largest": (_I32, [_P, _I64, _I64, _P, _P, _SZ, _P]),
+    "tgs_select_kth_largest2": (_I32, [_P, _I64, _I64, _I64, _P, _P, _SZ, _P]),
     "tgs_threshold_mask": (_I32, [_P, _I64, _P, _P, _P]),
     "tgs_project_bwd": (_I32, [_P, _I64, ctypes.POINTER(tgs_camera), ctypes.POINTER(tgs_raster_params),
                                _P, _P, _P, _P, _I32, _P]),
@@ -605,6 +606,11 @@ def tgs_view_error_sums(E, n_views, pixels, sums):
 
 def tgs_select_workspace_size() -> int:
     return int(lib().tgs_select_workspace_size())
+
+
+def tgs_select_kth_largest2(values, n, k0, k1, out, ws):
+    _check(lib().tgs_select_kth_largest2(_ptr(values), n, k0, k1, _ptr(out), _ptr(ws),
+                                         ws.numel() * ws.element_size(), _stream()), "tgs_select_kth_largest2")
 
 
 def tgs_select_kth_largest(values, n, k, out, ws):

@@ -34,19 +34,36 @@ __global__ void __launch_bounds__(256) density_score_kernel(const float* __restr
 }
 
 // ------------------------------------------------------------------ percentile
-// Exact k-th largest of n floats by an MSB-first radix select over the
-// order-preserving 32-bit keys (sign flipped for non-negative values, all
-// bits flipped for negative ones): four rounds of an 8-bit digit histogram
-// of the keys that still match the chosen prefix, each followed by a
-// one-workgroup pick of the digit that holds the k-th largest.  The state
-// (prefix, remaining rank, histogram) stays on the device, so the rounds
-// queue without a host round trip.
+// Exact k-th largest of n floats, for one or two k at once, by an MSB-first
+// radix select over the order-preserving 32-bit keys (sign flipped for
+// non-negative values, all bits flipped for negative ones): three rounds of
+// a histogram of an 11- or 10-bit digit of the keys that still match a
+// target's chosen prefix.  Every workgroup of a round first picks the last
+// round's digit for itself from that round's histogram (a scan of 2048
+// counts, less than a launch), so the rounds queue without a host round trip
+// and without a pick launch between them.
+//
+// The values are read once per round (6 MB at 1.5M); what a round costs beyond
+// that is LDS atomics on few counters (scores share their exponents, and many
+// Gaussians the score 0): a wave adds its first lane's digit once for all the
+// lanes that share it, and kCopies copies take the others.  Two targets of
+// 1.5M scores: 33 us in five launches, where one rank at a time in 8-bit rounds
+// with a pick launch each took 102 us in eighteen.
+constexpr int kSelBits = 11;
+constexpr int kSelBins = 1 << kSelBits;
+constexpr int kSelThreads = 1024;
+constexpr int kSelRounds = 3;
+constexpr int kSelTargets = 2;
+constexpr int kCopies = 4;
+
 struct SelectState {
-  uint32_t hist[256];
-  uint32_t prefix;
-  uint32_t k_rem;  // rank of the target among the keys that match the prefix
-  uint32_t pad[2];
+  uint32_t hist[kSelRounds][kSelTargets][kSelBins];  // the first round's is shared (target 0)
+  uint32_t prefix[kSelRounds][kSelTargets];          // before round r: the key's bits above shift r
+  uint32_t k_rem[kSelRounds][kSelTargets];           // rank of the target among the keys that match it
 };
+
+// Digit of round r: key bits [21, 32), [10, 21), [0, 10).
+__host__ __device__ constexpr int sel_shift(int r) { return r == 0 ? 21 : (r == 1 ? 10 : 0); }
 
 __device__ __forceinline__ uint32_t order_key(float f) {
   const uint32_t b = __float_as_uint(f);
@@ -57,56 +74,103 @@ __device__ __forceinline__ float key_value(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-__global__ void __launch_bounds__(256) select_init_kernel(SelectState* __restrict__ st, uint32_t k) {
-  st->hist[threadIdx.x] = 0u;
-  if (threadIdx.x == 0) {
-    st->prefix = 0u;
-    st->k_rem = k;
+__global__ void __launch_bounds__(kSelThreads) select_init_kernel(SelectState* __restrict__ st, uint32_t k0,
+                                                                  uint32_t k1) {
+  uint32_t* const h = &st->hist[0][0][0];
+  for (int i = blockIdx.x * kSelThreads + threadIdx.x; i < kSelRounds * kSelTargets * kSelBins;
+       i += gridDim.x * kSelThreads)
+    h[i] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x < kSelTargets) {
+    st->prefix[0][threadIdx.x] = 0u;
+    st->k_rem[0][threadIdx.x] = threadIdx.x == 0 ? k0 : k1;
   }
 }
 
-__global__ void __launch_bounds__(256) select_hist_kernel(const float* __restrict__ v, int64_t n, int shift,
-                                                          SelectState* __restrict__ st) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0u;
-  __syncthreads();
-  const uint32_t prefix = st->prefix;
-  const uint32_t hi_mask = shift == 24 ? 0u : ~((1u << (shift + 8)) - 1u);
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const uint32_t key = order_key(v[i]);
-    if ((key & hi_mask) == prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
+// The digit of round r - 1 that holds target t: above < k <= above + its
+// count, above the count of larger digits.  Returns the prefix and rank
+// before round r in s_pick[0..1] (every thread of the workgroup calls).
+__device__ __forceinline__ void select_pick(const SelectState* __restrict__ st, int r, int t, uint32_t* lds,
+                                            uint32_t* s_pick) {
+  constexpr int kPer = kSelBins / kSelThreads;
+  const uint32_t* const h = st->hist[r - 1][r == 1 ? 0 : t];
+  const uint32_t k = st->k_rem[r - 1][t];
+  uint32_t c[kPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {  // from the largest digit down
+    c[i] = h[kSelBins - 1 - ((int)threadIdx.x * kPer + i)];
+    sum += c[i];
+  }
+  uint32_t all;
+  uint32_t above = block_exclusive_scan<kSelThreads, uint32_t>(sum, lds, &all);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (above < k && k <= above + c[i]) {
+      s_pick[0] = st->prefix[r - 1][t] | (uint32_t)(kSelBins - 1 - ((int)threadIdx.x * kPer + i)) << sel_shift(r - 1);
+      s_pick[1] = k - above;
+    }
+    above += c[i];
   }
   __syncthreads();
-  if (h[threadIdx.x] != 0u) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// One workgroup of 256: digit d's count of keys with a larger digit is a
-// suffix sum (an inclusive Hillis-Steele scan from the top, eight rounds);
-// the digit with above < k_rem <= above + hist[d] holds the target.
-__global__ void __launch_bounds__(256) select_pick_kernel(int shift, SelectState* __restrict__ st,
-                                                          float* __restrict__ out) {
-  __shared__ uint32_t sfx[256];
-  const int d = threadIdx.x;
-  const uint32_t hd = st->hist[d];
-  sfx[d] = hd;
+template <int kRound>
+__global__ void __launch_bounds__(kSelThreads) select_hist_kernel(const float* __restrict__ v, int64_t n, int targets,
+                                                                  SelectState* __restrict__ st) {
+  constexpr int kSets = kRound == 0 ? 1 : kSelTargets;  // histograms of the round
+  constexpr int kCopy = kCopies / kSets;
+  constexpr uint32_t kMask = kRound == kSelRounds - 1 ? (1u << 10) - 1u : (uint32_t)kSelBins - 1u;
+  constexpr uint32_t kAbove = kRound == 0 ? 0u : ~0u << sel_shift(kRound == 0 ? 0 : kRound - 1);
+  __shared__ uint32_t h[kSets][kSelBins * kCopy];
+  __shared__ uint32_t lds[kSelThreads / kWave];
+  __shared__ uint32_t s_pick[kSelTargets][2];
+  const int lane = lane_id(), copy = lane & (kCopy - 1);
+  for (int i = threadIdx.x; i < kSets * kSelBins * kCopy; i += kSelThreads) (&h[0][0])[i] = 0u;
   __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const uint32_t add = d + off < 256 ? sfx[d + off] : 0u;
-    __syncthreads();
-    sfx[d] += add;
-    __syncthreads();
+  if constexpr (kRound > 0) {
+    for (int t = 0; t < targets; ++t) {
+      select_pick(st, kRound, t, lds, s_pick[t]);
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->prefix[kRound][t] = s_pick[t][0];
+        st->k_rem[kRound][t] = s_pick[t][1];
+      }
+    }
   }
-  const uint32_t above = sfx[d] - hd;
-  const uint32_t k = st->k_rem;
+  const int sets = kRound == 0 ? 1 : targets;
+  for (int64_t i0 = (int64_t)blockIdx.x * kSelThreads; i0 < n; i0 += (int64_t)gridDim.x * kSelThreads) {
+    const int64_t i = i0 + threadIdx.x;
+    const uint32_t key = i < n ? order_key(v[i]) : 0u;
+    const uint32_t d = (key >> sel_shift(kRound)) & kMask;
+#pragma unroll
+    for (int t = 0; t < kSets; ++t) {
+      if (t >= sets) continue;
+      const bool match = i < n && (kRound == 0 || (key & kAbove) == s_pick[t][0]);
+      const uint64_t mm = ballot(match);
+      if (mm == 0ull) continue;
+      const int first = __builtin_ctzll(mm);
+      const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+      const uint64_t same = ballot(match && d == d0);
+      if (lane == first) atomicAdd(&h[t][d0 * kCopy + copy], (uint32_t)__builtin_popcountll(same));
+      else if (match && d != d0) atomicAdd(&h[t][d * kCopy + copy], 1u);
+    }
+  }
   __syncthreads();
-  const bool mine = above < k && k <= above + hd;
-  st->hist[d] = 0u;  // cleared for the next round
-  __syncthreads();
-  if (mine) {
-    const uint32_t prefix = st->prefix | ((uint32_t)d << shift);
-    st->prefix = prefix;
-    st->k_rem = k - above;
-    if (shift == 0) *out = key_value(prefix);
+  for (int t = 0; t < sets; ++t)
+    for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int q = 0; q < kCopy; ++q) c += h[t][b * kCopy + q];
+      if (c != 0u) atomicAdd(&st->hist[kRound][t][b], c);
+    }
+}
+
+__global__ void __launch_bounds__(kSelThreads) select_out_kernel(int targets, const SelectState* __restrict__ st,
+                                                                 float* __restrict__ out) {
+  __shared__ uint32_t lds[kSelThreads / kWave];
+  __shared__ uint32_t s_pick[2];
+  for (int t = 0; t < targets; ++t) {
+    select_pick(st, kSelRounds, t, lds, s_pick);
+    if (threadIdx.x == 0) out[t] = key_value(s_pick[0]);
+    __syncthreads();
   }
 }
 
@@ -390,23 +454,34 @@ extern "C" int32_t tgs_density_topology_apply(const float* params, const float* 
 
 extern "C" size_t tgs_select_workspace_size(void) { return sizeof(SelectState); }
 
-extern "C" int32_t tgs_select_kth_largest(const float* values, int64_t n, int64_t k, float* out, void* ws,
-                                          size_t ws_bytes, void* stream) {
-  TGS_REQUIRE(n > 0 && n < (1ll << 31), "tgs_select_kth_largest: n %lld out of range", (long long)n);
-  TGS_REQUIRE(k >= 1 && k <= n, "tgs_select_kth_largest: k %lld not in [1, %lld]", (long long)k, (long long)n);
-  TGS_REQUIRE(values && out && ws, "tgs_select_kth_largest: null pointer");
-  TGS_REQUIRE(ws_bytes >= sizeof(SelectState), "tgs_select_kth_largest: workspace %zu bytes < %zu", ws_bytes,
-              sizeof(SelectState));
-  TGS_REQUIRE(((uintptr_t)ws & 15) == 0, "tgs_select_kth_largest: workspace must be 16-byte aligned");
+static int32_t select_kth(const float* values, int64_t n, const int64_t* k, int32_t n_k, float* out, void* ws,
+                          size_t ws_bytes, void* stream, const char* who) {
+  TGS_REQUIRE(n > 0 && n < (1ll << 31), "%s: n %lld out of range", who, (long long)n);
+  for (int t = 0; t < n_k; ++t)
+    TGS_REQUIRE(k[t] >= 1 && k[t] <= n, "%s: k %lld not in [1, %lld]", who, (long long)k[t], (long long)n);
+  TGS_REQUIRE(values && out && ws, "%s: null pointer", who);
+  TGS_REQUIRE(ws_bytes >= sizeof(SelectState), "%s: workspace %zu bytes < %zu", who, ws_bytes, sizeof(SelectState));
+  TGS_REQUIRE(((uintptr_t)ws & 15) == 0, "%s: workspace must be 16-byte aligned", who);
   hipStream_t s = as_stream(stream);
   SelectState* st = (SelectState*)ws;
-  const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(n, (int64_t)256 * 8), 2048);
-  hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, s, st, (uint32_t)k);
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(select_hist_kernel, dim3(grid), dim3(256), 0, s, values, n, shift, st);
-    hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(256), 0, s, shift, st, out);
-  }
-  return hip_status("tgs_select_kth_largest");
+  const dim3 grid((unsigned)std::min<int64_t>(ceil_div(n, (int64_t)kSelThreads * 4), 512)), block(kSelThreads);
+  hipLaunchKernelGGL(select_init_kernel, dim3(12), block, 0, s, st, (uint32_t)k[0], (uint32_t)k[n_k - 1]);
+  hipLaunchKernelGGL(select_hist_kernel<0>, grid, block, 0, s, values, n, (int)n_k, st);
+  hipLaunchKernelGGL(select_hist_kernel<1>, grid, block, 0, s, values, n, (int)n_k, st);
+  hipLaunchKernelGGL(select_hist_kernel<2>, grid, block, 0, s, values, n, (int)n_k, st);
+  hipLaunchKernelGGL(select_out_kernel, dim3(1), block, 0, s, (int)n_k, st, out);
+  return hip_status(who);
+}
+
+extern "C" int32_t tgs_select_kth_largest(const float* values, int64_t n, int64_t k, float* out, void* ws,
+                                          size_t ws_bytes, void* stream) {
+  return select_kth(values, n, &k, 1, out, ws, ws_bytes, stream, "tgs_select_kth_largest");
+}
+
+extern "C" int32_t tgs_select_kth_largest2(const float* values, int64_t n, int64_t k0, int64_t k1, float* out,
+                                           void* ws, size_t ws_bytes, void* stream) {
+  const int64_t k[2] = {k0, k1};
+  return select_kth(values, n, k, 2, out, ws, ws_bytes, stream, "tgs_select_kth_largest2");
 }
 
 extern "C" int32_t tgs_threshold_mask(const float* values, int64_t n, const float* thr, uint8_t* mask,

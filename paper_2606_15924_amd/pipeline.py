@@ -927,9 +927,8 @@ class Trainer:
             self._select_ws = torch.empty(B.tgs_select_workspace_size(), dtype=torch.uint8, device=self.dev)
         thr = torch.empty(2, dtype=torch.float32, device=self.dev)
         masks = torch.empty((2, self.n), dtype=torch.uint8, device=self.dev)
-        for j, frac in enumerate((1.0 - eta_topk, eta_final)):
-            k = max(1, math.ceil(frac * self.n - 1e-9))
-            B.tgs_select_kth_largest(sc, self.n, k, thr[j:j + 1], self._select_ws)
+        k0, k1 = (max(1, math.ceil(frac * self.n - 1e-9)) for frac in (1.0 - eta_topk, eta_final))
+        B.tgs_select_kth_largest2(sc, self.n, k0, k1, thr, self._select_ws)
         if tau_grad is None:
             # ungated: the two percentile masks alone
             B.tgs_threshold_mask(sc, self.n, thr[0:1], masks[0])
