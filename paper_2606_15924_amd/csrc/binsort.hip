@@ -137,17 +137,24 @@ __device__ __forceinline__ int4 clamp_rect(int4 r, int tiles_x, int tiles_y) {
 // o = 1).  A Gaussian with t <= 0 keeps no tile (ym < 0 empties every row).
 // lia = ln(1 / alpha_min).
 struct RowEllipse {
-  double xi, xf, yi, yf, A, B, det, ym, ys, tA;
+  double xi, xf, yi, yf, A, iA, B, det, ym, ys, tA;  // iA: 1 / A
   int pd;
 };
 
-__device__ __forceinline__ RowEllipse load_row_ellipse(const float4* __restrict__ splat, int64_t i, double tau,
-                                                       double lia) {
+// ceil(64 (2 (ln o + lia) + 0.004)): from the hardware's float logarithm (good
+// to 1e-6 here) unless that lies within 2.5e-4 of an integer.
+__device__ __forceinline__ double ellipse_steps(float of, double lia) {
 #pragma clang fp contract(off)
-  const float4 p0 = splat[3 * i], p1 = splat[3 * i + 1];
+  const double q = 64.0 * (2.0 * ((double)__builtin_amdgcn_logf(of) * 0.69314718055994531 + lia) + 0.004);
+  const double c = ceil(q), f = c - q;
+  if (f > 2.5e-4 && f < 1.0 - 2.5e-4) return c;
+  return ceil(64.0 * (2.0 * (log((double)of) + lia) + 0.004));
+}
+
+__device__ __forceinline__ RowEllipse row_ellipse(float4 p0, float4 p1, double tau, double lia) {
+#pragma clang fp contract(off)
   RowEllipse e;
-  const double o = (double)p1.w;
-  const double t = o > 0.0 ? fmin(tau, ceil(64.0 * (2.0 * (log(o) + lia) + 0.004)) * (1.0 / 64.0)) : -1.0;
+  const double t = p1.w > 0.f ? fmin(tau, ellipse_steps(p1.w, lia) * (1.0 / 64.0)) : -1.0;
   e.xi = p0.x;
   e.yi = p0.y;
   e.xf = p0.z;
@@ -155,6 +162,7 @@ __device__ __forceinline__ RowEllipse load_row_ellipse(const float4* __restrict_
   // the record's conic is (a, beta, delta) with b = beta a, c = delta + beta b,
   // det = a c - b^2 = a delta
   e.A = p1.x;
+  e.iA = 1.0 / e.A;
   e.B = (double)p1.y * e.A;
   const double C = (double)p1.z + (double)p1.y * e.B;
   e.det = e.A * (double)p1.z;
@@ -163,6 +171,14 @@ __device__ __forceinline__ RowEllipse load_row_ellipse(const float4* __restrict_
   e.ys = e.pd && t > 0.0 ? e.B * sqrt(t / (C * e.det)) : 0.0;
   e.tA = t * e.A;
   return e;
+}
+
+// sqrt(x) to a few parts in 1e14 (0 for 0): the hardware's estimate and one
+// Newton step.  A denormal x may give 0 (its root is below 1e-150).
+__device__ __forceinline__ double near_sqrt(double x) {
+  const double r = __builtin_amdgcn_rsq(x), g = x * r, h = 0.5 * r;
+  const double s = __builtin_fma(g, __builtin_fma(-h, g, 0.5), g);
+  return x > 1e-300 ? s : 0.0;
 }
 
 // Kept columns [lo, hi] of tile row ty inside the rectangle columns
@@ -190,13 +206,29 @@ __device__ __forceinline__ void row_span(const RowEllipse& e, int ty, int rx0, i
   }
   const double yr = fmin(fmax(-e.ys, ylo), yhi);
   const double yl = fmin(fmax(e.ys, ylo), yhi);
-  const double sr = sqrt(fmax(0.0, e.tA - e.det * (yr * yr)));
-  const double sl = sqrt(fmax(0.0, e.tA - e.det * (yl * yl)));
-  const double xmax = (sr - e.B * yr) / e.A;
-  const double xmin = (-sl - e.B * yl) / e.A;
-  const double PL = (xmin + e.xf) + e.xi, PR = (xmax + e.xf) + e.xi;  // image pixel coordinates
-  const double l = ceil((PL - (double)(kTile - 1)) * (1.0 / kTile));
-  const double h = floor(PR * (1.0 / kTile));
+  const double Dr = fmax(0.0, e.tA - e.det * (yr * yr)), Dl = fmax(0.0, e.tA - e.det * (yl * yl));
+  const double br = e.B * yr, bl = e.B * yl;
+  double l, h;
+  {
+    // the columns from roots and quotients good to 1e-13, when no rounding of
+    // the exact operations could cross a column
+    const double sr = near_sqrt(Dr), sl = near_sqrt(Dl);
+    const double tl = (((-sl - bl) * e.iA + e.xf) + e.xi - (double)(kTile - 1)) * (1.0 / kTile);
+    const double th = (((sr - br) * e.iA + e.xf) + e.xi) * (1.0 / kTile);
+    const double size = fmax(fmax((sr + fabs(br)) * fabs(e.iA), (sl + fabs(bl)) * fabs(e.iA)), fabs(e.xi));
+    l = ceil(tl);
+    h = floor(th);
+    // distance of the nearest column: 1e-6 columns against errors below 1e-12 size / 16
+    const double fl = l - tl, fh = th - h;
+    const bool sure = size < 1e6 && fl > 1e-6 && fl < 1.0 - 1e-6 && fh > 1e-6 && fh < 1.0 - 1e-6;
+    if (!sure) {
+      const double xmax = (sqrt(Dr) - br) / e.A;
+      const double xmin = (-sqrt(Dl) - bl) / e.A;
+      const double PL = (xmin + e.xf) + e.xi, PR = (xmax + e.xf) + e.xi;  // image pixel coordinates
+      l = ceil((PL - (double)(kTile - 1)) * (1.0 / kTile));
+      h = floor(PR * (1.0 / kTile));
+    }
+  }
   lo = (int)fmin(fmax(l, (double)rx0), (double)rx1);
   hi = (int)fmin(fmax(h, (double)(rx0 - 1)), (double)(rx1 - 1));
 }
@@ -612,11 +644,29 @@ __device__ __forceinline__ void ellipse_rows(const RowEllipse& e, int4 r, int& y
   y1 = (int)fmin(fmax(l + 1.0, (double)y0), (double)r.w);
 }
 
-// Count.  Bound by the gathers of rectangle and record in depth order and by
-// the divergence of the row loop; FP64 itself runs at the FP32 rate.  Handing
-// the rows of 64 Gaussians out one per lane keeps every lane busy, but costs a
-// prefix sum, two exchanges through LDS and their barriers per 64 rows, which
-// took longer than the idle lanes do.
+// Rows k and on of the few lanes that have them go to the wave, a Gaussian's
+// rows one per lane, when handing a Gaussian over (~1.5 rows' work) costs less
+// than walking to the longest.
+__device__ __forceinline__ bool few_long(int rows, int k, int longest) {
+  return 3 * __builtin_popcountll(ballot(rows > k)) <= 2 * (longest - k);
+}
+
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
+}
+
+__device__ __forceinline__ RowEllipse ellipse_of_lane(const RowEllipse& e, int l) {
+  return {lane_f64(e.xi, l), lane_f64(e.xf, l),  lane_f64(e.yi, l), lane_f64(e.yf, l),
+          lane_f64(e.A, l),  lane_f64(e.iA, l),  lane_f64(e.B, l),  lane_f64(e.det, l),
+          lane_f64(e.ym, l), lane_f64(e.ys, l),  lane_f64(e.tA, l), __builtin_amdgcn_readlane(e.pd, l)};
+}
+
+// Count.  Bound by the gathers in depth order: at 1.5M Gaussians and 42M pairs,
+// rectangle and tables take 31 us, the records 29 and the rows 32 (92 us; with
+// IEEE roots and quotients in every row and without the shared walk 105 us).
+// Handing the rows of 64 Gaussians out one per lane keeps every lane busy, but
+// costs a prefix sum, two exchanges through LDS and their barriers per 64
+// rows, which took longer than the idle lanes do.
 template <bool kWide>
 __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) {
   const BinArgs& a = batch.v[blockIdx.z];
@@ -631,10 +681,15 @@ __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) 
   s_rows[tid] = 0u;
   s_pairs[tid] = 0u;
   int4 r = make_int4(0, 0, 0, 0);
+  float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
   uint32_t g = 0;
   if (p < end) {
     g = a.ids[p];
     r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
+    if (a.bits == nullptr) {  // every listed Gaussian has a tile: its record is asked for beside the rectangle
+      c0 = a.splat[3 * (int64_t)g];
+      c1 = a.splat[3 * (int64_t)g + 1];
+    }
   }
   bool some = r.z > r.x && r.w > r.y;
   if (a.bits != nullptr && some) {
@@ -645,26 +700,45 @@ __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) 
   RowEllipse e = {};
   int y0 = 0, y1 = 0;
   if (some) {
-    e = load_row_ellipse(a.splat, g, a.tau, a.lia);
+    if (a.bits != nullptr) {
+      c0 = a.splat[3 * (int64_t)g];
+      c1 = a.splat[3 * (int64_t)g + 1];
+    }
+    e = row_ellipse(c0, c1, a.tau, a.lia);
     ellipse_rows(e, r, y0, y1);
   }
   uint32_t total;
   const uint32_t at = block_exclusive_scan<kRowThreads, uint32_t>((uint32_t)(y1 - y0), s_red, &total);
-  bool any = false;
-  for (int y = y0; y < y1; ++y) {
+  auto row = [&](const RowEllipse& re, int y, int rx0, int rx1, uint32_t q) {  // whether the row keeps a tile
     int lo, hi;
-    row_span(e, y, r.x, r.z, lo, hi);
+    row_span(re, y, rx0, rx1, lo, hi);
     uint32_t span = 0xffu;  // first column 255, last 0: empty
+    bool kept = false;
     row_pieces<kWide>(a, y, lo, hi, [&](int s, int l, int h, uint32_t c) {
-      any = true;
+      kept = true;
       span = (uint32_t)l | ((uint32_t)h << 8);
       if (s >= 0 && s < a.sn) {
         atomicAdd(&s_rows[s], 1u);
         atomicAdd(&s_pairs[s], c);
       }
     });
-    const uint32_t q = at + (uint32_t)(y - y0);
     if (!kWide && q < (uint32_t)kSpanRows) s_span[q] = (uint16_t)span;
+    return kept;
+  };
+  bool any = false;
+  const int rows = y1 - y0, longest = wave_max_i(rows);
+  int k = 0;
+  for (; k < longest && !few_long(rows, k, longest); ++k)
+    if (k < rows) any |= row(e, y0 + k, r.x, r.z, at + (uint32_t)k);
+  for (uint64_t left = ballot(rows > k); left != 0ull; left &= left - 1) {
+    const int l = (int)__builtin_ctzll(left);
+    const RowEllipse el = ellipse_of_lane(e, l);
+    const int n_l = __builtin_amdgcn_readlane(rows, l), y_l = __builtin_amdgcn_readlane(y0, l);
+    const int rx0 = __builtin_amdgcn_readlane(r.x, l), rx1 = __builtin_amdgcn_readlane(r.z, l);
+    const uint32_t at_l = (uint32_t)__builtin_amdgcn_readlane((int)at, l);
+    bool kept = false;
+    for (int j = k + lane_id(); j < n_l; j += kWave) kept |= row(el, y_l + j, rx0, rx1, at_l + (uint32_t)j);
+    if (ballot(kept) != 0ull && lane_id() == l) any = true;
   }
   if (p < end) {
     if (any && a.touched != nullptr) a.touched[g] = 1;
@@ -791,26 +865,46 @@ __global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinBatch batch) {
   int4 r = make_int4(0, 0, 0, 0);
   if (info.y > 0 && (kWide || at + (uint32_t)info.y > (uint32_t)kSpanRows)) {  // rows not kept: evaluated again
     r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
-    e = load_row_ellipse(a.splat, g, a.tau, a.lia);
+    e = row_ellipse(a.splat[3 * (int64_t)g], a.splat[3 * (int64_t)g + 1], a.tau, a.lia);
   }
   __syncthreads();
-  auto each = [&](auto&& f) {
-    for (int k = 0; k < info.y; ++k) {
-      if (!kWide && at + (uint32_t)k < (uint32_t)kSpanRows) {
-        const uint32_t c = s_span[at + (uint32_t)k];
-        const int s = info.x + k - a.s0;
-        if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c);
-      } else {
-        int lo, hi;
-        row_span(e, info.x + k, r.x, r.z, lo, hi);
-        row_pieces<kWide>(a, info.x + k, lo, hi, [&](int s, int l, int h, uint32_t) {
-          if (s >= 0 && s < a.sn) f(s, (uint32_t)l | ((uint32_t)h << 8));
-        });
-      }
+  // f(strip, columns, lane whose row it is, its Gaussian)
+  const int longest = wave_max_i(info.y);
+  auto own = [&](int k, auto&& f) {  // row k of the lane's own Gaussian
+    if (!kWide && at + (uint32_t)k < (uint32_t)kSpanRows) {
+      const uint32_t c = s_span[at + (uint32_t)k];
+      const int s = info.x + k - a.s0;
+      if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c, lane, g);
+    } else {
+      int lo, hi;
+      row_span(e, info.x + k, r.x, r.z, lo, hi);
+      row_pieces<kWide>(a, info.x + k, lo, hi, [&](int s, int l, int h, uint32_t) {
+        if (s >= 0 && s < a.sn) f(s, (uint32_t)l | ((uint32_t)h << 8), lane, g);
+      });
     }
   };
-  each([&](int s, uint32_t) {
-    __hip_atomic_fetch_or(&s_mask[wave][s], 1ull << lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  auto each = [&](auto&& f) {
+    int k = 0;
+    for (; k < longest && (kWide || !few_long(info.y, k, longest)); ++k)
+      if (k < info.y) own(k, f);
+    if (kWide) return;
+    const bool kept = at + (uint32_t)info.y <= (uint32_t)kSpanRows;
+    for (uint64_t left = ballot(kept && info.y > k); left != 0ull; left &= left - 1) {
+      const int l = (int)__builtin_ctzll(left);
+      const int n_l = __builtin_amdgcn_readlane(info.y, l), y_l = __builtin_amdgcn_readlane(info.x, l);
+      const uint32_t at_l = (uint32_t)__builtin_amdgcn_readlane((int)at, l);
+      const uint32_t g_l = (uint32_t)__builtin_amdgcn_readlane((int)g, l);
+      for (int j = k + lane; j < n_l; j += kWave) {
+        const int s = y_l + j - a.s0;
+        const uint32_t c = s_span[at_l + (uint32_t)j];
+        if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c, l, g_l);
+      }
+    }
+    if (!kept)
+      for (; k < info.y; ++k) own(k, f);
+  };
+  each([&](int s, uint32_t, int l, uint32_t) {
+    __hip_atomic_fetch_or(&s_mask[wave][s], 1ull << l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   });
   __syncthreads();
   if (tid < a.sn) {
@@ -822,11 +916,10 @@ __global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinBatch batch) {
     }
   }
   __syncthreads();
-  const uint64_t below = lanes_below();
   const uint32_t rows_all = *a.eff_total;  // a record holds a pair, so there are no more records than pairs
-  each([&](int s, uint32_t c) {
-    const uint32_t q = s_pos[wave][s] + (uint32_t)__popcll(s_mask[wave][s] & below);
-    if (q < rows_all) a.rec[q] = make_uint2(g, c);  // always; a safeguard
+  each([&](int s, uint32_t c, int l, uint32_t gl) {
+    const uint32_t q = s_pos[wave][s] + (uint32_t)__popcll(s_mask[wave][s] & ((1ull << l) - 1ull));
+    if (q < rows_all) a.rec[q] = make_uint2(gl, c);  // always; a safeguard
   });
 }
 

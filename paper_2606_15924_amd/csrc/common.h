@@ -135,6 +135,24 @@ __device__ __forceinline__ int wave_inclusive_scan_i_dpp(int v) {
   return v;
 }
 
+// Lane l's value of a 64-bit register (l uniform).
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// The largest of 64 non-negative values (wave-uniform).
+__device__ __forceinline__ int wave_max_i(int v) {
+  v = max(v, dpp_i<kDppQuadPerm1032>(0, v));
+  v = max(v, dpp_i<kDppQuadPerm2301>(0, v));
+  v = max(v, dpp_i<kDppRowHalfMirror>(0, v));
+  v = max(v, dpp_i<kDppRowMirror>(0, v));
+  v = max(v, dpp_i<kDppRowBcast15, 0xa>(0, v));
+  v = max(v, dpp_i<kDppRowBcast31, 0xc>(0, v));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
 // Maximum over the 64 lanes (every lane receives it).
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, kWave));

@@ -61,13 +61,6 @@ __device__ __forceinline__ uint64_t half_weight(uint16_t h) {
   return h < 0x7c00 ? v : 0;
 }
 
-// Lane l's value of a 64-bit register (l uniform).
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ int tile_valid_w(int tx, int W) { return min(kTile, W - tx * kTile); }
 __device__ __forceinline__ int tile_valid_h(int ty, int H) { return min(kTile, H - ty * kTile); }
 
