@@ -273,6 +273,17 @@ int32_t tgs_bin_sort_async(const int32_t* rect, const float* splat, const float*
                            uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges,
                            uint8_t* touched, int64_t* counts, void* ws, size_t ws_bytes, void* stream);
 
+/* The lists of a tgs_bin_sort_async call that did not fit its capacity,
+ * without its depth order and counts being made again: the same arguments
+ * (touched is not written again) and unchanged inputs, with larger vals,
+ * keys and ws, and that call's workspace ws1 (ws1_bytes, its capacity1),
+ * which is read and written.  Results as of tgs_bin_sort_async. */
+int32_t tgs_bin_sort_resume_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,
+                                  const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,
+                                  const void* ws1, size_t ws1_bytes, int64_t capacity1, uint64_t* keys,
+                                  uint32_t* vals, int64_t capacity, uint32_t* ranges, uint8_t* touched,
+                                  int64_t* counts, void* ws, size_t ws_bytes, void* stream);
+
 /* Depth-prefix lists (an exact shortcut for the forward walk's early
  * stop): the lists of tgs_bin_sort_async restricted to the first `prefix`
  * Gaussians in (depth, id) order (Gaussians with a non-empty rectangle,

@@ -104,6 +104,8 @@ PROTOTYPES = {
     "tgs_loss_views": (_I32, [_P, _I32, _P, ctypes.POINTER(tgs_loss_params), _P]),
     "tgs_ema_age_update_views": (_I32, [_P, _I32, ctypes.c_float, _P]),
     "tgs_render_bwd_views": (_I32, [_P, _I32, ctypes.POINTER(tgs_raster_params), _P, _I64, _P, _P]),
+    "tgs_bin_sort_resume_async": (_I32, [_P, _P, _P, _I64, _P, _I32, _I32, ctypes.c_float, _P, _SZ, _I64, _P, _P, _I64,
+                                         _P, _P, _P, _P, _SZ, _P]),
     "tgs_bin_sort_views_async": (_I32, [_P, _I32, _I64, ctypes.c_float, _I64, _P]),
     "tgs_bin_sort_continue_async": (_I32, [_P, _I64, _P, _P, _I32, _I32, ctypes.c_float, _I64, _I64, _P, _SZ, _P,
                                            _I64, _P, _P, _P, _SZ, _P]),
@@ -386,6 +388,16 @@ def tgs_bin_sort_async(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha
                                     float(alpha_min), _ptr(keys), _ptr(vals), capacity, _ptr(ranges), _ptr(touched),
                                     _ptr(counts), _ptr(ws), ws.numel() * ws.element_size(), _stream()),
            "tgs_bin_sort_async")
+
+
+def tgs_bin_sort_resume_async(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, ws1, capacity1, keys, vals,
+                              capacity, ranges, touched, counts, ws):
+    """The lists of a tgs_bin_sort_async call that did not fit (its workspace
+    ws1 and capacity1) into larger arrays."""
+    _check(lib().tgs_bin_sort_resume_async(_ptr(rect), _ptr(splat), _ptr(depth), n, _ptr(tile_slot), tiles_x, tiles_y,
+                                           alpha_min, _ptr(ws1), ws1.numel(), capacity1, _ptr(keys), _ptr(vals),
+                                           capacity, _ptr(ranges), _ptr(touched), _ptr(counts), _ptr(ws), ws.numel(),
+                                           _stream()), "tgs_bin_sort_resume_async")
 
 
 def tgs_bin_sort_prefix_async(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, prefix, keys, vals,

@@ -592,6 +592,7 @@ struct BinArgs {
   int64_t m, capacity;        // m >= 0: a depth-prefix call over m positions
   unsigned long long* counts; // the call's counts in its workspace
   unsigned long long* out;    // nullable: the caller's
+  bool counted;               // the tables hold the counts (of one group of strips)
 };
 using BinBatch = Batch<BinArgs>;
 
@@ -1292,8 +1293,10 @@ static void list_pairs(BinBatch& b, int views, hipStream_t s) {
     if (kb > 0) hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads), 0, s, b);
     hipLaunchKernelGGL(strip_scan_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
   };
-  if (subset) hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)rows, 1, nv), dim3(kWave), 0, s, b);
-  for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
+  if (subset && !b.v[0].counted)
+    hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)rows, 1, nv), dim3(kWave), 0, s, b);
+  const bool counted = b.v[0].counted;  // a view's lists resumed, alone in its batch
+  for (int64_t s0 = 0; s0 < strips && !counted; s0 += kGroup) {
     group(s0);
     count();
   }
@@ -1440,6 +1443,27 @@ static int32_t bin_sort_one(const int32_t* rect, const float* splat, const float
   return bin_sort_queue(d, b, 1, n, s, who);
 }
 
+// A call that did not fit its capacity, taken up again with larger arrays: the
+// depth order, the tile bits and the counts are in its workspace w1 (whose
+// layout holds the arrays that grow with the capacity last), so the records
+// and lists are all that is left: an autograd pass over 300k Gaussians, whose
+// first capacity is too small, 658 us with the whole call repeated, 550 so.
+static void resume_view(BinArgs& a, const SortWs& w1) {
+  a.counted = true;
+  a.ids = w1.ids_sorted;
+  a.n_keyed = w1.n_keyed;
+  a.bits = a.tile_slot != nullptr ? w1.bits : nullptr;
+  a.rows_tab = w1.rows_tab;
+  a.pairs_tab = w1.pairs_tab;
+  a.spans = w1.spans;
+  a.rowinfo = w1.rowinfo;
+  a.row_tot = w1.row_tot;
+  a.pair_tot = w1.pair_tot;
+  a.row_base = w1.row_base;
+  a.pair_base = w1.pair_base;
+  a.blk_base = w1.blk_base;
+}
+
 // The continuation of depth-prefix lists: the pairs of the Gaussians from
 // depth rank `prefix` on in the flagged tiles, from the depth order and the
 // rectangles that the prefix call left in its workspace w1, with the tables
@@ -1490,6 +1514,35 @@ extern "C" int32_t tgs_bin_sort_async(const int32_t* rect, const float* splat, c
               "tgs_bin_sort_async: counts must be an 8-byte aligned device pointer");
   return bin_sort_one(rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity, ranges,
                       touched, w, as_stream(stream), "tgs_bin_sort_async", (unsigned long long*)counts);
+}
+
+extern "C" int32_t tgs_bin_sort_resume_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,
+                                             const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y,
+                                             float alpha_min, const void* ws1, size_t ws1_bytes, int64_t capacity1,
+                                             uint64_t* keys, uint32_t* vals, int64_t capacity, uint32_t* ranges,
+                                             uint8_t* touched, int64_t* counts, void* ws, size_t ws_bytes,
+                                             void* stream) {
+  const char* who = "tgs_bin_sort_resume_async";
+  const int64_t n_t = grid_tiles(tiles_x, tiles_y);
+  const SortWs w = layout(ws, n, capacity, n_t);
+  if (int32_t e = bin_sort_check(rect, splat, depth, n, tiles_x, tiles_y, alpha_min, vals, capacity, ranges, ws,
+                                 ws_bytes, w, who))
+    return e;
+  TGS_REQUIRE(counts != nullptr && ((uintptr_t)counts & 7) == 0, "%s: counts must be an 8-byte aligned device pointer",
+              who);
+  TGS_REQUIRE(ws1 != nullptr && ((uintptr_t)ws1 & 15) == 0 && ws1 != ws && capacity1 >= 0 && capacity1 < (1ll << 32),
+              "%s: bad first workspace", who);
+  const SortWs w1 = layout((void*)ws1, n, capacity1, n_t);
+  TGS_REQUIRE(ws1_bytes >= w1.bytes, "%s: first workspace %zu bytes < %zu", who, ws1_bytes, w1.bytes);
+  DepthBatch d{};
+  BinBatch b{};
+  bin_sort_view(d.v[0], b.v[0], rect, splat, depth, n, tile_slot, tiles_x, tiles_y, alpha_min, keys, vals, capacity,
+                ranges, touched, w, (unsigned long long*)counts, -1);
+  resume_view(b.v[0], w1);
+  // more strips than one group: their tables were overwritten group by group
+  if (b.v[0].sc > 1 || strips_of(b.v[0]) > kGroup) b.v[0].counted = false;
+  list_all(b, 1, as_stream(stream));
+  return hip_status(who);
 }
 
 extern "C" int32_t tgs_bin_sort_prefix_async(const int32_t* rect, const float* splat, const float* depth, int64_t n,

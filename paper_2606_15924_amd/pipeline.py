@@ -180,14 +180,20 @@ class ViewBuffers:
     def bin_sort(self, touched=None, alpha_min: float = 1.0 / 255.0) -> int:
         """Bin and sort, waiting for the count: grows the pair arrays and
         repeats when they are too small.  Returns the list length."""
+        self.bin_sort_async(touched, alpha_min)
         while True:
-            self.bin_sort_async(touched, alpha_min)
             valid, need = (int(x) for x in self.counts[:2].cpu().tolist())
             if need <= self.capacity:
                 self.n_pairs = valid
                 self.sized = True
                 return valid
+            ws1, capacity1 = self.sort_ws, self.capacity
             self._alloc_pairs(int(need * 1.5) + 1024)
+            # the depth order and the counts are there: the lists alone
+            tile_slot = self.tile_slot if self.bin_sort_needs_samples() else None
+            B.tgs_bin_sort_resume_async(self.rect, self.splat, self.depth, self.n, tile_slot, self.tiles_x,
+                                        self.tiles_y, alpha_min, ws1, capacity1, self.keys, self.vals, self.capacity,
+                                        self.ranges, touched, self.counts, self.sort_ws)
 
     def bin_sort_async(self, touched=None, alpha_min: float = 1.0 / 255.0):
         """Bin and sort without a host wait (tgs_bin_sort_async); the counts
