@@ -37,7 +37,7 @@ class SparseRasterize(torch.autograd.Function):
         rp = rp if rp is not None else B.raster_params()
         n = params.shape[1]
         params = params.contiguous()
-        vb = ViewBuffers(n, cam.width, cam.height, None, -1, params.device)
+        vb = ViewBuffers(n, cam.width, cam.height, None, -1, params.device, supervised=False)
         if samples.valid_tiles is not None:
             vb.dense = False
             vb.valid_tiles, vb.tile_off, vb.pix = samples.valid_tiles, samples.tile_off, samples.pix
@@ -62,7 +62,7 @@ class SparseRasterize(torch.autograd.Function):
             return vb.out64[: vb.P, :3].clone()
         if params.dtype != torch.float32:
             raise TypeError("SparseRasterize: parameters must be float32 or float64")
-        vb.project(params, c, rp)
+        vb.project(params, c, rp, clear=False)   # render_bwd clears its gradient
         vb.bin_sort(alpha_min=rp.alpha_min)
         vb.render_fwd(rp)
         return vb.out[: vb.P, :3].clone()

@@ -72,7 +72,7 @@ class ViewBuffers:
 
     def __init__(self, n: int, width: int, height: int, n_pix: int | None, n_tiles_sel: int,
                  device, capacity: int | None = None, keep_keys: bool = False,
-                 counts: torch.Tensor | None = None):
+                 counts: torch.Tensor | None = None, supervised: bool = True):
         self.n, self.width, self.height = n, width, height
         self.keep_keys = keep_keys
         self.tiles_x, self.tiles_y = (width + TILE - 1) // TILE, (height + TILE - 1) // TILE
@@ -102,10 +102,11 @@ class ViewBuffers:
         self.ranges = torch.empty((self.n_t, 2), dtype=torch.int32, device=dev)
         self.out = torch.empty((max(self.P_cap, 1), 4), dtype=torch.float32, device=dev)
         self.ncontrib = torch.empty(max(self.P_cap, 1), dtype=torch.int32, device=dev)
-        self.dL = torch.zeros((max(self.P_cap, 1), 4), dtype=torch.float32, device=dev)
-        self.err = torch.empty(max(self.P_cap, 1), dtype=torch.float32, device=dev)
-        self.lam = torch.empty(max(self.n_st, 1), dtype=torch.float32, device=dev)
-        self.tile_loss = torch.zeros((max(self.n_st, 1), 2), dtype=torch.float32, device=dev)
+        if supervised:   # what the loss writes; a caller with a gradient of its own needs none of it
+            self.dL = torch.zeros((max(self.P_cap, 1), 4), dtype=torch.float32, device=dev)
+            self.err = torch.empty(max(self.P_cap, 1), dtype=torch.float32, device=dev)
+            self.lam = torch.empty(max(self.n_st, 1), dtype=torch.float32, device=dev)
+            self.tile_loss = torch.zeros((max(self.n_st, 1), 2), dtype=torch.float32, device=dev)
         self.g2d = torch.empty((n, B.G2D_FLOATS), dtype=torch.float32, device=dev)
         # per-pixel (T, colour) at the backward's chunk starts, kept by the forward
         n_state = B.tgs_render_state_size(self.n_st, self.n_pix) // 4
@@ -168,10 +169,11 @@ class ViewBuffers:
         B.tgs_sample(E, A, self.height, self.width, sp, self.valid_tiles, self.tile_off, self.pix,
                      self.tile_slot, totals, self.sample_ws, tile_pred=tile_pred)
 
-    def project(self, params, cam: B.tgs_camera, rp):
-        # also clears the screen-space gradient that the backward accumulates into
+    def project(self, params, cam: B.tgs_camera, rp, clear: bool = True):
+        # also clears the screen-space gradient that the backward accumulates
+        # into, unless that clears it itself
         B.tgs_project(params, self.n, cam, rp, self.splat, self.depth, self.radius, self.rect, self.clamp,
-                      self.g2d)
+                      self.g2d if clear else None)
 
     def bin_sort_needs_samples(self) -> bool:
         """Binning reads the tile map only when the sampler keeps a subset of tiles."""
