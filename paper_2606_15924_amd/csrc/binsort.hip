@@ -32,8 +32,8 @@
 // Sorting row records instead of pairs moves 8 bytes per 4-5 pairs through
 // the partition and writes each pair once; the pair-wise form (emit keys, two
 // radix passes with their histograms, find the tile boundaries) moved every
-// pair six times.  300k Gaussians, 1296 x 840, 5.7M pairs: 216 -> 159 us; 1.5M
-// Gaussians, 1600 x 1060, 42M pairs: 745 -> 461 us.
+// pair six times.  300k Gaussians, 1296 x 840, 5.7M pairs: 216 -> 155 us; 1.5M
+// Gaussians, 1600 x 1060, 42M pairs: 745 -> 450 us.
 #include <algorithm>
 #include <climits>
 #include <cmath>

@@ -94,18 +94,7 @@ __device__ __forceinline__ int mask_rank(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Inclusive prefix sum over the wave (Hillis-Steele with shuffles).
-__device__ __forceinline__ uint64_t wave_inclusive_scan_u64(uint64_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint64_t t = __shfl_up(v, o, kWave);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
-// The same scan on DPP alone: rows of 16 by shifts of 1, 2, 4 and 8 lanes,
+// Inclusive scan over the wave on DPP alone: rows of 16 by shifts of 1, 2, 4 and 8 lanes,
 // then the row totals chained by the row broadcasts of lanes 15 and 31.  A
 // lane whose DPP source lies before its row (or in a masked row) reads 0.
 template <int Ctrl, int RowMask = 0xf>
@@ -151,32 +140,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
   v = max(v, dpp_i<kDppRowBcast15, 0xa>(0, v));
   v = max(v, dpp_i<kDppRowBcast31, 0xc>(0, v));
   return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Maximum over the 64 lanes (every lane receives it).
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-  return v;
-}
-
-__device__ __forceinline__ uint32_t wave_inclusive_scan_u32(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, kWave);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
-__device__ __forceinline__ int wave_inclusive_scan_i(int v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    int t = __shfl_up(v, o, kWave);
-    if (lane >= o) v += t;
-  }
-  return v;
 }
 
 }  // namespace tgs
