@@ -132,6 +132,9 @@ def test_maps_shared_by_two_views_are_refused(B):
 @pytest.mark.parametrize("views,kw", [([0, 1, 2], {}), ([0, 1, 0], {}), ([2, 1], {"density_stats": True}),
                                       ([0, 1, 2, 3, 4], {"n_tiles_sel": 20}), ([0, 2, 1], {"rate_permille": None}),
                                       ([1, 0], {"deterministic": True}),
+                                      ([0, 1, 2], {"prefix_fraction": 0.2}),
+                                      ([2, 0, 1, 2], {"prefix_fraction": 0.05, "n_tiles_sel": 11}),
+                                      ([1, 2, 0], {"fuse_optimizer": False, "density_stats": True}),
                                       ([0, 3, 0], {"n_tiles_sel": 9, "learned_tiles": True})])
 def test_second_step_equals_views_in_turn(B, views, kw):
     """The second step of a slot runs its views together on one stream; with
@@ -150,7 +153,7 @@ def test_second_step_equals_views_in_turn(B, views, kw):
         E = [dev(synth.error_map(h, w, 60 + k).view(np.int16)) for k, (w, h) in enumerate(sizes)]
         A = [dev(synth.age_map(h, w, 70 + k).view(np.int16)) for k, (w, h) in enumerate(sizes)]
         tr = Trainer(dev(p.copy()), cams, gts, StepConfig(**{"rate_permille": 250, "view_streams": streams,
-                                                             "fuse_views": streams == 1, **kw}), E=E, A=A)
+                                                             "fuse_views": streams == 1 and kw.get("fuse_optimizer", True), **kw}), E=E, A=A)
         for _ in range(2):
             used = tr.step(views)
         torch.cuda.synchronize()
