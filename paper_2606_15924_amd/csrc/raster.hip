@@ -367,27 +367,25 @@ struct DensityArgs {
 // the pixel's offset from the centre, every gradient of the Gaussian is a
 // moment of q or w over the pixels: sum q, sum q d, sum q d d^T and sum w g
 // (g = dL/d colour of the pixel).  Summing nine values across a wave with
-// lane swaps and DPP adds took ~40 of the ~83 vector instructions of a
-// (Gaussian, wave) step, and the walk is bound by vector issue, so the sums
-// run on the matrix cores instead: for four Gaussians at a time, matrices of 4
-// Gaussians x 64 pixels (q dx, q dy, q and w) times 64 pixels x 4 columns (1,
-// x, y; or the colour gradients), as v_mfma_f32_4x4x1 (16 blocks, one pixel
-// per block and instruction, FP32 products and sums).  The x, y columns are
-// relative to the tile's centre, the same for every Gaussian; the offset of
-// the Gaussian's centre is taken off afterwards (sum q dx dx = sum (q dx) x -
-// cx sum q dx): one factor of each product is formed per pixel, so only the
-// linear shift is subtracted from a sum.  Going from a lane per pixel to the
-// matrix operand (a lane per Gaussian and block) is a transposition through
-// LDS private to the wave, whose LDS operations execute in order.  The 16
-// blocks' partial sums are folded with lane swaps and row rotations, 24
-// instructions per four Gaussians, into a table; at the end of a batch a
-// thread per Gaussian combines its row (over the workgroup's waves, in wave
-// order) and consecutive lanes add the nine gradients of consecutive
-// Gaussians (36-byte runs).  46 vector instructions per step; 300k Gaussians,
-// 1296 x 840: 89 -> 78 us at 64 samples per tile, 274 -> 228 us dense (there
-// the waves of a tile also share one set of atomics; plain stores in their
-// place take the same time).  Of the 78 us, 9 are the workgroups' dispatch, 11
-// the loads before the walk; the walk issues vector instructions 90% of its time.
+// lane swaps and DPP adds takes ~40 of the ~83 vector instructions of a
+// (Gaussian, wave) step, and the walk is bound by vector issue.  Instead q and
+// w of four Gaussians go, through LDS private to the wave (whose LDS
+// operations execute in order), from a lane per pixel to a lane per Gaussian
+// and four pixels.  There a lane sums the moments of q over its four pixels,
+// each product formed per pixel from that pixel's own offset and each moment
+// in a sum of its own, and the colour sums run on the matrix cores as 4
+// Gaussians x 64 pixels times 64 pixels x 4 columns (v_mfma_f32_4x4x1, 16
+// blocks, one pixel per block and instruction, FP32 products and sums).  Lane
+// swaps and row rotations fold the 16 lanes (or blocks) of a Gaussian into a
+// table; at the end of a batch a thread per Gaussian combines its row (over
+// the workgroup's waves, in wave order) and consecutive lanes add the nine
+// gradients of consecutive Gaussians (36-byte runs).
+// 300k Gaussians, 1296 x 840: 73 us at 64 samples per tile and 214 us dense,
+// with nine lane sums 89 and 274.  Moments about the tile's centre, formed with
+// the columns (1, x, y) on the matrix cores and shifted to the Gaussian's
+// centre after the sums, took 76 and 235 us and lost up to a factor of the
+// tile's half width over |d| in precision; an overflow in one moment also
+// reached the others of its matrix.
 constexpr int kBwdBatch = TGS_RENDER_CHUNK_LEN;  // Gaussians per batch: one short chunk
 constexpr int kBwdGroup = 4;                     // Gaussians per matrix
 constexpr int kBwdStage = 2 * kBwdBatch;         // Gaussians loaded per round
@@ -515,26 +513,26 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
   };
   if (stager) stage(begin);
 
-  // the pixels' columns as matrix operands: lane l of instruction s holds
-  // column l % 4 of pixel 16 s + l / 4
+  // the pixels as the sums take them: lane l's are 16 s + l / 4, s = 0 .. 3;
+  // their positions, and as a matrix operand column l % 4 of their colour gradients
   float* const tr = &s_tr[wave][0][0];
   float* const s_fin = &s_tr[0][0][0];  // the batch's gradients, after the walk
   static_assert(kBwdBatch * kFields <= 2 * kWave * kBwdGroup, "the gradients fit one wave's buffer");
   {
     float4* row = reinterpret_cast<float4*>(tr);
-    row[2 * lane] = make_float4(1.f, lx - 7.5f, ly - 7.5f, 0.f);
+    row[2 * lane] = make_float4(lx, ly, 0.f, 0.f);
     row[2 * lane + 1] = make_float4(g0, g1, g2, e_pix);
   }
   __syncthreads();
-  const int col = lane & 3;
-  float b0[4], bw[4];  // columns 1, x, y, 0 and the colour gradients (and the pixel's error)
+  const int sub = lane & 3;  // the lane's Gaussian of a group, and its column
+  float xs[4], ys[4], bw[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     const float* row = tr + (16 * s + (lane >> 2)) * 8;
-    b0[s] = row[col];
-    bw[s] = row[4 + col];
+    xs[s] = row[0];
+    ys[s] = row[1];
+    bw[s] = row[4 + sub];
   }
-  const float e3 = col == 3 ? 1.f : 0.f;  // the fourth column
 
   for (uint32_t start = begin; start < end; start += kBwdBatch) {
     if (__syncthreads_count(lim <= start - range.x) == kBlock) break;
@@ -552,7 +550,7 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
     uint32_t hit = 0;  // wave-uniform
     for (int j = 0; j < cnt; j += kBwdGroup) {
       if (ballot(pos0 + (uint32_t)j < lim) == 0ull) break;  // the whole wave has finished
-      float q[4], qx[4], qy[4], w[4], e2[4];
+      float q[4], w[4];
       uint32_t some = 0;
 #pragma unroll
       for (int u = 0; u < kBwdGroup; ++u) {
@@ -574,50 +572,49 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
         // dL/dalpha = T_before sum_c g_c colour_c - S / (1 - alpha)
         const float dalpha = __builtin_fmaf(T_before, gc, -S * inv);
         q[u] = ok && ap.y * G < amax ? G * dalpha : 0.f;  // clamped alphas pass nothing
-        qx[u] = q[u] * dx;
-        qy[u] = q[u] * dy;
-        if constexpr (kDensity) e2[u] = ok ? p2 : 0.f;
         some |= __builtin_amdgcn_ballot_w64(ok) != 0ull ? 1u << u : 0u;
       }
       if (some == 0u) continue;  // wave-uniform: no pixel of the wave composited any of the four
       hit |= some << j;
-      v4f m0 = {0.f, 0.f, 0.f, 0.f}, m1 = m0, m2 = m0, m3 = m0;
-      transpose2(tr, lane, q, qx, [&](int s, float x, float y) {
-        m0 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, b0[s], m0, 0, 0, 0);
-        m0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, e3, m0, 0, 0, 0);
-      });
-      transpose2(tr, lane, w, qy, [&](int s, float x, float y) {
-        m1 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, b0[s], m1, 0, 0, 0);
-        m2 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, bw[s], m2, 0, 0, 0);
-        if constexpr (kDensity) m1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, e3, m1, 0, 0, 0);
-      });
-      if constexpr (kDensity) {
-        // D w (D = the distance, sqrt(-2 power)) and the norm of the pixel's own centre gradient
-        constexpr float kTwoLn2 = 1.3862943611198906f;
-        float dw[4], nrm[4];
-#pragma unroll
-        for (int u = 0; u < kBwdGroup; ++u) {
-          const float4 cn = b_con[j + u];
-          const float opac = b_app[j + u].y;
-          dw[u] = __builtin_amdgcn_sqrtf(fmaxf(-kTwoLn2 * e2[u], 0.f)) * w[u];
-          const float nx = hw * ((cn.x * qx[u] + cn.y * qy[u]) * opac);
-          const float ny = hh * ((cn.y * qx[u] + cn.z * qy[u]) * opac);
-          nrm[u] = __builtin_amdgcn_sqrtf(nx * nx + ny * ny);
+      const float4 ge = b_geo[j + sub];
+      v4f mc = {0.f, 0.f, 0.f, 0.f};
+      float m0 = 0.f, mx = 0.f, my = 0.f, mxx = 0.f, mxy = 0.f, myy = 0.f;
+      float mw = 0.f, md = 0.f, mn = 0.f;  // density: w, w D and the norm of the pixel's own centre gradient
+      transpose2(tr, lane, q, w, [&](int s, float qs, float ws) {
+        const float dx = xs[s] - ge.x, dy = ys[s] - ge.y;
+        const float qx = qs * dx, qy = qs * dy;
+        m0 += qs;
+        mx += qx;
+        my += qy;
+        mxx = __builtin_fmaf(qx, dx, mxx);
+        mxy = __builtin_fmaf(qx, dy, mxy);
+        myy = __builtin_fmaf(qy, dy, myy);
+        mc = __builtin_amdgcn_mfma_f32_4x4x1f32(ws, bw[s], mc, 0, 0, 0);
+        if constexpr (kDensity) {
+          // D = the distance, sqrt(-2 power)
+          constexpr float kTwoLn2 = 1.3862943611198906f;
+          const float4 ap = b_app[j + sub], cn = b_con[j + sub];
+          const float p2 = splat_exponent(dx, dy, ge.z, ge.w, ap.x);
+          const float dist = __builtin_amdgcn_sqrtf(fmaxf(-kTwoLn2 * p2, 0.f));
+          const float nx = hw * ((cn.x * dx + cn.y * dy) * (ap.y * qs));
+          const float ny = hh * ((cn.y * dx + cn.z * dy) * (ap.y * qs));
+          mw += ws;
+          md += ws > 0.f ? dist * ws : 0.f;
+          mn += __builtin_amdgcn_sqrtf(nx * nx + ny * ny);
         }
-        transpose2(tr, lane, dw, nrm, [&](int, float x, float y) {
-          m3 = __builtin_amdgcn_mfma_f32_4x4x1f32(x, col == 0 ? 1.f : 0.f, m3, 0, 0, 0);
-          m3 = __builtin_amdgcn_mfma_f32_4x4x1f32(y, col == 1 ? 1.f : 0.f, m3, 0, 0, 0);
-        });
-      }
-      const float r0 = block_sums(m0), r1 = block_sums(m1), r2 = block_sums(m2);
-      const int quad = (lane >> 2) & 3, row = lane >> 4;
+      });
+      // four values per register and row of 16 lanes; the colours' rows are Gaussians, the others' the values
+      const float r0 = row_sum_quads(swap_sum16(swap_sum32(mx, my), swap_sum32(mxx, mxy)));
+      const float r1 = row_sum_quads(swap_sum16(swap_sum32(myy, m0), kDensity ? swap_sum32(mw, md) : 0.f));
+      const float r2 = block_sums(mc);
+      const int quad = (lane >> 2) & 3, row = lane >> 4, in = ((row & 1) << 1) | (row >> 1);
       float val = quad == 0 ? r0 : (quad == 1 ? r1 : r2);
       if constexpr (kDensity) {
-        const float r3 = block_sums(m3);
+        const float r3 = row_sum_quads(swap_sum16(swap_sum32(mn, 0.f), 0.f));
         val = quad == 3 ? r3 : val;
       }
       if (kDensity || quad < 3)
-        s_tab[wave][(j + (((row & 1) << 1) | (row >> 1))) * kCols + quad * 4 + col] = val;
+        s_tab[wave][(j + (quad == 2 ? in : sub)) * kCols + quad * 4 + (quad == 2 ? sub : in)] = val;
     }
     if (lane == 0) s_hit[wave] = hit;
     __syncthreads();
@@ -626,8 +623,8 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
     for (int v = 0; v < kWaves; ++v) any |= s_hit[v];
     if (any == 0u) continue;  // workgroup-uniform
     if (tid < kBwdBatch && (any >> tid) & 1u) {
-      // row of the table: sum q dx, q dx x, q dx y, q; q dy, q dy x, q dy y, w
-      // (density); w g0, w g1, w g2, w e; w D, |n|, -, -
+      // row of the table: sum q dx, q dy, q dx dx, q dx dy; q dy dy, q, (density)
+      // w, w D; w g0, w g1, w g2, w e; |n|, -, -, -
       float t[kCols];
 #pragma unroll
       for (int k = 0; k < kCols; ++k) t[k] = 0.f;
@@ -644,27 +641,23 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
           t[4 * k + 3] += x.w;
         }
       }
-      const float4 ge = b_geo[tid], cn = b_con[tid];
+      const float4 cn = b_con[tid];
       const float opac = b_app[tid].y;
-      const float cx = ge.x - 7.5f, cy = ge.y - 7.5f;  // centre relative to the tile's
-      const float sx = t[0], sy = t[4];
-      const float sxx = __builtin_fmaf(-cx, sx, t[1]), sxy = __builtin_fmaf(-cy, sx, t[2]);
-      const float syy = __builtin_fmaf(-cy, sy, t[6]);
       float* fin = s_fin + tid * kFields;
-      fin[0] = opac * __builtin_fmaf(cn.x, sx, cn.y * sy);
-      fin[1] = opac * __builtin_fmaf(cn.y, sx, cn.z * sy);
-      fin[2] = -0.5f * opac * sxx;
-      fin[3] = -opac * sxy;
-      fin[4] = -0.5f * opac * syy;
-      fin[5] = t[3];
+      fin[0] = opac * __builtin_fmaf(cn.x, t[0], cn.y * t[1]);
+      fin[1] = opac * __builtin_fmaf(cn.y, t[0], cn.z * t[1]);
+      fin[2] = -0.5f * opac * t[2];
+      fin[3] = -opac * t[3];
+      fin[4] = -0.5f * opac * t[4];
+      fin[5] = t[5];
       fin[6] = t[8];
       fin[7] = t[9];
       fin[8] = t[10];
       if constexpr (kDensity) {
         fin[9] = t[11];
-        fin[10] = t[7];
-        fin[11] = t[12];
-        fin[12] = t[13];
+        fin[10] = t[6];
+        fin[11] = t[7];
+        fin[12] = t[12];
       }
       if (touched != nullptr) touched[b_gid[tid]] = 1u;  // composited at a sample
     }
