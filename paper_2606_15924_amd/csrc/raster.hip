@@ -591,16 +591,16 @@ __device__ __forceinline__ void render_bwd_view(const RasterArgs& a, const float
         myy = __builtin_fmaf(qy, dy, myy);
         mc = __builtin_amdgcn_mfma_f32_4x4x1f32(ws, bw[s], mc, 0, 0, 0);
         if constexpr (kDensity) {
-          // D = the distance, sqrt(-2 power)
+          // D = the distance, sqrt(-2 power); correctly rounded roots, as in the walk of its own below
           constexpr float kTwoLn2 = 1.3862943611198906f;
           const float4 ap = b_app[j + sub], cn = b_con[j + sub];
           const float p2 = splat_exponent(dx, dy, ge.z, ge.w, ap.x);
-          const float dist = __builtin_amdgcn_sqrtf(fmaxf(-kTwoLn2 * p2, 0.f));
+          const float dist = __builtin_sqrtf(fmaxf(-kTwoLn2 * p2, 0.f));
           const float nx = hw * ((cn.x * dx + cn.y * dy) * (ap.y * qs));
           const float ny = hh * ((cn.y * dx + cn.z * dy) * (ap.y * qs));
           mw += ws;
           md += ws > 0.f ? dist * ws : 0.f;
-          mn += __builtin_amdgcn_sqrtf(nx * nx + ny * ny);
+          mn += __builtin_sqrtf(nx * nx + ny * ny);
         }
       });
       // four values per register and row of 16 lanes; the colours' rows are Gaussians, the others' the values
