@@ -749,6 +749,13 @@ class Trainer:
         self._queue_count_check(used)
         return used
 
+    def _maps_apart(self, views) -> bool:
+        """Whether the views' error and age maps are distinct in memory (a
+        view drawn twice, or views given the same maps, share them)."""
+        spans = sorted((m.data_ptr(), m.data_ptr() + m.numel() * m.element_size())
+                       for v in views for m in (self.E[v], self.A[v]))
+        return all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+
     def _stacked_stages(self, used, views, rec, sampled):
         """Forward, loss, error maps and (unless it is the deterministic one)
         backward of a step's views, a call per stage, on the current stream;
@@ -767,12 +774,12 @@ class Trainer:
             self._lossed[0].record(main)
             self.side.wait_event(self._lossed[0])
             with torch.cuda.stream(self.side):
-                distinct = len(set(views)) == len(views)   # else a view's maps are updated in turn
-                if distinct:
+                apart = self._maps_apart(views)   # else they are updated in turn
+                if apart:
                     with st("ema_age"):
                         B.tgs_ema_age_update_views(rec, self.cfg.beta)
                 for k, (vb, v) in enumerate(zip(used, views)):
-                    if not distinct:
+                    if not apart:
                         with st("ema_age"):
                             vb.ema_age(self.E[v], self.A[v], self.cfg.beta)
                     if self.tiles is not None:
