@@ -613,8 +613,9 @@ class Trainer:
                                     [vb.rect for vb in used], [vb.clamp for vb in used], [vb.g2d for vb in used])
 
         def records():
-            return B.views_array([vb.record(v, self.gts[v], None if self.E is None else self.E[v],
-                                            None if self.A is None else self.A[v], pred)
+            # dense steps read no maps: theirs may be anything
+            return B.views_array([vb.record(v, self.gts[v], None if vb.dense else self.E[v],
+                                            None if vb.dense else self.A[v], pred)
                                   for vb, v, pred in zip(used, views, preds)])
 
         def bin_all():
