@@ -979,6 +979,7 @@ class Trainer:
             self.dstats = torch.zeros((self.n, 4), dtype=torch.float32, device=self.dev)
             self.gstats = torch.zeros((self.n, 4), dtype=torch.float32, device=self.dev)
         self._bufs = {}   # per-view buffers are sized by the Gaussian count
+        self._counts = torch.zeros_like(self._counts)   # the dropped sets keep their rows
         return n_out
 
     def moments(self):
