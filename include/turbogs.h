@@ -250,7 +250,9 @@ int32_t tgs_sample_noalloc(const uint16_t* E, const uint16_t* A, int32_t height,
  * count on the device, so the work is queued without waiting; this call then waits for the stream once
  * (a copy of the two counts into host memory) to return them.  The library
  * keeps no host or device memory of its own for it.
- *   n_tiles  of the workspace size: tiles_x * tiles_y of the calls */
+ *   n_tiles  of the workspace size: tiles_x * tiles_y of the calls (any
+ *            value for grids of up to 65,536 tiles, which every workspace
+ *            holds; 0 or less: up to 1,048,576 tiles) */
 size_t tgs_bin_sort_workspace_size(int64_t n, int64_t capacity, int32_t n_tiles);
 int32_t tgs_bin_sort(const int32_t* rect, const float* splat, const float* depth, int64_t n,
                      const int32_t* tile_slot, int32_t tiles_x, int32_t tiles_y, float alpha_min,

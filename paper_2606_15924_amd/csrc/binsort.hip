@@ -1181,7 +1181,7 @@ struct SortWs {
   uint16_t* spans;              // [kb][kSpanRows]
   int2* rowinfo;                // [n]
   int64_t kb;                   // blocks of depth positions
-  uint32_t* rows_tab;           // [min(n_tiles, kGroup)][kb]
+  uint32_t* rows_tab;           // [kGroup][kb]
   uint32_t* pairs_tab;
   unsigned long long* row_tot;  // [n_tiles] (at most a strip per tile)
   unsigned long long* pair_tot;
@@ -1190,12 +1190,18 @@ struct SortWs {
   uint32_t* blk_base;
   uint64_t* bits;               // [at most n_tiles] words
   uint2* rec;                   // [capacity]
-  uint32_t* hist;               // [capacity / kRecBlock + kGroup][columns]
+  uint32_t* hist;               // [capacity / kRecBlock + kGroup][kStripCols or fewer]
   size_t bytes;
 };
 
+// The workspace holds the tables of any grid of up to kTilesAlways tiles (36
+// bytes each), so a caller need not give the grid's size: the calls of one
+// workspace may have several grids.
+constexpr int64_t kTilesAlways = 1 << 16, kTilesUnknown = 1 << 20;
+
 static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
-  const int64_t cap = std::max<int64_t>(capacity, 1), nn = std::max<int64_t>(n, 1), nt = std::max<int64_t>(n_tiles, 1);
+  const int64_t cap = std::max<int64_t>(capacity, 1), nn = std::max<int64_t>(n, 1);
+  const int64_t nt = std::max(n_tiles, kTilesAlways);
   size_t o = 0;
   char* b = (char*)ws;
   auto take = [&](size_t bytes) {
@@ -1221,9 +1227,8 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
   w.kb = ceil_div(nn, kRowThreads);
   w.spans = (uint16_t*)take(sizeof(uint16_t) * kSpanRows * w.kb);
   w.rowinfo = (int2*)take(sizeof(int2) * nn);
-  const int64_t gs = std::min<int64_t>(nt, kGroup);
-  w.rows_tab = (uint32_t*)take(sizeof(uint32_t) * gs * w.kb);
-  w.pairs_tab = (uint32_t*)take(sizeof(uint32_t) * gs * w.kb);
+  w.rows_tab = (uint32_t*)take(sizeof(uint32_t) * kGroup * w.kb);
+  w.pairs_tab = (uint32_t*)take(sizeof(uint32_t) * kGroup * w.kb);
   w.row_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
   w.pair_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
   w.row_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
@@ -1231,7 +1236,7 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
   w.blk_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
   w.bits = (uint64_t*)take(sizeof(uint64_t) * nt);
   w.rec = (uint2*)take(sizeof(uint2) * cap);
-  w.hist = (uint32_t*)take(sizeof(uint32_t) * (cap / kRecBlock + gs + 1) * std::min<int64_t>(nt, kStripCols));
+  w.hist = (uint32_t*)take(sizeof(uint32_t) * (cap / kRecBlock + kGroup + 1) * kStripCols);
   w.bytes = o;
   return w;
 }
@@ -1380,7 +1385,7 @@ using namespace tgs;
 
 extern "C" size_t tgs_bin_sort_workspace_size(int64_t n, int64_t capacity, int32_t n_tiles) {
   if (n < 0 || capacity < 0) return 0;
-  return layout(nullptr, n, capacity, n_tiles).bytes;
+  return layout(nullptr, n, capacity, n_tiles > 0 ? n_tiles : kTilesUnknown).bytes;
 }
 
 // One view's call, after its argument checks: what goes into the batches.
@@ -1497,7 +1502,7 @@ static int32_t bin_sort_check(const int32_t* rect, const float* splat, const flo
   return TGS_OK;
 }
 
-// Tiles of a grid for the layout, 0 for a grid that the checks refuse.
+// Tiles of a grid for the layout; 0 for a grid that the checks refuse.
 static int64_t grid_tiles(int32_t tiles_x, int32_t tiles_y) {
   return tiles_x > 0 && tiles_y > 0 ? (int64_t)tiles_x * tiles_y : 0;
 }
