@@ -545,13 +545,27 @@ __device__ __forceinline__ uint32_t valid_in(const uint64_t* __restrict__ row, i
 // ------------------------------------------------------------------ row records
 // Strips: a tile row, cut into pieces of kStripCols columns when it has more
 // (strip (y, c) holds the tiles of row y with x / kStripCols = c), in tile
-// order.  The row stages keep a counter per strip in LDS, so grids of more
-// than kGroup strips are taken in groups of kGroup, one after the other.
+// order.  The count keeps two counters per strip in LDS and a table entry per
+// strip and block, so grids of more strips than a group holds are taken in
+// groups, one after the other, each counted again before its records and with
+// the rows of other groups left out.  The records need 24 times a counter's LDS:
+// a workgroup writes those of kSub strips.  Groups of kSub throughout made the
+// 272 rows of a 512 x 4352 image two groups and the 512 x 2 strips of 8192 x
+// 8192 four: 300k Gaussians 608 -> 243 us and 10k 1505 -> 245 us with one.
 constexpr int kStripCols = 256;  // a record's columns within its strip are 8 bits each
-constexpr int kGroup = 256;
+constexpr int kSub = 256;
 constexpr int kRowThreads = 256;  // depth positions per block of the row stages
 constexpr int kRowWaves = kRowThreads / kWave;
-constexpr int kSpanRows = 12 * kRowThreads;  // rows per block whose intervals the count keeps for the records
+// The count keeps the intervals of a block's first rows for the records, which
+// evaluate the others again: 36 rows per position, the most whose LDS leaves the
+// workgroups that the registers allow, or 24 (48 bytes per Gaussian) for many
+// Gaussians.  Few Gaussians, whose tables are small, also take larger groups.
+// 30k of 45 rows on average, 300 x 1920: 175 us, with 24 rows 205; 100k of 12,
+// 3840 x 2160: 234 us, with 12 rows 293; 10k in the 4096 strips of 16384 x
+// 16384: 201 us in one group, 468 in four.
+constexpr int64_t kFewGaussians = 1 << 17;
+constexpr int kSpans = 24 * kRowThreads, kSpansFew = 36 * kRowThreads;
+constexpr int kGroup = 1024, kGroupFew = 4096;
 constexpr int kRecThreads = 256;
 constexpr int kRecItems = 2;
 constexpr int kRecBlock = kRecThreads * kRecItems;  // records per block of the pair stages
@@ -567,11 +581,14 @@ struct BinArgs {
   int tiles_x, tiles_y, wpr;
   int sc;                     // strips per tile row
   int s0, sn;                 // the group: strips [s0, s0 + sn)
+  int y0, y1;                 // its tile rows
+  int group;                  // strips in a group
   double tau, lia;
   int64_t kb;                 // blocks of depth positions: row stride of the tables
+  int span_rows;              // rows of a block whose intervals are kept
   uint32_t* rows_tab;         // [sn][kb] records per strip and block, then their prefix
   uint32_t* pairs_tab;        // [sn][kb] pairs
-  uint16_t* spans;            // [blocks][kSpanRows] the block's rows' intervals, position after position
+  uint16_t* spans;            // [blocks][span_rows] the block's rows' intervals, position after position
   int2* rowinfo;              // [positions] first tile row, rows
   uint8_t* touched;
   // per strip (all groups)
@@ -669,24 +686,29 @@ __device__ __forceinline__ RowEllipse ellipse_of_lane(const RowEllipse& e, int l
 // costs a prefix sum, two exchanges through LDS and their barriers per 64
 // rows, which took longer than the idle lanes do.
 template <bool kWide>
-__global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) {
+__global__ void __launch_bounds__(kRowThreads, 6) bin_count_kernel(BinBatch batch) {
   const BinArgs& a = batch.v[blockIdx.z];
-  __shared__ uint32_t s_rows[kGroup], s_pairs[kGroup];
-  __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
+  extern __shared__ uint32_t s_dyn[];  // two counters per strip, then the kept rows' intervals
+  uint32_t* const s_rows = s_dyn;
+  uint32_t* const s_pairs = s_dyn + a.sn;
+  uint16_t* const s_span = reinterpret_cast<uint16_t*>(s_dyn + 2 * a.sn);
   __shared__ uint32_t s_red[kRowWaves];
   if (bin_nothing(a)) return;
   const int tid = threadIdx.x;
   const int64_t end = bin_end(a), p0 = a.pos0 + (int64_t)blockIdx.x * kRowThreads, p = p0 + tid;
   if (p0 >= end) return;  // workgroup-uniform
-  static_assert(kGroup == kRowThreads, "a thread per strip counter");
-  s_rows[tid] = 0u;
-  s_pairs[tid] = 0u;
+  for (int i = tid; i < a.sn; i += kRowThreads) {
+    s_rows[i] = 0u;
+    s_pairs[i] = 0u;
+  }
   int4 r = make_int4(0, 0, 0, 0);
   float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
   uint32_t g = 0;
   if (p < end) {
     g = a.ids[p];
     r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
+    r.y = max(r.y, a.y0);
+    r.w = max(min(r.w, a.y1), r.y);
     if (a.bits == nullptr) {  // every listed Gaussian has a tile: its record is asked for beside the rectangle
       c0 = a.splat[3 * (int64_t)g];
       c1 = a.splat[3 * (int64_t)g + 1];
@@ -723,7 +745,7 @@ __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) 
         atomicAdd(&s_pairs[s], c);
       }
     });
-    if (!kWide && q < (uint32_t)kSpanRows) s_span[q] = (uint16_t)span;
+    if (!kWide && q < (uint32_t)a.span_rows) s_span[q] = (uint16_t)span;
     return kept;
   };
   bool any = false;
@@ -747,13 +769,13 @@ __global__ void __launch_bounds__(kRowThreads) bin_count_kernel(BinBatch batch) 
   }
   __syncthreads();
   if (!kWide) {
-    const uint32_t words = (min(total, (uint32_t)kSpanRows) + 1u) / 2u;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(a.spans + (int64_t)blockIdx.x * kSpanRows);
+    const uint32_t words = (min(total, (uint32_t)a.span_rows) + 1u) / 2u;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(a.spans + (int64_t)blockIdx.x * a.span_rows);
     for (uint32_t i = tid; i < words; i += kRowThreads) dst[i] = reinterpret_cast<const uint32_t*>(s_span)[i];
   }
-  if (tid < a.sn) {
-    a.rows_tab[(int64_t)tid * a.kb + blockIdx.x] = s_rows[tid];
-    a.pairs_tab[(int64_t)tid * a.kb + blockIdx.x] = s_pairs[tid];
+  for (int i = tid; i < a.sn; i += kRowThreads) {
+    a.rows_tab[(int64_t)i * a.kb + blockIdx.x] = s_rows[i];
+    a.pairs_tab[(int64_t)i * a.kb + blockIdx.x] = s_pairs[i];
   }
 }
 
@@ -837,16 +859,19 @@ __global__ void __launch_bounds__(1024) strip_base_kernel(BinBatch batch) {
 // positions have a record there; a record's place is the strip's first one,
 // plus the earlier blocks', the earlier waves' and the earlier lanes' records.
 template <bool kWide>
-__global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinBatch batch) {
+__global__ void __launch_bounds__(kRowThreads, 6) bin_rows_kernel(BinBatch batch) {
   const BinArgs& a = batch.v[blockIdx.z];
-  __shared__ uint64_t s_mask[kRowWaves][kGroup];
-  __shared__ uint32_t s_pos[kRowWaves][kGroup];
-  __shared__ __align__(4) uint16_t s_span[kWide ? 2 : kSpanRows];
+  __shared__ uint64_t s_mask[kRowWaves][kSub];
+  __shared__ uint32_t s_pos[kRowWaves][kSub];
+  extern __shared__ uint32_t s_dyn[];  // the kept rows' intervals
+  uint16_t* const s_span = reinterpret_cast<uint16_t*>(s_dyn);
   __shared__ uint32_t s_red[kRowWaves];
   if (bin_nothing(a)) return;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int64_t end = bin_end(a), p0 = a.pos0 + (int64_t)blockIdx.x * kRowThreads, p = p0 + tid;
-  if (p0 >= end || *a.eff_total == 0u) return;  // workgroup-uniform
+  const int t0 = (int)blockIdx.y * kSub, tn = min(kSub, a.sn - t0);  // strips of the group
+  if (p0 >= end || *a.eff_total == 0u || tn <= 0) return;  // workgroup-uniform
+  static_assert(kSub == kRowThreads, "a thread per strip");
 #pragma unroll
   for (int w = 0; w < kRowWaves; ++w) s_mask[w][tid] = 0ull;
   int2 info = make_int2(0, 0);
@@ -856,60 +881,68 @@ __global__ void __launch_bounds__(kRowThreads) bin_rows_kernel(BinBatch batch) {
     g = a.ids[p];
   }
   uint32_t total;
-  const uint32_t at = block_exclusive_scan<kRowThreads, uint32_t>((uint32_t)info.y, s_red, &total);
+  uint32_t at = block_exclusive_scan<kRowThreads, uint32_t>((uint32_t)info.y, s_red, &total);
+  {
+    // the rows that these strips are of
+    const int s0 = a.s0 + t0, sc = kWide ? a.sc : 1, f = s0 / sc, l = (s0 + tn - 1) / sc + 1;
+    const int skip = min(max(f - info.x, 0), info.y);
+    at += (uint32_t)skip;
+    info = make_int2(info.x + skip, max(min(info.y - skip, l - info.x - skip), 0));
+  }
   if (!kWide) {
-    const uint32_t words = (min(total, (uint32_t)kSpanRows) + 1u) / 2u;
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.spans + (int64_t)blockIdx.x * kSpanRows);
+    const uint32_t words = (min(total, (uint32_t)a.span_rows) + 1u) / 2u;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.spans + (int64_t)blockIdx.x * a.span_rows);
     for (uint32_t i = tid; i < words; i += kRowThreads) reinterpret_cast<uint32_t*>(s_span)[i] = src[i];
   }
   RowEllipse e = {};
   int4 r = make_int4(0, 0, 0, 0);
-  if (info.y > 0 && (kWide || at + (uint32_t)info.y > (uint32_t)kSpanRows)) {  // rows not kept: evaluated again
+  if (info.y > 0 && (kWide || at + (uint32_t)info.y > (uint32_t)a.span_rows)) {  // rows not kept: evaluated again
     r = clamp_rect(a.rect[g], a.tiles_x, a.tiles_y);
     e = row_ellipse(a.splat[3 * (int64_t)g], a.splat[3 * (int64_t)g + 1], a.tau, a.lia);
   }
   __syncthreads();
-  // f(strip, columns, lane whose row it is, its Gaussian)
+  // f(strip of these, columns, lane whose row it is, its Gaussian)
   const int longest = wave_max_i(info.y);
-  auto own = [&](int k, auto&& f) {  // row k of the lane's own Gaussian
-    if (!kWide && at + (uint32_t)k < (uint32_t)kSpanRows) {
-      const uint32_t c = s_span[at + (uint32_t)k];
-      const int s = info.x + k - a.s0;
-      if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c, lane, g);
-    } else {
-      int lo, hi;
-      row_span(e, info.x + k, r.x, r.z, lo, hi);
-      row_pieces<kWide>(a, info.x + k, lo, hi, [&](int s, int l, int h, uint32_t) {
-        if (s >= 0 && s < a.sn) f(s, (uint32_t)l | ((uint32_t)h << 8), lane, g);
-      });
-    }
+  auto pieces = [&](const RowEllipse& re, int y, int rx0, int rx1, int l, uint32_t gl, auto&& f) {
+    int lo, hi;
+    row_span(re, y, rx0, rx1, lo, hi);
+    row_pieces<kWide>(a, y, lo, hi, [&](int s, int x0, int x1, uint32_t) {
+      if (s >= t0 && s < t0 + tn) f(s - t0, (uint32_t)x0 | ((uint32_t)x1 << 8), l, gl);
+    });
   };
+  auto stored = [&](int y, uint32_t q, int l, uint32_t gl, auto&& f) {
+    const uint32_t c = s_span[q];
+    const int s = y - a.s0 - t0;
+    if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < tn) f(s, c, l, gl);
+  };
+  const uint64_t kept = ballot(!kWide && at + (uint32_t)info.y <= (uint32_t)a.span_rows);
   auto each = [&](auto&& f) {
     int k = 0;
-    for (; k < longest && (kWide || !few_long(info.y, k, longest)); ++k)
-      if (k < info.y) own(k, f);
-    if (kWide) return;
-    const bool kept = at + (uint32_t)info.y <= (uint32_t)kSpanRows;
-    for (uint64_t left = ballot(kept && info.y > k); left != 0ull; left &= left - 1) {
+    for (; k < longest && !few_long(info.y, k, longest); ++k)
+      if (k < info.y) {
+        if (!kWide && at + (uint32_t)k < (uint32_t)a.span_rows) stored(info.x + k, at + (uint32_t)k, lane, g, f);
+        else pieces(e, info.x + k, r.x, r.z, lane, g, f);
+      }
+    for (uint64_t left = ballot(info.y > k); left != 0ull; left &= left - 1) {
       const int l = (int)__builtin_ctzll(left);
       const int n_l = __builtin_amdgcn_readlane(info.y, l), y_l = __builtin_amdgcn_readlane(info.x, l);
-      const uint32_t at_l = (uint32_t)__builtin_amdgcn_readlane((int)at, l);
       const uint32_t g_l = (uint32_t)__builtin_amdgcn_readlane((int)g, l);
-      for (int j = k + lane; j < n_l; j += kWave) {
-        const int s = y_l + j - a.s0;
-        const uint32_t c = s_span[at_l + (uint32_t)j];
-        if ((c & 0xffu) <= (c >> 8) && s >= 0 && s < a.sn) f(s, c, l, g_l);
+      if (!kWide && (kept >> l) & 1ull) {
+        const uint32_t at_l = (uint32_t)__builtin_amdgcn_readlane((int)at, l);
+        for (int j = k + lane; j < n_l; j += kWave) stored(y_l + j, at_l + (uint32_t)j, l, g_l, f);
+      } else {
+        const RowEllipse el = ellipse_of_lane(e, l);
+        const int rx0 = __builtin_amdgcn_readlane(r.x, l), rx1 = __builtin_amdgcn_readlane(r.z, l);
+        for (int j = k + lane; j < n_l; j += kWave) pieces(el, y_l + j, rx0, rx1, l, g_l, f);
       }
     }
-    if (!kept)
-      for (; k < info.y; ++k) own(k, f);
   };
   each([&](int s, uint32_t, int l, uint32_t) {
     __hip_atomic_fetch_or(&s_mask[wave][s], 1ull << l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   });
   __syncthreads();
-  if (tid < a.sn) {
-    uint32_t q = a.row_base[a.s0 + tid] + a.rows_tab[(int64_t)tid * a.kb + blockIdx.x];
+  if (tid < tn) {
+    uint32_t q = a.row_base[a.s0 + t0 + tid] + a.rows_tab[(int64_t)(t0 + tid) * a.kb + blockIdx.x];
 #pragma unroll
     for (int w = 0; w < kRowWaves; ++w) {
       s_pos[w][tid] = q;
@@ -944,10 +977,9 @@ struct RecSpan {
 __device__ __forceinline__ RecSpan rec_span(const BinArgs& a, uint32_t b, int* s_strip) {
   if (threadIdx.x == 0) *s_strip = 0;
   __syncthreads();
-  if ((int)threadIdx.x < a.sn) {
-    const uint32_t f = a.blk_base[a.s0];
-    if (a.blk_base[a.s0 + threadIdx.x] - f <= b && b < a.blk_base[a.s0 + threadIdx.x + 1] - f) *s_strip = threadIdx.x;
-  }
+  const uint32_t f = a.blk_base[a.s0];
+  for (int i = threadIdx.x; i < a.sn; i += kRecThreads)
+    if (a.blk_base[a.s0 + i] - f <= b && b < a.blk_base[a.s0 + i + 1] - f) *s_strip = i;
   __syncthreads();
   RecSpan q{*s_strip, 0u, 0u};
   const int s = a.s0 + q.strip;
@@ -964,7 +996,7 @@ __global__ void __launch_bounds__(kRecThreads) bin_hist_kernel(BinBatch batch) {
   __shared__ int s_red[kRecThreads / kWave];
   __shared__ int s_strip;
   if (*a.eff_total == 0u) return;
-  static_assert(kRecThreads == kStripCols && kRecThreads >= kGroup, "a thread per column and per strip");
+  static_assert(kRecThreads == kStripCols, "a thread per column");
   const int tid = threadIdx.x;
   const uint32_t blocks = group_blocks(a);
   for (uint32_t b = blockIdx.x; b < blocks; b += gridDim.x) {
@@ -1178,10 +1210,11 @@ struct SortWs {
   uint32_t* ids_sorted;         // [n] Gaussians in depth order
   uint32_t* part;               // few Gaussians: [chunks][n] partial ranks
   int4* rects;                  // [n] clamped rectangles (kept by a depth-prefix call)
-  uint16_t* spans;              // [kb][kSpanRows]
+  uint16_t* spans;              // [kb][span_rows]
   int2* rowinfo;                // [n]
   int64_t kb;                   // blocks of depth positions
-  uint32_t* rows_tab;           // [kGroup][kb]
+  int span_rows, group;         // rows of a block whose intervals are kept; strips in a group
+  uint32_t* rows_tab;           // [group][kb]
   uint32_t* pairs_tab;
   unsigned long long* row_tot;  // [n_tiles] (at most a strip per tile)
   unsigned long long* pair_tot;
@@ -1190,7 +1223,7 @@ struct SortWs {
   uint32_t* blk_base;
   uint64_t* bits;               // [at most n_tiles] words
   uint2* rec;                   // [capacity]
-  uint32_t* hist;               // [capacity / kRecBlock + kGroup][kStripCols or fewer]
+  uint32_t* hist;               // [capacity / kRecBlock + group][kStripCols or fewer]
   size_t bytes;
 };
 
@@ -1225,10 +1258,14 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
   w.part = (uint32_t*)take(nn <= kSmallSort ? sizeof(uint32_t) * nn * ceil_div(nn, kRankChunk) : 0);
   w.rects = (int4*)take(sizeof(int4) * nn);
   w.kb = ceil_div(nn, kRowThreads);
-  w.spans = (uint16_t*)take(sizeof(uint16_t) * kSpanRows * w.kb);
+  const bool few = nn <= kFewGaussians;
+  const int64_t group = few ? kGroupFew : kGroup;
+  w.span_rows = few ? kSpansFew : kSpans;
+  w.group = (int)group;
+  w.spans = (uint16_t*)take(sizeof(uint16_t) * w.span_rows * w.kb);
   w.rowinfo = (int2*)take(sizeof(int2) * nn);
-  w.rows_tab = (uint32_t*)take(sizeof(uint32_t) * kGroup * w.kb);
-  w.pairs_tab = (uint32_t*)take(sizeof(uint32_t) * kGroup * w.kb);
+  w.rows_tab = (uint32_t*)take(sizeof(uint32_t) * group * w.kb);
+  w.pairs_tab = (uint32_t*)take(sizeof(uint32_t) * group * w.kb);
   w.row_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
   w.pair_tot = (unsigned long long*)take(sizeof(unsigned long long) * nt);
   w.row_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
@@ -1236,7 +1273,7 @@ static SortWs layout(void* ws, int64_t n, int64_t capacity, int64_t n_tiles) {
   w.blk_base = (uint32_t*)take(sizeof(uint32_t) * (nt + 1));
   w.bits = (uint64_t*)take(sizeof(uint64_t) * nt);
   w.rec = (uint2*)take(sizeof(uint2) * cap);
-  w.hist = (uint32_t*)take(sizeof(uint32_t) * (cap / kRecBlock + kGroup + 1) * kStripCols);
+  w.hist = (uint32_t*)take(sizeof(uint32_t) * (cap / kRecBlock + group + 1) * kStripCols);
   w.bytes = o;
   return w;
 }
@@ -1271,6 +1308,8 @@ static int64_t strips_of(const BinArgs& a) { return (int64_t)a.sc * a.tiles_y; }
 // (pos0 .. pos_end).
 template <bool kWide>
 static void list_pairs(BinBatch& b, int views, hipStream_t s) {
+  const int64_t group_strips = b.v[0].group;  // of the Gaussian count: the same in all views
+  const size_t span_bytes = kWide ? 0 : sizeof(uint16_t) * b.v[0].span_rows;
   const unsigned nv = (unsigned)views;
   int64_t strips = 0, positions = 0, capacity = 0;
   int rows = 0, cols = 0;
@@ -1290,28 +1329,33 @@ static void list_pairs(BinBatch& b, int views, hipStream_t s) {
     for (int k = 0; k < views; ++k) {
       BinArgs& a = b.v[k];
       a.s0 = (int)s0;
-      a.sn = (int)std::min<int64_t>(kGroup, strips_of(a) - s0);
+      a.sn = (int)std::min<int64_t>(group_strips, strips_of(a) - s0);
+      a.y0 = (int)(s0 / a.sc);
+      a.y1 = (int)((s0 + a.sn - 1) / a.sc) + 1;
       sn = std::max(sn, (unsigned)a.sn);
     }
   };
   auto count = [&] {
-    if (kb > 0) hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads), 0, s, b);
+    if (kb > 0)
+      hipLaunchKernelGGL(bin_count_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads),
+                         2 * sizeof(uint32_t) * sn + span_bytes, s, b);
     hipLaunchKernelGGL(strip_scan_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
   };
   if (subset && !b.v[0].counted)
     hipLaunchKernelGGL(tile_bits_kernel, dim3((unsigned)rows, 1, nv), dim3(kWave), 0, s, b);
   const bool counted = b.v[0].counted;  // a view's lists resumed, alone in its batch
-  for (int64_t s0 = 0; s0 < strips && !counted; s0 += kGroup) {
+  for (int64_t s0 = 0; s0 < strips && !counted; s0 += group_strips) {
     group(s0);
     count();
   }
   hipLaunchKernelGGL(strip_base_kernel, dim3(1, 1, nv), dim3(1024), 0, s, b);
-  for (int64_t s0 = 0; s0 < strips; s0 += kGroup) {
+  for (int64_t s0 = 0; s0 < strips; s0 += group_strips) {
     group(s0);
-    if (strips > kGroup) count();  // the tables hold one group
+    if (strips > group_strips) count();  // the tables hold one group
     if (kb > 0 && capacity > 0) {
       const unsigned nb = (unsigned)std::min<int64_t>(capacity / kRecBlock + sn, kPairGrid);
-      hipLaunchKernelGGL(bin_rows_kernel<kWide>, dim3(kb, 1, nv), dim3(kRowThreads), 0, s, b);
+      hipLaunchKernelGGL(bin_rows_kernel<kWide>, dim3(kb, (unsigned)ceil_div((int)sn, kSub), nv),
+                         dim3(kRowThreads), span_bytes, s, b);
       hipLaunchKernelGGL(bin_hist_kernel, dim3(nb, 1, nv), dim3(kRecThreads), 0, s, b);
       hipLaunchKernelGGL(bin_offsets_kernel, dim3(sn, 1, nv), dim3(1024), 0, s, b);
       if (cols <= kStripCols / 2)  // half the LDS: more workgroups per compute unit
@@ -1328,7 +1372,7 @@ static void list_pairs(BinBatch& b, int views, hipStream_t s) {
 // one; the others together.
 static void list_all(BinBatch& b, int views, hipStream_t s) {
   bool together = true;
-  for (int k = 0; k < views; ++k) together = together && b.v[k].sc == 1 && strips_of(b.v[k]) <= kGroup;
+  for (int k = 0; k < views; ++k) together = together && b.v[k].sc == 1 && strips_of(b.v[k]) <= b.v[k].group;
   if (together) {
     list_pairs<false>(b, views, s);
     return;
@@ -1356,6 +1400,8 @@ static BinArgs bin_args(const SortWs& w, const float* splat, const int32_t* tile
   a.lia = std::log(1.0 / (double)alpha_min);
   a.tau = std::ceil(128.0 * a.lia * 1.001) / 64.0;
   a.kb = w.kb;
+  a.span_rows = w.span_rows;
+  a.group = w.group;
   a.rows_tab = w.rows_tab;
   a.pairs_tab = w.pairs_tab;
   a.spans = w.spans;
@@ -1545,7 +1591,7 @@ extern "C" int32_t tgs_bin_sort_resume_async(const int32_t* rect, const float* s
                 ranges, touched, w, (unsigned long long*)counts, -1);
   resume_view(b.v[0], w1);
   // more strips than one group: their tables were overwritten group by group
-  if (b.v[0].sc > 1 || strips_of(b.v[0]) > kGroup) b.v[0].counted = false;
+  if (b.v[0].sc > 1 || strips_of(b.v[0]) > b.v[0].group) b.v[0].counted = false;
   list_all(b, 1, as_stream(stream));
   return hip_status(who);
 }
