@@ -448,8 +448,11 @@ __global__ void __launch_bounds__(kSortThreads) depth_pass_kernel(DepthBatch bat
 // Few Gaussians: the rank of every key by counting the keys before it.  The
 // twelve launches above take ~5 us each whatever n is (57 us in all); n^2
 // comparisons spread over the chip take 18 us at 10,000 Gaussians, a sort
-// in one workgroup's LDS 47 us.  The comparisons overtake the passes at some
-// 30,000.
+// in one workgroup's LDS 47 us.  Whole calls on 256 x 256 images, ranks and
+// passes: one view of 10,000 Gaussians 58 and 100 us, 16,384 66 and 100, 24,000
+// 89 and 102, 28,000 104 and 104; four views in one call, which share the
+// passes' latency but not the comparisons, 10,000 79 and 109, 16,384 114 and 110,
+// 20,000 160 and 111.  The line lies where four views break even.
 //
 // rank: 256 Gaussians against 256 others per workgroup.  Keys tie-break by
 // index, so a chunk of others before the workgroup's Gaussians counts its
