@@ -220,7 +220,7 @@ def full_workload(dev):
     cams = synth.hemisphere_cameras(FULL_VIEWS, width=FULL_W, height=FULL_H)
     P_true = torch.from_numpy(synth.perturb(p, synth.SEED_PERTURB)).to(dev)
     rp = B.raster_params()
-    vb = ViewBuffers(FULL_N, FULL_W, FULL_H, None, -1, dev)
+    vb = ViewBuffers(FULL_N, FULL_W, FULL_H, None, -1, dev, supervised=False, backward=False)
     gen = torch.Generator(device=dev)
     gts = []
     for k, cam in enumerate(cams):
@@ -294,7 +294,7 @@ def matched_psnr(dev, dense_steps=PSNR_DENSE_STEPS, max_steps=PSNR_MAX_STEPS):
     held = [i for i in range(PSNR_CAMS) if i % 5 == 2]
     train = [i for i in range(PSNR_CAMS) if i % 5 != 2]
     rp = B.raster_params()
-    vb = ViewBuffers(N_GAUSS, WIDTH, HEIGHT, None, -1, dev)
+    vb = ViewBuffers(N_GAUSS, WIDTH, HEIGHT, None, -1, dev, supervised=False, backward=False)
 
     def render(params, cam):
         c = B.camera(cam)
@@ -397,7 +397,7 @@ def tile_priority(dev, n_views=TP_VIEWS, steps=TP_STEPS, eval_from=TP_EVAL_FROM)
     p_true = synth.perturb(p0, synth.SEED_PERTURB)
     cams = synth.hemisphere_cameras(n_views, width=WIDTH, height=HEIGHT, focal=300.0 * WIDTH / 256)
     rp = B.raster_params()
-    vb = ViewBuffers(N_GAUSS, WIDTH, HEIGHT, None, -1, dev)
+    vb = ViewBuffers(N_GAUSS, WIDTH, HEIGHT, None, -1, dev, supervised=False, backward=False)
     P_true = torch.from_numpy(p_true).to(dev)
     gts = []
     for k, cam in enumerate(cams):
@@ -515,7 +515,7 @@ def large_scene(dev, steps):
     cams = synth.trajectory_cameras(LARGE_VIEWS, width=LARGE_W, height=LARGE_H)
     P_true = torch.from_numpy(synth.perturb(p, synth.SEED_PERTURB)).to(dev)
     rp = B.raster_params()
-    vb = ViewBuffers(LARGE_N, LARGE_W, LARGE_H, None, -1, dev)
+    vb = ViewBuffers(LARGE_N, LARGE_W, LARGE_H, None, -1, dev, supervised=False, backward=False)
     gen = torch.Generator(device=dev)
     gts = []
     for k, cam in enumerate(cams):

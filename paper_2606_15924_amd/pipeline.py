@@ -72,7 +72,7 @@ class ViewBuffers:
 
     def __init__(self, n: int, width: int, height: int, n_pix: int | None, n_tiles_sel: int,
                  device, capacity: int | None = None, keep_keys: bool = False,
-                 counts: torch.Tensor | None = None, supervised: bool = True):
+                 counts: torch.Tensor | None = None, supervised: bool = True, backward: bool = True):
         self.n, self.width, self.height = n, width, height
         self.keep_keys = keep_keys
         self.tiles_x, self.tiles_y = (width + TILE - 1) // TILE, (height + TILE - 1) // TILE
@@ -107,10 +107,14 @@ class ViewBuffers:
             self.err = torch.empty(max(self.P_cap, 1), dtype=torch.float32, device=dev)
             self.lam = torch.empty(max(self.n_st, 1), dtype=torch.float32, device=dev)
             self.tile_loss = torch.zeros((max(self.n_st, 1), 2), dtype=torch.float32, device=dev)
-        self.g2d = torch.empty((n, B.G2D_FLOATS), dtype=torch.float32, device=dev)
-        # per-pixel (T, colour) at the backward's chunk starts, kept by the forward
-        n_state = B.tgs_render_state_size(self.n_st, self.n_pix) // 4
-        self.state = torch.empty(max(n_state, 4), dtype=torch.float32, device=dev)
+        # the screen-space gradient, and per-pixel (T, colour) at the backward's
+        # chunk starts, kept by the forward (a dense 1600x1060 view: 302 MB); a
+        # caller that only renders needs neither
+        self.g2d = self.state = None
+        if backward:
+            self.g2d = torch.empty((n, B.G2D_FLOATS), dtype=torch.float32, device=dev)
+            n_state = B.tgs_render_state_size(self.n_st, self.n_pix) // 4
+            self.state = torch.empty(max(n_state, 4), dtype=torch.float32, device=dev)
         # (list length, capacity needed[, whole-list pairs after a depth-prefix
         # call]) and the continuation's, in one row that the caller may give
         row = torch.zeros(5, dtype=torch.int64, device=dev) if counts is None else counts.zero_()
@@ -347,6 +351,8 @@ class ViewBuffers:
         sums; ``touched`` collects the Gaussians composited at a sample;
         ``deterministic`` selects the bitwise-reproducible reduction (not
         with ``stats``)."""
+        if self.g2d is None:
+            raise RuntimeError("buffers made without a backward")
         if zero:
             self.g2d.zero_()
         if self.two_part:
@@ -548,7 +554,8 @@ class Trainer:
             cam = self.cams[v]
             vb = bufs.get((cam.width, cam.height))
             if vb is None:
-                vb = bufs[(cam.width, cam.height)] = ViewBuffers(self.n, cam.width, cam.height, None, -1, self.dev)
+                vb = bufs[(cam.width, cam.height)] = ViewBuffers(self.n, cam.width, cam.height, None, -1, self.dev,
+                                                                 supervised=False, backward=False)
             vb.project(self.params, cam, self.rp)
             vb.bin_sort(alpha_min=self.rp.alpha_min)
             vb.render_fwd(self.rp)
