@@ -24,8 +24,9 @@ PARAM_ROWS = 59
 MOMENT_STRIDE = 64   # floats per Gaussian in the optimizer moments m, v ([n][64], Gaussian-major)
 TILE = 16
 COUNTER_SLOTS = 64
-RENDER_CHUNKS = 8
-RENDER_CHUNK_LEN = 32
+RENDER_CHUNKS = 8        # equal chunks of a tile's list
+RENDER_CHUNK_LEN = 32    # their list positions
+RENDER_LONG_CHUNKS = 4   # chunks after them: 2, 4, 8 times as long, the last takes the rest
 
 
 class tgs_camera(ctypes.Structure):
