@@ -757,12 +757,16 @@ class Trainer:
         self._queue_count_check(used)
         return used
 
-    def _maps_apart(self, views) -> bool:
-        """Whether the views' error and age maps are distinct in memory (a
+    @staticmethod
+    def _maps_apart(rec) -> bool:
+        """Whether the records' error and age maps are distinct in memory (a
         view drawn twice, or views given the same maps, share them)."""
-        spans = sorted((m.data_ptr(), m.data_ptr() + m.numel() * m.element_size())
-                       for v in views for m in (self.E[v], self.A[v]))
-        return all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+        spans = []
+        for r in rec:
+            size, e, a = 2 * r.width * r.height, r.E, r.A   # 16-bit maps
+            spans += ((e, e + size), (a, a + size))
+        spans.sort()
+        return all(x[1] <= y[0] for x, y in zip(spans, spans[1:]))
 
     def _stacked_stages(self, used, views, rec, sampled):
         """Forward, loss, error maps and (unless it is the deterministic one)
@@ -782,7 +786,7 @@ class Trainer:
             self._lossed[0].record(main)
             self.side.wait_event(self._lossed[0])
             with torch.cuda.stream(self.side):
-                apart = self._maps_apart(views)   # else they are updated in turn
+                apart = self._maps_apart(rec)   # else they are updated in turn
                 if apart:
                     with st("ema_age"):
                         B.tgs_ema_age_update_views(rec, self.cfg.beta)
