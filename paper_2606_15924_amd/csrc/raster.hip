@@ -15,15 +15,19 @@
 // colour) at the first position of every chunk of the list (chunk_begin); the
 // backward then runs one workgroup per (tile, chunk) that starts from the
 // recorded state.  The replay performs the same operations in the same
-// order, so every per-lane value equals the unchunked one; at 64 samples
+// order, so its decisions and transmittances are the unchunked ones (the colour
+// behind a Gaussian is formed anew from the recorded state); at 64 samples
 // per tile this turns one wave per tile into several, which the SIMDs need
 // to hide latency.  The nine screen-space gradients of a Gaussian are moments
-// over the pixels, so the sums over a wave's 64 pixels run on the matrix cores
-// (see render_bwd_kernel); the batch's sums then leave in one pass of atomics.
+// over the pixels, summed by lanes that hold one Gaussian and four pixels, the
+// colours' on the matrix cores (see render_bwd_view); the batch's sums then
+// leave in one pass of atomics.
 //
-// Both walks keep the next batch's loads in flight while the current batch
-// is evaluated: at 64 samples per tile a tile is one wave, so there are few
-// waves per SIMD to hide memory latency otherwise.
+// The forward and the density walk keep the next batch's records and the ids of
+// the one after it in flight while the current batch is evaluated: at 64
+// samples per tile a tile is one wave, so there are few waves per SIMD to hide
+// memory latency otherwise.  The backward keeps the next ids only (its walk
+// needs the registers).
 #include <algorithm>
 
 #include "common.h"
